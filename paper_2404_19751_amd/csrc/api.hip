@@ -55,7 +55,7 @@ struct MeshState {
     // all-pairs rows and the particles-by-face index
     int cap = kCandCap;  // row capacity of the last pass
     int ident_n = -1;    // rows hold the identity lists for this n
-    Buf fstart, forder, fcount;
+    Buf fstart, ffirst, ftgt, fcount;
 };
 
 struct TimingRec {
@@ -77,7 +77,7 @@ struct gsim_ctx {
     bool own_stream = false;
     std::string err;
     std::vector<MeshState *> meshes;
-    Buf stack, work, ctr, wstats, scan_scratch, sum_scratch, pf_over, prof, desc, vdist, ttab, roots, partials, vbits;
+    Buf stack, work, ctr, wstats, scan_scratch, sum_scratch, pf_over, prof, desc, vdist, ttab, roots, partials, vbits, split;
     Buf gtab;  // big-candidate target arrays of the resident wavefronts
     SurfDesc *desc_pinned = nullptr;  // staging for descriptor uploads
     std::vector<SurfDesc> desc_cached;
@@ -518,7 +518,8 @@ gsim_status prepare_surface(gsim_ctx *c, const Member &mb, bool small, int src_b
     HIPCHK(c, ensure(ms->fire, sizeof(FireState)));
     if (all) {
         HIPCHK(c, ensure(ms->fstart, sizeof(int32_t) * (m.nf + 1)));
-        HIPCHK(c, ensure(ms->forder, sizeof(int32_t) * n));
+        HIPCHK(c, ensure(ms->ffirst, sizeof(int32_t) * m.nf));
+        HIPCHK(c, ensure(ms->ftgt, sizeof(FaceTarget) * n));
         HIPCHK(c, ensure(ms->fcount, sizeof(int32_t) * m.nf));
         if (ms->ident_n != n || ms->cap != (int)cap) {
             HIPCHK(c, launch_identity_rows(n, (int)cap, P<int32_t>(ms->cand_cnt), P<int32_t>(ms->cand), c->stream));
@@ -542,7 +543,8 @@ gsim_status prepare_surface(gsim_ctx *c, const Member &mb, bool small, int src_b
     d.cap = (int)cap;
     d.all_pairs = all ? 1 : 0;
     d.fstart = all ? P<int32_t>(ms->fstart) : nullptr;
-    d.forder = all ? P<int32_t>(ms->forder) : nullptr;
+    d.ffirst = all ? P<int32_t>(ms->ffirst) : nullptr;
+    d.ftgt = all ? P<FaceTarget>(ms->ftgt) : nullptr;
     d.cand_cnt = P<int32_t>(ms->cand_cnt);
     d.cand = P<int32_t>(ms->cand);
     d.cdist = P<double>(ms->cdist);
@@ -595,6 +597,7 @@ struct Batch {
     bool all = false;     // all-pairs surfaces (no cutoff)
     int tcap = 0;         // all-pairs target-table capacity
     int64_t vstride = 0;  // all-pairs vertex-table stride
+    int64_t hstride = 0;  // all-pairs half-edge entries per wavefront (0: no surface has bend vertices)
     int64_t rstride = 0;  // bend-vertex table bytes per wavefront
     int32_t rcap = 0;     // its capacity (bend vertices)
     bool small = true;  // every surface bins in one workgroup
@@ -658,7 +661,7 @@ gsim_status prepare_batch(gsim_ctx *c, Batch &B) {
     B.any_fire = false;
     int nblk = 0;
     B.tcap = 0;
-    B.vstride = 0;
+    B.vstride = B.hstride = 0;
     B.rcap = 1;
     for (int i = 0; i < ns; ++i) {
         B.fire_blk.begin[i] = nblk;
@@ -666,6 +669,8 @@ gsim_status prepare_batch(gsim_ctx *c, Batch &B) {
         B.any_fire |= B.mem[i].integ && B.mem[i].integ->kind == GSIM_INT_FIRE;
         B.tcap = std::max(B.tcap, B.mem[i].ms->n);
         B.vstride = std::max<int64_t>(B.vstride, B.mem[i].ms->dm.nv);
+        if (B.mem[i].ms->dm.n_pseudo > 0 && !(c->prec == GSIM_FP32_MIXED && !finite_cutoff(B.mem[i].cutoff)))
+            B.hstride = std::max<int64_t>(B.hstride, 3 * (int64_t)B.mem[i].ms->dm.nf);
         B.rcap = std::max(B.rcap, B.mem[i].ms->dm.n_pseudo);
     }
     // persistent grid: as many wavefronts as can be resident, at most one per source
@@ -713,7 +718,7 @@ gsim_status prepare_batch(gsim_ctx *c, Batch &B) {
     B.nslots = std::min(std::min(total, c->cus * per_cu), c->max_slots);
     if (B.all) {
         // whole-mesh fronts are deep: fewer resident wavefronts rather than more memory
-        const double per_slot = 64.0 * c->stack_cap_all + 8.0 * B.vstride + (double)B.rstride + 32.0 * B.tcap;
+        const double per_slot = 64.0 * c->stack_cap_all + 8.0 * B.vstride + (double)B.rstride + 32.0 * B.tcap + 8.0 * B.hstride;
         const int64_t fit = (int64_t)(c->stack_budget / per_slot);
         B.nslots = (int)std::max<int64_t>(1, std::min<int64_t>(B.nslots, fit));
     }
@@ -750,6 +755,7 @@ gsim_status prepare_batch(gsim_ctx *c, Batch &B) {
     if (B.all) {
         HIPCHK(c, ensure(c->vdist, sizeof(double) * (size_t)std::max(B.nslots, 1) * B.vstride));
         HIPCHK(c, ensure(c->ttab, 4 * sizeof(double) * (size_t)std::max(B.nslots, 1) * B.tcap));
+        if (B.hstride) HIPCHK(c, ensure(c->split, sizeof(unsigned long long) * (size_t)std::max(B.nslots, 1) * B.hstride));
     }
     // bend-vertex tables: emptied once here, left empty by the kernels
     const int nsl = std::max(B.nslots, 1);
@@ -788,7 +794,8 @@ gsim_status geodesic_pass(gsim_ctx *c, Batch &B, bool advance, bool commit_in = 
         gp.max_windows = c->max_windows_all;
         Stage st(c, "geodesic");
         HIPCHK(c, launch_geodesic_all(desc_dev(c), B.bi, gp, B.shape, P<char>(c->stack), P<double>(c->vdist), B.vstride,
-                                      P<char>(c->roots), B.rstride, B.rcap, P<double2>(c->ttab), B.tcap,
+                                      P<char>(c->roots), B.rstride, B.rcap, c->ttab.p, B.tcap,
+                                      B.hstride ? P<unsigned long long>(c->split) : nullptr, B.hstride,
                                       P<int32_t>(c->work), P<Counters>(c->ctr), c->prec == GSIM_FP32_MIXED, s));
         c->passes++;
         return GSIM_OK;
@@ -919,10 +926,10 @@ std::string graph_key(gsim_ctx *c, const Batch &B, int steps) {
     put(&B.gcap, sizeof(B.gcap));
     put(&c->update_block, sizeof(int));
     put(&steps, sizeof(int));
-    void *ptrs[10] = {c->stack.p, c->work.p, c->ctr.p, c->desc.p, c->scan_scratch.p, c->vdist.p, c->ttab.p,
-                      c->roots.p, c->partials.p, c->gtab.p};
+    void *ptrs[11] = {c->stack.p, c->work.p, c->ctr.p, c->desc.p, c->scan_scratch.p, c->vdist.p, c->ttab.p,
+                      c->roots.p, c->partials.p, c->gtab.p, c->split.p};
     put(ptrs, sizeof(ptrs));
-    const int64_t sizes[4] = {B.rstride, B.rcap, B.tcap, B.vstride};
+    const int64_t sizes[5] = {B.rstride, B.rcap, B.tcap, B.vstride, B.hstride};
     put(sizes, sizeof(sizes));
     return k;
 }
@@ -1093,7 +1100,7 @@ void gsim_destroy(gsim_ctx *c) {
         for (Buf *b : {&ms->cell_of, &ms->cell_start, &ms->cell_fill, &ms->order, &ms->cand_cnt, &ms->cand,
                        &ms->tmp64, &ms->cdist, &ms->ctan, &ms->cflags, &ms->nbr_cnt, &ms->off, &ms->nbr, &ms->dist,
                        &ms->tan, &ms->flags, &ms->F, &ms->Ei, &ms->E, &ms->disp, &ms->wflags, &ms->step_dev,
-                       &ms->fire, &ms->fstart, &ms->forder, &ms->fcount, &ms->face_nx, &ms->bary_nx,
+                       &ms->fire, &ms->fstart, &ms->ffirst, &ms->ftgt, &ms->fcount, &ms->face_nx, &ms->bary_nx,
                        &ms->vel_nx})
             release(*b);
         for (void *p : {(void *)ms->face, (void *)ms->bary, (void *)ms->vel, (void *)ms->xyz})
@@ -1106,7 +1113,7 @@ void gsim_destroy(gsim_ctx *c) {
         delete ms;
     }
     for (Buf *b : {&c->stack, &c->work, &c->ctr, &c->wstats, &c->scan_scratch, &c->sum_scratch, &c->pf_over,
-                   &c->prof, &c->desc, &c->vdist, &c->ttab, &c->roots, &c->partials, &c->vbits, &c->gtab})
+                   &c->prof, &c->desc, &c->vdist, &c->ttab, &c->roots, &c->partials, &c->vbits, &c->gtab, &c->split})
         release(*b);
     if (c->desc_pinned) (void)hipHostFree(c->desc_pinned);
     if (c->own_stream) (void)hipStreamDestroy(c->stream);

@@ -179,8 +179,10 @@ struct SurfDesc {
     double *cdist, *ctan;
     uint8_t *cflags;
     double cutoff, cut2;
-    // particles by face (all-pairs target lookup): forder[fstart[f] .. fstart[f+1])
-    int32_t *fstart, *forder;
+    // particles by face (all-pairs target lookup): ftgt[fstart[f] .. fstart[f+1])
+    // (ffirst[f]: fstart[f], or -1 for a face without particles)
+    int32_t *fstart, *ffirst;
+    struct FaceTarget *ftgt;
     // potential and integrator of the fused update
     int32_t pkind, ikind;
     double pk, psigma, dt, mobility, kT, friction;
@@ -215,6 +217,15 @@ struct FireState {
     double dt, alpha, cv, cf;
     int32_t n_pos, init;
 };
+
+// A particle of the by-face index with what a target query reads of it, so
+// that the query waits for one load after the face's range.
+struct alignas(16) FaceTarget {
+    double b[3];  // barycentrics
+    int32_t j;     // particle
+    int32_t more;  // another one of the same face follows
+};
+static_assert(sizeof(FaceTarget) == 32, "FaceTarget must be a 32-byte record");
 
 constexpr int kMaxBatch = 64;
 // Surface boundaries of a batch, passed by value: surface s owns the
@@ -266,11 +277,13 @@ int64_t geodesic_gtab_bytes(int gcap);
 // particle of the surface is a target. vdist: per resident wavefront a table
 // of vstride vertex distances; roots: per resident wavefront a bend-vertex
 // table of rstride bytes for rcap bend vertices (bend_table_bytes); ttab:
-// per resident wavefront the state of tcap targets (4 doubles each).
+// per resident wavefront the state of tcap targets (4 doubles each); split:
+// per resident wavefront hstride half-edge entries (null when no surface has
+// bend vertices).
 hipError_t launch_geodesic_all(const SurfDesc *desc, const BatchIdx &bi, const GeoParams &gp, const GeoShape &shape,
                                char *stack_mem, double *vdist, int64_t vstride, char *roots, int64_t rstride,
-                               int rcap, double2 *ttab, int tcap, int32_t *work_ctr, Counters *ctr, bool fp32,
-                               hipStream_t s);
+                               int rcap, void *ttab, int tcap, unsigned long long *split, int64_t hstride,
+                               int32_t *work_ctr, Counters *ctr, bool fp32, hipStream_t s);
 // In-surface Voronoi neighbours (k_voronoi.hip): at most kVoronoiMax
 // particles (an n x n adjacency bitset). launch_voronoi_faces marks every
 // pair of particles whose cells share a boundary longer than tol; cell lists
@@ -343,7 +356,6 @@ hipError_t launch_cell_sort(const DevMesh &m, int n, const int32_t *face, const 
 // resident geodesic workgroups per compute unit for a stack size (0 on error)
 int geodesic_blocks_per_cu(int lds_stack_kb, bool fp32, bool big = false);
 
-hipError_t launch_i64_to_i32(const int64_t *in, int32_t *out, int n, hipStream_t s);
 
 hipError_t launch_count_rows(int n, const int32_t *cnt, int cap_c, const double *dist, double cutoff, int32_t *out,
                              hipStream_t s);

@@ -18,6 +18,8 @@
 //    ahead along one branch; once every target has been reached, windows
 //    whose key exceeds the largest target distance (widened by the tie gap)
 //    are dropped.
+// A third filter, one angle, one split (one_split), halves the windows of
+// surfaces with saddle or boundary vertices.
 // Bend vertices are launched by the rules of the cutoff kernel, from a table
 // that can hold every saddle and boundary vertex of the surface.
 //
@@ -27,6 +29,21 @@
 // (the overflow is two-ended: the current round grows from one end, the next
 // round from the other); targets are found through the surface's
 // particles-by-face index.
+//
+// What bounds it: the latency of one iteration of a wavefront (64 windows),
+// at two wavefronts per SIMD: two dependent rounds of loads (about 1.3k and
+// 1.5k cycles on the icosphere of 81,920 faces, mostly L2 misses) and about
+// 5k cycles of arithmetic and stack work. The domination tests therefore run
+// in squares (no square roots) and without branches, one body makes the
+// children of both sides, the interval is cut while the second round's loads
+// are on their way, a child takes its edge's vertex distances from its
+// parent, and global stack traffic goes a wavefront's worth at a time.
+// Together with records read in whole rounds: 2000 sources on that sphere
+// 0.953 -> 0.639 s a pass (22 -> 34 G windows/s), 100 sources on an aspect-3
+// torus of 3456 faces 18.7 -> 12.4 ms (and 18.8 -> 11.5 M windows). Fetching
+// the next half-edge record straight into LDS an iteration ahead was slower
+// (0.84 s, and 0.98 s with lanes sharing the loads): every later LDS access
+// of the iteration waits for such a fetch.
 #include <cmath>
 
 #include "gsim_internal.h"
@@ -40,6 +57,12 @@ using namespace wnd;
 constexpr int kChunks = 8;
 static_assert(kChunks == kWorkChunks, "one work counter per chunk");
 
+// One target of a source: best distance, best distance of another direction,
+// tangent of the best path. One 32-byte record, read as a whole.
+struct alignas(16) TgtState {
+    double d1 = INFINITY, d2 = INFINITY, tx = 0.0, ty = 0.0;
+};
+
 struct AllArgs {
     const SurfDesc *sd;
     BatchIdx bi;
@@ -52,7 +75,9 @@ struct AllArgs {
     int rcap;
     int32_t *work;
     Counters *ctr;
-    double2 *ttab;   // per wavefront: tcap target distances (best, tie), then tcap tangents
+    unsigned long long *split;  // per wavefront: hstride half-edge entries (null: no surface has bend vertices)
+    int64_t hstride;
+    TgtState *ttab;  // per wavefront: the state of tcap targets
     int tcap;
     int grab;
 };
@@ -67,6 +92,7 @@ struct AllLds {
 struct ACtx {
     double tol, tie_rel, tie_dir, root_keep, dom_rel, bucket;
     double cutoff;  // infinity for all pairs
+    double split_rel;  // one_split: relative gap of the two distances
     RootCfg rc;
 };
 
@@ -78,7 +104,9 @@ struct SrcStats {
 
 // Window stack of the round-by-round order: LDS first, then one end of the
 // wavefront's global area for the current round; the next round's windows
-// grow from the other end.
+// grow from the other end, gathered in an LDS buffer and written out a
+// wavefront's worth at a time (a store in flight would hold up the next
+// iteration's wait for its loads).
 template <typename R>
 struct RoundStack {
     using Rec = typename RecOf<R>::T;
@@ -88,6 +116,8 @@ struct RoundStack {
     int gcap;
     int lsp, gsp, dsp;
     int dir;
+    Rec *ldd;  // kWave records waiting to go to the next round's end
+    int dl;
 
     __device__ Rec &cur(int k) { return dir == 0 ? glb[k] : glb[gcap - 1 - k]; }
     __device__ Rec &def(int k) { return dir == 0 ? glb[gcap - 1 - k] : glb[k]; }
@@ -117,17 +147,38 @@ struct RoundStack {
         cnt = __popcll(m);
         if (cnt) {
             const int r = __popcll(m & lanemask_lt());
-            if (lat) {
-                const int pos = dsp + r;
-                if (pos + gsp < gcap) store_rec(def(pos), w);
-                else overflow = true;
-            }
-            dsp = min(dsp + cnt, gcap - gsp);
+            if (dl + cnt > kWave) flush(overflow);
+            if (lat) store_rec(ldd[dl + r], w);
+            dl += cnt;
         }
     }
+    // the buffered windows of the next round into its end of the global area
+    __device__ void flush(bool &overflow) {
+        __syncthreads();
+        const int l = lane_id();
+        if (l < dl) {
+            if (dsp + l + gsp < gcap) def(dsp + l) = ldd[l];
+            else overflow = true;
+        }
+        dsp = min(dsp + dl, gcap - gsp);
+        dl = 0;
+        __syncthreads();
+    }
+    // A wavefront's windows mostly arrive from the global area (a round's
+    // windows wait there), a few lanes' worth an iteration. They are taken
+    // over into the LDS stack a wavefront's worth at a time, so that one
+    // iteration in many, not each, waits for that memory.
     __device__ bool refill(bool &have, Win<R> &w) {
         const uint64_t need = __ballot(!have);
         const int nneed = __popcll(need);
+        if (lsp < nneed && gsp > 0) {
+            __syncthreads();  // make earlier global pushes of other lanes visible
+            const int take = min(min(kL - lsp, kWave), gsp);
+            if (lane_id() < take) lds[lsp + lane_id()] = cur(gsp - take + lane_id());
+            lsp += take;
+            gsp -= take;
+            __syncthreads();
+        }
         const int r = __popcll(need & lanemask_lt());
         const int take_l = min(nneed, lsp);
         if (!have && r < take_l) {
@@ -135,19 +186,11 @@ struct RoundStack {
             have = true;
         }
         lsp -= take_l;
-        if (nneed > take_l && gsp > 0) {
-            __syncthreads();  // make earlier global pushes of other lanes visible
-            const int take_g = min(nneed - take_l, gsp);
-            if (!have && r >= take_l && r < take_l + take_g) {
-                load_rec(cur(gsp - 1 - (r - take_l)), w);
-                have = true;
-            }
-            gsp -= take_g;
-        }
         return __ballot(have) != 0;
     }
     // the next round's windows become the current ones (the current round is empty)
-    __device__ void next_round() {
+    __device__ void next_round(bool &overflow) {
+        flush(overflow);
         dir ^= 1;
         gsp = dsp;
         dsp = 0;
@@ -160,32 +203,27 @@ __device__ inline void vdist_min(double *Dv, int v, double d) {
     atomicMin(reinterpret_cast<unsigned long long *>(Dv + v), (unsigned long long)__double_as_longlong(d));
 }
 
-// Target update: best distance, its tangent, and the best distance among
-// candidates whose direction differs (tie gap); `alt` is the distance of an
-// another-direction path that comes with the candidate. The lanes load their
-// targets together and leave when their candidate cannot change anything
-// (the stored distances only decrease); the others are applied one lane at a
-// time in registers, each result passed to every lane holding the same
-// target, and written back once (the tangent only where the best distance
-// fell).
-__device__ inline void target_update(AllLds &L, double2 *td, double2 *tt, const ACtx &C, bool ok, int j, double d,
-                                     double tx, double ty, double alt) {
+// Target update (j: the target's place in the by-face index): best distance,
+// its tangent, and the best distance among candidates whose direction differs
+// (tie gap); `alt` is the distance of an another-direction path that comes
+// with the candidate. The lanes load their targets together (or hand in the
+// entries `c` loaded earlier, with no other update in between) and leave when
+// their candidate cannot change anything (the stored distances only
+// decrease); the others are applied one lane at a time in registers, each
+// result passed to every lane holding the same target, and written back once
+// (its whole record).
+__device__ inline void target_update_loaded(AllLds &L, TgtState *td, const ACtx &C, bool ok, int j, double d,
+                                            double tx, double ty, double alt, const TgtState &c) {
     double c1 = INFINITY, c2 = INFINITY;
     if (ok) {
-        const double2 c = td[j];
-        c1 = c.x;
-        c2 = c.y;
+        c1 = c.d1;
+        c2 = c.d2;
         if (d >= c1 && d >= c2 && alt >= c2) ok = false;
     }
     uint64_t m = __ballot(ok);
     if (!m) return;
     const double c1_in = c1, c2_in = c2;
-    double ax = 0.0, ay = 0.0;
-    if (ok && c1 < INFINITY) {
-        const double2 t = tt[j];
-        ax = t.x;
-        ay = t.y;
-    }
+    double ax = c.tx, ay = c.ty;
     int reached = 0;  // targets found for the first time
     // lanes on different targets (the usual case) update at once, else one
     // lane at a time
@@ -243,63 +281,71 @@ __device__ inline void target_update(AllLds &L, double2 *td, double2 *tt, const 
         m &= m - 1;
     }
     if (ok) {
-        if (c1 < c1_in || c2 < c2_in) td[j] = make_double2(c1, c2);
-        if (c1 < c1_in) tt[j] = make_double2(ax, ay);
+        if (c1 < c1_in || c2 < c2_in) td[j] = TgtState{c1, c2, ax, ay};
     }
     if (lane_id() == 0 && reached) L.unfound -= reached;
     lane_step_barrier();
 }
 
+__device__ inline void target_update(AllLds &L, TgtState *td, const ACtx &C, bool ok, int j, double d, double tx,
+                                     double ty, double alt) {
+    TgtState c;
+    if (ok) c = td[j];
+    target_update_loaded(L, td, C, ok, j, d, tx, ty, alt, c);
+}
+
+// The domination tests below compare a window's distance f(x) = sg + |p - X|
+// at a point X of the child edge with the length of a path through a vertex,
+// in squares: with r = |p - X|^2, f(x) > d exactly when d < sg or
+// r > (d - sg)^2. No square root is taken, and the rounding stays at that of
+// the distances themselves, far inside the widening by rel.
+__device__ inline bool longer(double r, double d_sg) { return d_sg < 0.0 || r > d_sg * d_sg; }
+
 // Trim a child interval [x0, x1] on an edge S -> E (length Lc, child frame
-// origin S) against the paths through S and through E; returns false when
-// nothing is left. f(x) = sg + |p - (x, 0)|. The path through S and then
-// along the edge has length DS + x; it is shorter than the window where
+// origin S, root image (px, py)) against the paths through S and through E;
+// returns false when nothing is left. The path through S and then along the
+// edge has length DS + x; it is shorter than the window where
 // g(x) = f(x) - x - DS > 0, and g is non-increasing, so the dominated part
 // is [x0, x*). Likewise h(x) = f(x) - (Lc - x) - DE is non-decreasing and
 // the part dominated by the path through E is (x**, x1]. The vertex path
 // lengths are widened by the factor 1 + rel first, so only parts dominated
-// beyond the rounding error of the working precision are cut. f0 and f1
-// return f at the final ends (each square root is taken once per end).
+// beyond the rounding error of the working precision are cut. r0 and r1: the
+// squared distances from p at the ends, updated with them.
 __device__ inline bool vertex_trim(double px, double py, double sg, double Lc, double DS, double DE, double rel,
-                                   double &x0, double &x1, double &f0, double &f1) {
+                                   double &x0, double &x1, double &r0, double &r1) {
     // the vertex paths count as shorter only by more than `rel` of their length
-    DS *= 1.0 + rel;
-    DE *= 1.0 + rel;
-    const double eps_x = 1e-9 * Lc;
-    auto f = [&](double x) { return sg + sqrt((x - px) * (x - px) + py * py); };
-    f0 = f(x0);
-    f1 = f(x1);
-    if (DS < INFINITY) {
-        if (f1 - x1 - DS > 0.0) return false;
-        if (f0 - x0 - DS > 0.0) {
-            // g(x*) = 0: sqrt((x - px)^2 + py^2) = dl + x, dl = DS - sg
-            const double dl = DS - sg;
+    const double dl = DS * (1.0 + rel) - sg;       // through S: dl + x
+    const double mm = DE * (1.0 + rel) + Lc - sg;  // through E: mm - x
+    const double eps_x = 1e-9 * Lc, h2 = py * py;
+    // the far end of S's part, or the near end of E's, dominated: nothing is
+    // left. Most windows pass all four tests, so they run without a branch
+    // and the trims share one.
+    const bool s0 = longer(r0, dl + x0), s1 = longer(r1, dl + x1);
+    const bool e0 = longer(r0, mm - x0), e1 = longer(r1, mm - x1);
+    bool left = x1 - x0 > 1e-12 * Lc && !s1 && !e0;
+    if (left && (s0 || e1)) {
+        if (s0) {
+            // g(x*) = 0: sqrt((x - px)^2 + py^2) = dl + x
             const double den = 2.0 * (px + dl);
-            if (den > 0.0) {
-                const double xs = (px * px + py * py - dl * dl) / den;
-                if (xs - eps_x > x0) {
-                    x0 = fmin(x1, xs - eps_x);
-                    f0 = f(x0);
-                }
+            const double xs = (px * px + h2 - dl * dl) / den;
+            if (den > 0.0 && xs - eps_x > x0) {
+                x0 = fmin(x1, xs - eps_x);
+                r0 = (x0 - px) * (x0 - px) + h2;
+                if (longer(r0, mm - x0)) left = false;
             }
         }
-    }
-    if (DE < INFINITY) {
-        if (f0 - (Lc - x0) - DE > 0.0) return false;
-        if (f1 - (Lc - x1) - DE > 0.0) {
-            // h(x**) = 0: sqrt((x - px)^2 + py^2) = mm - x, mm = DE + Lc - sg
-            const double mm = DE + Lc - sg;
+        if (e1) {
+            // h(x**) = 0: sqrt((x - px)^2 + py^2) = mm - x
             const double den = 2.0 * (px - mm);
-            if (den < 0.0) {
-                const double xs = (px * px + py * py - mm * mm) / den;
-                if (xs + eps_x < x1) {
-                    x1 = fmax(x0, xs + eps_x);
-                    f1 = f(x1);
-                }
+            const double xs = (px * px + h2 - mm * mm) / den;
+            if (den < 0.0 && xs + eps_x < x1) {
+                x1 = fmax(x0, xs + eps_x);
+                r1 = (x1 - px) * (x1 - px) + h2;
             }
         }
+        left = left && x1 - x0 > 1e-12 * Lc;
     }
-    return x1 - x0 > 1e-12 * Lc;
+    return left;
 }
 
 // Is the whole child interval [x0, x1] dominated by the path through the
@@ -307,74 +353,108 @@ __device__ inline bool vertex_trim(double px, double py, double sg, double Lc, d
 // the edge), i.e. DO + |O - X| < f(X)? The points of the edge line where that
 // holds are the line's intersection with one branch region of a hyperbola
 // with foci p and O, which is convex: domination at both ends means
-// domination everywhere in between. f0, f1: f at the two ends. The test at
-// a point compares squares (f - DO > 0 and |O - X|^2 < (f - DO)^2): no
-// square root, and its rounding stays far inside the widening by rel.
-__device__ inline bool opposite_dominates(double ox, double oy, double DO, double rel, double x0, double x1, double f0,
-                                          double f1) {
-    if (!(DO < INFINITY)) return false;
-    DO *= 1.0 + rel;
-    auto dom = [&](double x, double f) {
-        const double r = f - DO;
-        return r > 0.0 && (x - ox) * (x - ox) + oy * oy < r * r;
+// domination everywhere in between. With e = DO - sg, A = |O - X|^2 and
+// r = |p - X|^2 the test e + sqrt(A) < sqrt(r) is squared twice.
+__device__ inline bool opposite_dominates(double ox, double oy, double DO, double sg, double rel, double x0, double x1,
+                                          double r0, double r1) {
+    const double e = DO * (1.0 + rel) - sg, e2 = e * e;
+    auto dom = [&](double x, double r) {
+        const double A = (x - ox) * (x - ox) + oy * oy;
+        // e >= 0: sqrt(r) > e + sqrt(A); e < 0: not sqrt(A) >= |e| + sqrt(r)
+        const double P = e >= 0.0 ? A : r, Q = e >= 0.0 ? r : A;
+        const double t = Q - P - e2, tt = t * t, pp = 4.0 * e2 * P;
+        return e >= 0.0 ? t > 0.0 && tt > pp : !(t >= 0.0 && tt >= pp);
     };
-    return dom(x0, f0) && dom(x1, f1);
+    return dom(x0, r0) && dom(x1, r1);
 }
 
-// Key (smallest distance) of a child window on [x0, x1] whose distance at
-// the ends is f0, f1. In FP64 the ends are the window's own, so the key
-// reuses them; FP32 windows take it from their rounded fields.
-template <typename R>
-__device__ inline double child_key(const Win<R> &c, double f0, double f1) {
-    if constexpr (sizeof(R) == 8) {
-        return c.px < c.b0 ? f0 : (c.px > c.b1 ? f1 : c.sg + fabs(c.py));
-    } else {
-        return (double)c.sg + (double)seg_dist(c.px, c.py, c.b0, c.b1);
-    }
+// One angle, one split (Chen and Han, SoCG 1990): when another window of the
+// same half-edge has reached the face's third vertex C by a shorter path, the
+// rays of this window on that path's side of C are longer than it. Their
+// paths cross the other's in the wedge between this window's ray to C and
+// themselves (both windows leave the wedge's faces unfolded the same way), and
+// are longer there: at most one child is left, the left one when the other
+// ray crosses the half-edge to the right of this window's ray, else the right
+// one. Hv keeps per half-edge the shortest such path and its crossing, packed
+// as two floats so that one 64-bit minimum updates both (the distance rounded
+// up). The distances must differ by rel, far more than the floats' rounding
+// and than any tie band carried on to the targets; crossings closer than a
+// thousandth of the edge decide nothing.
+// Returns the sides still open: bit 0 the left child, bit 1 the right one.
+__device__ inline int one_split(unsigned long long *Hv, int he, unsigned long long hw, double d, double x, double len,
+                                double rel) {
+    const float hd = __uint_as_float((unsigned)(hw >> 32)), hx = __uint_as_float((unsigned)hw);
+    const bool other = hw != ~0ull && (double)hd * (1.0 + rel) < d;
+    const int sides = other && (double)hx > x + 1e-3 * len ? 1 : other && (double)hx < x - 1e-3 * len ? 2 : 3;
+    const unsigned long long mine =
+        ((unsigned long long)__float_as_uint(__double2float_ru(d)) << 32) | __float_as_uint((float)x);
+    if (mine < hw) atomicMin(Hv + he, mine);
+    return sides;
 }
 
-// Targets in face g (entry half-edge slot k of g) seen through window w.
+// Where the rays through the ends of a window's interval leave through the
+// far edge A -> C (left) or C -> B: child_left and child_right of the cutoff
+// kernel with the side selected per lane.
 template <typename R>
-__device__ inline void query_face(const SurfDesc &sd, AllLds &L, const BendTable &G, double2 *td, double2 *tt,
-                                  const ACtx &C, bool have, int src, int g, int k, const He<R> &H,
-                                  const Win<R> &w) {
-    int q = 0, q1 = 0;
-    if (have) {
-        q = sd.fstart[g];
-        q1 = sd.fstart[g + 1];
-    }
-    while (__ballot(q < q1)) {
+__device__ inline void far_ends(const He<R> &h, const Win<R> &w, double txc, bool left, double &x0, double &x1) {
+    const double px = w.px, py = w.py, b0 = w.b0, b1 = w.b1, cx = h.cx, cy = h.cy, L = h.L;
+    const double Lc = left ? (double)h.Lp : (double)h.Ln;
+    auto cut = [&](double b) {
+        const double db = b - px;
+        const double num = left ? py * b : (px - cx) * (-py) - (py - cy) * db;
+        const double den = left ? py * cx + cy * db : (L - cx) * (-py) + cy * db;
+        return Lc * num / den;
+    };
+    const double c0 = cut(b0), c1 = cut(b1);
+    x0 = b0 <= (left ? 0.0 : txc) ? 0.0 : c0;
+    x1 = b1 >= (left ? txc : L) ? Lc : c1;
+    x0 = fmin(fmax(x0, 0.0), Lc);
+    x1 = fmin(fmax(x1, 0.0), Lc);
+}
+
+// Targets of the by-face index from q on (-1: none), in the face with entry half-edge
+// slot k, seen through window w whose root has the tangent (rtx, rty) and
+// other-direction distance rD2 (bend vertices). t0 and c0: the first one's
+// record and distances, loaded by the caller.
+template <typename R>
+__device__ inline void query_face(const FaceTarget *ftgt, AllLds &L, TgtState *td, const ACtx &C, int q,
+                                  int src, int k, const He<R> &H, const Win<R> &w, double rtx, double rty,
+                                  double rD2, FaceTarget t0, TgtState c0) {
+    while (__ballot(q >= 0)) {
         bool ok = false;
-        int j = 0;
         double d = 0, tx = 0, ty = 0, alt = INFINITY;
-        if (q < q1) {
-            j = sd.forder[q];
-            if (j != src) {
-                const double *b = sd.bary + 3 * (int64_t)j;
-                const R qx = (R)b[(k + 1) % 3] * H.L + (R)b[(k + 2) % 3] * H.cx;
-                const R qy = (R)b[(k + 2) % 3] * H.cy;
-                const R xq = w.px + (qx - w.px) * (-w.py) / (qy - w.py);
-                const R sl = (R)C.tol * H.L;
-                if (xq >= w.b0 - sl && xq <= w.b1 + sl) {
-                    R dx = qx - w.px, dy = qy - w.py;
-                    const R l = sqrt(dx * dx + dy * dy);
-                    d = (double)w.sg + (double)l;
-                    ok = true;
-                    if (w.root < 0) {
-                        dx /= l;
-                        dy /= l;
-                        tx = (double)(w.c * dx - w.s * dy);
-                        ty = (double)(w.s * dx + w.c * dy);
-                    } else {
-                        tx = G.rtx[w.root];
-                        ty = G.rty[w.root];
-                        alt = G.rD2[w.root] + (double)l;
-                    }
+        if (q >= 0 && t0.j != src) {
+            // barycentrics in the entry half-edge's order (selects: a lane's
+            // index into the record would put it in scratch)
+            const double bh = k == 0 ? t0.b[1] : k == 1 ? t0.b[2] : t0.b[0];
+            const double bo = k == 0 ? t0.b[2] : k == 1 ? t0.b[0] : t0.b[1];
+            const R qx = (R)bh * H.L + (R)bo * H.cx;
+            const R qy = (R)bo * H.cy;
+            const R xq = w.px + (qx - w.px) * (-w.py) / (qy - w.py);
+            const R sl = (R)C.tol * H.L;
+            if (xq >= w.b0 - sl && xq <= w.b1 + sl) {
+                R dx = qx - w.px, dy = qy - w.py;
+                const R l = sqrt(dx * dx + dy * dy);
+                d = (double)w.sg + (double)l;
+                ok = true;
+                if (w.root < 0) {
+                    dx /= l;
+                    dy /= l;
+                    tx = (double)(w.c * dx - w.s * dy);
+                    ty = (double)(w.s * dx + w.c * dy);
+                } else {
+                    tx = rtx;
+                    ty = rty;
+                    alt = rD2 + (double)l;
                 }
             }
-            ++q;
         }
-        target_update(L, td, tt, C, ok, j, d, tx, ty, alt);
+        target_update_loaded(L, td, C, ok, q, d, tx, ty, alt, c0);
+        q = q >= 0 && t0.more ? q + 1 : -1;
+        if (q >= 0) {
+            t0 = ftgt[q];
+            c0 = td[q];
+        }
     }
 }
 
@@ -382,8 +462,8 @@ __device__ inline void query_face(const SurfDesc &sd, AllLds &L, const BendTable
 // direction changed, or a tie appeared), their fans flattened over the lanes
 // a chunk of vertices at a time.
 template <typename R>
-__device__ void launch_roots(const AllArgs &a, const SurfDesc &sd, AllLds &L, const BendTable &G, double2 *td,
-                             double2 *tt, double *Dv, const ACtx &C, RoundStack<R> &S,
+__device__ void launch_roots(const AllArgs &a, const SurfDesc &sd, AllLds &L, const BendTable &G, TgtState *td,
+                             double *Dv, const ACtx &C, RoundStack<R> &S,
                              double T, int src, SrcStats &st) {
     const int lane = lane_id();
     const DevMesh &M = sd.m;
@@ -487,9 +567,10 @@ __device__ void launch_roots(const AllArgs &a, const SurfDesc &sd, AllLds &L, co
                 int j = 0;
                 double d = 0;
                 if (q < q1) {
-                    j = sd.forder[q];
-                    if (j != src) {
-                        const double *b = sd.bary + 3 * (int64_t)j;
+                    const FaceTarget t = sd.ftgt[q];
+                    j = q;
+                    if (t.j != src) {
+                        const double *b = t.b;
                         const int32_t *Tg = M.T + 3 * (int64_t)g;
                         double x[3] = {0, 0, 0};
                         for (int c = 0; c < 3; ++c)
@@ -500,7 +581,7 @@ __device__ void launch_roots(const AllArgs &a, const SurfDesc &sd, AllLds &L, co
                     }
                     ++q;
                 }
-                target_update(L, td, tt, C, ok, j, d, vtx, vty, D2 + (d - D));
+                target_update(L, td, C, ok, j, d, vtx, vty, D2 + (d - D));
             }
             // the two other vertices of face(h), reached along its edges
             const int u1 = Rh.head, u2 = Rh.opp_flags >> 1;
@@ -527,14 +608,20 @@ __device__ void launch_roots(const AllArgs &a, const SurfDesc &sd, AllLds &L, co
 // as a call, the FP32 kernel spills around it and holds one wave per SIMD.
 template <typename R>
 __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, const SurfDesc &sd, AllLds &L,
-                                                              double2 *td, double2 *tt, unsigned char *stk,
-                                                              int stk_bytes, int src, int slot, bool guard,
+                                                              TgtState *td, unsigned char *stk,
+                                                              int stk_bytes, unsigned char *later, int src, int slot, bool guard,
                                                               SrcStats &st) {
     const int lane = lane_id();
     const bool fp32 = sizeof(R) == 4;
     const int n = sd.n;
+    // the mesh and the target index through local pointers: read from the
+    // descriptor where they are used, each would be loaded again after every
+    // store (and the loads that need it wait for that one)
     const DevMesh &M = sd.m;
-    const HeRec *__restrict__ he = M.he;
+    const HeRec *const he = uniform(M.he);
+    const HeRecF *const hef = uniform(M.hef);
+    const int32_t *const pidx = uniform(M.pidx), *const ffirst = uniform(sd.ffirst);
+    const FaceTarget *const ftgt = uniform(sd.ftgt);
     ACtx C;
     C.tol = fp32 ? a.gp.cone_tol32 : a.gp.cone_tol;
     C.tie_rel = fp32 ? a.gp.tie_rel32 : a.gp.tie_rel;
@@ -547,20 +634,30 @@ __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, 
     C.bucket = a.gp.bucket > 0.0 ? a.gp.bucket : (M.n_pseudo > 0 ? 4.0 : 16.0) * M.max_edge;
     C.cutoff = sd.cutoff;
     double *Dv = a.vdist + (int64_t)slot * a.vstride;
+    // one_split: FP64 passes (the FP32 pass's tie band is as wide as its
+    // distances' errors) on surfaces with bend vertices, whose windows split
+    // often (an aspect-3 torus of 3456 faces: 188k windows a source without
+    // it, 112k with it); on a convex sphere one window in a hundred covers a
+    // vertex, and the entries would cost more than the 1 % of windows they
+    // save
+    unsigned long long *Hv = !fp32 && M.n_pseudo > 0 && a.split ? a.split + (int64_t)slot * a.hstride : nullptr;
+    C.split_rel = fmax(1e-6, 64.0 * C.tie_rel);
     const BendTable G = bend_table(a.roots, a.rstride, slot, a.rcap);
     RoundStack<R> S;
     S.lds = reinterpret_cast<typename RecOf<R>::T *>(stk);
     S.kL = stk_bytes / (int)sizeof(typename RecOf<R>::T);
     S.glb = reinterpret_cast<typename RecOf<R>::T *>(reinterpret_cast<Rec64 *>(a.stack) + (size_t)slot * a.gp.stack_cap);
     S.gcap = fp32 ? 2 * a.gp.stack_cap : a.gp.stack_cap;
-    S.lsp = S.gsp = S.dsp = 0;
+    S.lsp = S.gsp = S.dsp = S.dl = 0;
     S.dir = 0;
+    S.ldd = reinterpret_cast<typename RecOf<R>::T *>(later);
 
     // ---- tables
     for (int v = lane; v < M.nv; v += kWave) Dv[v] = INFINITY;
+    if (Hv)
+        for (int h = lane; h < 3 * M.nf; h += kWave) Hv[h] = ~0ull;
     for (int j = lane; j < n; j += kWave) {
-        td[j] = make_double2(INFINITY, INFINITY);
-        tt[j] = make_double2(0.0, 0.0);
+        td[j] = TgtState{};
     }
     if (lane == 0) {
         L.B.npend = 0;
@@ -588,9 +685,10 @@ __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, 
             int j = 0;
             double d = 0, tx = 0, ty = 0;
             if (q < q1) {
-                j = sd.forder[q];
-                if (j != src) {
-                    const double *b = sd.bary + 3 * (int64_t)j;
+                const FaceTarget t = sd.ftgt[q];
+                j = q;
+                if (t.j != src) {
+                    const double *b = t.b;
                     const double qx = b[1] * P[1][0] + b[2] * P[2][0], qy = b[1] * P[1][1] + b[2] * P[2][1];
                     const double dx = qx - sx, dy = qy - sy;
                     d = sqrt(dx * dx + dy * dy);
@@ -602,7 +700,7 @@ __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, 
                 }
                 ++q;
             }
-            target_update(L, td, tt, C, ok, j, d, tx, ty, INFINITY);
+            target_update(L, td, C, ok, j, d, tx, ty, INFINITY);
         }
     }
     {
@@ -673,9 +771,10 @@ __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, 
                 int j = 0;
                 double d = 0, tx = 0, ty = 0;
                 if (q < q1) {
-                    j = sd.forder[q];
-                    if (j != src) {
-                        const double *b = sd.bary + 3 * (int64_t)j;
+                    const FaceTarget tg = sd.ftgt[q];
+                    j = q;
+                    if (tg.j != src) {
+                        const double *b = sd.bary + 3 * (int64_t)tg.j;
                         const double qx = b[(m + 1) % 3] * Rt.L + b[(m + 2) % 3] * Rt.cx;
                         const double qy = b[(m + 2) % 3] * Rt.cy;
                         double dx = qx - ptx, dy = qy;
@@ -690,7 +789,7 @@ __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, 
                     }
                     ++q;
                 }
-                target_update(L, td, tt, C, ok, j, d, tx, ty, INFINITY);
+                target_update(L, td, C, ok, j, d, tx, ty, INFINITY);
             }
             const double dx = Rt.cx - ptx, dy = Rt.cy;
             const double d = sqrt(dx * dx + dy * dy);
@@ -707,27 +806,28 @@ __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, 
     // ---- propagation, round by round
     bool have = false;
     Win<R> w;
+    double DA = INFINITY, DB = INFINITY;  // vertex distances of the window's half-edge (infinite: not read yet)
     unsigned long long nwin = 0;
     int pruned = 0, depth = 0;
     for (;;) {
         if (__ballot(overflow)) overflow = true;
         if (overflow) break;
-        depth = max(depth, S.lsp + S.gsp + S.dsp);
+        depth = max(depth, S.lsp + S.gsp + S.dsp + S.dl);
         bool busy = S.refill(have, w);
         if (!busy && L.B.npend > 0) {
-            launch_roots(a, sd, L, G, td, tt, Dv, C, S, T, src, st);
+            launch_roots(a, sd, L, G, td, Dv, C, S, T, src, st);
             busy = S.refill(have, w);
         }
         if (!busy) {
-            if (S.dsp == 0 && L.B.npend == 0) break;
+            if (S.dsp + S.dl == 0 && L.B.npend == 0) break;
             // next round; once every target is reached, bound the keys
-            S.next_round();
+            S.next_round(overflow);
             T += C.bucket;
             if (L.unfound == 0) {
                 __syncthreads();  // every lane's target stores are visible
                 double mx = 0.0;
-                for (int j = lane; j < n; j += kWave)
-                    if (j != src) mx = fmax(mx, td[j].x);
+                for (int q = lane; q < n; q += kWave)
+                    if (sd.ftgt[q].j != src) mx = fmax(mx, td[q].d1);
                 for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o));
                 if (lane == 0) L.maxb = fmin(L.maxb, mx * (1.0 + C.tie_rel) + 1e-12 * mx);
             }
@@ -739,128 +839,173 @@ __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, 
             overflow = true;
             break;
         }
-        // stale: from an earlier launch of its root, or a new launch is due
-        if (have && w.root >= 0 && bend_stale(G.rD[w.root], G.rL[w.root], w, C.rc)) {
-            have = false;
-            ++st.stale;
-        }
+        // Three rounds of loads an iteration, each issued as a whole: the
+        // records that the window names (half-edge and its entry, the face's
+        // first target, the root's entry), then what those name (vertex
+        // distances, the target, the third vertex's number), then the third
+        // vertex's bend entry, which the children's arithmetic covers.
         He<R> H;
+        int vA = 0, vB = 0, q0 = -1;
+        bool act = have;
         double txc = 0.0;
-        int f = -1, k = 0, vA = 0, vB = 0;
-        if (have) {
-            f = w.he / 3;
-            k = w.he % 3;
-            H = load_he(M, w.he, R(0));
+        int k = 0;
+        double wtx = 0.0, wty = 0.0, wD2 = INFINITY;  // the root's tangent and other-direction distance
+        unsigned long long hw = ~0ull;
+        if (act) {
+            const int f = w.he / 3;
+            k = w.he - 3 * f;
+            H = load_he(he, hef, w.he, R(0));
             vA = he[w.he].tail;
             vB = he[w.he].head;
-            txc = (double)w.px + ((double)H.cx - (double)w.px) * (-(double)w.py) / ((double)H.cy - (double)w.py);
+            q0 = ffirst[f];
+            if (Hv) hw = Hv[w.he];
+            double rD = 0.0, rL = INFINITY;
+            if (w.root >= 0) {
+                rD = G.rD[w.root];
+                rL = G.rL[w.root];
+                wtx = G.rtx[w.root];
+                wty = G.rty[w.root];
+                wD2 = G.rD2[w.root];
+                // stale: from an earlier launch of its root, or a new launch is due
+                if (bend_stale(rD, rL, w, C.rc)) {
+                    act = have = false;
+                    ++st.stale;
+                }
+            }
+            if (!act) {
+                q0 = -1;
+                DA = DB = INFINITY;
+            }
         }
-        // vertices of the face reached through this window: the table's
-        // values are read first (independent loads) and combined with this
-        // window's own paths, which then go to the table
-        double DA = INFINITY, DB = INFINITY, DC = INFINITY;
-        bool cin = false;
-        double dcv = 0.0;
-        if (have) {
-            DA = Dv[vA];
-            DB = Dv[vB];
+        double DC = INFINITY;
+        bool cin = false, go_l = false, go_r = false;
+        double dcv = 0.0, xa = 0.0, xb = 0.0;
+        int eo = -1;
+        FaceTarget t0{{0.0, 0.0, 0.0}, -1, 0};  // none
+        TgtState c0;
+        if (act) {
+            // a lane that goes on with a child has the distances of the
+            // half-edge's ends from the parent's face
+            if (!(DA < INFINITY)) DA = Dv[vA];
+            if (!(DB < INFINITY)) DB = Dv[vB];
             DC = Dv[H.opp];
+            if (q0 >= 0) {
+                t0 = ftgt[q0];
+                c0 = td[q0];
+            }
+            if (H.pseudo) eo = pidx[H.opp];
             const double px = w.px, py = w.py, sg = w.sg;
-            if ((double)w.b0 <= 0.0) {
-                const double d = sg + sqrt(px * px + py * py);
-                if (d < DA) {
-                    DA = d;
-                    vdist_min(Dv, vA, d);
-                }
-            }
-            if ((double)w.b1 >= (double)H.L) {
-                const double d = sg + sqrt((H.L - px) * (H.L - px) + py * py);
-                if (d < DB) {
-                    DB = d;
-                    vdist_min(Dv, vB, d);
-                }
-            }
+            txc = px + ((double)H.cx - px) * (-py) / ((double)H.cy - py);
             const double sl = C.tol * (double)H.L;
             cin = txc >= (double)w.b0 - sl && txc <= (double)w.b1 + sl;
-            if (cin) {
+            go_l = H.tp >= 0 && (double)w.b0 < txc;
+            go_r = H.tn >= 0 && (double)w.b1 > txc;
+            // the first child's interval, while the loads above are on their way
+            if (Hv && cin) {
                 const double dx = (double)H.cx - px, dy = (double)H.cy - py;
                 dcv = sg + sqrt(dx * dx + dy * dy);
-                if (dcv < DC) {
-                    DC = dcv;
-                    vdist_min(Dv, H.opp, dcv);
+                const int sides = one_split(Hv, w.he, hw, dcv, txc, (double)H.L, C.split_rel);
+                go_l = go_l && (sides & 1);
+                go_r = go_r && (sides & 2);
+            }
+            far_ends(H, w, txc, go_l, xa, xb);
+            // vertices of the face reached through this window: the table's
+            // values are combined with this window's own paths, which then go
+            // to the table (compared in squares first: few are shorter)
+            const double rA = px * px + py * py, rB = ((double)H.L - px) * ((double)H.L - px) + py * py;
+            if ((double)w.b0 <= 0.0 && !longer(rA, DA - sg)) {
+                DA = fmin(DA, sg + sqrt(rA));
+                vdist_min(Dv, vA, DA);
+            }
+            if ((double)w.b1 >= (double)H.L && !longer(rB, DB - sg)) {
+                DB = fmin(DB, sg + sqrt(rB));
+                vdist_min(Dv, vB, DB);
+            }
+            if (cin) {
+                const double dx = (double)H.cx - px, dy = (double)H.cy - py;
+                const double rC = dx * dx + dy * dy;
+                if (!Hv) dcv = sg + sqrt(rC);
+                if (!longer(rC, DC - sg)) {
+                    DC = fmin(DC, dcv);
+                    vdist_min(Dv, H.opp, DC);
                 }
             }
         }
-        query_face(sd, L, G, td, tt, C, have, src, f, k, H, w);
-        // third vertex as a bend vertex
+        query_face(ftgt, L, td, C, q0, src, k, H, w, wtx, wty, wD2, t0, c0);
+        // third vertex as a bend vertex: its entry is loaded here and updated
+        // after the children
+        const bool ok3 = eo >= 0 && cin;
+        BendEntry e3;
+        if (ok3) e3 = bend_load(G, eo);
+        // children, trimmed against the vertex paths and bounded by maxb. One
+        // body serves both sides, its constants selected per lane: nearly
+        // every window has one child, on either side, and the few with two
+        // (the third vertex in their cone) run it again for the right one.
+        Win<R> c1, c2;
+        bool h1 = false, h2 = false;
+        bool l1 = false, l2 = false;  // left for the next round
+        const double maxb = L.maxb;
+        auto child = [&](bool left, double x0, double x1, Win<R> &c, bool &hc, bool &lc) {
+            const double hcx = H.cx, hcy = H.cy, hL = H.L;
+            const double Lc = left ? (double)H.Lp : (double)H.Ln;
+            // the child frame: axis (ax, ay), origin A (left: edge A -> C, S =
+            // A, E = C) or C (right: edge C -> B, S = C, E = B)
+            const R ax = left ? H.ex : H.ux, ay = left ? H.ey : H.uy;
+            const R qx = left ? w.px : w.px - H.cx, qy = left ? w.py : w.py - H.cy;
+            c.px = ax * qx + ay * qy;
+            c.py = ax * qy - ay * qx;
+            c.sg = w.sg;
+            c.c = w.c * ax - w.s * ay;
+            c.s = w.s * ax + w.c * ay;
+            c.he = left ? H.tp : H.tn;
+            c.root = w.root;
+            const double DS = left ? DA : DC, DE = left ? DC : DB, DO = left ? DB : DA;
+            // the face's remaining vertex (B or A) in the child frame
+            const double rx = left ? hL : -hcx, ry = left ? 0.0 : -hcy;
+            const double ox = (double)ax * rx + (double)ay * ry, oy = (double)ax * ry - (double)ay * rx;
+            const double cpx = c.px, cpy = c.py, sg = c.sg;
+            double r0 = (x0 - cpx) * (x0 - cpx) + cpy * cpy, r1 = (x1 - cpx) * (x1 - cpx) + cpy * cpy;
+            if (vertex_trim(cpx, cpy, sg, Lc, DS, DE, C.dom_rel, x0, x1, r0, r1) &&
+                !opposite_dominates(ox, oy, DO, sg, C.dom_rel, x0, x1, r0, r1)) {
+                c.b0 = (R)x0;
+                c.b1 = (R)x1;
+                // the child's key (its smallest distance) against the bound
+                // and the round's threshold
+                const double rk = cpx < x0 ? r0 : cpx > x1 ? r1 : cpy * cpy;
+                hc = !longer(rk, maxb - sg);
+                lc = T <= sg || rk >= (T - sg) * (T - sg);
+            }
+            if (!hc) ++pruned;
+        };
+        if (go_l || go_r) child(go_l, xa, xb, c1, h1, l1);
+        if (go_l && go_r) {
+            far_ends(H, w, txc, false, xa, xb);
+            child(false, xa, xb, c2, h2, l2);
+        }
         {
-            bool ok = have && H.pseudo && cin;
-            double tx = 0, ty = 0, alt = INFINITY;
-            if (ok) {
+            double tx = wtx, ty = wty, alt = INFINITY;
+            if (ok3) {
                 if (w.root < 0) {
                     R dx = H.cx - w.px, dy = H.cy - w.py;
                     const R l = sqrt(dx * dx + dy * dy);
                     tx = (double)(w.c * (dx / l) - w.s * (dy / l));
                     ty = (double)(w.s * (dx / l) + w.c * (dy / l));
                 } else {
-                    tx = G.rtx[w.root];
-                    ty = G.rty[w.root];
-                    alt = G.rD2[w.root] + (dcv - (double)w.sg);
+                    alt = wD2 + (dcv - (double)w.sg);
                 }
             }
-            const int eo = ok ? M.pidx[H.opp] : -1;
-            bend_update(G, L.B, C.rc, ok, eo, dcv, tx, ty, alt);
-        }
-        // children, trimmed against the vertex paths and bounded by maxb
-        Win<R> cl, cr;
-        bool hl = false, hr = false;
-        double kl = 0, kr = 0;
-        if (have) {
-            const double maxb = L.maxb;
-            if (H.tp >= 0 && (double)w.b0 < txc) {
-                double x0, x1;
-                child_left(H, w, txc, false, x0, x1);
-                make_left(H, w, x0, x1, cl);
-                // edge A -> C: S = A, E = C; the face's third vertex B sits at
-                // (ex L, -ey L) in the child frame
-                double f0, f1;
-                if (x1 - x0 > 1e-12 * (double)H.Lp &&
-                    vertex_trim(cl.px, cl.py, cl.sg, H.Lp, DA, DC, C.dom_rel, x0, x1, f0, f1) &&
-                    !opposite_dominates((double)H.ex * (double)H.L, -(double)H.ey * (double)H.L, DB, C.dom_rel, x0,
-                                        x1, f0, f1)) {
-                    cl.b0 = (R)x0;
-                    cl.b1 = (R)x1;
-                    kl = child_key(cl, f0, f1);
-                    hl = kl < maxb;
-                }
-                if (!hl) ++pruned;
-            }
-            if (H.tn >= 0 && (double)w.b1 > txc) {
-                double x0, x1;
-                child_right(H, w, txc, false, x0, x1);
-                make_right(H, w, x0, x1, cr);
-                // edge C -> B: S = C, E = B; the third vertex A sits at
-                // (-ux cx - uy cy, uy cx - ux cy) in the child frame
-                const double ux = H.ux, uy = H.uy, hcx = H.cx, hcy = H.cy;
-                double f0, f1;
-                if (x1 - x0 > 1e-12 * (double)H.Ln &&
-                    vertex_trim(cr.px, cr.py, cr.sg, H.Ln, DC, DB, C.dom_rel, x0, x1, f0, f1) &&
-                    !opposite_dominates(-ux * hcx - uy * hcy, uy * hcx - ux * hcy, DA, C.dom_rel, x0, x1, f0, f1)) {
-                    cr.b0 = (R)x0;
-                    cr.b1 = (R)x1;
-                    kr = child_key(cr, f0, f1);
-                    hr = kr < maxb;
-                }
-                if (!hr) ++pruned;
-            }
+            bend_update_loaded(G, L.B, C.rc, ok3, eo, dcv, tx, ty, alt, e3);
         }
         // children of the next round wait; of the two of this round, the lane keeps one
-        const bool keep_l = hl && kl < T, keep_r = hr && kr < T;
-        S.push(hl && !(keep_l), kl >= T, cl, overflow);
-        S.push(hr && (keep_l || !keep_r), kr >= T, cr, overflow);
-        if (have) {
-            if (keep_l) w = cl;
-            else if (keep_r) w = cr;
+        const bool keep1 = h1 && !l1, keep2 = h2 && !l2;
+        S.push(h1 && !keep1, true, c1, overflow);
+        S.push(h2 && (keep1 || !keep2), l2, c2, overflow);
+        if (act) {
+            // the kept child's half-edge runs A -> C (left) or C -> B
+            DA = keep1 && go_l ? DA : keep1 || keep2 ? DC : INFINITY;
+            DB = keep1 && go_l ? DC : keep1 || keep2 ? DB : INFINITY;
+            if (keep1) w = c1;
+            else if (keep2) w = c2;
             else have = false;
         }
     }
@@ -880,20 +1025,20 @@ __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, 
     const int64_t c0 = (int64_t)src * sd.cap;
     bool near_cut = false;
     __syncthreads();  // every lane's tangent stores are visible
-    for (int j = lane; j < n; j += kWave) {
+    for (int q = lane; q < n; q += kWave) {
+        const int j = sd.ftgt[q].j;
         const int64_t o = c0 + j;
-        const double2 dd = td[j];
-        double d = dd.x;
+        const TgtState t = td[q];
+        double d = t.d1;
         uint8_t fl = guard ? GSIM_PAIR_GUARD_BIT : 0;
         if (j == src) d = INFINITY;
         else if (ovf) d = NAN;
-        if (j != src && dd.y - d <= C.tie_rel * d) fl |= GSIM_PAIR_TIE_BIT;
+        if (j != src && t.d2 - d <= C.tie_rel * d) fl |= GSIM_PAIR_TIE_BIT;
         if (d == 0.0) fl |= GSIM_PAIR_ZERO_BIT;
         near_cut |= C.cutoff < INFINITY && fabs(d - C.cutoff) <= a.gp.guard_rel * C.cutoff;
         sd.cdist[o] = d;
         sd.cflags[o] = fl;
-        const double2 t = tt[j];
-        for (int qd = 0; qd < 3; ++qd) sd.ctan[3 * o + qd] = t.x * ex3[qd] + t.y * ey3[qd];
+        for (int qd = 0; qd < 3; ++qd) sd.ctan[3 * o + qd] = t.tx * ex3[qd] + t.ty * ey3[qd];
     }
     if (sd.prof && lane == 0) {
         long long *qp = sd.prof + 8 * (int64_t)src;
@@ -908,10 +1053,11 @@ __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, 
 }
 
 template <bool kMixed, int kStk>
-__global__ __launch_bounds__(kWave) void k_geodesic_all(AllArgs a) {
+__global__ __launch_bounds__(kWave, 2) void k_geodesic_all(AllArgs a) {
     __shared__ AllLds L;
     __shared__ alignas(16) unsigned char stk[kStk];
-    double2 *td = a.ttab + (size_t)blockIdx.x * 2 * a.tcap, *tt = td + a.tcap;
+    __shared__ alignas(16) unsigned char later[kWave * sizeof(Rec64)];
+    TgtState *td = a.ttab + (size_t)blockIdx.x * a.tcap;
     const int lane = lane_id();
     const int total = a.bi.begin[a.bi.nsurf];
     int chunk = blockIdx.x % kChunks, chunks_left = kChunks;
@@ -948,11 +1094,11 @@ __global__ __launch_bounds__(kWave) void k_geodesic_all(AllArgs a) {
         if (lane == 0) sd.cand_cnt[src] = sd.n;
         st.overflow = false;
         bool again = !kMixed;
-        if (kMixed) again = run_all<float>(a, sd, L, td, tt, stk, kStk, src, blockIdx.x, false, st);
+        if (kMixed) again = run_all<float>(a, sd, L, td, stk, kStk, later, src, blockIdx.x, false, st);
         if (again) {
             // FP64 (the plain path, or the recompute of an FP32 source whose
             // results come too close to the cutoff to decide in FP32)
-            run_all<double>(a, sd, L, td, tt, stk, kStk, src, blockIdx.x, kMixed, st);
+            run_all<double>(a, sd, L, td, stk, kStk, later, src, blockIdx.x, kMixed, st);
             st.guards += kMixed ? 1 : 0;
         }
         if (st.overflow) ++c_limited;
@@ -991,9 +1137,11 @@ void launch_variant(int kb, int nslots, const AllArgs &a, hipStream_t s) {
 
 hipError_t launch_geodesic_all(const SurfDesc *desc, const BatchIdx &bi, const GeoParams &gp, const GeoShape &shape,
                                char *stack_mem, double *vdist, int64_t vstride, char *roots, int64_t rstride,
-                               int rcap, double2 *ttab, int tcap, int32_t *work_ctr, Counters *ctr, bool fp32,
-                               hipStream_t s) {
+                               int rcap, void *ttab, int tcap, unsigned long long *split, int64_t hstride,
+                               int32_t *work_ctr, Counters *ctr, bool fp32, hipStream_t s) {
     AllArgs a;
+    a.split = split;
+    a.hstride = hstride;
     a.sd = desc;
     a.bi = bi;
     a.gp = gp;
@@ -1008,7 +1156,7 @@ hipError_t launch_geodesic_all(const SurfDesc *desc, const BatchIdx &bi, const G
     a.tcap = tcap;
     a.grab = shape.grab < 1 ? 1 : shape.grab;
     if (shape.nslots < 1 || bi.begin[bi.nsurf] < 1) return hipSuccess;
-    a.ttab = ttab;
+    a.ttab = static_cast<TgtState *>(ttab);
     if (fp32) launch_variant<true>(shape.lds_stack_kb, shape.nslots, a, s);
     else launch_variant<false>(shape.lds_stack_kb, shape.nslots, a, s);
     return hipGetLastError();

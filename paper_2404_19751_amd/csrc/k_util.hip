@@ -104,11 +104,6 @@ __global__ void k_scan_final(const int32_t *__restrict__ in, int n, const int64_
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) out[n] = part[gridDim.x];
 }
 
-__global__ void k_i64_to_i32(const int64_t *in, int32_t *out, int n) {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i <= n) out[i] = int32_t(in[i]);
-}
-
 // ------------------------------------------------------------ prefilter
 __device__ inline void cell_coords(const double *x, const PrefilterBufs &b, const double *bbmin, int c[3]) {
     for (int d = 0; d < 3; ++d) {
@@ -428,13 +423,24 @@ __global__ void k_face_count(int n, const int32_t *__restrict__ face, int32_t *_
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) atomicAdd(&counts[face[i]], 1);
 }
-__global__ void k_face_scatter(int n, const int32_t *__restrict__ face, const int32_t *__restrict__ fstart,
-                               int32_t *__restrict__ counts, int32_t *__restrict__ forder) {
+__global__ void k_face_scatter(int n, const int32_t *__restrict__ face, const double *__restrict__ bary,
+                               const int32_t *__restrict__ fstart, int32_t *__restrict__ counts,
+                               FaceTarget *__restrict__ ftgt) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) {
         const int f = face[i];
-        forder[fstart[f] + atomicAdd(&counts[f], 1)] = i;
+        const int64_t b = 3 * (int64_t)i;
+        const int pos = fstart[f] + atomicAdd(&counts[f], 1);
+        ftgt[pos] = FaceTarget{{bary[b], bary[b + 1], bary[b + 2]}, i, pos + 1 < fstart[f + 1] ? 1 : 0};
     }
+}
+// int32 starts of the faces' ranges, and the first particle of each face (-1: none)
+__global__ void k_face_starts(const int64_t *__restrict__ in, int32_t *__restrict__ fstart,
+                              int32_t *__restrict__ ffirst, int nf) {
+    const int f = blockIdx.x * blockDim.x + threadIdx.x;
+    if (f > nf) return;
+    fstart[f] = (int32_t)in[f];
+    if (f < nf) ffirst[f] = in[f + 1] > in[f] ? (int32_t)in[f] : -1;
 }
 __global__ void k_identity_rows(int n, int cap, int32_t *__restrict__ cand_cnt, int32_t *__restrict__ cand) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -595,10 +601,6 @@ hipError_t launch_fill_u64(unsigned long long *p, int64_t n, unsigned long long 
     hipLaunchKernelGGL(k_fill_u64, dim3(nblocks(n)), dim3(kBlock), 0, s, p, n, v);
     return hipGetLastError();
 }
-hipError_t launch_i64_to_i32(const int64_t *in, int32_t *out, int n, hipStream_t s) {
-    hipLaunchKernelGGL(k_i64_to_i32, dim3(nblocks(n + 1)), dim3(kBlock), 0, s, in, out, n);
-    return hipGetLastError();
-}
 
 hipError_t launch_count_rows(int n, const int32_t *cnt, int cap_c, const double *dist, double cutoff, int32_t *out,
                              hipStream_t s) {
@@ -656,9 +658,10 @@ hipError_t launch_face_sort(const SurfDesc &d, int32_t *counts, int64_t *tmp64, 
     if ((e = launch_zero_i32(counts, nf, s)) != hipSuccess) return e;
     hipLaunchKernelGGL(k_face_count, dim3(nblocks(n)), dim3(kBlock), 0, s, n, d.face, counts);
     if ((e = launch_scan_i32_to_i64(counts, tmp64, nf, scan_scratch, s)) != hipSuccess) return e;
-    if ((e = launch_i64_to_i32(tmp64, d.fstart, nf, s)) != hipSuccess) return e;
+    hipLaunchKernelGGL(k_face_starts, dim3(nblocks(nf + 1)), dim3(kBlock), 0, s, tmp64, d.fstart, d.ffirst, nf);
     if ((e = launch_zero_i32(counts, nf, s)) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_face_scatter, dim3(nblocks(n)), dim3(kBlock), 0, s, n, d.face, d.fstart, counts, d.forder);
+    hipLaunchKernelGGL(k_face_scatter, dim3(nblocks(n)), dim3(kBlock), 0, s, n, d.face, d.bary,
+                       d.fstart, counts, d.ftgt);
     return hipGetLastError();
 }
 hipError_t launch_identity_rows(int n, int cap, int32_t *cand_cnt, int32_t *cand, hipStream_t s) {

@@ -82,14 +82,31 @@ struct He {
     int tn, tp, opp;
     bool pseudo;
 };
-__device__ inline He<double> load_he(const DevMesh &m, int h, double) {
-    const HeRec r = m.he[h];
+__device__ inline He<double> load_he(const HeRec *he, const HeRecF *, int h, double) {
+    const HeRec r = he[h];
     return {r.L, r.cx, r.cy, r.Lp, r.Ln, r.ex, r.ey, r.ux, r.uy, r.tn, r.tp, r.opp_flags >> 1, (r.opp_flags & 1) != 0};
 }
-__device__ inline He<float> load_he(const DevMesh &m, int h, float) {
-    const HeRecF r = m.hef[h];
+__device__ inline He<float> load_he(const HeRec *, const HeRecF *hef, int h, float) {
+    const HeRecF r = hef[h];
     return {r.L, r.cx, r.cy, r.Lp, r.Ln, r.ex, r.ey, r.ux, r.uy, r.tn, r.tp, r.opp_flags >> 1,
             (r.opp_flags & 1) != 0};
+}
+
+template <typename R>
+__device__ inline He<R> load_he(const DevMesh &m, int h, R r) {
+    return load_he(m.he, m.hef, h, r);
+}
+// A wave-uniform pointer in scalar registers. Fields of the surface
+// descriptor that a loop uses are taken out of it once this way: the
+// compiler cannot know that the loop's stores leave the descriptor alone, so
+// it would load each again from memory at every use, and whatever the
+// pointer is needed for waits for that load first.
+template <typename T>
+__device__ inline T *uniform(T *p) {
+    const unsigned long long b = reinterpret_cast<unsigned long long>(p);
+    const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)b);
+    const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(b >> 32));
+    return reinterpret_cast<T *>(((unsigned long long)hi << 32) | lo);
 }
 
 __device__ inline int lane_id() { return threadIdx.x; }
