@@ -109,6 +109,13 @@ __device__ inline T *uniform(T *p) {
     return reinterpret_cast<T *>(((unsigned long long)hi << 32) | lo);
 }
 
+__device__ inline double uniform(double x) {
+    const unsigned long long b = (unsigned long long)__double_as_longlong(x);
+    const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)b);
+    const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(b >> 32));
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
 __device__ inline int lane_id() { return threadIdx.x; }
 // Ends one step of a loop that applies the lanes' updates to a shared table
 // one lane at a time: the next lane's loads must see this lane's stores. To
@@ -180,8 +187,24 @@ struct BendLds {
     int32_t sface[8];  // the faces of the wavefront's sources (cutoff kernel)
     int32_t sel[kLaunchChunk];       // bend vertices of the chunk
     int32_t pref[kLaunchChunk + 1];  // prefix sums of their fan sizes
+    uint8_t win[256];                // claim
 };
 
+// Updates of a table by many lanes at once run in rounds: each lane still to
+// do writes its number to the table `win` at its entry's low bits and reads
+// back who won; the winners, all on different entries, apply their updates
+// together, the others go on from the winner's result (when it is their
+// entry's) in the next round. Two LDS accesses a round, however many lanes
+// take part; comparing the lanes' entries one by one had cost 50 cycles a
+// lane. claim returns the winner (the lane itself when it has nothing to do).
+constexpr int kWinners = 256;
+__device__ inline int claim(uint8_t *win, bool todo, int e) {
+    if (todo) win[e & (kWinners - 1)] = (uint8_t)lane_id();
+    lane_step_barrier();
+    const int w = todo ? win[e & (kWinners - 1)] : lane_id();
+    lane_step_barrier();
+    return w;
+}
 // Bend-vertex update (insert or improve): keep the smallest distance and
 // its tangent, and the smallest distance of a path in another initial
 // direction (directions closer than tie_dir count as one); `alt` is such a
@@ -193,8 +216,8 @@ struct BendLds {
 // reached through the vertex then learns the new tangent or the tie.
 // The lanes load their entries together and leave when their candidate
 // cannot change anything (the stored distances only decrease); the others
-// are applied one lane at a time in registers, each result passed to every
-// lane holding the same vertex, and written back once.
+// are applied in registers, lanes with the same vertex one after another (in
+// rounds).
 // bend_update_loaded takes the entry loaded by the caller (bend_load,
 // earlier, so that its latency overlaps other work; no other update of the
 // table may come in between).
@@ -234,50 +257,11 @@ __device__ inline void bend_update_loaded(const BendTable &G, BendLds &L, const 
     if (!m) return;
     // list lengths, wave-uniform in registers
     int np = L.npend, nt = L.ntouched;
-    // The usual case: every lane holds a different entry, so each update is
-    // the lane's own, and they run at once (the lists are appended in lane
-    // order, as one lane at a time would). Otherwise one lane at a time,
-    // each result passed on to the lanes holding the same entry.
-    bool dup = false;
-    for (uint64_t r = m; r; r &= r - 1) {
-        const int l = __ffsll((unsigned long long)r) - 1;
-        dup |= ok && e == __builtin_amdgcn_readlane(e, l) && lane_id() != l;
-    }
-    if (!__ballot(dup)) {
+    for (bool todo = ok; m;) {
+        const int w = m & (m - 1) ? claim(L.win, todo, e) : lane_id();  // one lane alone: no contest
+        const bool mine = todo && w == lane_id();
         int app = 0, fresh = 0;
-        if (ok) {
-            fresh = !(cD < INFINITY);
-            const bool differ = fabs(ax * ty - ay * tx) > rc.tie_dir || ax * tx + ay * ty < 0.0;
-            const bool tied = cD2 - cD <= rc.tie_rel * cD;
-            if (d < cD) {
-                if (differ) {
-                    cD2 = fmin(cD2, cD);
-                    cL = INFINITY;
-                }
-                cD = d;
-                ax = tx;
-                ay = ty;
-            } else if (differ) {
-                cD2 = fmin(cD2, d);
-            }
-            cD2 = fmin(cD2, alt);
-            if (!tied && cD2 - cD <= rc.tie_rel * cD) cL = INFINITY;
-            if (cD < cL * rc.keep && !qd) {
-                qd = 1;
-                app = 1;
-            }
-        }
-        const uint64_t ma = __ballot(app), mf = __ballot(fresh);
-        if (app) G.pend[np + __popcll(ma & lanemask_lt())] = e;
-        if (fresh) G.touched[nt + __popcll(mf & lanemask_lt())] = e;
-        np += __popcll(ma);
-        nt += __popcll(mf);
-        m = 0;
-    }
-    while (m) {
-        const int l = __ffsll((unsigned long long)m) - 1;
-        int app = 0, fresh = 0;
-        if (lane_id() == l) {
+        if (mine) {
             // a fresh entry has cD = cL = cD2 = infinity: every branch below then inserts
             fresh = !(cD < INFINITY);
             const bool differ = fabs(ax * ty - ay * tx) > rc.tie_dir || ax * tx + ay * ty < 0.0;
@@ -298,33 +282,36 @@ __device__ inline void bend_update_loaded(const BendTable &G, BendLds &L, const 
             if (cD < cL * rc.keep && !qd) {
                 qd = 1;
                 app = 1;
-                G.pend[np] = e;
             }
-            if (fresh) G.touched[nt] = e;
         }
-        np += __builtin_amdgcn_readlane(app, l);
-        nt += __builtin_amdgcn_readlane(fresh, l);
-        const int el = __builtin_amdgcn_readlane(e, l);
-        const double bD = readlane_d(cD, l), bD2 = readlane_d(cD2, l), bL = readlane_d(cL, l);
-        const double bx = readlane_d(ax, l), by = readlane_d(ay, l);
-        const int bq = __builtin_amdgcn_readlane(qd, l);
-        if (ok && e == el) {
-            cD = bD;
-            cD2 = bD2;
-            cL = bL;
-            ax = bx;
-            ay = by;
-            qd = bq;
+        const uint64_t ma = __ballot(app), mf = __ballot(fresh);
+        if (app) G.pend[np + __popcll(ma & lanemask_lt())] = e;
+        if (fresh) G.touched[nt + __popcll(mf & lanemask_lt())] = e;
+        np += __popcll(ma);
+        nt += __popcll(mf);
+        if (mine) {
+            G.rD[e] = cD;
+            G.rD2[e] = cD2;
+            G.rL[e] = cL;
+            G.rtx[e] = ax;
+            G.rty[e] = ay;
+            G.queued[e] = qd;
         }
-        m &= m - 1;
-    }
-    if (ok) {
-        G.rD[e] = cD;
-        G.rD2[e] = cD2;
-        G.rL[e] = cL;
-        G.rtx[e] = ax;
-        G.rty[e] = ay;
-        G.queued[e] = qd;
+        todo = todo && !mine;
+        m = __ballot(todo);
+        if (m) {
+            const double wD = __shfl(cD, w), wD2 = __shfl(cD2, w), wL = __shfl(cL, w);
+            const double wx = __shfl(ax, w), wy = __shfl(ay, w);
+            const int wq = __shfl(qd, w), we = __shfl(e, w);
+            if (todo && we == e) {
+                cD = wD;
+                cD2 = wD2;
+                cL = wL;
+                ax = wx;
+                ay = wy;
+                qd = wq;
+            }
+        }
     }
     if (lane_id() == 0) {
         L.npend = np;
