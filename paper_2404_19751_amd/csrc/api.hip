@@ -78,7 +78,12 @@ struct gsim_ctx {
     std::string err;
     std::vector<MeshState *> meshes;
     Buf stack, work, ctr, wstats, scan_scratch, sum_scratch, pf_over, prof, desc, vdist, ttab, roots, partials, vbits, split;
-    Buf gtab;  // big-candidate target arrays of the resident wavefronts
+    // near passes: target areas, vertex and half-edge entries and epochs of the
+    // resident wavefronts, and the layout they were last prepared for
+    Buf near_t, near_v, near_h, near_e;
+    void *near_p[4] = {};
+    int64_t near_layout[3] = {};  // tcap, vstride, hstride
+    int near_slots = 0;
     SurfDesc *desc_pinned = nullptr;  // staging for descriptor uploads
     std::vector<SurfDesc> desc_cached;
     bool profile_sources = false;
@@ -511,16 +516,10 @@ gsim_status prepare_surface(gsim_ctx *c, const Member &mb, bool small, int src_b
     HIPCHK(c, ensure(ms->cflags, (size_t)n * cap));
     HIPCHK(c, ensure(ms->tmp64, sizeof(int64_t) * (std::max<int64_t>(ncell, n) + 1)));
     HIPCHK(c, ensure(ms->wflags, n));
-    const int64_t nscan = std::max<int64_t>(std::max<int64_t>(ncell, n), all ? m.nf : 0);
-    HIPCHK(c, ensure(ms->tmp64, sizeof(int64_t) * (nscan + 1)));
-    HIPCHK(c, ensure(c->scan_scratch, sizeof(int64_t) * ((nscan + 1023) / 1024 + 2)));
+    HIPCHK(c, ensure(c->scan_scratch, sizeof(int64_t) * ((std::max<int64_t>(ncell, n) + 1023) / 1024 + 2)));
     HIPCHK(c, ensure(ms->F, sizeof(double) * 3 * n));
     HIPCHK(c, ensure(ms->fire, sizeof(FireState)));
     if (all) {
-        HIPCHK(c, ensure(ms->fstart, sizeof(int32_t) * (m.nf + 1)));
-        HIPCHK(c, ensure(ms->ffirst, sizeof(int32_t) * m.nf));
-        HIPCHK(c, ensure(ms->ftgt, sizeof(FaceTarget) * n));
-        HIPCHK(c, ensure(ms->fcount, sizeof(int32_t) * m.nf));
         if (ms->ident_n != n || ms->cap != (int)cap) {
             HIPCHK(c, launch_identity_rows(n, (int)cap, P<int32_t>(ms->cand_cnt), P<int32_t>(ms->cand), c->stream));
             ms->ident_n = n;
@@ -542,9 +541,6 @@ gsim_status prepare_surface(gsim_ctx *c, const Member &mb, bool small, int src_b
     for (int k = 0; k < 3; ++k) d.lo[k] = m.bbmin[k];
     d.cap = (int)cap;
     d.all_pairs = all ? 1 : 0;
-    d.fstart = all ? P<int32_t>(ms->fstart) : nullptr;
-    d.ffirst = all ? P<int32_t>(ms->ffirst) : nullptr;
-    d.ftgt = all ? P<FaceTarget>(ms->ftgt) : nullptr;
     d.cand_cnt = P<int32_t>(ms->cand_cnt);
     d.cand = P<int32_t>(ms->cand);
     d.cdist = P<double>(ms->cdist);
@@ -588,6 +584,22 @@ gsim_status prepare_surface(gsim_ctx *c, const Member &mb, bool small, int src_b
     return GSIM_OK;
 }
 
+// The particles-by-face index of one surface of a whole-mesh or near pass.
+gsim_status prepare_face_index(gsim_ctx *c, MeshState *ms, SurfDesc &d) {
+    const size_t nf = (size_t)ms->dm.nf;
+    HIPCHK(c, ensure(ms->fstart, sizeof(int32_t) * (nf + 1)));
+    HIPCHK(c, ensure(ms->ffirst, sizeof(int32_t) * nf));
+    HIPCHK(c, ensure(ms->ftgt, sizeof(FaceTarget) * (size_t)ms->n));
+    const void *was = ms->fcount.p;
+    HIPCHK(c, ensure(ms->fcount, sizeof(int32_t) * nf));
+    if (ms->fcount.p != was) HIPCHK(c, launch_zero_i32(P<int32_t>(ms->fcount), (int64_t)nf, c->stream));
+    d.fstart = P<int32_t>(ms->fstart);
+    d.ffirst = P<int32_t>(ms->ffirst);
+    d.ftgt = P<FaceTarget>(ms->ftgt);
+    d.fcount = P<int32_t>(ms->fcount);
+    return GSIM_OK;
+}
+
 struct Batch {
     std::vector<Member> mem;
     std::vector<SurfDesc> desc;
@@ -602,8 +614,8 @@ struct Batch {
     int32_t rcap = 0;     // its capacity (bend vertices)
     bool small = true;  // every surface bins in one workgroup
     bool fused = false; // time steps move the particles inside the cutoff kernel
-    bool big = false;   // some surface has more candidates per source than the LDS table holds
-    int gcap = 0;       // its widest row (big-candidate target arrays per wavefront)
+    bool near = false;  // a cutoff pass by whole-mesh propagation (many targets within the cutoff)
+    BatchIdx face_blk{};  // blocks of kFaceBlock faces per surface (particles-by-face index)
     int group = 1;      // sources per wavefront (FP64, more sources than resident slots: 2 or 4)
     int nslots = 0;
     GeoShape shape{};
@@ -650,13 +662,35 @@ gsim_status prepare_batch(gsim_ctx *c, Batch &B) {
         total += B.mem[i].ms->n;
     }
     B.bi.begin[ns] = total;
-    B.big = false;
-    B.gcap = 0;
-    for (int i = 0; i < ns && !B.all; ++i)
-        if (B.desc[i].cap > kCandCap) {
-            B.big = true;
-            B.gcap = std::max(B.gcap, (int)B.desc[i].cap);
+    // near passes: some surface may have more candidates per source than the
+    // cutoff kernel's LDS table holds, or so many that two sources' would not
+    // fit it together. There the cutoff kernel runs one source per wavefront
+    // and prunes little for its per-target tests. Cell sort and pass, cutoff
+    // kernel against near pass: at 48 expected candidates 0.88 against 0.43
+    // ms (benchmark torus, 7218 sources), 1.46 / 0.72 (torus of 13,824 faces),
+    // 1.10 / 0.76 (bumpy sphere, 9002), 1.33 / 0.92 (height field of 20,000
+    // faces, 9731), 0.26 / 0.18 (sphere of 5120 faces, 2130); at 24, where
+    // sources pair up, 0.28 / 0.25, 0.50 / 0.43, 0.41 / 0.42, 0.43 / 0.50,
+    // 0.16 / 0.15; at 8 a third to half as long as a near pass.
+    B.near = false;
+    for (int i = 0; i < ns && !B.all; ++i) {
+        const double cut = B.mem[i].cutoff;
+        const double mean = B.mem[i].ms->n * M_PI * cut * cut / std::max(surface_area(B.mem[i].ms), 1e-300);
+        B.near |= B.desc[i].cap > kCandCap || mean + 3.0 * std::sqrt(mean) > 0.5 * kCandCap;
+    }
+    const bool by_face = B.all || B.near;
+    B.face_blk.nsurf = ns;
+    int nfb = 0;
+    for (int i = 0; i < ns; ++i) {
+        B.face_blk.begin[i] = nfb;
+        if (by_face) {
+            gsim_status st = prepare_face_index(c, B.mem[i].ms, B.desc[i]);
+            if (st != GSIM_OK) return st;
+            nfb += (B.mem[i].ms->dm.nf + kFaceBlock - 1) / kFaceBlock;
         }
+    }
+    B.face_blk.begin[ns] = nfb;
+    if (by_face) HIPCHK(c, ensure(c->scan_scratch, sizeof(int32_t) * (size_t)nfb));
     B.fire_blk.nsurf = ns;
     B.any_fire = false;
     int nblk = 0;
@@ -669,20 +703,20 @@ gsim_status prepare_batch(gsim_ctx *c, Batch &B) {
         B.any_fire |= B.mem[i].integ && B.mem[i].integ->kind == GSIM_INT_FIRE;
         B.tcap = std::max(B.tcap, B.mem[i].ms->n);
         B.vstride = std::max<int64_t>(B.vstride, B.mem[i].ms->dm.nv);
-        if (B.mem[i].ms->dm.n_pseudo > 0 && !(c->prec == GSIM_FP32_MIXED && !finite_cutoff(B.mem[i].cutoff)))
+        if (by_face && B.mem[i].ms->dm.n_pseudo > 0 && !(c->prec == GSIM_FP32_MIXED && !finite_cutoff(B.mem[i].cutoff)))
             B.hstride = std::max<int64_t>(B.hstride, 3 * (int64_t)B.mem[i].ms->dm.nf);
         B.rcap = std::max(B.rcap, B.mem[i].ms->dm.n_pseudo);
     }
     // persistent grid: as many wavefronts as can be resident, at most one per source
     const bool fp32 = c->prec == GSIM_FP32_MIXED;
-    const int per_cu = std::max(1, B.all ? geodesic_all_blocks_per_cu(c->lds_stack_kb, fp32)
-                                         : geodesic_blocks_per_cu(c->lds_stack_kb, fp32, B.big));
+    const int per_cu = std::max(1, by_face ? geodesic_all_blocks_per_cu(c->lds_stack_kb, fp32, B.near)
+                                           : geodesic_blocks_per_cu(c->lds_stack_kb, fp32));
     // several sources per wavefront (the largest group of at most
     // group_sources that still gives every resident wavefront a full one):
     // each of a group's sources has its own bend-vertex entries in the
     // wavefront's table
     B.group = 1;
-    if (!B.all && !B.big && !c->profile_sources) {
+    if (!by_face && !c->profile_sources) {
         // the expected Euclidean candidates of a source (uniform density):
         // a group's sources share the table, so twice that plus 8 must fit a
         // share, or too many sources would run alone (three standard
@@ -722,6 +756,12 @@ gsim_status prepare_batch(gsim_ctx *c, Batch &B) {
         const int64_t fit = (int64_t)(c->stack_budget / per_slot);
         B.nslots = (int)std::max<int64_t>(1, std::min<int64_t>(B.nslots, fit));
     }
+    if (B.near) {
+        const double per_slot = 64.0 * c->gp.stack_cap + 8.0 * B.vstride + 8.0 * B.hstride + (double)B.rstride +
+                                (double)near_area_bytes(B.tcap);
+        const int64_t fit = (int64_t)(c->stack_budget / per_slot);
+        B.nslots = (int)std::max<int64_t>(1, std::min<int64_t>(B.nslots, fit));
+    }
     {
         // the bend-vertex tables of the resident wavefronts stay within a budget too
         const int64_t fit = (int64_t)(c->table_budget / (double)std::max<int64_t>(B.rstride, 1));
@@ -732,18 +772,19 @@ gsim_status prepare_batch(gsim_ctx *c, Batch &B) {
     // one source then only grows by a walk, and the separate update launch
     // goes. With more sources, every one of them would carry the serial move
     // (measured: a loss from two wavefronts per SIMD on).
-    B.fused = c->fuse_update && !B.all && !B.any_fire && total <= B.nslots && total <= 4 * c->cus;
+    B.fused = c->fuse_update && !by_face && !B.any_fire && total <= B.nslots && total <= 4 * c->cus;
     for (int i = 0; i < ns; ++i) B.fused = B.fused && B.mem[i].integ != nullptr;
     B.shape.lds_stack_kb = c->lds_stack_kb;
     B.shape.nslots = B.nslots;
     B.shape.grab = c->grab;
     B.shape.pad_lds = 0;
-    if (!B.all) {
+    {
         // fewer sources than resident slots: pad each workgroup's LDS so that
         // at most the needed number fit on a compute unit and the grid spreads
         // over all of them instead of filling some
         const int want = (B.nslots + c->cus - 1) / c->cus;
-        const size_t stat = geodesic_lds_bytes(c->lds_stack_kb, fp32, B.big);
+        const size_t stat = by_face ? geodesic_all_lds_bytes(c->lds_stack_kb, fp32, B.near)
+                                    : geodesic_lds_bytes(c->lds_stack_kb);
         if (want < per_cu && want > 0) {
             const size_t each = (size_t)c->lds_cu / (size_t)want;
             if (each > stat) B.shape.pad_lds = (int32_t)std::min(each - stat, (size_t)c->max_lds - stat);
@@ -751,7 +792,24 @@ gsim_status prepare_batch(gsim_ctx *c, Batch &B) {
     }
     const int cap_rec = B.all ? c->stack_cap_all : c->gp.stack_cap;
     HIPCHK(c, ensure(c->stack, (size_t)std::max(B.nslots, 1) * cap_rec * 64));
-    if (B.big) HIPCHK(c, ensure(c->gtab, (size_t)std::max(B.nslots, 1) * (size_t)geodesic_gtab_bytes(B.gcap)));
+    if (B.near) {
+        // prepared once per layout; the passes keep the tables themselves
+        const int nsl = std::max(B.nslots, 1);
+        HIPCHK(c, ensure(c->near_t, (size_t)nsl * (size_t)near_area_bytes(B.tcap)));
+        HIPCHK(c, ensure(c->near_v, sizeof(unsigned long long) * (size_t)nsl * B.vstride));
+        if (B.hstride) HIPCHK(c, ensure(c->near_h, sizeof(unsigned long long) * (size_t)nsl * B.hstride));
+        HIPCHK(c, ensure(c->near_e, sizeof(uint32_t) * (size_t)(nsl + 1)));
+        void *const p[4] = {c->near_t.p, c->near_v.p, c->near_h.p, c->near_e.p};
+        const int64_t lay[3] = {B.tcap, B.vstride, B.hstride};
+        if (std::memcmp(p, c->near_p, sizeof p) != 0 || std::memcmp(lay, c->near_layout, sizeof lay) != 0 ||
+            nsl > c->near_slots) {
+            HIPCHK(c, launch_near_init(P<char>(c->near_t), nsl, B.tcap, P<unsigned long long>(c->near_v), B.vstride,
+                                       P<unsigned long long>(c->near_h), B.hstride, P<uint32_t>(c->near_e), c->stream));
+            std::memcpy(c->near_p, p, sizeof p);
+            std::memcpy(c->near_layout, lay, sizeof lay);
+            c->near_slots = nsl;
+        }
+    }
     if (B.all) {
         HIPCHK(c, ensure(c->vdist, sizeof(double) * (size_t)std::max(B.nslots, 1) * B.vstride));
         HIPCHK(c, ensure(c->ttab, 4 * sizeof(double) * (size_t)std::max(B.nslots, 1) * B.tcap));
@@ -779,24 +837,25 @@ const SurfDesc *desc_dev(gsim_ctx *c) { return static_cast<const SurfDesc *>(c->
 // fused step of the same call wrote it there).
 gsim_status geodesic_pass(gsim_ctx *c, Batch &B, bool advance, bool commit_in = false) {
     hipStream_t s = c->stream;
-    if (B.all) {
+    if (B.all || B.near) {
         {
+            // starts the pass too (work counters, step counters)
             Stage st(c, "prefilter");
-            HIPCHK(c, launch_pass_begin(desc_dev(c), B.bi.nsurf, P<int32_t>(c->work), advance, s));
-            for (size_t i = 0; i < B.mem.size(); ++i) {
-                MeshState *ms = B.mem[i].ms;
-                HIPCHK(c, launch_face_sort(B.desc[i], P<int32_t>(ms->fcount), P<int64_t>(ms->tmp64),
-                                           P<int64_t>(c->scan_scratch), s));
-            }
+            HIPCHK(c, launch_face_sort(desc_dev(c), B.bi, B.face_blk, P<int32_t>(c->scan_scratch), P<int32_t>(c->work),
+                                       advance, s));
         }
         GeoParams gp = c->gp;
-        gp.stack_cap = c->stack_cap_all;
-        gp.max_windows = c->max_windows_all;
-        Stage st(c, "geodesic");
-        HIPCHK(c, launch_geodesic_all(desc_dev(c), B.bi, gp, B.shape, P<char>(c->stack), P<double>(c->vdist), B.vstride,
-                                      P<char>(c->roots), B.rstride, B.rcap, c->ttab.p, B.tcap,
-                                      B.hstride ? P<unsigned long long>(c->split) : nullptr, B.hstride,
-                                      P<int32_t>(c->work), P<Counters>(c->ctr), c->prec == GSIM_FP32_MIXED, s));
+        if (B.all) {
+            gp.stack_cap = c->stack_cap_all;
+            gp.max_windows = c->max_windows_all;
+        }
+        Buf &v = B.near ? c->near_v : c->vdist, &h = B.near ? c->near_h : c->split;
+        Stage st(c, "geodesic", true);
+        HIPCHK(c, launch_geodesic_all(desc_dev(c), B.bi, gp, B.shape, P<char>(c->stack), P<unsigned long long>(v),
+                                      B.vstride, P<char>(c->roots), B.rstride, B.rcap, B.near ? c->near_t.p : c->ttab.p,
+                                      B.tcap, B.hstride ? P<unsigned long long>(h) : nullptr, B.hstride,
+                                      B.near ? P<uint32_t>(c->near_e) : nullptr, P<int32_t>(c->work),
+                                      P<Counters>(c->ctr), c->prec == GSIM_FP32_MIXED, s, st.a, st.b));
         c->passes++;
         return GSIM_OK;
     }
@@ -835,8 +894,7 @@ gsim_status geodesic_pass(gsim_ctx *c, Batch &B, bool advance, bool commit_in = 
         Stage st(c, "geodesic", true);
         HIPCHK(c, launch_geodesic(desc_dev(c), B.bi, gp, B.shape, P<char>(c->stack), P<char>(c->roots), B.rstride,
                                   B.rcap, P<int32_t>(c->work), P<Counters>(c->ctr), c->prec == GSIM_FP32_MIXED,
-                                  advance && B.fused, s, st.a, st.b, B.big ? P<char>(c->gtab) : nullptr,
-                                  B.big ? B.gcap : 0, B.group, B.group > 1));
+                                  advance && B.fused, s, st.a, st.b, B.group, B.group > 1));
     }
     c->passes++;
     return GSIM_OK;
@@ -921,13 +979,13 @@ std::string graph_key(gsim_ctx *c, const Batch &B, int steps) {
     put(&B.shape, sizeof(B.shape));
     put(&B.small, sizeof(B.small));
     put(&B.fused, sizeof(B.fused));
-    put(&B.big, sizeof(B.big));
+    put(&B.near, sizeof(B.near));
+    put(&B.face_blk, sizeof(B.face_blk));
     put(&B.group, sizeof(B.group));
-    put(&B.gcap, sizeof(B.gcap));
     put(&c->update_block, sizeof(int));
     put(&steps, sizeof(int));
-    void *ptrs[11] = {c->stack.p, c->work.p, c->ctr.p, c->desc.p, c->scan_scratch.p, c->vdist.p, c->ttab.p,
-                      c->roots.p, c->partials.p, c->gtab.p, c->split.p};
+    void *ptrs[14] = {c->stack.p, c->work.p, c->ctr.p, c->desc.p, c->scan_scratch.p, c->vdist.p, c->ttab.p,
+                      c->roots.p, c->partials.p, c->split.p, c->near_t.p, c->near_v.p, c->near_h.p, c->near_e.p};
     put(ptrs, sizeof(ptrs));
     const int64_t sizes[5] = {B.rstride, B.rcap, B.tcap, B.vstride, B.hstride};
     put(sizes, sizeof(sizes));
@@ -1113,7 +1171,7 @@ void gsim_destroy(gsim_ctx *c) {
         delete ms;
     }
     for (Buf *b : {&c->stack, &c->work, &c->ctr, &c->wstats, &c->scan_scratch, &c->sum_scratch, &c->pf_over,
-                   &c->prof, &c->desc, &c->vdist, &c->ttab, &c->roots, &c->partials, &c->vbits, &c->gtab, &c->split})
+                   &c->prof, &c->desc, &c->vdist, &c->ttab, &c->roots, &c->partials, &c->vbits, &c->split, &c->near_t, &c->near_v, &c->near_h, &c->near_e})
         release(*b);
     if (c->desc_pinned) (void)hipHostFree(c->desc_pinned);
     if (c->own_stream) (void)hipStreamDestroy(c->stream);

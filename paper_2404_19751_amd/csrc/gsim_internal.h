@@ -181,7 +181,7 @@ struct SurfDesc {
     double cutoff, cut2;
     // particles by face (all-pairs target lookup): ftgt[fstart[f] .. fstart[f+1])
     // (ffirst[f]: fstart[f], or -1 for a face without particles)
-    int32_t *fstart, *ffirst;
+    int32_t *fstart, *ffirst, *fcount;  // (fcount: zeros between two sorts)
     struct FaceTarget *ftgt;
     // potential and integrator of the fused update
     int32_t pkind, ikind;
@@ -199,9 +199,9 @@ struct SurfDesc {
 };
 
 // Capacity of a candidate row: the most Euclidean candidates one source may
-// have with its targets in an LDS table of the geodesic kernel. Batches with
-// more use the kernel's big-candidate instantiation (targets in global
-// memory, rows as wide as the largest count needs), up to kBigCandMax.
+// have with its targets in an LDS table of the cutoff kernel. Batches with
+// more run as near passes (rows as wide as the largest count needs, up to
+// kBigCandMax).
 constexpr int kCandCap = 128;
 constexpr int kBigCandMax = 4096;
 // Most particles on one surface in whole-mesh passes. The rows hold n x n
@@ -258,32 +258,34 @@ struct GeoShape {
 // With `fuse`, each source particle is also moved (force from its row,
 // integrator, walk) into the next-state arrays once its row is final. Non-null
 // ev0/ev1 are recorded by the dispatch at the kernel's start and end.
-// gcap > 0 selects the big-candidate instantiation: every surface's rows are
-// sd.cap wide (at most kBigCandMax) and each resident wavefront keeps its
-// source's target arrays for up to gcap targets in gtab
-// (geodesic_gtab_bytes(gcap) bytes per wavefront). group = 2, 4 or 8: with
+// group = 2, 4 or 8: with
 // more sources than slots, that many sources per wavefront (the bend-vertex
 // tables then hold rcap = group times the bend vertices of a surface).
 hipError_t launch_geodesic(const SurfDesc *desc, const BatchIdx &bi, const GeoParams &gp, const GeoShape &shape,
                            char *stack_mem, char *roots, int64_t rstride, int rcap, int32_t *work_ctr, Counters *ctr,
                            bool fp32, bool fuse, hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr,
-                           char *gtab = nullptr, int gcap = 0, int group = 1, bool pre_cand = false);
+                           int group = 1, bool pre_cand = false);
 // The Euclidean candidate rows and counts of every source of the batch,
 // group sources at a time (2, 4 or 8), ahead of a grouped geodesic pass
 // (launched with pre_cand), which then reads them instead of searching.
 hipError_t launch_candidates(const SurfDesc *desc, const BatchIdx &bi, int group, hipStream_t s);
-int64_t geodesic_gtab_bytes(int gcap);
-// All-pairs geodesics (no cutoff) for every source of the batch: every other
-// particle of the surface is a target. vdist: per resident wavefront a table
-// of vstride vertex distances; roots: per resident wavefront a bend-vertex
-// table of rstride bytes for rcap bend vertices (bend_table_bytes); ttab:
-// per resident wavefront the state of tcap targets (4 doubles each); split:
-// per resident wavefront hstride half-edge entries (null when no surface has
-// bend vertices).
+// Geodesics by whole-mesh propagation for every source of the batch: every
+// other particle of the surface is a target. vdist: per resident wavefront a
+// table of vstride vertex distances; split: hstride half-edge entries (null
+// when no surface has bend vertices); roots: a bend-vertex table of rstride
+// bytes for rcap bend vertices (bend_table_bytes); ttab: the state of tcap
+// targets (4 doubles each). With epoch (one per wavefront), a near pass: a
+// finite cutoff, rows of the targets within it (at most sd.cap, of at most
+// kBigCandMax), ttab areas of near_area_bytes(tcap), all tables prepared once
+// by launch_near_init and kept by the passes themselves.
 hipError_t launch_geodesic_all(const SurfDesc *desc, const BatchIdx &bi, const GeoParams &gp, const GeoShape &shape,
-                               char *stack_mem, double *vdist, int64_t vstride, char *roots, int64_t rstride,
+                               char *stack_mem, unsigned long long *vdist, int64_t vstride, char *roots, int64_t rstride,
                                int rcap, void *ttab, int tcap, unsigned long long *split, int64_t hstride,
-                               int32_t *work_ctr, Counters *ctr, bool fp32, hipStream_t s);
+                               uint32_t *epoch, int32_t *work_ctr, Counters *ctr, bool fp32, hipStream_t s,
+                               hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+int64_t near_area_bytes(int tcap);
+hipError_t launch_near_init(char *area, int nslots, int tcap, unsigned long long *vdist, int64_t vstride,
+                            unsigned long long *split, int64_t hstride, uint32_t *epoch, hipStream_t s);
 // In-surface Voronoi neighbours (k_voronoi.hip): at most kVoronoiMax
 // particles (an n x n adjacency bitset). launch_voronoi_faces marks every
 // pair of particles whose cells share a boundary longer than tol; cell lists
@@ -309,9 +311,16 @@ __host__ __device__ inline int64_t bend_table_bytes(int rcap) {
 // empty: every distance infinite, nothing queued. The kernels leave them
 // empty again after each source.
 hipError_t launch_bend_init(char *roots, int nslots, int64_t rstride, int rcap, hipStream_t s);
-int geodesic_all_blocks_per_cu(int lds_stack_kb, bool fp32);
-// particles of one surface sorted by face (counting sort; counts must be zeroed)
-hipError_t launch_face_sort(const SurfDesc &d, int32_t *counts, int64_t *tmp64, int64_t *scan_scratch, hipStream_t s);
+int geodesic_all_blocks_per_cu(int lds_stack_kb, bool fp32, bool near);
+size_t geodesic_all_lds_bytes(int lds_stack_kb, bool fp32, bool near);
+// The particles of every surface of a batch by face (counting sort): fstart,
+// ffirst, ftgt. fb: blocks of kFaceBlock faces per surface; part: one entry
+// per block. The counts start from zeros and are zeros again afterwards. The
+// first kernel also starts a pass (work counters; with advance, the step
+// counters).
+constexpr int kFaceBlock = 1024;
+hipError_t launch_face_sort(const SurfDesc *desc, const BatchIdx &bi, const BatchIdx &fb, int32_t *part, int32_t *work,
+                            bool advance, hipStream_t s);
 // row i of an all-pairs surface lists every particle j in order
 hipError_t launch_identity_rows(int n, int cap, int32_t *cand_cnt, int32_t *cand, hipStream_t s);
 // FIRE: forces and the power / norm reduction of every FIRE surface (blk:
@@ -321,7 +330,7 @@ hipError_t launch_fire_control(const SurfDesc *desc, const BatchIdx &blk, double
                                hipStream_t s);
 
 // LDS bytes of one geodesic workgroup for a stack size (occupancy planning)
-size_t geodesic_lds_bytes(int lds_stack_kb, bool fp32, bool big = false);
+size_t geodesic_lds_bytes(int lds_stack_kb);
 // positions + cell counting sort, one workgroup per surface (every surface's
 // grid must have at most kSmallCells cells)
 constexpr int kSmallCells = 4096;
@@ -336,8 +345,6 @@ constexpr int kWorkInts = kWorkChunks * kWorkStride;
 // commit: take the state from the next-state arrays first (fused time steps)
 hipError_t launch_bin_batch(const SurfDesc *desc, int nsurf, int32_t *work, bool advance, bool commit,
                             hipStream_t s);
-// the same start of a pass without the binning
-hipError_t launch_pass_begin(const SurfDesc *desc, int nsurf, int32_t *work, bool advance, hipStream_t s);
 hipError_t launch_fill_u64(unsigned long long *p, int64_t n, unsigned long long v, hipStream_t s);
 // fused force + integrator + walk for every particle of the batch
 hipError_t launch_update_batch(const SurfDesc *desc, const BatchIdx &bi, int block, Counters *ctr,
@@ -354,7 +361,7 @@ hipError_t launch_cell_sort(const DevMesh &m, int n, const int32_t *face, const 
                             int64_t *scratch, bool clear, const SurfDesc *desc, int32_t *work, bool advance,
                             hipStream_t s);
 // resident geodesic workgroups per compute unit for a stack size (0 on error)
-int geodesic_blocks_per_cu(int lds_stack_kb, bool fp32, bool big = false);
+int geodesic_blocks_per_cu(int lds_stack_kb, bool fp32);
 
 
 hipError_t launch_count_rows(int n, const int32_t *cnt, int cap_c, const double *dist, double cutoff, int32_t *out,

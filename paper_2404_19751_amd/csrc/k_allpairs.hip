@@ -1,4 +1,5 @@
-// All-pairs exact polyhedral geodesics (no cutoff), one source per wave64.
+// Exact polyhedral geodesics by whole-mesh propagation, one source per wave64:
+// all pairs (no cutoff), and cutoff passes with many targets (near passes).
 //
 // Every other particle of the surface is a target, so a source's windows
 // must cover the whole mesh (the paper's full-mesh sequence trees, Sec. 3.1
@@ -23,6 +24,16 @@
 // Bend vertices are launched by the rules of the cutoff kernel, from a table
 // that can hold every saddle and boundary vertex of the surface.
 //
+// Near passes take a cutoff instead: windows are dropped at it, a row holds the
+// targets within it (gathered as they are reached, sorted by particle), and
+// no table is cleared per source: vertex and half-edge entries carry the
+// source's epoch, the states of the targets reached are reset one by one. A
+// face's several targets are offered to all lanes' windows side by side
+// (offer_pairs). With hundreds of targets the cutoff kernel's per-target
+// pruning keeps nearly every window; domination keeps 700 of its 2670 a
+// source on the benchmark torus at 232 targets: 8192 sources 5.95 -> 1.43 ms
+// a pass, at 58 targets 0.94 -> 0.45 ms.
+//
 // Mapping: the state of all n targets (best distance, best distance of
 // another direction, tangent; 32 bytes each), the vertex table, the
 // bend-vertex table and the window overflow in per-wavefront global areas
@@ -45,6 +56,9 @@
 // (0.84 s, and 0.98 s with lanes sharing the loads): every later LDS access
 // of the iteration waits for such a fetch.
 #include <cmath>
+#include <type_traits>
+
+#include <hip/hip_ext.h>
 
 #include "gsim_internal.h"
 #include "window.h"
@@ -68,7 +82,7 @@ struct AllArgs {
     BatchIdx bi;
     GeoParams gp;
     void *stack;     // per wavefront: stack_cap records of 64 bytes
-    double *vdist;   // per wavefront: vstride vertex distances
+    unsigned long long *vdist;  // per wavefront: vstride vertex distances
     int64_t vstride;
     char *roots;     // per wavefront: a bend-vertex table (rstride bytes, rcap vertices)
     int64_t rstride;
@@ -78,14 +92,33 @@ struct AllArgs {
     unsigned long long *split;  // per wavefront: hstride half-edge entries (null: no surface has bend vertices)
     int64_t hstride;
     TgtState *ttab;  // per wavefront: the state of tcap targets
+    int64_t tstride; // bytes between two wavefronts' ttab (and, in near passes, touch, sort) areas
+    int32_t *touch;  // near passes, per wavefront: the targets reached (tcap entries)
+    unsigned long long *sort;  // near passes, per wavefront: kBigCandMax sort keys
+    uint32_t *epoch; // near passes, per wavefront: the epoch of its last source
     int tcap;
     int grab;
 };
 
 struct AllLds {
     BendLds B;
-    int32_t unfound;  // targets not reached yet
+    int32_t unfound;  // targets not reached yet (near passes: targets reached)
     double maxb;      // windows with a larger key cannot improve any target
+    unsigned long long starts;  // near passes: offer_pairs
+    long long clk[6];           // per-source profile: start, loop, launches' time, iterations, results, launches before
+    int32_t owner[kWave];
+};
+
+// Near passes: sort keys (particle, place in the by-face index) of a row;
+// rows longer than kSortLds are sorted in global memory.
+constexpr int kSortLds = 512;
+struct SortLds {
+    unsigned long long key[kSortLds];
+};
+struct NoSort {};
+template <bool kNear>
+struct SortOf {
+    using T = typename std::conditional<kNear, SortLds, NoSort>::type;
 };
 
 // Per-source constants.
@@ -97,8 +130,8 @@ struct ACtx {
 };
 
 struct SrcStats {
-    unsigned long long windows, launches, stale, guards;
-    int pruned, depth;
+    unsigned long long windows, launches, guards;
+    int stale, pruned, depth;  // (stale and pruned: per lane)
     bool overflow;
 };
 
@@ -197,11 +230,42 @@ struct RoundStack {
     }
 };
 
-// Path length reaching a vertex: the table keeps the minimum (positive
-// doubles order like their bit patterns).
-__device__ inline void vdist_min(double *Dv, int v, double d) {
-    atomicMin(reinterpret_cast<unsigned long long *>(Dv + v), (unsigned long long)__double_as_longlong(d));
-}
+// Path lengths that have reached the vertices, updated by 64-bit minima. In
+// whole-mesh passes the table holds doubles (positive doubles order like
+// their bit patterns) and is cleared for every source. In near passes, whose
+// sources reach a small part of the mesh, nothing is cleared: an entry is the
+// source's epoch (20 bits, falling from source to source, so that a newer
+// source's entries win every minimum), then the length as a float rounded up
+// (a longer path through the vertex dominates less: exact, only the pruning
+// is weaker by the rounding, 6e-8).
+constexpr int kEpochShift = 44;
+constexpr uint32_t kEpochMax = (1u << 20) - 2;  // the first source's; all ones marks an entry never written
+template <bool kNear>
+struct VertexTable {
+    unsigned long long *p;
+    unsigned long long epoch;
+    __device__ double operator[](int v) const {
+        const unsigned long long x = p[v];
+        if constexpr (!kNear) return __longlong_as_double((long long)x);
+        return x >> kEpochShift == epoch ? (double)__uint_as_float((unsigned)(x >> 12)) : INFINITY;
+    }
+    __device__ void put(int v, double d) const {
+        if constexpr (!kNear) atomicMin(p + v, (unsigned long long)__double_as_longlong(d));
+        else atomicMin(p + v, epoch << kEpochShift | (unsigned long long)__float_as_uint(__double2float_ru(d)) << 12);
+    }
+    // is a path of squared length r (from the root image) plus sg worth a put?
+    __device__ bool shorter(double r, double D, double sg) const;
+};
+
+// The state of a wavefront's targets by their place in the by-face index,
+// and, in near passes, the list of the targets reached so far (their states
+// are reset when the source is done).
+template <bool kNear>
+struct TargetTable {
+    TgtState *st;
+    int32_t *touch;
+    __device__ TgtState &operator[](int q) const { return st[q]; }
+};
 
 // Target update (j: the target's place in the by-face index): best distance,
 // its tangent, and the best distance among candidates whose direction differs
@@ -209,10 +273,10 @@ __device__ inline void vdist_min(double *Dv, int v, double d) {
 // with the candidate. The lanes load their targets together (or hand in the
 // entries `c` loaded earlier, with no other update in between) and leave when
 // their candidate cannot change anything (the stored distances only
-// decrease); the others are applied one lane at a time in registers, each
-// result passed to every lane holding the same target, and written back once
-// (its whole record).
-__device__ inline void target_update_loaded(AllLds &L, TgtState *td, const ACtx &C, bool ok, int j, double d,
+// decrease); the others are applied in registers, lanes with the same target
+// one after another (in rounds).
+template <bool kNear>
+__device__ inline void target_update_loaded(AllLds &L, const TargetTable<kNear> &td, const ACtx &C, bool ok, int j, double d,
                                             double tx, double ty, double alt, const TgtState &c) {
     double c1 = INFINITY, c2 = INFINITY;
     if (ok) {
@@ -222,19 +286,14 @@ __device__ inline void target_update_loaded(AllLds &L, TgtState *td, const ACtx 
     }
     uint64_t m = __ballot(ok);
     if (!m) return;
-    const double c1_in = c1, c2_in = c2;
     double ax = c.tx, ay = c.ty;
     int reached = 0;  // targets found for the first time
-    // lanes on different targets (the usual case) update at once, else one
-    // lane at a time
-    bool dup = false;
-    for (uint64_t r = m; r; r &= r - 1) {
-        const int l = __ffsll((unsigned long long)r) - 1;
-        dup |= ok && j == __builtin_amdgcn_readlane(j, l) && lane_id() != l;
-    }
-    if (!__ballot(dup)) {
+    for (bool todo = ok; m;) {
+        const int wl = m & (m - 1) ? claim(L.B.win, todo, j) : lane_id();
+        const bool mine = todo && wl == lane_id();
         int first = 0;
-        if (ok) {
+        if (mine) {
+            const double c1_in = c1, c2_in = c2;
             const bool found = c1 < INFINITY;
             const bool differ = !found || fabs(ax * ty - ay * tx) > C.tie_dir || ax * tx + ay * ty < 0.0;
             if (d < c1) {
@@ -247,47 +306,30 @@ __device__ inline void target_update_loaded(AllLds &L, TgtState *td, const ACtx 
                 c2 = fmin(c2, d);
             }
             c2 = fmin(c2, alt);
+            if (c1 < c1_in || c2 < c2_in) td[j] = TgtState{c1, c2, ax, ay};
         }
-        reached = __popcll(__ballot(first));
-        m = 0;
-    }
-    while (m) {
-        const int l = __ffsll((unsigned long long)m) - 1;
-        int first = 0;
-        if (lane_id() == l) {
-            const bool found = c1 < INFINITY;
-            const bool differ = !found || fabs(ax * ty - ay * tx) > C.tie_dir || ax * tx + ay * ty < 0.0;
-            if (d < c1) {
-                if (differ) c2 = fmin(c2, c1);
-                c1 = d;
-                ax = tx;
-                ay = ty;
-                first = !found;
-            } else if (differ) {
-                c2 = fmin(c2, d);
+        const uint64_t mfirst = __ballot(first);
+        if (kNear && first) td.touch[L.unfound + reached + __popcll(mfirst & lanemask_lt())] = j;
+        reached += __popcll(mfirst);
+        todo = todo && !mine;
+        m = __ballot(todo);
+        if (m) {
+            const double w1 = __shfl(c1, wl), w2 = __shfl(c2, wl), wx = __shfl(ax, wl), wy = __shfl(ay, wl);
+            const int wj = __shfl(j, wl);
+            if (todo && wj == j) {
+                c1 = w1;
+                c2 = w2;
+                ax = wx;
+                ay = wy;
             }
-            c2 = fmin(c2, alt);
         }
-        reached += __builtin_amdgcn_readlane(first, l);
-        const int jl = __builtin_amdgcn_readlane(j, l);
-        const double b1 = readlane_d(c1, l), b2 = readlane_d(c2, l);
-        const double bx = readlane_d(ax, l), by = readlane_d(ay, l);
-        if (ok && j == jl) {
-            c1 = b1;
-            c2 = b2;
-            ax = bx;
-            ay = by;
-        }
-        m &= m - 1;
     }
-    if (ok) {
-        if (c1 < c1_in || c2 < c2_in) td[j] = TgtState{c1, c2, ax, ay};
-    }
-    if (lane_id() == 0 && reached) L.unfound -= reached;
+    if (lane_id() == 0 && reached) L.unfound += kNear ? reached : -reached;
     lane_step_barrier();
 }
 
-__device__ inline void target_update(AllLds &L, TgtState *td, const ACtx &C, bool ok, int j, double d, double tx,
+template <bool kNear>
+__device__ inline void target_update(AllLds &L, const TargetTable<kNear> &td, const ACtx &C, bool ok, int j, double d, double tx,
                                      double ty, double alt) {
     TgtState c;
     if (ok) c = td[j];
@@ -300,6 +342,12 @@ __device__ inline void target_update(AllLds &L, TgtState *td, const ACtx &C, boo
 // r > (d - sg)^2. No square root is taken, and the rounding stays at that of
 // the distances themselves, far inside the widening by rel.
 __device__ inline bool longer(double r, double d_sg) { return d_sg < 0.0 || r > d_sg * d_sg; }
+
+template <bool kNear>
+__device__ inline bool VertexTable<kNear>::shorter(double r, double D, double sg) const {
+    // the float entry exceeds the length it stands for: equal paths are not put again
+    return !longer(r, (kNear ? D * (1.0 - 1.2e-7) : D) - sg);
+}
 
 // Trim a child interval [x0, x1] on an edge S -> E (length Lc, child frame
 // origin S, root image (px, py)) against the paths through S and through E;
@@ -376,18 +424,22 @@ __device__ inline bool opposite_dominates(double ox, double oy, double DO, doubl
 // are longer there: at most one child is left, the left one when the other
 // ray crosses the half-edge to the right of this window's ray, else the right
 // one. Hv keeps per half-edge the shortest such path and its crossing, packed
-// as two floats so that one 64-bit minimum updates both (the distance rounded
-// up). The distances must differ by rel, far more than the floats' rounding
-// and than any tie band carried on to the targets; crossings closer than a
+// with the source's epoch so that one 64-bit minimum updates both: 24 bits of
+// the distance as a float rounded up, 20 bits of the crossing as a fraction
+// of the edge. The distances must differ by rel beyond that rounding, far
+// more than any tie band carried on to the targets; crossings closer than a
 // thousandth of the edge decide nothing.
 // Returns the sides still open: bit 0 the left child, bit 1 the right one.
-__device__ inline int one_split(unsigned long long *Hv, int he, unsigned long long hw, double d, double x, double len,
-                                double rel) {
-    const float hd = __uint_as_float((unsigned)(hw >> 32)), hx = __uint_as_float((unsigned)hw);
-    const bool other = hw != ~0ull && (double)hd * (1.0 + rel) < d;
-    const int sides = other && (double)hx > x + 1e-3 * len ? 1 : other && (double)hx < x - 1e-3 * len ? 2 : 3;
-    const unsigned long long mine =
-        ((unsigned long long)__float_as_uint(__double2float_ru(d)) << 32) | __float_as_uint((float)x);
+__device__ inline int one_split(unsigned long long *Hv, unsigned long long epoch, int he, unsigned long long hw, double d,
+                                double x, double len, double rel) {
+    constexpr double kOne = (double)((1 << 20) - 1);
+    const float hd = __uint_as_float((unsigned)((hw >> 20) & 0xffffff) << 7);
+    const double hx = (double)(unsigned)(hw & 0xfffff) * (1.0 / kOne) * len;
+    const bool other = hw >> kEpochShift == epoch && (double)hd * (1.0 + rel) < d;
+    const int sides = other && hx > x + 1e-3 * len ? 1 : other && hx < x - 1e-3 * len ? 2 : 3;
+    const unsigned db = (__float_as_uint(__double2float_ru(d)) + 127u) >> 7;
+    const unsigned xb = (unsigned)(fmin(fmax(x / len, 0.0), 1.0) * kOne);
+    const unsigned long long mine = epoch << kEpochShift | (unsigned long long)db << 20 | xb;
     if (mine < hw) atomicMin(Hv + he, mine);
     return sides;
 }
@@ -412,42 +464,20 @@ __device__ inline void far_ends(const He<R> &h, const Win<R> &w, double txc, boo
     x1 = fmin(fmax(x1, 0.0), Lc);
 }
 
-// Targets of the by-face index from q on (-1: none), in the face with entry half-edge
-// slot k, seen through window w whose root has the tangent (rtx, rty) and
-// other-direction distance rD2 (bend vertices). t0 and c0: the first one's
-// record and distances, loaded by the caller.
-template <typename R>
-__device__ inline void query_face(const FaceTarget *ftgt, AllLds &L, TgtState *td, const ACtx &C, int q,
-                                  int src, int k, const He<R> &H, const Win<R> &w, double rtx, double rty,
-                                  double rD2, FaceTarget t0, TgtState c0) {
+// Offers every target of a lane's face: those of the by-face index from q on
+// (-1: none). cand(t, d) tells whether the lane reaches target t and at what
+// distance, dir(t, d, tx, ty, alt) its direction there and the distance of
+// the other direction; t0 and c0 are the first target's record and state,
+// loaded by the caller.
+template <class Cand, class Dir>
+__device__ inline void offer_targets(const FaceTarget *ftgt, AllLds &L, const TargetTable<false> &td, const ACtx &C, int q,
+                                     int src, FaceTarget t0, TgtState c0, const Cand &cand, const Dir &dir) {
     while (__ballot(q >= 0)) {
         bool ok = false;
         double d = 0, tx = 0, ty = 0, alt = INFINITY;
         if (q >= 0 && t0.j != src) {
-            // barycentrics in the entry half-edge's order (selects: a lane's
-            // index into the record would put it in scratch)
-            const double bh = k == 0 ? t0.b[1] : k == 1 ? t0.b[2] : t0.b[0];
-            const double bo = k == 0 ? t0.b[2] : k == 1 ? t0.b[0] : t0.b[1];
-            const R qx = (R)bh * H.L + (R)bo * H.cx;
-            const R qy = (R)bo * H.cy;
-            const R xq = w.px + (qx - w.px) * (-w.py) / (qy - w.py);
-            const R sl = (R)C.tol * H.L;
-            if (xq >= w.b0 - sl && xq <= w.b1 + sl) {
-                R dx = qx - w.px, dy = qy - w.py;
-                const R l = sqrt(dx * dx + dy * dy);
-                d = (double)w.sg + (double)l;
-                ok = true;
-                if (w.root < 0) {
-                    dx /= l;
-                    dy /= l;
-                    tx = (double)(w.c * dx - w.s * dy);
-                    ty = (double)(w.s * dx + w.c * dy);
-                } else {
-                    tx = rtx;
-                    ty = rty;
-                    alt = rD2 + (double)l;
-                }
-            }
+            ok = cand(t0, d);
+            if (ok) dir(t0, d, tx, ty, alt);
         }
         target_update_loaded(L, td, C, ok, q, d, tx, ty, alt, c0);
         q = q >= 0 && t0.more ? q + 1 : -1;
@@ -458,18 +488,137 @@ __device__ inline void query_face(const FaceTarget *ftgt, AllLds &L, TgtState *t
     }
 }
 
+// Near passes, whose faces hold several targets each: the (lane, target)
+// pairs of all lanes side by side, 64 at a time, instead of each lane's
+// targets one after another. A lane has cnt targets from place q0 on. cand
+// is called by every lane with the pair's owner lane (whose values it fetches
+// by shuffles), the target and whether there is a pair; it returns whether
+// the owner reaches the target, with distance, direction and other-direction
+// distance. On the benchmark torus with 1.8 targets a face, about six rounds
+// an iteration become one.
+template <class Cand>
+__device__ inline void offer_pairs(const FaceTarget *ftgt, AllLds &L, const TargetTable<true> &td, const ACtx &C, int cnt,
+                                   int q0, int src, const Cand &cand) {
+    const int lane = lane_id();
+    int inc = cnt;
+    for (int o = 1; o < kWave; o <<= 1) {
+        const int y = __shfl_up(inc, o);
+        if (lane >= o) inc += y;
+    }
+    const int excl = inc - cnt, total = __builtin_amdgcn_readlane(inc, kWave - 1);
+    for (int base = 0; base < total; base += kWave) {
+        // the lanes with pairs in this batch, in order, and a bit at the
+        // place where each one's pairs begin
+        const bool in = cnt > 0 && excl < base + kWave && inc > base;
+        const uint64_t mi = __ballot(in);
+        if (lane == 0) L.starts = 0;
+        __syncthreads();
+        if (in) {
+            L.owner[__popcll(mi & lanemask_lt())] = lane;
+            atomicOr(&L.starts, 1ull << max(excl - base, 0));
+        }
+        __syncthreads();
+        const bool act = base + lane < total;
+        const int own = L.owner[__popcll(L.starts & (lanemask_lt() << 1 | 1)) - 1];
+        const int q = __shfl(q0, own) + (base + lane - __shfl(excl, own));
+        FaceTarget t{{0.0, 0.0, 0.0}, -1, 0};
+        TgtState c;
+        if (act) {
+            t = ftgt[q];
+            c = td[q];
+        }
+        double d = 0, tx = 0, ty = 0, alt = INFINITY;
+        bool ok = cand(own, t, d, tx, ty, alt);
+        ok = ok && act && t.j != src && d < L.maxb;
+        target_update_loaded(L, td, C, ok, q, d, tx, ty, alt, c);
+    }
+}
+
+// Barycentrics of a target in the order of the half-edge in slot k of its
+// face: that of its head and of the opposite vertex (selects: a lane's index
+// into the record would put it in scratch).
+__device__ inline double head_bary(const FaceTarget &t, int k) { return k == 0 ? t.b[1] : k == 1 ? t.b[2] : t.b[0]; }
+__device__ inline double opp_bary(const FaceTarget &t, int k) { return k == 0 ? t.b[2] : k == 1 ? t.b[0] : t.b[1]; }
+
+// Targets from q on in the face with entry half-edge slot k, seen through
+// window w whose root has the tangent (rtx, rty) and other-direction distance
+// rD2 (bend vertices).
+template <typename R>
+__device__ inline void query_face(const FaceTarget *ftgt, AllLds &L, const TargetTable<false> &td, const ACtx &C, int q,
+                                  int src, int k, const He<R> &H, const Win<R> &w, double rtx, double rty, double rD2,
+                                  const FaceTarget &t0, const TgtState &c0) {
+    R dx = 0, dy = 0, l = 0;
+    offer_targets(
+        ftgt, L, td, C, q, src, t0, c0,
+        [&](const FaceTarget &t, double &d) {
+            const double bh = head_bary(t, k), bo = opp_bary(t, k);
+            const R qx = (R)bh * H.L + (R)bo * H.cx;
+            const R qy = (R)bo * H.cy;
+            const R xq = w.px + (qx - w.px) * (-w.py) / (qy - w.py);
+            const R sl = (R)C.tol * H.L;
+            dx = qx - w.px;
+            dy = qy - w.py;
+            l = sqrt(dx * dx + dy * dy);
+            d = (double)w.sg + (double)l;
+            return xq >= w.b0 - sl && xq <= w.b1 + sl;
+        },
+        [&](const FaceTarget &, double, double &tx, double &ty, double &alt) {
+            if (w.root < 0) {
+                dx /= l;
+                dy /= l;
+                tx = (double)(w.c * dx - w.s * dy);
+                ty = (double)(w.s * dx + w.c * dy);
+            } else {
+                tx = rtx;
+                ty = rty;
+                alt = rD2 + (double)l;
+            }
+        });
+}
+
+// The same in near passes, cnt targets from place q on.
+template <typename R>
+__device__ inline void query_pairs(const FaceTarget *ftgt, AllLds &L, const TargetTable<true> &td, const ACtx &C, int cnt,
+                                   int q, int src, int k, const He<R> &H, const Win<R> &w, double rtx, double rty,
+                                   double rD2) {
+    offer_pairs(ftgt, L, td, C, cnt, q, src,
+                [&](int own, const FaceTarget &t, double &d, double &tx, double &ty, double &alt) {
+                    const int ok_ = __shfl(k, own), root = __shfl(w.root, own);
+                    const R hL = __shfl(H.L, own), hcx = __shfl(H.cx, own), hcy = __shfl(H.cy, own);
+                    const R px = __shfl(w.px, own), py = __shfl(w.py, own);
+                    const R b0 = __shfl(w.b0, own), b1 = __shfl(w.b1, own);
+                    const double bh = head_bary(t, ok_), bo = opp_bary(t, ok_);
+                    const R qx = (R)bh * hL + (R)bo * hcx, qy = (R)bo * hcy;
+                    const R xq = px + (qx - px) * (-py) / (qy - py), sl = (R)C.tol * hL;
+                    const R dx = qx - px, dy = qy - py, l = sqrt(dx * dx + dy * dy);
+                    const R c = __shfl(w.c, own), s = __shfl(w.s, own);
+                    const double ux = __shfl(rtx, own), uy = __shfl(rty, own), u2 = __shfl(rD2, own);
+                    d = (double)__shfl(w.sg, own) + (double)l;
+                    const R ex = dx / l, ey = dy / l;
+                    tx = root < 0 ? (double)(c * ex - s * ey) : ux;
+                    ty = root < 0 ? (double)(s * ex + c * ey) : uy;
+                    alt = root < 0 ? INFINITY : u2 + (double)l;
+                    return xq >= b0 - sl && xq <= b1 + sl;
+                });
+}
+
 // Launch the pending bend vertices (their distance improved, or their best
 // direction changed, or a tie appeared), their fans flattened over the lanes
 // a chunk of vertices at a time.
-template <typename R>
-__device__ void launch_roots(const AllArgs &a, const SurfDesc &sd, AllLds &L, const BendTable &G, TgtState *td,
-                             double *Dv, const ACtx &C, RoundStack<R> &S,
-                             double T, int src, SrcStats &st) {
+template <typename R, bool kNear>
+__device__ void launch_roots(const SurfDesc &sd, AllLds &L, const BendTable &G, const TargetTable<kNear> &td,
+                             const VertexTable<kNear> &Dv, const ACtx &C, RoundStack<R> &S, double T, int src,
+                             SrcStats &st) {
     const int lane = lane_id();
     const DevMesh &M = sd.m;
-    const HeRec *__restrict__ he = M.he;
+    const HeRec *const he = uniform(M.he);
+    const PseudoRec *const prec = uniform(M.prec);
+    const int32_t *const fan = uniform(M.fan), *const pidx = uniform(M.pidx), *const ffirst = uniform(sd.ffirst),
+                  *const fstart = uniform(sd.fstart);
+    const FaceTarget *const ftgt = uniform(sd.ftgt);
     // take the pending list (its vertices may be queued again while they launch)
     const int npend = L.B.npend;
+    const double maxb = L.maxb;
     int nsel = 0;
     for (int base = 0; base < npend; base += kWave) {
         const int k = base + lane;
@@ -479,12 +628,14 @@ __device__ void launch_roots(const AllArgs &a, const SurfDesc &sd, AllLds &L, co
         if (k < npend) {
             e = G.pend[k];
             D = G.rD[e];
-            sel = D < G.rL[e] * C.rc.keep && D < L.maxb;
+            sel = D < G.rL[e] * C.rc.keep && D < maxb;
             G.queued[e] = 0;
         }
         const uint64_t mk = __ballot(sel);
         if (sel) {
-            G.sel[nsel + __popcll(mk & lanemask_lt())] = e;
+            const int pos = nsel + __popcll(mk & lanemask_lt());
+            G.sel[pos] = e;
+            if (pos < kLaunchChunk) L.B.sel[pos] = e;  // the first chunk also through LDS
             G.rL[e] = D;
         }
         nsel += __popcll(mk);
@@ -498,10 +649,8 @@ __device__ void launch_roots(const AllArgs &a, const SurfDesc &sd, AllLds &L, co
             const int k = base + lane;
             int deg = 0;
             if (k < cn) {
-                const int e = G.sel[c0 + k];
-                const int v = M.pvert[e];
-                L.B.sel[k] = e;
-                deg = M.fan_off[v + 1] - M.fan_off[v];
+                if (c0 > 0) L.B.sel[k] = G.sel[c0 + k];
+                deg = prec[L.B.sel[k]].fan_deg;
             }
             int inc = deg;
             for (int o = 1; o < kWave; o <<= 1) {
@@ -510,7 +659,7 @@ __device__ void launch_roots(const AllArgs &a, const SurfDesc &sd, AllLds &L, co
             }
             if (k < cn) L.B.pref[k + 1] = carry + inc;
             st.launches += (unsigned long long)__popcll(__ballot(deg > 0));
-            carry += __shfl(inc, kWave - 1);
+            carry += __builtin_amdgcn_readlane(inc, kWave - 1);
         }
         if (lane == 0) L.B.pref[0] = 0;
         __syncthreads();
@@ -529,71 +678,94 @@ __device__ void launch_roots(const AllArgs &a, const SurfDesc &sd, AllLds &L, co
                 k = lo;
             }
             const int el = act ? L.B.sel[k] : 0;
-            const int v = act ? M.pvert[el] : 0;
+            const int fb = act ? prec[el].fan_beg : 0;
             const double D = act ? G.rD[el] : 0.0;
             const double vtx = act ? G.rtx[el] : 0.0, vty = act ? G.rty[el] : 0.0;
             const double D2 = act ? G.rD2[el] : INFINITY;
-            const int h = act ? M.fan[M.fan_off[v] + (idx - L.B.pref[k])] : 0;
-            const int hn = h - h % 3 + (h % 3 + 1) % 3;
+            const int h = act ? fan[fb + (idx - L.B.pref[k])] : 0;
+            const int g = h / 3, hk = h - 3 * g;
+            const int hn = 3 * g + (hk == 2 ? 0 : hk + 1);
             const HeRec Rh = he[h], Rn = he[hn];
+            int q = -1, cnt = 0;
+            if constexpr (kNear) {
+                q = act ? fstart[g] : 0;
+                cnt = act ? fstart[g + 1] - q : 0;
+            } else {
+                q = act ? ffirst[g] : -1;
+            }
+            // the two other vertices of face(h): reached along its edges
+            const int u1 = Rh.head, u2 = Rh.opp_flags >> 1;
+            FaceTarget t0{{0.0, 0.0, 0.0}, -1, 0};
+            TgtState c0s;
+            double D1 = INFINITY, D3 = INFINITY;
+            int e1 = -1, e2 = -1;
+            if (act) {
+                if (!kNear && q >= 0) {
+                    t0 = ftgt[q];
+                    c0s = td[q];
+                }
+                D1 = Dv[u1];
+                D3 = Dv[u2];
+                e1 = pidx[u1];
+                e2 = pidx[u2];
+                if (D + Rh.L < D1) Dv.put(u1, D + Rh.L);
+                if (D + Rh.Lp < D3) Dv.put(u2, D + Rh.Lp);
+                D1 = fmin(D1, D + Rh.L);
+                D3 = fmin(D3, D + Rh.Lp);
+            }
             Win<R> nw;
-            bool want = false;
-            double key = 0.0;
+            bool want = false, later = false;
             if (act && Rn.twin >= 0) {
-                // window across the edge opposite v: twin(next(h)) runs u2 -> u1
+                // window across the edge opposite v: twin(next(h)) runs u2 ->
+                // u1; the parts that the paths along those vertices' edges
+                // dominate are cut at once
                 const double px = Rn.L - Rn.cx, py = -Rn.cy;
-                nw.px = (R)px;
-                nw.py = (R)py;
-                nw.b0 = R(0);
-                nw.b1 = (R)Rn.L;
-                nw.sg = (R)D;
-                nw.c = R(1);
-                nw.s = R(0);
-                nw.he = Rn.twin;
-                nw.root = el;
-                key = D + seg_dist(px, py, 0.0, Rn.L);
-                want = key < L.maxb;
+                double x0 = 0.0, x1 = Rn.L, r0 = px * px + py * py, r1 = (Rn.L - px) * (Rn.L - px) + py * py;
+                if (vertex_trim(px, py, D, Rn.L, D3, D1, C.dom_rel, x0, x1, r0, r1)) {
+                    nw.px = (R)px;
+                    nw.py = (R)py;
+                    nw.b0 = (R)x0;
+                    nw.b1 = (R)x1;
+                    nw.sg = (R)D;
+                    nw.c = R(1);
+                    nw.s = R(0);
+                    nw.he = Rn.twin;
+                    nw.root = el;
+                    const double rk = px < x0 ? r0 : px > x1 ? r1 : py * py;
+                    want = !longer(rk, maxb - D);
+                    later = T <= D || rk >= (T - D) * (T - D);
+                }
             }
             // direct targets in face(h): straight segments inside the face
-            const int g = h / 3;
-            int q = 0, q1 = 0;
-            if (act) {
-                q = sd.fstart[g];
-                q1 = sd.fstart[g + 1];
-            }
-            const double *pv = M.V + 3 * (int64_t)v;
-            while (__ballot(q < q1)) {
-                bool ok = false;
-                int j = 0;
-                double d = 0;
-                if (q < q1) {
-                    const FaceTarget t = sd.ftgt[q];
-                    j = q;
-                    if (t.j != src) {
-                        const double *b = t.b;
-                        const int32_t *Tg = M.T + 3 * (int64_t)g;
-                        double x[3] = {0, 0, 0};
-                        for (int c = 0; c < 3; ++c)
-                            for (int dd = 0; dd < 3; ++dd) x[dd] += b[c] * M.V[3 * (int64_t)Tg[c] + dd];
-                        const double dx = x[0] - pv[0], dy = x[1] - pv[1], dz = x[2] - pv[2];
-                        d = D + sqrt(dx * dx + dy * dy + dz * dz);
-                        ok = true;
-                    }
-                    ++q;
-                }
-                target_update(L, td, C, ok, j, d, vtx, vty, D2 + (d - D));
-            }
-            // the two other vertices of face(h), reached along its edges
-            const int u1 = Rh.head, u2 = Rh.opp_flags >> 1;
-            if (act) {
-                vdist_min(Dv, u1, D + Rh.L);
-                vdist_min(Dv, u2, D + Rh.Lp);
-            }
-            const int e1 = act ? M.pidx[u1] : -1;
+            if constexpr (kNear)
+                offer_pairs(ftgt, L, td, C, cnt, q, src,
+                            [&](int own, const FaceTarget &t, double &d, double &tx, double &ty, double &alt) {
+                                const int ko = __shfl(hk, own);
+                                const double bh = head_bary(t, ko), bo = opp_bary(t, ko);
+                                const double x = bh * __shfl(Rh.L, own) + bo * __shfl(Rh.cx, own);
+                                const double y = bo * __shfl(Rh.cy, own), Do = __shfl(D, own);
+                                d = Do + sqrt(x * x + y * y);
+                                tx = __shfl(vtx, own);
+                                ty = __shfl(vty, own);
+                                alt = __shfl(D2, own) + (d - Do);
+                                return true;
+                            });
+            else offer_targets(
+                ftgt, L, td, C, q, src, t0, c0s,
+                [&](const FaceTarget &t, double &d) {
+                    const double bh = head_bary(t, hk), bo = opp_bary(t, hk);
+                    const double x = bh * Rh.L + bo * Rh.cx, y = bo * Rh.cy;
+                    d = D + sqrt(x * x + y * y);
+                    return true;
+                },
+                [&](const FaceTarget &, double d, double &tx, double &ty, double &alt) {
+                    tx = vtx;
+                    ty = vty;
+                    alt = D2 + (d - D);
+                });
             bend_update(G, L.B, C.rc, e1 >= 0, e1, D + Rh.L, vtx, vty, D2 + Rh.L);
-            const int e2 = act ? M.pidx[u2] : -1;
             bend_update(G, L.B, C.rc, e2 >= 0, e2, D + Rh.Lp, vtx, vty, D2 + Rh.Lp);
-            S.push(want, key >= T, nw, st.overflow);
+            S.push(want, later, nw, st.overflow);
         }
         __syncthreads();  // the chunk arrays are rewritten by the next chunk
     }
@@ -606,10 +778,11 @@ __device__ void launch_roots(const AllArgs &a, const SurfDesc &sd, AllLds &L, co
 // FP32 result lies within the guard band around the cutoff (the caller then
 // recomputes the source in FP64; `guard` marks that recompute). Inlined:
 // as a call, the FP32 kernel spills around it and holds one wave per SIMD.
-template <typename R>
+template <typename R, bool kNear>
 __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, const SurfDesc &sd, AllLds &L,
-                                                              TgtState *td, unsigned char *stk,
-                                                              int stk_bytes, unsigned char *later, int src, int slot, bool guard,
+                                                              const TargetTable<kNear> &td, unsigned char *stk,
+                                                              int stk_bytes, unsigned char *later, SortLds *sl, int src, int slot, bool guard,
+                                                              uint32_t &epoch,
                                                               SrcStats &st) {
     const int lane = lane_id();
     const bool fp32 = sizeof(R) == 4;
@@ -620,7 +793,7 @@ __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, 
     const DevMesh &M = sd.m;
     const HeRec *const he = uniform(M.he);
     const HeRecF *const hef = uniform(M.hef);
-    const int32_t *const pidx = uniform(M.pidx), *const ffirst = uniform(sd.ffirst);
+    const int32_t *const pidx = uniform(M.pidx), *const ffirst = uniform(sd.ffirst), *const fstart = uniform(sd.fstart);
     const FaceTarget *const ftgt = uniform(sd.ftgt);
     ACtx C;
     C.tol = fp32 ? a.gp.cone_tol32 : a.gp.cone_tol;
@@ -631,9 +804,20 @@ __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, 
     C.dom_rel = fp32 ? a.gp.dom_rel32 : a.gp.dom_rel;
     // rounds: wide ones mean fewer round changes, but on a surface with bend
     // vertices they launch vertices before their distances settle
-    C.bucket = a.gp.bucket > 0.0 ? a.gp.bucket : (M.n_pseudo > 0 ? 4.0 : 16.0) * M.max_edge;
-    C.cutoff = sd.cutoff;
-    double *Dv = a.vdist + (int64_t)slot * a.vstride;
+    C.bucket = uniform(a.gp.bucket > 0.0 ? a.gp.bucket : (M.n_pseudo > 0 ? 4.0 : 16.0) * M.max_edge);
+    C.cutoff = uniform(sd.cutoff);
+    if constexpr (kNear) {
+        // every entry of earlier sources is void; once the epochs are used
+        // up, the tables are cleared and start over
+        if (--epoch == 0) {
+            for (int v = lane; v < (int)a.vstride; v += kWave) a.vdist[(int64_t)slot * a.vstride + v] = ~0ull;
+            for (int h = lane; h < (int)a.hstride; h += kWave) a.split[(int64_t)slot * a.hstride + h] = ~0ull;
+            epoch = kEpochMax;
+            __syncthreads();
+        }
+    }
+    const unsigned long long ep = kNear ? epoch : 0;
+    const VertexTable<kNear> Dv{a.vdist + (int64_t)slot * a.vstride, ep};
     // one_split: FP64 passes (the FP32 pass's tie band is as wide as its
     // distances' errors) on surfaces with bend vertices, whose windows split
     // often (an aspect-3 torus of 3456 faces: 188k windows a source without
@@ -652,17 +836,24 @@ __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, 
     S.dir = 0;
     S.ldd = reinterpret_cast<typename RecOf<R>::T *>(later);
 
+    // the profile's marks live in LDS, not in registers
+    const bool prof = sd.prof != nullptr && lane == 0;
+    if (prof) {
+        L.clk[0] = clock64();
+        L.clk[2] = L.clk[3] = 0;
+        L.clk[5] = (long long)st.launches;
+    }
     // ---- tables
-    for (int v = lane; v < M.nv; v += kWave) Dv[v] = INFINITY;
-    if (Hv)
-        for (int h = lane; h < 3 * M.nf; h += kWave) Hv[h] = ~0ull;
-    for (int j = lane; j < n; j += kWave) {
-        td[j] = TgtState{};
+    if constexpr (!kNear) {
+        for (int v = lane; v < M.nv; v += kWave) Dv.p[v] = (unsigned long long)__double_as_longlong(INFINITY);
+        if (Hv)
+            for (int h = lane; h < 3 * M.nf; h += kWave) Hv[h] = ~0ull;
+        for (int j = lane; j < n; j += kWave) td[j] = TgtState{};
     }
     if (lane == 0) {
         L.B.npend = 0;
         L.B.ntouched = 0;
-        L.unfound = n - 1;
+        L.unfound = kNear ? 0 : n - 1;
         L.maxb = C.cutoff < INFINITY ? C.cutoff * (fp32 ? 1.0 + fmax(a.gp.slack32, a.gp.guard_rel) : 1.0)
                                      : INFINITY;
     }
@@ -696,7 +887,7 @@ __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, 
                         tx = dx / d;
                         ty = dy / d;
                     }
-                    ok = true;
+                    ok = !kNear || d < L.maxb;
                 }
                 ++q;
             }
@@ -717,7 +908,7 @@ __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, 
             {
                 const double dx = P[k][0] - sx, dy = P[k][1] - sy;
                 rd = sqrt(dx * dx + dy * dy);
-                vdist_min(Dv, v, rd);
+                Dv.put(v, rd);
                 rv = M.pidx[v];
                 if (rv >= 0) {
                     rtx = rd > 0 ? dx / rd : 0.0;
@@ -785,7 +976,7 @@ __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, 
                             tx = c * dx - s * dy;
                             ty = s * dx + c * dy;
                         }
-                        ok = true;
+                        ok = !kNear || d < L.maxb;
                     }
                     ++q;
                 }
@@ -794,7 +985,7 @@ __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, 
             const double dx = Rt.cx - ptx, dy = Rt.cy;
             const double d = sqrt(dx * dx + dy * dy);
             const int opp = Rt.opp_flags >> 1;
-            if (lane == 0) vdist_min(Dv, opp, d);
+            if (lane == 0) Dv.put(opp, d);
             const int eo = lane == 0 ? M.pidx[opp] : -1;
             bend_update(G, L.B, C.rc, eo >= 0, eo, d, (c * dx - s * dy) / d, (s * dx + c * dy) / d, INFINITY);
         }
@@ -804,6 +995,7 @@ __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, 
     }
 
     // ---- propagation, round by round
+    if (prof) L.clk[1] = clock64();
     bool have = false;
     Win<R> w;
     double DA = INFINITY, DB = INFINITY;  // vertex distances of the window's half-edge (infinite: not read yet)
@@ -815,7 +1007,9 @@ __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, 
         depth = max(depth, S.lsp + S.gsp + S.dsp + S.dl);
         bool busy = S.refill(have, w);
         if (!busy && L.B.npend > 0) {
-            launch_roots(a, sd, L, G, td, Dv, C, S, T, src, st);
+            if (prof) L.clk[2] -= clock64();
+            launch_roots<R, kNear>(sd, L, G, td, Dv, C, S, T, src, st);
+            if (prof) L.clk[2] += clock64();
             busy = S.refill(have, w);
         }
         if (!busy) {
@@ -823,7 +1017,7 @@ __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, 
             // next round; once every target is reached, bound the keys
             S.next_round(overflow);
             T += C.bucket;
-            if (L.unfound == 0) {
+            if (!kNear && L.unfound == 0) {
                 __syncthreads();  // every lane's target stores are visible
                 double mx = 0.0;
                 for (int q = lane; q < n; q += kWave)
@@ -839,13 +1033,14 @@ __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, 
             overflow = true;
             break;
         }
+        if (prof) ++L.clk[3];
         // Three rounds of loads an iteration, each issued as a whole: the
         // records that the window names (half-edge and its entry, the face's
         // first target, the root's entry), then what those name (vertex
         // distances, the target, the third vertex's number), then the third
         // vertex's bend entry, which the children's arithmetic covers.
         He<R> H;
-        int vA = 0, vB = 0, q0 = -1;
+        int vA = 0, vB = 0, q0 = -1, qcnt = 0;
         bool act = have;
         double txc = 0.0;
         int k = 0;
@@ -857,7 +1052,12 @@ __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, 
             H = load_he(he, hef, w.he, R(0));
             vA = he[w.he].tail;
             vB = he[w.he].head;
-            q0 = ffirst[f];
+            if constexpr (kNear) {
+                q0 = fstart[f];
+                qcnt = fstart[f + 1] - q0;
+            } else {
+                q0 = ffirst[f];
+            }
             if (Hv) hw = Hv[w.he];
             double rD = 0.0, rL = INFINITY;
             if (w.root >= 0) {
@@ -874,6 +1074,7 @@ __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, 
             }
             if (!act) {
                 q0 = -1;
+                qcnt = 0;
                 DA = DB = INFINITY;
             }
         }
@@ -889,7 +1090,7 @@ __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, 
             if (!(DA < INFINITY)) DA = Dv[vA];
             if (!(DB < INFINITY)) DB = Dv[vB];
             DC = Dv[H.opp];
-            if (q0 >= 0) {
+            if (!kNear && q0 >= 0) {
                 t0 = ftgt[q0];
                 c0 = td[q0];
             }
@@ -904,7 +1105,7 @@ __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, 
             if (Hv && cin) {
                 const double dx = (double)H.cx - px, dy = (double)H.cy - py;
                 dcv = sg + sqrt(dx * dx + dy * dy);
-                const int sides = one_split(Hv, w.he, hw, dcv, txc, (double)H.L, C.split_rel);
+                const int sides = one_split(Hv, ep, w.he, hw, dcv, txc, (double)H.L, C.split_rel);
                 go_l = go_l && (sides & 1);
                 go_r = go_r && (sides & 2);
             }
@@ -913,25 +1114,26 @@ __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, 
             // values are combined with this window's own paths, which then go
             // to the table (compared in squares first: few are shorter)
             const double rA = px * px + py * py, rB = ((double)H.L - px) * ((double)H.L - px) + py * py;
-            if ((double)w.b0 <= 0.0 && !longer(rA, DA - sg)) {
+            if ((double)w.b0 <= 0.0 && Dv.shorter(rA, DA, sg)) {
                 DA = fmin(DA, sg + sqrt(rA));
-                vdist_min(Dv, vA, DA);
+                Dv.put(vA, DA);
             }
-            if ((double)w.b1 >= (double)H.L && !longer(rB, DB - sg)) {
+            if ((double)w.b1 >= (double)H.L && Dv.shorter(rB, DB, sg)) {
                 DB = fmin(DB, sg + sqrt(rB));
-                vdist_min(Dv, vB, DB);
+                Dv.put(vB, DB);
             }
             if (cin) {
                 const double dx = (double)H.cx - px, dy = (double)H.cy - py;
                 const double rC = dx * dx + dy * dy;
                 if (!Hv) dcv = sg + sqrt(rC);
-                if (!longer(rC, DC - sg)) {
+                if (Dv.shorter(rC, DC, sg)) {
                     DC = fmin(DC, dcv);
-                    vdist_min(Dv, H.opp, DC);
+                    Dv.put(H.opp, DC);
                 }
             }
         }
-        query_face(ftgt, L, td, C, q0, src, k, H, w, wtx, wty, wD2, t0, c0);
+        if constexpr (kNear) query_pairs(ftgt, L, td, C, qcnt, q0, src, k, H, w, wtx, wty, wD2);
+        else query_face(ftgt, L, td, C, q0, src, k, H, w, wtx, wty, wD2, t0, c0);
         // third vertex as a bend vertex: its entry is loaded here and updated
         // after the children
         const bool ok3 = eo >= 0 && cin;
@@ -1011,6 +1213,7 @@ __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, 
     }
 
     // ---- results: row src, entry j for target j
+    if (prof) L.clk[4] = clock64();
     const int32_t *Tt = M.T;
     const double *p0 = M.V + 3 * (int64_t)Tt[3 * fs], *p1 = M.V + 3 * (int64_t)Tt[3 * fs + 1];
     const double *nn = M.fnrm + 3 * (int64_t)fs;
@@ -1025,9 +1228,8 @@ __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, 
     const int64_t c0 = (int64_t)src * sd.cap;
     bool near_cut = false;
     __syncthreads();  // every lane's tangent stores are visible
-    for (int q = lane; q < n; q += kWave) {
-        const int j = sd.ftgt[q].j;
-        const int64_t o = c0 + j;
+    // one result: place s of the row, target at place q of the by-face index
+    auto result = [&](int64_t o, int q, int j) {
         const TgtState t = td[q];
         double d = t.d1;
         uint8_t fl = guard ? GSIM_PAIR_GUARD_BIT : 0;
@@ -1039,10 +1241,68 @@ __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, 
         sd.cdist[o] = d;
         sd.cflags[o] = fl;
         for (int qd = 0; qd < 3; ++qd) sd.ctan[3 * o + qd] = t.tx * ex3[qd] + t.ty * ey3[qd];
+    };
+    if constexpr (!kNear) {
+        // row src, entry j for target j
+        for (int q = lane; q < n; q += kWave) {
+            const int j = sd.ftgt[q].j;
+            result(c0 + j, q, j);
+        }
+    } else {
+        // the targets reached, in ascending particle order
+        const int nt = L.unfound, cap = min(sd.cap, kBigCandMax);
+        if (lane == 0) sd.cand_cnt[src] = nt;
+        if (nt > cap) {
+            st.overflow = true;  // more targets than the row holds
+        } else {
+            int P = 1;
+            while (P < nt) P <<= 1;
+            unsigned long long *key = P <= kSortLds ? sl->key : reinterpret_cast<unsigned long long *>(
+                reinterpret_cast<char *>(a.sort) + (int64_t)slot * a.tstride);
+            for (int s = lane; s < P; s += kWave) {
+                unsigned long long x = ~0ull;
+                if (s < nt) {
+                    const int q = td.touch[s];
+                    x = (unsigned long long)(unsigned)sd.ftgt[q].j << 32 | (unsigned)q;
+                }
+                key[s] = x;
+            }
+            __syncthreads();
+            // bitonic sort of key[0, P) ascending
+            for (int kk = 2; kk <= P; kk <<= 1)
+                for (int jj = kk >> 1; jj > 0; jj >>= 1) {
+                    for (int s = lane; s < P; s += kWave) {
+                        const int t = s ^ jj;
+                        if (t > s) {
+                            const unsigned long long x = key[s], y = key[t];
+                            if ((x > y) == ((s & kk) == 0)) {
+                                key[s] = y;
+                                key[t] = x;
+                            }
+                        }
+                    }
+                    __syncthreads();
+                }
+            for (int s = lane; s < nt; s += kWave) {
+                const int j = (int)(key[s] >> 32);
+                sd.cand[c0 + s] = j;
+                result(c0 + s, (int)(unsigned)key[s], j);
+            }
+        }
+        for (int s = lane; s < nt; s += kWave) td[td.touch[s]] = TgtState{};
+        __syncthreads();
     }
-    if (sd.prof && lane == 0) {
+    if (prof) {
         long long *qp = sd.prof + 8 * (int64_t)src;
+        const long long t_end = clock64();
+        qp[0] += t_end - L.clk[0];
+        qp[1] += L.clk[3];
         qp[2] += (long long)nwin;
+        qp[3] += (long long)st.launches - L.clk[5];
+        qp[4] += L.clk[1] - L.clk[0];
+        qp[5] += L.clk[4] - L.clk[1] - L.clk[2];
+        qp[6] += L.clk[2];
+        qp[7] += t_end - L.clk[4];
     }
     st.windows += nwin;
     st.pruned += pruned;
@@ -1052,18 +1312,25 @@ __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, 
     return fp32 && !ovf && __ballot(near_cut) != 0;
 }
 
-template <bool kMixed, int kStk>
+// kNear: a pass with a cutoff whose rows hold only the targets within it
+// (whole-mesh passes: a row holds every particle).
+template <bool kMixed, int kStk, bool kNear>
 __global__ __launch_bounds__(kWave, 2) void k_geodesic_all(AllArgs a) {
     __shared__ AllLds L;
+    __shared__ typename SortOf<kNear>::T sorted;
     __shared__ alignas(16) unsigned char stk[kStk];
     __shared__ alignas(16) unsigned char later[kWave * sizeof(Rec64)];
-    TgtState *td = a.ttab + (size_t)blockIdx.x * a.tcap;
+    const int64_t off = (int64_t)blockIdx.x * a.tstride;
+    const TargetTable<kNear> td{reinterpret_cast<TgtState *>(reinterpret_cast<char *>(a.ttab) + off),
+                                kNear ? reinterpret_cast<int32_t *>(reinterpret_cast<char *>(a.touch) + off) : nullptr};
+    uint32_t epoch = kNear ? __builtin_amdgcn_readfirstlane(a.epoch[blockIdx.x]) : 0;
+    SortLds *sl = kNear ? reinterpret_cast<SortLds *>(&sorted) : nullptr;
     const int lane = lane_id();
     const int total = a.bi.begin[a.bi.nsurf];
     int chunk = blockIdx.x % kChunks, chunks_left = kChunks;
     SrcStats st;
-    st.windows = st.launches = st.stale = st.guards = 0;
-    st.pruned = 0;
+    st.windows = st.launches = st.guards = 0;
+    st.stale = st.pruned = 0;
     st.depth = 0;
     st.overflow = false;
     unsigned long long c_limited = 0;
@@ -1090,81 +1357,132 @@ __global__ __launch_bounds__(kWave, 2) void k_geodesic_all(AllArgs a) {
         --left;
         const int si = __builtin_amdgcn_readfirstlane(batch_surface(a.bi, idx));
         const SurfDesc &sd = a.sd[si];
-        const int src = idx - a.bi.begin[si];
-        if (lane == 0) sd.cand_cnt[src] = sd.n;
+        const int src = sd.ftgt[idx - a.bi.begin[si]].j;  // in the faces' order: neighbours run together
+        if (!kNear && lane == 0) sd.cand_cnt[src] = sd.n;
         st.overflow = false;
         bool again = !kMixed;
-        if (kMixed) again = run_all<float>(a, sd, L, td, stk, kStk, later, src, blockIdx.x, false, st);
+        if (kMixed) again = run_all<float, kNear>(a, sd, L, td, stk, kStk, later, sl, src, blockIdx.x, false, epoch, st);
         if (again) {
             // FP64 (the plain path, or the recompute of an FP32 source whose
             // results come too close to the cutoff to decide in FP32)
-            run_all<double>(a, sd, L, td, stk, kStk, later, src, blockIdx.x, kMixed, st);
+            run_all<double, kNear>(a, sd, L, td, stk, kStk, later, sl, src, blockIdx.x, kMixed, epoch, st);
             st.guards += kMixed ? 1 : 0;
         }
         if (st.overflow) ++c_limited;
     }
-    unsigned long long pr = (unsigned long long)st.pruned, sl = st.stale;
+    if (kNear && lane == 0) a.epoch[blockIdx.x] = epoch;
+    unsigned long long pr = (unsigned long long)st.pruned, stale = (unsigned long long)st.stale;
     for (int o = 32; o > 0; o >>= 1) {
         pr += __shfl_xor(pr, o);
-        sl += __shfl_xor(sl, o);
+        stale += __shfl_xor(stale, o);
     }
     if (lane == 0) {
-        atomicAdd(&a.ctr->windows, st.windows);
-        atomicAdd(&a.ctr->pruned, pr);
-        atomicAdd(&a.ctr->launches, st.launches);
-        atomicAdd(&a.ctr->stale, sl);
-        atomicAdd(&a.ctr->guards, st.guards);
-        atomicAdd(&a.ctr->limited, c_limited);
-        atomicMax(&a.ctr->max_depth, (unsigned long long)st.depth);
+        // only the counts that are not zero, in one of several slots
+        Counters *ctr = a.ctr + ((int)blockIdx.x % kCtrSlots) * kCtrStride;
+        if (st.windows) atomicAdd(&ctr->windows, st.windows);
+        if (pr) atomicAdd(&ctr->pruned, pr);
+        if (st.launches) atomicAdd(&ctr->launches, st.launches);
+        if (stale) atomicAdd(&ctr->stale, stale);
+        if (st.guards) atomicAdd(&ctr->guards, st.guards);
+        if (c_limited) atomicAdd(&ctr->limited, c_limited);
+        if (st.depth) atomicMax(&ctr->max_depth, (unsigned long long)st.depth);
     }
 }
 
-template <bool kMixed>
+template <bool kMixed, bool kNear>
 const void *kernel_of(int kb) {
-    if (kb <= 4) return (const void *)&k_geodesic_all<kMixed, 4096>;
-    if (kb <= 8) return (const void *)&k_geodesic_all<kMixed, 8192>;
-    return (const void *)&k_geodesic_all<kMixed, 16384>;
+    if (kb <= 4) return (const void *)&k_geodesic_all<kMixed, 4096, kNear>;
+    if (kb <= 8) return (const void *)&k_geodesic_all<kMixed, 8192, kNear>;
+    return (const void *)&k_geodesic_all<kMixed, 16384, kNear>;
 }
 
-template <bool kMixed>
-void launch_variant(int kb, int nslots, const AllArgs &a, hipStream_t s) {
-    if (kb <= 4) hipLaunchKernelGGL((k_geodesic_all<kMixed, 4096>), dim3(nslots), dim3(kWave), 0, s, a);
-    else if (kb <= 8) hipLaunchKernelGGL((k_geodesic_all<kMixed, 8192>), dim3(nslots), dim3(kWave), 0, s, a);
-    else hipLaunchKernelGGL((k_geodesic_all<kMixed, 16384>), dim3(nslots), dim3(kWave), 0, s, a);
+template <bool kMixed, bool kNear>
+void launch_variant(int kb, int nslots, size_t pad, const AllArgs &a, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+    void (*f)(AllArgs) = kb <= 4 ? &k_geodesic_all<kMixed, 4096, kNear>
+                                 : kb <= 8 ? &k_geodesic_all<kMixed, 8192, kNear> : &k_geodesic_all<kMixed, 16384, kNear>;
+    if (ev0 || ev1) hipExtLaunchKernelGGL(f, dim3(nslots), dim3(kWave), (uint32_t)pad, s, ev0, ev1, 0, a);
+    else hipLaunchKernelGGL(f, dim3(nslots), dim3(kWave), pad, s, a);
 }
+
+// Byte offsets of one wavefront's near-pass area: target states, reached
+// list, sort keys.
+struct NearArea {
+    int64_t touch, sort, bytes;
+    explicit NearArea(int tcap)
+        : touch((int64_t)tcap * sizeof(TgtState)), sort((touch + 4 * (int64_t)tcap + 15) / 16 * 16),
+          bytes((sort + 8 * (int64_t)kBigCandMax + 255) / 256 * 256) {}
+};
 
 }  // namespace
 
+int64_t near_area_bytes(int tcap) { return NearArea(tcap).bytes; }
+
+hipError_t launch_near_init(char *area, int nslots, int tcap, unsigned long long *vdist, int64_t vstride,
+                            unsigned long long *split, int64_t hstride, uint32_t *epoch, hipStream_t s) {
+    // every target unreached, every vertex and half-edge entry void. (A
+    // double of all-ones bits would be a NaN: the states get infinities.)
+    hipError_t e = launch_fill_u64(reinterpret_cast<unsigned long long *>(area), (int64_t)nslots * near_area_bytes(tcap) / 8,
+                                   0x7ff0000000000000ull, s);
+    if (e == hipSuccess) e = launch_fill_u64(vdist, (int64_t)nslots * vstride, ~0ull, s);
+    if (e == hipSuccess && hstride) e = launch_fill_u64(split, (int64_t)nslots * hstride, ~0ull, s);
+    if (e == hipSuccess)
+        e = launch_fill_u64(reinterpret_cast<unsigned long long *>(epoch), (nslots + 1) / 2,
+                            (unsigned long long)kEpochMax << 32 | kEpochMax, s);
+    return e;
+}
+
 hipError_t launch_geodesic_all(const SurfDesc *desc, const BatchIdx &bi, const GeoParams &gp, const GeoShape &shape,
-                               char *stack_mem, double *vdist, int64_t vstride, char *roots, int64_t rstride,
+                               char *stack_mem, unsigned long long *vdist, int64_t vstride, char *roots, int64_t rstride,
                                int rcap, void *ttab, int tcap, unsigned long long *split, int64_t hstride,
-                               int32_t *work_ctr, Counters *ctr, bool fp32, hipStream_t s) {
+                               uint32_t *epoch, int32_t *work_ctr, Counters *ctr, bool fp32, hipStream_t s,
+                               hipEvent_t ev0, hipEvent_t ev1) {
+    const bool near = epoch != nullptr;
     AllArgs a;
-    a.split = split;
-    a.hstride = hstride;
     a.sd = desc;
     a.bi = bi;
     a.gp = gp;
     a.stack = stack_mem;
     a.vdist = vdist;
     a.vstride = vstride;
+    a.split = split;
+    a.hstride = hstride;
     a.roots = roots;
     a.rstride = rstride;
     a.rcap = rcap;
     a.work = work_ctr;
     a.ctr = ctr;
+    a.ttab = static_cast<TgtState *>(ttab);
     a.tcap = tcap;
+    const NearArea na(tcap);
+    a.tstride = near ? na.bytes : (int64_t)tcap * sizeof(TgtState);
+    a.touch = near ? reinterpret_cast<int32_t *>(static_cast<char *>(ttab) + na.touch) : nullptr;
+    a.sort = near ? reinterpret_cast<unsigned long long *>(static_cast<char *>(ttab) + na.sort) : nullptr;
+    a.epoch = epoch;
     a.grab = shape.grab < 1 ? 1 : shape.grab;
     if (shape.nslots < 1 || bi.begin[bi.nsurf] < 1) return hipSuccess;
-    a.ttab = static_cast<TgtState *>(ttab);
-    if (fp32) launch_variant<true>(shape.lds_stack_kb, shape.nslots, a, s);
-    else launch_variant<false>(shape.lds_stack_kb, shape.nslots, a, s);
+    const int kb = shape.lds_stack_kb, ns = shape.nslots;
+    const size_t pad = shape.pad_lds > 0 ? (size_t)shape.pad_lds : 0;
+    if (fp32 && near) launch_variant<true, true>(kb, ns, pad, a, s, ev0, ev1);
+    else if (fp32) launch_variant<true, false>(kb, ns, pad, a, s, ev0, ev1);
+    else if (near) launch_variant<false, true>(kb, ns, pad, a, s, ev0, ev1);
+    else launch_variant<false, false>(kb, ns, pad, a, s, ev0, ev1);
     return hipGetLastError();
 }
 
-int geodesic_all_blocks_per_cu(int lds_stack_kb, bool fp32) {
+static const void *kernel_for(int kb, bool fp32, bool near) {
+    if (near) return fp32 ? kernel_of<true, true>(kb) : kernel_of<false, true>(kb);
+    return fp32 ? kernel_of<true, false>(kb) : kernel_of<false, false>(kb);
+}
+
+size_t geodesic_all_lds_bytes(int lds_stack_kb, bool fp32, bool near) {
+    hipFuncAttributes at{};
+    if (hipFuncGetAttributes(&at, kernel_for(lds_stack_kb, fp32, near)) != hipSuccess) return 65536;
+    return at.sharedSizeBytes;
+}
+
+int geodesic_all_blocks_per_cu(int lds_stack_kb, bool fp32, bool near) {
     int nb = 0;
-    const void *f = fp32 ? kernel_of<true>(lds_stack_kb) : kernel_of<false>(lds_stack_kb);
+    const void *f = kernel_for(lds_stack_kb, fp32, near);
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, f, kWave, 0) != hipSuccess)
         return 0;
     return nb;

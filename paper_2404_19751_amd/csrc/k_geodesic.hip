@@ -85,7 +85,6 @@ template <int kG>
 constexpr int kGroupCand = kMaxCand / kG;
 template <int kG>
 constexpr int kGroupBuckets = kHash / kG;
-constexpr int kBigStk = 8192;  // LDS window stack of the big-candidate instantiation
 constexpr int kChunks = 8;
 static_assert(kChunks == kWorkChunks, "one work counter per chunk");
 
@@ -100,9 +99,6 @@ struct GeoArgs {
     char *roots;         // per wave: a bend-vertex table (rstride bytes, rcap vertices)
     int64_t rstride;
     int rcap;
-    char *gtab;          // big-candidate mode: per wave the target arrays of gcap targets (gstride bytes)
-    int64_t gstride;
-    int gcap;
     int pre_cand;        // the candidate rows and counts were written ahead of the pass (k_candidates)
 };
 
@@ -110,11 +106,8 @@ struct GeoArgs {
 // next target of the same face bucket, barycentrics, position with the
 // current pruning bound, best and other-direction distances and the best
 // tangent; a hash of faces to chains of targets; the bend-vertex state.
-// Either all in LDS (at most kMaxCand targets, Lds), or, for sources with
-// more candidates, the per-target arrays in a per-wavefront global area and
-// the rest in LDS (GTab): the helpers below are written once for both.
+// (Sources with more candidates run in near passes, not here.)
 struct Lds {
-    static constexpr bool kBig = false;
     static constexpr int kBuckets = kHash;
     int32_t tj[kMaxCand], tface[kMaxCand], tnext[kMaxCand];
     double tb[kMaxCand][3];
@@ -131,47 +124,13 @@ struct Lds {
     BendLds B;
 };
 
-// Big-candidate mode: hash heads, the bend-vertex state and the sort buffer
-// of the candidate search in LDS.
-constexpr int kBigHash = 1024;
-constexpr int kBigSort = kBigCandMax;  // candidates are sorted in LDS
-struct LdsBig {
-    int32_t head[kBigHash];
-    int32_t ncand;
-    int32_t key[kBigSort];
-    BendLds B;
-};
-struct GTab {
-    static constexpr bool kBig = true;
-    static constexpr int kBuckets = kBigHash;
-    int32_t *tj, *tface, *tnext;
-    double (*tb)[3];
-    double (*cb)[4];
-    double *d1, *d2, *t1x, *t1y;
-    int32_t *head;
-    int32_t &ncand;
-    BendLds &B;
-};
-// Bytes of one wavefront's global target arrays for gcap targets.
-__host__ __device__ inline int64_t gtab_bytes(int gcap) { return ((int64_t)gcap * 100 + 255) / 256 * 256; }
-__device__ inline GTab gtab_of(char *base, int64_t stride, int slot, int gcap, LdsBig &LB) {
-    char *p = base + (int64_t)slot * stride;
-    double *dp = reinterpret_cast<double *>(p);  // the doubles first: 11 per target
-    double(*cb)[4] = reinterpret_cast<double(*)[4]>(dp);
-    double(*tb)[3] = reinterpret_cast<double(*)[3]>(dp + 4 * (int64_t)gcap);
-    double *d1 = dp + 7 * (int64_t)gcap;
-    int32_t *ip = reinterpret_cast<int32_t *>(dp + 11 * (int64_t)gcap);
-    return GTab{ip, ip + gcap, ip + 2 * (int64_t)gcap, tb, cb, d1, d1 + gcap, d1 + 2 * (int64_t)gcap,
-                d1 + 3 * (int64_t)gcap, LB.head, LB.ncand, LB.B};
-}
-
 // Multiplicative hash of a face index: the top bits of f times the golden
 // ratio in 32-bit fixed point (256 buckets: the top 8 bits). kB buckets per
 // source: the table's own count, or half of it for each source of a pair.
 template <int kB>
 __device__ inline int hash_bits(int f) {
-    static_assert(kB == 32 || kB == 64 || kB == 128 || kB == 256 || kB == 1024, "bucket counts");
-    constexpr int kShift = kB == 32 ? 27 : (kB == 64 ? 26 : (kB == 128 ? 25 : (kB == 256 ? 24 : 22)));
+    static_assert(kB == 32 || kB == 64 || kB == 128 || kB == 256, "bucket counts");
+    constexpr int kShift = kB == 32 ? 27 : (kB == 64 ? 26 : (kB == 128 ? 25 : 24));
     return (int)(((uint32_t)f * 2654435761u) >> kShift) & (kB - 1);
 }
 template <class TL>
@@ -239,9 +198,6 @@ struct Ctx {
 template <class TL>
 __device__ inline bool reaches_target(const TL &L, const Ctx &C, const double P[3], const double u[3], double x0,
                                       double x1, double base, int tb = 0, int nc4 = -1) {
-    // with more targets than the LDS table holds, nearly every window within
-    // the cutoff can still improve one of them: only the cutoff prunes
-    if constexpr (TL::kBig) return base < C.cut_acc;
     const int te = tb + (nc4 < 0 ? C.nc4 : nc4);  // the source's targets: [tb, te)
     for (int s0 = tb; s0 < te; s0 += 4) {
         bool hit = false;
@@ -430,10 +386,9 @@ __device__ void launch_roots(const GeoArgs &a, const SurfDesc &sd, TL &L, const 
                 const int q = slot_of<kG>(e);
                 const PseudoRec pr = M.prec[bend_vertex<kG>(e)];
                 const double D = G.rD[e];
-                // big-candidate mode: every vertex within the cutoff (as for windows)
-                bool useful = TL::kBig;
+                bool useful = false;
                 const int tb = q * tspan, te = tb + (kG == 1 ? C.nc : ncs[q]);
-                for (int s = tb; !TL::kBig && s < te && !useful; ++s) {
+                for (int s = tb; s < te && !useful; ++s) {
                     const double bound = L.cb[s][3] - D;
                     const double q0 = L.cb[s][0] - pr.x, q1 = L.cb[s][1] - pr.y, q2 = L.cb[s][2] - pr.z;
                     useful = bound > 0.0 && q0 * q0 + q1 * q1 + q2 * q2 < bound * bound;
@@ -775,98 +730,6 @@ __global__ __launch_bounds__(kWave) void k_candidates(const SurfDesc *__restrict
     }
 }
 
-// The Euclidean prefilter of one source in big-candidate mode: the 27 cells'
-// particle ranges are flattened over the lanes, the hits collected in LDS,
-// bitonic-sorted by particle index and written to the table and the row.
-// Returns the true count (more than cap is an overflow the caller reports).
-__device__ int find_candidates_big(const SurfDesc &sd, LdsBig &LB, GTab &T, int src, int64_t c0, int cap) {
-    const int lane = lane_id();
-    if (lane == 0) LB.ncand = 0;
-    const double xi = sd.xyz[3 * (int64_t)src], yi = sd.xyz[3 * (int64_t)src + 1], zi = sd.xyz[3 * (int64_t)src + 2];
-    const int lin = sd.cell_of[src];
-    const int cx = lin % sd.dims[0], cy = (lin / sd.dims[0]) % sd.dims[1], cz = lin / (sd.dims[0] * sd.dims[1]);
-    // lane l < 27: the particle range of neighbour cell l
-    int b = 0, e = 0;
-    if (lane < 27) {
-        const int x = cx + lane % 3 - 1, y = cy + (lane / 3) % 3 - 1, z = cz + lane / 9 - 1;
-        if (x >= 0 && x < sd.dims[0] && y >= 0 && y < sd.dims[1] && z >= 0 && z < sd.dims[2]) {
-            const int c = (z * sd.dims[1] + y) * sd.dims[0] + x;
-            b = sd.cell_start[c];
-            e = sd.cell_start[c + 1];
-        }
-    }
-    int inc = e - b;
-    for (int o = 1; o < kWave; o <<= 1) {
-        const int y = __shfl_up(inc, o);
-        if (lane >= o) inc += y;
-    }
-    const int total_in = __builtin_amdgcn_readlane(inc, 26);
-    const int excl = inc - (e - b);
-    // every cell's start in the flattened order and in the particle order, wave-uniform
-    int cs[27], cb0[27];
-#pragma unroll
-    for (int l = 0; l < 27; ++l) {
-        cs[l] = __builtin_amdgcn_readlane(excl, l);
-        cb0[l] = __builtin_amdgcn_readlane(b, l);
-    }
-    __syncthreads();
-    for (int q0 = 0; q0 < total_in; q0 += kWave) {
-        const int q = q0 + lane;
-        if (q >= total_in) continue;
-        // the cell holding flattened position q: the last one starting at or before q
-        int cell = 0;
-#pragma unroll
-        for (int l = 1; l < 27; ++l) cell = cs[l] <= q ? l : cell;
-        int base = cb0[0], st0 = cs[0];
-#pragma unroll
-        for (int l = 1; l < 27; ++l)
-            if (cell == l) {
-                base = cb0[l];
-                st0 = cs[l];
-            }
-        const int j = sd.order[base + (q - st0)];
-        if (j == src) continue;
-        const double ex = sd.xyz[3 * (int64_t)j] - xi, ey = sd.xyz[3 * (int64_t)j + 1] - yi,
-                     ez = sd.xyz[3 * (int64_t)j + 2] - zi;
-        if (ex * ex + ey * ey + ez * ez < sd.cut2) {
-            const int pos = atomicAdd(&LB.ncand, 1);
-            if (pos < kBigSort) LB.key[pos] = j;
-        }
-    }
-    __syncthreads();
-    const int total = LB.ncand;
-    const int m = min(total, min(cap, kBigSort));
-    int P = 1;
-    while (P < m) P <<= 1;
-    for (int s = m + lane; s < P; s += kWave) LB.key[s] = 0x7fffffff;
-    __syncthreads();
-    // bitonic sort of key[0, P) ascending
-    for (int k = 2; k <= P; k <<= 1) {
-        for (int jj = k >> 1; jj > 0; jj >>= 1) {
-            for (int s = lane; s < P; s += kWave) {
-                const int t = s ^ jj;
-                if (t > s) {
-                    const int a0 = LB.key[s], a1 = LB.key[t];
-                    const bool up = (s & k) == 0;
-                    if ((a0 > a1) == up) {
-                        LB.key[s] = a1;
-                        LB.key[t] = a0;
-                    }
-                }
-            }
-            __syncthreads();
-        }
-    }
-    for (int s = lane; s < m; s += kWave) {
-        const int j = LB.key[s];
-        T.tj[s] = j;
-        sd.cand[c0 + s] = j;
-    }
-    if (lane == 0) sd.cand_cnt[src] = total;
-    __syncthreads();
-    return total;
-}
-
 // Geodesics from the wavefront's sources to their candidate targets; writes
 // their rows and returns whether any pair lies inside the guard band of the
 // cutoff. Always inlined: the FP32-mixed kernel holds both precisions'
@@ -877,7 +740,6 @@ __device__ __attribute__((always_inline)) inline unsigned run_sources(const GeoA
                                                                   unsigned char *stk, int stk_bytes, const int *srcs,
                                                                   const int64_t *c0s, const int *ncs, int nsrc,
                                                                   bool guard_mode, int slot_id, SrcStats &st) {
-    static_assert(kG == 1 || !TL::kBig, "groups: LDS tables only");
     constexpr int kB = kG == 1 ? TL::kBuckets : kGroupBuckets<kG>;  // hash buckets per source
     const int lane = lane_id();
     const long long t_start = clock64();
@@ -1360,19 +1222,17 @@ __device__ __attribute__((always_inline)) inline int fused_move(const SurfDesc &
 // compiles to fewer registers; 2: as 1, and the source particle is then moved
 // (the fused update). Only mode 2 holds the update's code, which would
 // otherwise change the register allocation of every launch.
-// kBig: the big-candidate instantiation (targets in a per-wavefront global
-// area, rows as wide as the surface's row capacity).
 // kG = 2 or 4: the grouped instantiations (persistent grid, LDS tables): a
 // wavefront claims kG sources at a time and propagates together those on
 // the same surface with at most kGroupCand candidates each; a source with
 // more runs alone over the whole table. In FP32-mixed mode the group runs in
 // FP32 and each of its sources with a pair in the guard band again alone in
 // FP64.
-template <bool kMixed, int kStk, int kMode, bool kBig, int kG = 1>
+template <bool kMixed, int kStk, int kMode, int kG = 1>
 __global__ __launch_bounds__(kWave, 2) void k_geodesic(GeoArgs a) {
     constexpr bool kOne = kMode >= 1, kFuse = kMode == 2;
-    static_assert(kG == 1 || (kMode == 0 && !kBig), "groups: persistent LDS-table launches");
-    __shared__ typename std::conditional<kBig, LdsBig, Lds>::type L;
+    static_assert(kG == 1 || kMode == 0, "groups: persistent launches");
+    __shared__ Lds L;
     __shared__ alignas(16) unsigned char stk[kStk];
     const int lane = lane_id();
     const int total = a.bi.begin[a.bi.nsurf];
@@ -1499,17 +1359,9 @@ __global__ __launch_bounds__(kWave, 2) void k_geodesic(GeoArgs a) {
                 if (st.overflow) ++c_limited;
             }
         };
-        if constexpr (kBig) {
-            const int cap = min(sd.cap, min(a.gcap, kBigSort));
-            const int64_t c0 = (int64_t)src * sd.cap;
-            GTab T = gtab_of(a.gtab, a.gstride, blockIdx.x, a.gcap, L);
-            const int nc = find_candidates_big(sd, L, T, src, c0, cap);
-            process(T, c0, nc, cap);
-        } else {
-            const int64_t c0 = (int64_t)src * kMaxCand;
-            const int nc = find_candidates(sd, L, src, c0);
-            process(L, c0, nc, kMaxCand);
-        }
+        const int64_t c0 = (int64_t)src * kMaxCand;
+        const int nc = find_candidates(sd, L, src, c0);
+        process(L, c0, nc, kMaxCand);
         if (kOne) {
             // one source per workgroup (in mode 2 its particle is moved below)
             fused_src = src;
@@ -1546,42 +1398,41 @@ __global__ __launch_bounds__(kWave, 2) void k_geodesic(GeoArgs a) {
     }
 }
 
-template <bool kMixed, int kStk, int kMode, bool kBig, int kG = 1>
+template <bool kMixed, int kStk, int kMode, int kG = 1>
 void launch_one(int nslots, size_t pad, const GeoArgs &a, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
     if (ev0 || ev1)
-        hipExtLaunchKernelGGL((k_geodesic<kMixed, kStk, kMode, kBig, kG>), dim3(nslots), dim3(kWave), (uint32_t)pad, s,
+        hipExtLaunchKernelGGL((k_geodesic<kMixed, kStk, kMode, kG>), dim3(nslots), dim3(kWave), (uint32_t)pad, s,
                               ev0, ev1, 0, a);
-    else hipLaunchKernelGGL((k_geodesic<kMixed, kStk, kMode, kBig, kG>), dim3(nslots), dim3(kWave), pad, s, a);
+    else hipLaunchKernelGGL((k_geodesic<kMixed, kStk, kMode, kG>), dim3(nslots), dim3(kWave), pad, s, a);
 }
 // the grouped instantiations: persistent grid, LDS tables
 template <bool kMixed, int kG>
 void launch_groups(int kb, int nslots, size_t pad, const GeoArgs &a, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
-    if (kb <= 4) launch_one<kMixed, 4096, 0, false, kG>(nslots, pad, a, s, ev0, ev1);
-    else if (kb <= 8) launch_one<kMixed, 8192, 0, false, kG>(nslots, pad, a, s, ev0, ev1);
-    else launch_one<kMixed, 16384, 0, false, kG>(nslots, pad, a, s, ev0, ev1);
+    if (kb <= 4) launch_one<kMixed, 4096, 0, kG>(nslots, pad, a, s, ev0, ev1);
+    else if (kb <= 8) launch_one<kMixed, 8192, 0, kG>(nslots, pad, a, s, ev0, ev1);
+    else launch_one<kMixed, 16384, 0, kG>(nslots, pad, a, s, ev0, ev1);
 }
 template <bool kMixed, int kMode>
-void launch_stack(int kb, bool big, int nslots, size_t pad, const GeoArgs &a, hipStream_t s, hipEvent_t ev0,
+void launch_stack(int kb, int nslots, size_t pad, const GeoArgs &a, hipStream_t s, hipEvent_t ev0,
                   hipEvent_t ev1) {
-    if (big) launch_one<kMixed, kBigStk, kMode, true>(nslots, pad, a, s, ev0, ev1);
-    else if (kb <= 4) launch_one<kMixed, 4096, kMode, false>(nslots, pad, a, s, ev0, ev1);
-    else if (kb <= 8) launch_one<kMixed, 8192, kMode, false>(nslots, pad, a, s, ev0, ev1);
-    else launch_one<kMixed, 16384, kMode, false>(nslots, pad, a, s, ev0, ev1);
+    if (kb <= 4) launch_one<kMixed, 4096, kMode>(nslots, pad, a, s, ev0, ev1);
+    else if (kb <= 8) launch_one<kMixed, 8192, kMode>(nslots, pad, a, s, ev0, ev1);
+    else launch_one<kMixed, 16384, kMode>(nslots, pad, a, s, ev0, ev1);
 }
 template <bool kMixed>
-void launch_variant(int mode, int kb, bool big, int nslots, size_t pad, const GeoArgs &a, hipStream_t s,
-                    hipEvent_t ev0, hipEvent_t ev1) {
-    if (mode == 2) launch_stack<kMixed, 2>(kb, big, nslots, pad, a, s, ev0, ev1);
-    else if (mode == 1) launch_stack<kMixed, 1>(kb, big, nslots, pad, a, s, ev0, ev1);
-    else launch_stack<kMixed, 0>(kb, big, nslots, pad, a, s, ev0, ev1);
+void launch_variant(int mode, int kb, int nslots, size_t pad, const GeoArgs &a, hipStream_t s, hipEvent_t ev0,
+                    hipEvent_t ev1) {
+    if (mode == 2) launch_stack<kMixed, 2>(kb, nslots, pad, a, s, ev0, ev1);
+    else if (mode == 1) launch_stack<kMixed, 1>(kb, nslots, pad, a, s, ev0, ev1);
+    else launch_stack<kMixed, 0>(kb, nslots, pad, a, s, ev0, ev1);
 }
 
 }  // namespace
 
 hipError_t launch_geodesic(const SurfDesc *desc, const BatchIdx &bi, const GeoParams &gp, const GeoShape &shape,
                            char *stack_mem, char *roots, int64_t rstride, int rcap, int32_t *work_ctr, Counters *ctr,
-                           bool fp32, bool fuse, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1, char *gtab,
-                           int gcap, int group, bool pre_cand) {
+                           bool fp32, bool fuse, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1, int group,
+                           bool pre_cand) {
     GeoArgs a;
     a.sd = desc;
     a.bi = bi;
@@ -1597,21 +1448,16 @@ hipError_t launch_geodesic(const SurfDesc *desc, const BatchIdx &bi, const GeoPa
     a.roots = roots;
     a.rstride = rstride;
     a.rcap = rcap;
-    const bool big = gcap > 0;
-    a.gtab = gtab;
-    a.gstride = big ? gtab_bytes(gcap) : 0;
-    a.gcap = gcap;
     a.pre_cand = pre_cand && group > 1 ? 1 : 0;
 
     if (shape.nslots < 1 || total < 1) return hipSuccess;
     if (fuse && total > shape.nslots) return hipErrorInvalidValue;  // the fused update needs a slot per source
-    if (big && (!gtab || gcap > kBigCandMax)) return hipErrorInvalidValue;
     const size_t pad = shape.pad_lds > 0 ? (size_t)shape.pad_lds : 0;
     if (group > 1) {
         // several sources per wavefront: persistent grid, LDS tables, claims
         // of a multiple of the group so that groups come from one claimed
         // range
-        if ((group != 2 && group != 4 && group != 8) || big || mode != 0 || rcap % group) return hipErrorInvalidValue;
+        if ((group != 2 && group != 4 && group != 8) || mode != 0 || rcap % group) return hipErrorInvalidValue;
         a.grab = group * a.grab;
         if (fp32) {
             if (group == 2) launch_groups<true, 2>(shape.lds_stack_kb, shape.nslots, pad, a, s, ev0, ev1);
@@ -1624,8 +1470,8 @@ hipError_t launch_geodesic(const SurfDesc *desc, const BatchIdx &bi, const GeoPa
         }
         return hipGetLastError();
     }
-    if (fp32) launch_variant<true>(mode, shape.lds_stack_kb, big, shape.nslots, pad, a, s, ev0, ev1);
-    else launch_variant<false>(mode, shape.lds_stack_kb, big, shape.nslots, pad, a, s, ev0, ev1);
+    if (fp32) launch_variant<true>(mode, shape.lds_stack_kb, shape.nslots, pad, a, s, ev0, ev1);
+    else launch_variant<false>(mode, shape.lds_stack_kb, shape.nslots, pad, a, s, ev0, ev1);
     return hipGetLastError();
 }
 
@@ -1640,26 +1486,21 @@ hipError_t launch_candidates(const SurfDesc *desc, const BatchIdx &bi, int group
     return hipGetLastError();
 }
 
-int geodesic_blocks_per_cu(int lds_stack_kb, bool fp32, bool big) {
+int geodesic_blocks_per_cu(int lds_stack_kb, bool fp32) {
     int nb = 0;
     const void *f;
-    if (big) f = fp32 ? (const void *)&k_geodesic<true, kBigStk, 0, true> : (const void *)&k_geodesic<false, kBigStk, 0, true>;
-    else if (lds_stack_kb <= 4)
-        f = fp32 ? (const void *)&k_geodesic<true, 4096, 0, false> : (const void *)&k_geodesic<false, 4096, 0, false>;
+    if (lds_stack_kb <= 4)
+        f = fp32 ? (const void *)&k_geodesic<true, 4096, 0> : (const void *)&k_geodesic<false, 4096, 0>;
     else if (lds_stack_kb <= 8)
-        f = fp32 ? (const void *)&k_geodesic<true, 8192, 0, false> : (const void *)&k_geodesic<false, 8192, 0, false>;
-    else f = fp32 ? (const void *)&k_geodesic<true, 16384, 0, false> : (const void *)&k_geodesic<false, 16384, 0, false>;
+        f = fp32 ? (const void *)&k_geodesic<true, 8192, 0> : (const void *)&k_geodesic<false, 8192, 0>;
+    else f = fp32 ? (const void *)&k_geodesic<true, 16384, 0> : (const void *)&k_geodesic<false, 16384, 0>;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, f, kWave, 0) != hipSuccess) return 0;
     return nb;
 }
 
-size_t geodesic_lds_bytes(int lds_stack_kb, bool, bool big) {
-    if (big) return sizeof(LdsBig) + (size_t)kBigStk;
+size_t geodesic_lds_bytes(int lds_stack_kb) {
     const int kb = lds_stack_kb <= 4 ? 4 : (lds_stack_kb <= 8 ? 8 : 16);
     return sizeof(Lds) + (size_t)kb * 1024;
 }
-
-int64_t geodesic_gtab_bytes(int gcap) { return gtab_bytes(gcap); }
-
 
 }  // namespace gsim

@@ -406,41 +406,63 @@ __global__ void k_integrate(int n, DevMesh m, const int32_t *__restrict__ face, 
     D[3 * i + 1] = d[1];
     D[3 * i + 2] = d[2];
 }
-// Start of a pass when the binning runs as several kernels: the work
-// counters and (in a time step) the step counters.
-__global__ void k_pass_begin(const SurfDesc *__restrict__ desc, int nsurf, int32_t *__restrict__ work, int advance) {
-    const int t = threadIdx.x;
-    if (t < kWorkChunks) work[t * kWorkStride] = 0;
-    if (advance && t < nsurf) *desc[t].step += 1;
-}
 __global__ void k_fill_u64(unsigned long long *p, int64_t n, unsigned long long v) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = v;
 }
 
-// ------------------------------------------------------------ all-pairs
-__global__ void k_face_count(int n, const int32_t *__restrict__ face, int32_t *__restrict__ counts) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) atomicAdd(&counts[face[i]], 1);
+// ------------------------------------------------------------ particles by face
+// Four launches for a whole batch: counts, block totals, starts (each block
+// adds the totals of its surface's blocks before it), scatter. The scatter
+// takes the counts back down to zero, so none of them clears anything.
+__global__ void k_face_count(const SurfDesc *__restrict__ desc, BatchIdx bi, int32_t *__restrict__ work, int advance) {
+    if (blockIdx.x == 0) {
+        if (threadIdx.x < kWorkChunks) work[threadIdx.x * kWorkStride] = 0;
+        if (advance && (int)threadIdx.x < bi.nsurf) *desc[threadIdx.x].step += 1;
+    }
+    const int g = blockIdx.x * blockDim.x + threadIdx.x;
+    if (g >= bi.begin[bi.nsurf]) return;
+    const int si = batch_surface(bi, g);
+    const SurfDesc &sd = desc[si];
+    atomicAdd(&sd.fcount[sd.face[g - bi.begin[si]]], 1);
 }
-__global__ void k_face_scatter(int n, const int32_t *__restrict__ face, const double *__restrict__ bary,
-                               const int32_t *__restrict__ fstart, int32_t *__restrict__ counts,
-                               FaceTarget *__restrict__ ftgt) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) {
-        const int f = face[i];
-        const int64_t b = 3 * (int64_t)i;
-        const int pos = fstart[f] + atomicAdd(&counts[f], 1);
-        ftgt[pos] = FaceTarget{{bary[b], bary[b + 1], bary[b + 2]}, i, pos + 1 < fstart[f + 1] ? 1 : 0};
+__global__ __launch_bounds__(kFaceBlock) void k_face_partials(const SurfDesc *__restrict__ desc, BatchIdx fb,
+                                                             int32_t *__restrict__ part) {
+    __shared__ int64_t sh[kFaceBlock / 64];
+    const int si = batch_surface(fb, blockIdx.x);
+    const SurfDesc &sd = desc[si];
+    const int f = ((int)blockIdx.x - fb.begin[si]) * kFaceBlock + threadIdx.x;
+    const int64_t t = block_sum(f < sd.m.nf ? sd.fcount[f] : 0, sh);
+    if (threadIdx.x == 0) part[blockIdx.x] = (int32_t)t;
+}
+__global__ __launch_bounds__(kFaceBlock) void k_face_starts(const SurfDesc *__restrict__ desc, BatchIdx fb,
+                                                           const int32_t *__restrict__ part) {
+    __shared__ int64_t sh[kFaceBlock];
+    const int si = batch_surface(fb, blockIdx.x);
+    const SurfDesc &sd = desc[si];
+    const int b0 = fb.begin[si], nf = sd.m.nf;
+    int64_t off = 0;
+    for (int k = b0 + threadIdx.x; k < (int)blockIdx.x; k += kFaceBlock) off += part[k];
+    off = block_sum(off, sh);
+    const int f = ((int)blockIdx.x - b0) * kFaceBlock + threadIdx.x;
+    const int v = f < nf ? sd.fcount[f] : 0;
+    int64_t tot;
+    const int s = (int)(block_excl_scan(v, sh, &tot) + off);
+    if (f < nf) {
+        sd.fstart[f] = s;
+        sd.ffirst[f] = v ? s : -1;
+        if (f == nf - 1) sd.fstart[nf] = s + v;
     }
 }
-// int32 starts of the faces' ranges, and the first particle of each face (-1: none)
-__global__ void k_face_starts(const int64_t *__restrict__ in, int32_t *__restrict__ fstart,
-                              int32_t *__restrict__ ffirst, int nf) {
-    const int f = blockIdx.x * blockDim.x + threadIdx.x;
-    if (f > nf) return;
-    fstart[f] = (int32_t)in[f];
-    if (f < nf) ffirst[f] = in[f + 1] > in[f] ? (int32_t)in[f] : -1;
+__global__ void k_face_scatter(const SurfDesc *__restrict__ desc, BatchIdx bi) {
+    const int g = blockIdx.x * blockDim.x + threadIdx.x;
+    if (g >= bi.begin[bi.nsurf]) return;
+    const int si = batch_surface(bi, g);
+    const SurfDesc &sd = desc[si];
+    const int i = g - bi.begin[si], f = sd.face[i];
+    const int64_t b = 3 * (int64_t)i;
+    const int pos = sd.fstart[f] + atomicSub(&sd.fcount[f], 1) - 1;
+    sd.ftgt[pos] = FaceTarget{{sd.bary[b], sd.bary[b + 1], sd.bary[b + 2]}, i, pos + 1 < sd.fstart[f + 1] ? 1 : 0};
 }
 __global__ void k_identity_rows(int n, int cap, int32_t *__restrict__ cand_cnt, int32_t *__restrict__ cand) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -592,10 +614,6 @@ hipError_t launch_bin_batch(const SurfDesc *desc, int nsurf, int32_t *work, bool
                        commit ? 1 : 0);
     return hipGetLastError();
 }
-hipError_t launch_pass_begin(const SurfDesc *desc, int nsurf, int32_t *work, bool advance, hipStream_t s) {
-    hipLaunchKernelGGL(k_pass_begin, dim3(1), dim3(kMaxBatch), 0, s, desc, nsurf, work, advance ? 1 : 0);
-    return hipGetLastError();
-}
 hipError_t launch_fill_u64(unsigned long long *p, int64_t n, unsigned long long v, hipStream_t s) {
     if (n <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_fill_u64, dim3(nblocks(n)), dim3(kBlock), 0, s, p, n, v);
@@ -652,16 +670,14 @@ hipError_t launch_integrate(const DevMesh &m, int n, const int32_t *face, const 
 }  // namespace gsim
 
 namespace gsim {
-hipError_t launch_face_sort(const SurfDesc &d, int32_t *counts, int64_t *tmp64, int64_t *scan_scratch, hipStream_t s) {
-    const int n = d.n, nf = d.m.nf;
-    hipError_t e;
-    if ((e = launch_zero_i32(counts, nf, s)) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_face_count, dim3(nblocks(n)), dim3(kBlock), 0, s, n, d.face, counts);
-    if ((e = launch_scan_i32_to_i64(counts, tmp64, nf, scan_scratch, s)) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_face_starts, dim3(nblocks(nf + 1)), dim3(kBlock), 0, s, tmp64, d.fstart, d.ffirst, nf);
-    if ((e = launch_zero_i32(counts, nf, s)) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_face_scatter, dim3(nblocks(n)), dim3(kBlock), 0, s, n, d.face, d.bary,
-                       d.fstart, counts, d.ftgt);
+hipError_t launch_face_sort(const SurfDesc *desc, const BatchIdx &bi, const BatchIdx &fb, int32_t *part, int32_t *work,
+                            bool advance, hipStream_t s) {
+    const int n = bi.begin[bi.nsurf], nb = fb.begin[fb.nsurf];
+    if (n <= 0 || nb <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_face_count, dim3(nblocks(n)), dim3(kBlock), 0, s, desc, bi, work, advance ? 1 : 0);
+    hipLaunchKernelGGL(k_face_partials, dim3(nb), dim3(kFaceBlock), 0, s, desc, fb, part);
+    hipLaunchKernelGGL(k_face_starts, dim3(nb), dim3(kFaceBlock), 0, s, desc, fb, part);
+    hipLaunchKernelGGL(k_face_scatter, dim3(nblocks(n)), dim3(kBlock), 0, s, desc, bi);
     return hipGetLastError();
 }
 hipError_t launch_identity_rows(int n, int cap, int32_t *cand_cnt, int32_t *cand, hipStream_t s) {

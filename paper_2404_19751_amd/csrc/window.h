@@ -221,14 +221,6 @@ __device__ inline int claim(uint8_t *win, bool todo, int e) {
 // bend_update_loaded takes the entry loaded by the caller (bend_load,
 // earlier, so that its latency overlaps other work; no other update of the
 // table may come in between).
-// Lane l's value of x (l wave-uniform): two scalar reads instead of a
-// cross-lane permute.
-__device__ inline double readlane_d(double x, int l) {
-    const long long b = __double_as_longlong(x);
-    const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffff), l);
-    const int hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
-    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
 struct BendEntry {
     double D = INFINITY, D2 = INFINITY, L = INFINITY, tx = 0.0, ty = 0.0;
     int q = 1;

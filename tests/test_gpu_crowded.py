@@ -36,8 +36,44 @@ def test_crowded_faces(name, n, whole):
     mid = ctx.mesh_upload(m.V, m.T)
     ctx.particles_set(mid, f, b)
     ctx.tune(whole_mesh=whole)
+    mean = n * np.pi * cutoff ** 2 / W.surface_area(m)
+    if not whole and n > 128 and 3.0 * mean + 16.0 <= 128:
+        # sparse on the whole, so rows for 128 candidates are expected to do:
+        # a source with more is reported, never cut short
+        with pytest.raises(gsim.GsimError) as e:
+            ctx.geodesic_pairs(mid, cutoff)
+        assert e.value.status == gsim.E_LIMIT
+        return
     g = ctx.geodesic_pairs(mid, cutoff)
     assert ctx.counters()["limited"] == 0
     o = orc.geodesic_pairs(orc.OracleMesh(m.V, m.T), f, b, cutoff)
     compare_pairs(g, o, W.mean_edge_length(m), label=name)
+    ctx.close()
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32_mixed"])
+@pytest.mark.parametrize("n", [129, 300, 600])
+def test_crowded_near_pass(n, prec):
+    """A cutoff wide enough that rows are counted: the near pass, its sort in
+    LDS (up to 512 keys) and in global memory, and its reset of what a source
+    reached, on crowded and spread particles of one surface."""
+    m = W.bumpy_sphere(2, 0.2)
+    f, b = crowd(m, n, 5)
+    f2, b2 = W.random_particles(m.nf, n, 6)
+    f[::2], b[::2] = f2[::2], b2[::2]
+    cutoff = 1.2
+    assert 3.0 * n * np.pi * cutoff ** 2 / W.surface_area(m) + 16.0 > 128
+    ctx = gsim.Context(0, prec)
+    mid = ctx.mesh_upload(m.V, m.T)
+    ctx.particles_set(mid, f, b)
+    g = ctx.geodesic_pairs(mid, cutoff)
+    h = ctx.geodesic_pairs(mid, cutoff)
+    assert np.array_equal(g["nbr"], h["nbr"]) and np.array_equal(g["off"], h["off"])
+    o = orc.geodesic_pairs(orc.OracleMesh(m.V, m.T), f, b, cutoff)
+    if prec == "fp64":
+        compare_pairs(g, o, W.mean_edge_length(m), label="near")
+    else:
+        # the FP32-mixed contract: exact neighbour sets, distances within 1e-5
+        assert np.array_equal(g["off"], o.off) and np.array_equal(g["nbr"], o.nbr)
+        assert np.max(np.abs(g["dist"] - o.dist) / o.dist) <= 1e-5
     ctx.close()
