@@ -1010,6 +1010,9 @@ __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, 
             if (prof) L.clk[2] -= clock64();
             launch_roots<R, kNear>(sd, L, G, td, Dv, C, S, T, src, st);
             if (prof) L.clk[2] += clock64();
+            // no lane holds a window here: nothing of one has to live through the launch
+            w = Win<R>{};
+            DA = DB = INFINITY;
             busy = S.refill(have, w);
         }
         if (!busy) {
