@@ -49,7 +49,7 @@ struct MeshState {
     Buf nbr_cnt, off, nbr, dist, tan, flags;
     int64_t n_pairs = 0;
     // forces / integrator
-    Buf F, Ei, E, disp, wflags, step_dev, fire;
+    Buf F, E, disp, wflags, step_dev, fire;
     Buf face_nx, bary_nx, vel_nx;  // next state of a fused time step
     uint64_t step = 0;  // steps taken since the state was set: the noise counter (host mirror)
     // all-pairs rows and the particles-by-face index
@@ -77,13 +77,16 @@ struct gsim_ctx {
     bool own_stream = false;
     std::string err;
     std::vector<MeshState *> meshes;
-    Buf stack, work, ctr, wstats, scan_scratch, sum_scratch, pf_over, prof, desc, vdist, ttab, roots, partials, vbits, split;
+    Buf stack, work, ctr, wpart, scan_scratch, sum_scratch, prof, desc, vdist, ttab, roots, partials, vbits, split;
     // near passes: target areas, vertex and half-edge entries and epochs of the
     // resident wavefronts, and the layout they were last prepared for
     Buf near_t, near_v, near_h, near_e;
     void *near_p[4] = {};
     int64_t near_layout[3] = {};  // tcap, vstride, hstride
     int near_slots = 0;
+    Buf bad;                  // device counts of a state check or of Voronoi limits: zeros between calls
+    HostOut *hout = nullptr;  // pinned: what kernels hand to the host
+    bool ctr_clean = false;   // the device counters hold zeros
     SurfDesc *desc_pinned = nullptr;  // staging for descriptor uploads
     std::vector<SurfDesc> desc_cached;
     bool profile_sources = false;
@@ -125,8 +128,7 @@ struct gsim_ctx {
 };
 
 // ---- scratch of the allocation-free walk (gsim_displace_on_surface_noalloc)
-// One row of 8 walk counts per workgroup of kWalkBlock particles, then the
-// 8 totals: 512 KiB, enough for kNoAllocMaxParticles particles. Every GPU the
+// One row of 8 walk counts per workgroup of kWalkBlock particles: 512 KiB, enough for kNoAllocMaxParticles particles. Every GPU the
 // library runs on holds its own copy until the process ends. Host code never
 // passes the array's name to a kernel (that is a host-side stand-in, not a
 // device address): it uses the address hipGetSymbolAddress gave for the
@@ -134,7 +136,7 @@ struct gsim_ctx {
 constexpr int kNoAllocBlocks = 8192;
 constexpr int64_t kNoAllocMaxParticles = (int64_t)kNoAllocBlocks * kWalkBlock;  // 2,097,152
 constexpr int kMaxDevices = 64;
-static __device__ __align__(256) unsigned long long scratch[8 * (kNoAllocBlocks + 1)];
+static __device__ __align__(256) unsigned long long scratch[8 * kNoAllocBlocks];
 static std::mutex g_scratch_mu;
 static unsigned long long *g_scratch[kMaxDevices] = {};
 
@@ -331,43 +333,29 @@ gsim_status nonfinite_status(gsim_ctx *c, unsigned long long count) {
 }
 
 // ---------------------------------------------------------------- calls
-// A call (geodesic_pairs, compute_forces, step) zeroes the device counters,
-// queues its work without any host synchronisation, and reads the counters
-// back once at the end.
+// A call (geodesic_pairs, compute_forces, step) starts from zeroed device
+// counters, queues its work without any host synchronisation, and ends with
+// one kernel that sums the counters into host memory and zeroes them again.
 gsim_status begin_call(gsim_ctx *c) {
-    HIPCHK(c, launch_zero_u64(P<unsigned long long>(c->ctr), (int64_t)kCtrWords * kCtrSlots * kCtrStride, c->stream));
-    HIPCHK(c, launch_zero_i32(P<int32_t>(c->pf_over), 1, c->stream));
+    if (!c->ctr_clean)
+        HIPCHK(c, launch_zero_u64(P<unsigned long long>(c->ctr), (int64_t)kCtrWords * kCtrSlots * kCtrStride, c->stream));
+    c->ctr_clean = false;
     c->passes = 0;
     return GSIM_OK;
 }
 
-gsim_status end_call(gsim_ctx *c) {
-    int32_t over = 0;
-    Counters slots[kCtrSlots * kCtrStride];
-    HIPCHK(c, hipMemcpyAsync(slots, c->ctr.p, sizeof(slots), hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(c, hipMemcpyAsync(&over, c->pf_over.p, sizeof(int32_t), hipMemcpyDeviceToHost, c->stream));
+// With an energy: the sum of nb block energies goes into it (device memory).
+gsim_status end_call(gsim_ctx *c, const double *epart = nullptr, int nb = 0, double *energy = nullptr) {
+    HIPCHK(c, launch_call_end(P<Counters>(c->ctr), &c->hout->ctr, epart, nb, energy, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
-    Counters &L = c->last;
-    L = Counters{};
-    for (int k = 0; k < kCtrSlots; ++k) {
-        const Counters &q = slots[k * kCtrStride];
-        L.windows += q.windows;
-        L.pruned += q.pruned;
-        L.launches += q.launches;
-        L.stale += q.stale;
-        L.guards += q.guards;
-        L.nbr_pairs += q.nbr_pairs;
-        L.limited += q.limited;
-        L.max_depth = std::max(L.max_depth, q.max_depth);
-        L.nonfinite += q.nonfinite;
-        L.crossings += q.crossings;
-    }
+    c->ctr_clean = true;
+    c->last = c->hout->ctr;
     c->cum_pairs += c->last.nbr_pairs;
     c->cum_windows += c->last.windows;
     c->cum_passes += c->passes;
-    if (over || c->last.limited)
+    if (c->last.limited)
         return fail(c, GSIM_E_LIMIT,
-                    std::to_string(over + (long long)c->last.limited) +
+                    std::to_string((long long)c->last.limited) +
                         " source(s) exceeded a per-source limit (more candidate targets within the cutoff than "
                         "the row capacity set at the start of the call, window stack or window count); the results "
                         "of this call are incomplete. Passes of the whole-mesh kernel (the \"whole_mesh\" knob, up "
@@ -597,6 +585,15 @@ gsim_status prepare_face_index(gsim_ctx *c, MeshState *ms, SurfDesc &d) {
     d.ffirst = P<int32_t>(ms->ffirst);
     d.ftgt = P<FaceTarget>(ms->ftgt);
     d.fcount = P<int32_t>(ms->fcount);
+    return GSIM_OK;
+}
+
+// The counts of a state check or of Voronoi limits, after the kernels set the
+// host flag: copied out and zeroed for the next call.
+gsim_status take_bad(gsim_ctx *c, int32_t hb[4]) {
+    HIPCHK(c, hipMemcpyAsync(hb, c->bad.p, sizeof(int32_t) * 4, hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(c, launch_zero_i32(P<int32_t>(c->bad), 4, c->stream));
+    HIPCHK(c, hipStreamSynchronize(c->stream));
     return GSIM_OK;
 }
 
@@ -918,52 +915,43 @@ gsim_status single(gsim_ctx *c, MeshState *ms, double cutoff, const gsim_potenti
     return geodesic_pass(c, B, false);
 }
 
-// Compact the candidate rows into the caller-facing CSR (host sync for the size).
-gsim_status compact_pairs(gsim_ctx *c, MeshState *ms, double cutoff) {
+// The pairs' row offsets; their total arrives in host memory with the end of
+// the call.
+gsim_status count_pairs(gsim_ctx *c, MeshState *ms, double cutoff) {
     hipStream_t s = c->stream;
-    const int n = ms->n, cap = ms->cap;
-    if (!finite_cutoff(cutoff)) cutoff = INFINITY;
+    const int n = ms->n;
     Stage st(c, "compact");
     HIPCHK(c, ensure(ms->nbr_cnt, sizeof(int32_t) * (n + 1)));
     HIPCHK(c, ensure(ms->off, sizeof(int64_t) * (n + 1)));
-    HIPCHK(c, launch_count_rows(n, P<int32_t>(ms->cand_cnt), cap, P<double>(ms->cdist), cutoff,
+    HIPCHK(c, ensure(c->scan_scratch, sizeof(int64_t) * ((size_t)(n + 1023) / 1024 + 2)));
+    HIPCHK(c, launch_count_rows(n, P<int32_t>(ms->cand_cnt), ms->cap, P<double>(ms->cdist), cutoff,
                                 P<int32_t>(ms->nbr_cnt), s));
-    HIPCHK(c, launch_scan_i32_to_i64(P<int32_t>(ms->nbr_cnt), P<int64_t>(ms->off), n, P<int64_t>(c->scan_scratch), s));
-    int64_t total = 0;
-    HIPCHK(c, hipMemcpyAsync(&total, P<int64_t>(ms->off) + n, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    HIPCHK(c, hipStreamSynchronize(s));
-    ms->n_pairs = total;
-    {
-        const size_t t1 = (size_t)total + 1;
-        gsim_status cs = check_room(c, {{&ms->nbr, 4 * t1}, {&ms->dist, 8 * t1}, {&ms->tan, 24 * t1}, {&ms->flags, t1}},
-                                    "the " + std::to_string(total) + " pairs of this call (37 bytes each)");
-        if (cs != GSIM_OK) return cs;
-    }
-    HIPCHK(c, ensure(ms->nbr, sizeof(int32_t) * (total + 1)));
-    HIPCHK(c, ensure(ms->dist, sizeof(double) * (total + 1)));
-    HIPCHK(c, ensure(ms->tan, sizeof(double) * 3 * (total + 1)));
-    HIPCHK(c, ensure(ms->flags, total + 1));
-    HIPCHK(c, launch_compact_rows(n, P<int32_t>(ms->cand_cnt), cap, P<int32_t>(ms->cand), P<double>(ms->cdist),
-                                  P<double>(ms->ctan), P<uint8_t>(ms->cflags), cutoff, P<int64_t>(ms->off),
-                                  P<int32_t>(ms->nbr), P<double>(ms->dist), P<double>(ms->tan), P<uint8_t>(ms->flags),
-                                  s));
+    HIPCHK(c, launch_scan_i32_to_i64(P<int32_t>(ms->nbr_cnt), P<int64_t>(ms->off), n, P<int64_t>(c->scan_scratch),
+                                     &c->hout->total, s));
     return GSIM_OK;
 }
 
-gsim_status run_forces(gsim_ctx *c, MeshState *ms, const gsim_potential *pot) {
+// The candidate rows as CSR into the given device arrays (flags may be null).
+gsim_status compact_pairs(gsim_ctx *c, MeshState *ms, double cutoff, int32_t *nbr, double *dist, double *tan,
+                          uint8_t *flags) {
+    Stage st(c, "compact");
+    HIPCHK(c, launch_compact_rows(ms->n, P<int32_t>(ms->cand_cnt), ms->cap, P<int32_t>(ms->cand), P<double>(ms->cdist),
+                                  P<double>(ms->ctan), P<uint8_t>(ms->cflags), cutoff, P<int64_t>(ms->off), nbr, dist,
+                                  tan, flags, c->stream));
+    return GSIM_OK;
+}
+
+// Forces into F (device memory) and block energies into sum_scratch.
+gsim_status run_forces(gsim_ctx *c, MeshState *ms, const gsim_potential *pot, double *F) {
     const int n = ms->n;
     const double cutoff = finite_cutoff(pot->cutoff) ? pot->cutoff : INFINITY;
-    HIPCHK(c, ensure(ms->F, sizeof(double) * 3 * n));
-    HIPCHK(c, ensure(ms->Ei, sizeof(double) * n));
-    HIPCHK(c, ensure(ms->E, sizeof(double) * 4));
-    HIPCHK(c, ensure(c->sum_scratch, sizeof(double) * ((n + 255) / 256 + 2)));
+    HIPCHK(c, ensure(c->sum_scratch, sizeof(double) * (size_t)force_blocks(n)));
     HIPCHK(c, ensure(ms->wflags, n));
     Stage st(c, "forces");
     HIPCHK(c, launch_forces_rows(n, P<int32_t>(ms->cand_cnt), ms->cap, P<double>(ms->cdist), P<double>(ms->ctan),
-                                 cutoff, pot->kind, pot->k, pot->sigma, P<double>(ms->F), P<double>(ms->Ei),
+                                 cutoff, pot->kind, pot->k, pot->sigma, F, P<double>(c->sum_scratch),
                                  &P<Counters>(c->ctr)->nbr_pairs, P<uint8_t>(ms->wflags),
                                  &P<Counters>(c->ctr)->nonfinite, c->stream));
-    HIPCHK(c, launch_sum(P<double>(ms->Ei), n, P<double>(ms->E), P<double>(c->sum_scratch), c->stream));
     return GSIM_OK;
 }
 
@@ -1132,8 +1120,9 @@ gsim_status gsim_create(int device, gsim_precision prec, void *hip_stream, gsim_
     c->gp.max_windows = 4000000;
     c->max_windows_all = 1 << 26;
     if (ensure(c->work, sizeof(int32_t) * kWorkInts) != hipSuccess || ensure(c->ctr, sizeof(Counters) * kCtrSlots * kCtrStride) != hipSuccess ||
-        ensure(c->wstats, sizeof(unsigned long long) * 8) != hipSuccess ||
-        ensure(c->pf_over, sizeof(int32_t) * 4) != hipSuccess ||
+        hipHostMalloc((void **)&c->hout, sizeof(HostOut), hipHostMallocDefault) != hipSuccess ||
+        ensure(c->bad, sizeof(int32_t) * 4) != hipSuccess ||
+        launch_zero_i32(P<int32_t>(c->bad), 4, c->stream) != hipSuccess ||
         ensure(c->desc, sizeof(SurfDesc) * kMaxBatch) != hipSuccess ||
         hipHostMalloc((void **)&c->desc_pinned, sizeof(SurfDesc) * kMaxBatch, hipHostMallocDefault) != hipSuccess) {
         gsim_destroy(c);
@@ -1157,7 +1146,7 @@ void gsim_destroy(gsim_ctx *c) {
         if (!ms) continue;
         for (Buf *b : {&ms->cell_of, &ms->cell_start, &ms->cell_fill, &ms->order, &ms->cand_cnt, &ms->cand,
                        &ms->tmp64, &ms->cdist, &ms->ctan, &ms->cflags, &ms->nbr_cnt, &ms->off, &ms->nbr, &ms->dist,
-                       &ms->tan, &ms->flags, &ms->F, &ms->Ei, &ms->E, &ms->disp, &ms->wflags, &ms->step_dev,
+                       &ms->tan, &ms->flags, &ms->F, &ms->E, &ms->disp, &ms->wflags, &ms->step_dev,
                        &ms->fire, &ms->fstart, &ms->ffirst, &ms->ftgt, &ms->fcount, &ms->face_nx, &ms->bary_nx,
                        &ms->vel_nx})
             release(*b);
@@ -1170,10 +1159,11 @@ void gsim_destroy(gsim_ctx *c) {
             if (p) (void)hipFree(p);
         delete ms;
     }
-    for (Buf *b : {&c->stack, &c->work, &c->ctr, &c->wstats, &c->scan_scratch, &c->sum_scratch, &c->pf_over,
+    for (Buf *b : {&c->stack, &c->work, &c->ctr, &c->wpart, &c->bad, &c->scan_scratch, &c->sum_scratch,
                    &c->prof, &c->desc, &c->vdist, &c->ttab, &c->roots, &c->partials, &c->vbits, &c->split, &c->near_t, &c->near_v, &c->near_h, &c->near_e})
         release(*b);
     if (c->desc_pinned) (void)hipHostFree(c->desc_pinned);
+    if (c->hout) (void)hipHostFree(c->hout);
     if (c->own_stream) (void)hipStreamDestroy(c->stream);
     delete c;
 }
@@ -1298,17 +1288,12 @@ static gsim_status check_state(gsim_ctx *c, const MeshState *ms, int32_t n, cons
     return GSIM_OK;
 }
 
-static gsim_status reset_state(gsim_ctx *c, MeshState *ms, const double *vel, hipMemcpyKind kind) {
-    hipStream_t s = c->stream;
-    const int n = ms->n;
-    if (vel) HIPCHK(c, hipMemcpyAsync(ms->vel, vel, sizeof(double) * 3 * n, kind, s));
-    else HIPCHK(c, launch_zero_u64(reinterpret_cast<unsigned long long *>(ms->vel), 3 * (int64_t)n, s));
-    HIPCHK(c, launch_fill_u64(P<unsigned long long>(ms->step_dev), 1, ~0ull, s));
+// The particle arrays and the rest of the state for n particles.
+static gsim_status ensure_state(gsim_ctx *c, MeshState *ms, int32_t n) {
+    gsim_status st = alloc_particles(c, ms, n);
+    if (st != GSIM_OK) return st;
     HIPCHK(c, ensure(ms->fire, sizeof(FireState)));
-    HIPCHK(c, launch_zero_u64(P<unsigned long long>(ms->fire), sizeof(FireState) / 8, s));
-    // no flags until a walk, step or force call sets them
     HIPCHK(c, ensure(ms->wflags, (size_t)n + 4));
-    HIPCHK(c, launch_zero_i32(P<int32_t>(ms->wflags), (n + 3) / 4, s));
     ms->step = 0;
     return GSIM_OK;
 }
@@ -1321,11 +1306,13 @@ gsim_status gsim_particles_set(gsim_ctx *c, int32_t id, int32_t n, const int32_t
         if (!ms || n < 1 || !face || !bary) return fail(c, GSIM_E_ARG, "bad particle arguments");
         gsim_status st = check_state(c, ms, n, face, bary, vel);
         if (st != GSIM_OK) return st;
-        if ((st = alloc_particles(c, ms, n)) != GSIM_OK) return st;
+        if ((st = ensure_state(c, ms, n)) != GSIM_OK) return st;
         hipStream_t s = c->stream;
         HIPCHK(c, hipMemcpyAsync(ms->face, face, sizeof(int32_t) * n, hipMemcpyHostToDevice, s));
         HIPCHK(c, hipMemcpyAsync(ms->bary, bary, sizeof(double) * 3 * n, hipMemcpyHostToDevice, s));
-        if ((st = reset_state(c, ms, vel, hipMemcpyHostToDevice)) != GSIM_OK) return st;
+        if (vel) HIPCHK(c, hipMemcpyAsync(ms->vel, vel, sizeof(double) * 3 * n, hipMemcpyHostToDevice, s));
+        HIPCHK(c, launch_take_state(n, ms->face, ms->bary, vel ? ms->vel : nullptr, ms->face, ms->bary, ms->vel,
+                                    P<uint8_t>(ms->wflags), P<FireState>(ms->fire), P<uint64_t>(ms->step_dev), s));
         HIPCHK(c, hipStreamSynchronize(s));
         return GSIM_OK;
     }
@@ -1340,21 +1327,22 @@ gsim_status gsim_particles_set_dev(gsim_ctx *c, int32_t id, int32_t n, const int
         if (!ms || n < 1 || !face || !bary) return fail(c, GSIM_E_ARG, "bad particle arguments");
         hipStream_t s = c->stream;
         // the same checks as the host path, on the device, before the state is taken
-        int32_t *bad = P<int32_t>(c->wstats);
-        int32_t hb[3] = {0, 0, 0};
-        HIPCHK(c, launch_zero_i32(bad, 3, s));
-        HIPCHK(c, launch_validate_state(ms->dm.nf, n, face, bary, vel, bad, s));
-        HIPCHK(c, hipMemcpyAsync(hb, bad, sizeof(hb), hipMemcpyDeviceToHost, s));
+        c->hout->bad = 0;  // host memory: written only where something is wrong
+        HIPCHK(c, launch_validate_state(ms->dm.nf, n, face, bary, vel, P<int32_t>(c->bad), &c->hout->bad, s));
         HIPCHK(c, hipStreamSynchronize(s));
-        if (hb[0] || hb[1] || hb[2])
+        if (c->hout->bad) {
+            int32_t hb[4];
+            gsim_status st = take_bad(c, hb);
+            if (st != GSIM_OK) return st;
             return fail(c, GSIM_E_ARG, std::to_string(hb[0]) + " face index(es) out of range, " + std::to_string(hb[1]) +
                                            " barycentric triple(s) not in [0,1], not summing to 1 or on a vertex, " +
                                            std::to_string(hb[2]) + " non-finite velocity(ies); state unchanged");
-        gsim_status st = alloc_particles(c, ms, n);
+        }
+        gsim_status st = ensure_state(c, ms, n);
         if (st != GSIM_OK) return st;
-        HIPCHK(c, hipMemcpyAsync(ms->face, face, sizeof(int32_t) * n, hipMemcpyDeviceToDevice, s));
-        HIPCHK(c, hipMemcpyAsync(ms->bary, bary, sizeof(double) * 3 * n, hipMemcpyDeviceToDevice, s));
-        return reset_state(c, ms, vel, hipMemcpyDeviceToDevice);
+        HIPCHK(c, launch_take_state(n, face, bary, vel, ms->face, ms->bary, ms->vel, P<uint8_t>(ms->wflags),
+                                    P<FireState>(ms->fire), P<uint64_t>(ms->step_dev), s));
+        return GSIM_OK;
     }
     GSIM_CATCH(c)
 }
@@ -1387,10 +1375,7 @@ gsim_status gsim_particles_get_dev(gsim_ctx *c, int32_t id, int32_t *face, doubl
         if (!ms) return fail(c, GSIM_E_ARG, "unknown mesh id");
         if (ms->n <= 0) return fail(c, GSIM_E_STATE, "no particles on this mesh");
         hipStream_t s = c->stream;
-        const int n = ms->n;
-        if (face) HIPCHK(c, hipMemcpyAsync(face, ms->face, sizeof(int32_t) * n, hipMemcpyDeviceToDevice, s));
-        if (bary) HIPCHK(c, hipMemcpyAsync(bary, ms->bary, sizeof(double) * 3 * n, hipMemcpyDeviceToDevice, s));
-        if (vel) HIPCHK(c, hipMemcpyAsync(vel, ms->vel, sizeof(double) * 3 * n, hipMemcpyDeviceToDevice, s));
+        HIPCHK(c, launch_give_state(ms->n, ms->face, ms->bary, ms->vel, face, bary, vel, s));
         return GSIM_OK;
     }
     GSIM_CATCH(c)
@@ -1407,23 +1392,43 @@ static gsim_status pairs_to(gsim_ctx *c, int32_t id, double cutoff, gsim_pairs *
         Batch B;
         if ((st = begin_call(c)) != GSIM_OK) return st;
         if ((st = single(c, ms, cutoff, nullptr, B)) != GSIM_OK) return st;
-        if ((st = compact_pairs(c, ms, cutoff)) != GSIM_OK) return st;
+        if (!finite_cutoff(cutoff)) cutoff = INFINITY;
+        if ((st = count_pairs(c, ms, cutoff)) != GSIM_OK) return st;
         if ((st = end_call(c)) != GSIM_OK) return st;
-        c->last.nbr_pairs = (unsigned long long)ms->n_pairs;
+        const int64_t total = c->hout->total;
+        ms->n_pairs = total;
+        c->last.nbr_pairs = (unsigned long long)total;
         c->cum_pairs += c->last.nbr_pairs;
-        out->count = ms->n_pairs;
-        if (out->capacity < ms->n_pairs || !out->off || (ms->n_pairs && (!out->nbr || !out->dist || !out->tan)))
-            return fail(c, GSIM_E_CAPACITY, "pair buffers too small: " + std::to_string(ms->n_pairs) + " needed");
         hipStream_t s = c->stream;
-        const int64_t P_ = ms->n_pairs;
-        HIPCHK(c, hipMemcpyAsync(out->off, ms->off.p, sizeof(int64_t) * (ms->n + 1), kind, s));
-        if (P_) {
-            HIPCHK(c, hipMemcpyAsync(out->nbr, ms->nbr.p, sizeof(int32_t) * P_, kind, s));
-            HIPCHK(c, hipMemcpyAsync(out->dist, ms->dist.p, sizeof(double) * P_, kind, s));
-            HIPCHK(c, hipMemcpyAsync(out->tan, ms->tan.p, sizeof(double) * 3 * P_, kind, s));
-            if (out->flags) HIPCHK(c, hipMemcpyAsync(out->flags, ms->flags.p, P_, kind, s));
+        const bool fits = out->capacity >= total && out->off && (!total || (out->nbr && out->dist && out->tan));
+        if (kind == hipMemcpyDeviceToDevice) {
+            // the caller's arrays are device memory: the rows go straight there
+            out->count = total;
+            if (!fits) return fail(c, GSIM_E_CAPACITY, "pair buffers too small: " + std::to_string(total) + " needed");
+            HIPCHK(c, hipMemcpyAsync(out->off, ms->off.p, sizeof(int64_t) * (ms->n + 1), kind, s));
+            return total ? compact_pairs(c, ms, cutoff, out->nbr, out->dist, out->tan, out->flags) : GSIM_OK;
         }
-        if (kind == hipMemcpyDeviceToHost) HIPCHK(c, hipStreamSynchronize(s));
+        const size_t t1 = (size_t)total + 1;
+        st = check_room(c, {{&ms->nbr, 4 * t1}, {&ms->dist, 8 * t1}, {&ms->tan, 24 * t1}, {&ms->flags, t1}},
+                        "the " + std::to_string(total) + " pairs of this call (37 bytes each)");
+        if (st != GSIM_OK) return st;
+        out->count = total;
+        if (!fits) return fail(c, GSIM_E_CAPACITY, "pair buffers too small: " + std::to_string(total) + " needed");
+        HIPCHK(c, ensure(ms->nbr, sizeof(int32_t) * t1));
+        HIPCHK(c, ensure(ms->dist, sizeof(double) * t1));
+        HIPCHK(c, ensure(ms->tan, sizeof(double) * 3 * t1));
+        HIPCHK(c, ensure(ms->flags, t1));
+        HIPCHK(c, hipMemcpyAsync(out->off, ms->off.p, sizeof(int64_t) * (ms->n + 1), kind, s));
+        if (total) {
+            st = compact_pairs(c, ms, cutoff, P<int32_t>(ms->nbr), P<double>(ms->dist), P<double>(ms->tan),
+                               P<uint8_t>(ms->flags));
+            if (st != GSIM_OK) return st;
+            HIPCHK(c, hipMemcpyAsync(out->nbr, ms->nbr.p, sizeof(int32_t) * total, kind, s));
+            HIPCHK(c, hipMemcpyAsync(out->dist, ms->dist.p, sizeof(double) * total, kind, s));
+            HIPCHK(c, hipMemcpyAsync(out->tan, ms->tan.p, sizeof(double) * 3 * total, kind, s));
+            if (out->flags) HIPCHK(c, hipMemcpyAsync(out->flags, ms->flags.p, total, kind, s));
+        }
+        HIPCHK(c, hipStreamSynchronize(s));
         return GSIM_OK;
     }
     GSIM_CATCH(c)
@@ -1457,7 +1462,11 @@ gsim_status gsim_voronoi_neighbours(gsim_ctx *c, int32_t id, int64_t *off, int32
         const int64_t ncell = (int64_t)dims[0] * dims[1] * dims[2];
         HIPCHK(c, ensure(ms->cell_of, sizeof(int32_t) * n));
         HIPCHK(c, ensure(ms->cell_start, sizeof(int32_t) * (ncell + 1)));
-        HIPCHK(c, ensure(ms->cell_fill, sizeof(int32_t) * ncell));
+        {
+            const void *was = ms->cell_fill.p;
+            HIPCHK(c, ensure(ms->cell_fill, sizeof(int32_t) * ncell));
+            if (ms->cell_fill.p != was) ms->fill_zero = 0;
+        }
         HIPCHK(c, ensure(ms->order, sizeof(int32_t) * n));
         HIPCHK(c, ensure(ms->tmp64, sizeof(int64_t) * (std::max<int64_t>(ncell, n) + 1)));
         HIPCHK(c, ensure(c->scan_scratch, sizeof(int64_t) * ((std::max<int64_t>(ncell, n) + 1023) / 1024 + 2)));
@@ -1465,7 +1474,6 @@ gsim_status gsim_voronoi_neighbours(gsim_ctx *c, int32_t id, int64_t *off, int32
         HIPCHK(c, ensure(c->vbits, sizeof(unsigned long long) * (size_t)n * words));
         HIPCHK(c, ensure(ms->nbr_cnt, sizeof(int32_t) * (n + 1)));
         HIPCHK(c, ensure(ms->off, sizeof(int64_t) * (n + 1)));
-        HIPCHK(c, ensure(c->wstats, sizeof(unsigned long long) * 8));
         PrefilterBufs pb{};
         pb.xyz = ms->xyz;
         pb.cell_of = P<int32_t>(ms->cell_of);
@@ -1475,28 +1483,29 @@ gsim_status gsim_voronoi_neighbours(gsim_ctx *c, int32_t id, int64_t *off, int32
         pb.cap_c = kCandCap;
         for (int k = 0; k < 3; ++k) pb.dims[k] = dims[k];
         pb.cell = cell;
-        int32_t *err = P<int32_t>(c->wstats);
+        c->hout->bad = 0;  // host memory: written only where a limit is met
         {
             Stage st(c, "voronoi");
-            HIPCHK(c, launch_cell_sort(m, n, ms->face, ms->bary, pb, P<int64_t>(c->scan_scratch), true, nullptr,
+            HIPCHK(c, launch_cell_sort(m, n, ms->face, ms->bary, pb, P<int64_t>(c->scan_scratch), ms->fill_zero < ncell, nullptr,
                                        nullptr, false, s));
-            ms->fill_zero = ncell;
+            ms->fill_zero = std::max<int64_t>(ms->fill_zero, ncell);
             HIPCHK(c, launch_zero_u64(P<unsigned long long>(c->vbits), (int64_t)n * words, s));
-            HIPCHK(c, launch_zero_i32(err, 2, s));
             HIPCHK(c, launch_voronoi_faces(m, n, ms->xyz, pb.cell_start, pb.order, dims, m.bbmin, cell,
-                                           P<unsigned long long>(c->vbits), words, 1e-10 * m.mean_edge, err, s));
+                                           P<unsigned long long>(c->vbits), words, 1e-10 * m.mean_edge, P<int32_t>(c->bad), &c->hout->bad,
+                                           s));
             HIPCHK(c, launch_voronoi_count(P<unsigned long long>(c->vbits), n, words, P<int32_t>(ms->nbr_cnt), s));
             HIPCHK(c, launch_scan_i32_to_i64(P<int32_t>(ms->nbr_cnt), P<int64_t>(ms->off), n,
-                                             P<int64_t>(c->scan_scratch), s));
+                                             P<int64_t>(c->scan_scratch), &c->hout->total, s));
         }
-        int32_t errs[2] = {0, 0};
-        int64_t total = 0;
-        HIPCHK(c, hipMemcpyAsync(errs, err, sizeof(errs), hipMemcpyDeviceToHost, s));
-        HIPCHK(c, hipMemcpyAsync(&total, P<int64_t>(ms->off) + n, sizeof(int64_t), hipMemcpyDeviceToHost, s));
         HIPCHK(c, hipStreamSynchronize(s));
-        if (errs[0] || errs[1])
-            return fail(c, GSIM_E_LIMIT, std::to_string(errs[0]) + " face(s) with more than 64 candidate particles, " +
-                                             std::to_string(errs[1]) + " cell piece(s) with more than 16 vertices");
+        const int64_t total = c->hout->total;
+        if (c->hout->bad) {
+            int32_t err[4];
+            gsim_status st = take_bad(c, err);
+            if (st != GSIM_OK) return st;
+            return fail(c, GSIM_E_LIMIT, std::to_string(err[0]) + " face(s) with more than 64 candidate particles, " +
+                                             std::to_string(err[1]) + " cell piece(s) with more than 16 vertices");
+        }
         *count = total;
         if (capacity < total || (total && !nbr))
             return fail(c, GSIM_E_CAPACITY, "neighbour buffer too small: " + std::to_string(total) + " needed");
@@ -1524,12 +1533,20 @@ static gsim_status forces_to(gsim_ctx *c, int32_t id, const gsim_potential *pot,
         Batch B;
         if ((st = begin_call(c)) != GSIM_OK) return st;
         if ((st = single(c, ms, pot->cutoff, pot, B)) != GSIM_OK) return st;
-        if ((st = run_forces(c, ms, pot)) != GSIM_OK) return st;
-        hipStream_t s = c->stream;
-        HIPCHK(c, hipMemcpyAsync(force, ms->F.p, sizeof(double) * 3 * ms->n, kind, s));
-        if (energy) HIPCHK(c, hipMemcpyAsync(energy, ms->E.p, sizeof(double), kind, s));
-        // the counters are read (a synchronisation) after the copies are queued
-        return end_call(c);
+        const bool dev = kind == hipMemcpyDeviceToDevice;
+        if (!dev) HIPCHK(c, ensure(ms->F, sizeof(double) * 3 * ms->n));
+        HIPCHK(c, ensure(ms->E, sizeof(double)));
+        // device buffers of the caller are written in place
+        double *F = dev ? force : P<double>(ms->F);
+        if ((st = run_forces(c, ms, pot, F)) != GSIM_OK) return st;
+        if (!dev) HIPCHK(c, hipMemcpyAsync(force, F, sizeof(double) * 3 * ms->n, kind, c->stream));
+        double *E = dev && energy ? energy : P<double>(ms->E);
+        st = end_call(c, P<double>(c->sum_scratch), force_blocks(ms->n), E);
+        if (!dev && energy && (st == GSIM_OK || st == GSIM_E_NONFINITE || st == GSIM_E_LIMIT)) {
+            HIPCHK(c, hipMemcpyAsync(energy, E, sizeof(double), kind, c->stream));
+            HIPCHK(c, hipStreamSynchronize(c->stream));
+        }
+        return st;
     }
     GSIM_CATCH(c)
 }
@@ -1549,14 +1566,13 @@ static gsim_status walk_dev(gsim_ctx *c, MeshState *ms, const double *disp, int 
     const int n = ms->n;
     hipStream_t s = c->stream;
     HIPCHK(c, ensure(ms->wflags, n));
-    HIPCHK(c, launch_zero_u64(P<unsigned long long>(c->wstats), 8, s));
+    HIPCHK(c, ensure(c->wpart, sizeof(unsigned long long) * 8 * (size_t)((n + kWalkBlock - 1) / kWalkBlock)));
+    const unsigned long long *h = c->hout->walk;
     {
         Stage st(c, "walk");
-        HIPCHK(c, launch_walk(ms->dm, n, ms->face, ms->bary, disp, transport_velocity ? ms->vel : nullptr,
-                              P<unsigned long long>(c->wstats), P<uint8_t>(ms->wflags), s));
+        HIPCHK(c, launch_walk_blocks(ms->dm, n, ms->face, ms->bary, disp, transport_velocity ? ms->vel : nullptr,
+                                     P<uint8_t>(ms->wflags), P<unsigned long long>(c->wpart), c->hout->walk, s));
     }
-    unsigned long long h[8];
-    HIPCHK(c, hipMemcpyAsync(h, c->wstats.p, sizeof(h), hipMemcpyDeviceToHost, s));
     HIPCHK(c, hipStreamSynchronize(s));
     if (stats) {
         stats->crossings = (int64_t)h[0];
@@ -1611,11 +1627,9 @@ gsim_status gsim_displace_on_surface_noalloc(gsim_ctx *c, int32_t id, const doub
         // and the device's scratch array only; every row of the scratch the
         // kernels read is written by this call first
         hipStream_t s = c->stream;
-        unsigned long long *tot = part + 8 * (int64_t)kNoAllocBlocks;
+        const unsigned long long *h = c->hout->walk;
         HIPCHK(c, launch_walk_blocks(ms->dm, ms->n, ms->face, ms->bary, disp, transport_velocity ? ms->vel : nullptr,
-                                     flags, part, tot, s));
-        unsigned long long h[8];
-        HIPCHK(c, hipMemcpyAsync(h, tot, sizeof(h), hipMemcpyDeviceToHost, s));
+                                     flags, part, c->hout->walk, s));
         HIPCHK(c, hipStreamSynchronize(s));
         if (stats) {
             stats->crossings = (int64_t)h[0];

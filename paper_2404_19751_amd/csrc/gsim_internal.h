@@ -146,13 +146,27 @@ static_assert(sizeof(Counters) == 128, "one counter slot per 128-byte line");
 constexpr int kCtrSlots = 64;
 constexpr int kCtrStride = 1;  // Counters between two slots
 constexpr int kCtrWords = (int)(sizeof(Counters) / 8);  // 64-bit words of one slot
+constexpr int kCtrUsed = 10;  // those that count something
+constexpr int kCtrDepth = 7;  // max_depth among them
+// What kernels hand to the host at the end of a call, in pinned host memory
+// that they write directly (a copy of its own would cost a launch and a
+// staging pass): read after the stream has been waited for.
+struct HostOut {
+    Counters ctr;
+    unsigned long long walk[8];  // walk statistics
+    int64_t total;               // entries of a CSR result
+    int32_t bad;                 // a state check or a Voronoi limit counted something (HostOut holds no counts
+                                 // itself: atomics belong in device memory)
+};
 
 // launchers (return hipError_t of the launch)
 hipError_t launch_xyz(const DevMesh &m, int n, const int32_t *face, const double *bary, double *xyz,
                       hipStream_t s);
 hipError_t launch_zero_i32(int32_t *p, int64_t n, hipStream_t s);
 hipError_t launch_zero_u64(unsigned long long *p, int64_t n, hipStream_t s);
-hipError_t launch_scan_i32_to_i64(const int32_t *in, int64_t *out, int n, int64_t *scratch, hipStream_t s);
+// out[0..n] = exclusive sums of in[0..n); *total = out[n] (may be host memory)
+hipError_t launch_scan_i32_to_i64(const int32_t *in, int64_t *out, int n, int64_t *scratch, int64_t *total,
+                                  hipStream_t s);
 
 // One surface of a batch (a single surface is a batch of one): everything
 // the binning, geodesic and update kernels read or write for it. The host
@@ -290,11 +304,13 @@ hipError_t launch_near_init(char *area, int nslots, int tcap, unsigned long long
 // particles (an n x n adjacency bitset). launch_voronoi_faces marks every
 // pair of particles whose cells share a boundary longer than tol; cell lists
 // of a grid with origin lo (cell size `cell`, dims) over xyz; err[0] counts
-// faces with too many candidates, err[1] cells with too many vertices.
+// faces with too many candidates, err[1] cells with too many vertices, and
+// *host_flag (host memory) becomes 1 when either does.
 constexpr int kVoronoiMax = 32768;
 hipError_t launch_voronoi_faces(const DevMesh &m, int n, const double *xyz, const int32_t *cell_start,
                                 const int32_t *order, const int dims[3], const double lo[3], double cell,
-                                unsigned long long *bits, int64_t words, double tol, int32_t *err, hipStream_t s);
+                                unsigned long long *bits, int64_t words, double tol, int32_t *err, int32_t *host_flag,
+                                hipStream_t s);
 hipError_t launch_voronoi_count(const unsigned long long *bits, int n, int64_t words, int32_t *cnt, hipStream_t s);
 hipError_t launch_voronoi_fill(const unsigned long long *bits, int n, int64_t words, const int64_t *off, int32_t *nbr,
                                hipStream_t s);
@@ -369,36 +385,41 @@ hipError_t launch_count_rows(int n, const int32_t *cnt, int cap_c, const double 
 hipError_t launch_compact_rows(int n, const int32_t *cnt, int cap_c, const int32_t *cand, const double *dist,
                                const double *tan, const uint8_t *flags, double cutoff, const int64_t *off,
                                int32_t *nbr, double *odist, double *otan, uint8_t *oflags, hipStream_t s);
-// F_i and E_i from the rows; pflags[i] (may be null) receives PF_NONFINITE
+// F_i from the rows, and the energies of blocks of particles (force_blocks(n)
+// of them) in epart; pflags[i] (may be null) receives PF_NONFINITE
 // when either is not finite, and nonfinite counts such particles.
 hipError_t launch_forces_rows(int n, const int32_t *cnt, int cap_c, const double *dist, const double *tan,
-                              double cutoff, int kind, double k, double sigma, double *F, double *Ei,
+                              double cutoff, int kind, double k, double sigma, double *F, double *epart,
                               unsigned long long *npairs, uint8_t *pflags, unsigned long long *nonfinite,
                               hipStream_t s);
 // Checks a particle state before it is used: bad[0] counts face indices
 // outside [0, nf), bad[1] barycentric triples that are not finite, outside
 // [0, 1], do not sum to 1 within 1e-9 or put the particle on a vertex,
-// bad[2] velocities (vel may be null) that are not finite. bad[0..2] must be
-// zero beforehand.
+// bad[2] velocities (vel may be null) that are not finite; *host_flag (host
+// memory) becomes 1 when any is counted. bad[0..2] must be zero beforehand.
 hipError_t launch_validate_state(int nf, int n, const int32_t *face, const double *bary, const double *vel,
-                                 int32_t *bad, hipStream_t s);
+                                 int32_t *bad, int32_t *host_flag, hipStream_t s);
 // cnt[i] = the particles j != i within sqrt(cut2) of particle i, from the
 // cell lists in b (cells no smaller than the cutoff)
 hipError_t launch_count_candidates(int n, const PrefilterBufs &b, double cut2, int32_t *cnt, hipStream_t s);
-hipError_t launch_sum(const double *x, int n, double *out, double *scratch, hipStream_t s);
-hipError_t launch_integrate(const DevMesh &m, int n, const int32_t *face, const double *F, int kind, double dt,
-                            double mobility, double kT, double friction, uint64_t seed, uint64_t step,
-                            double *disp, hipStream_t s);
-// The walk of every particle; stats[8] (zeroed beforehand) receive the
-// crossings, vertex hits, boundary hits, crossing-cap hits, near-vertex
-// passes and the particles left in place because their displacement or
-// velocity was not finite; flags[n] (may be null) the PF_* bits.
-hipError_t launch_walk(const DevMesh &m, int n, int32_t *face, double *bary, const double *disp, double *vel,
-                       unsigned long long *stats, uint8_t *flags, hipStream_t s);
-// The same walk with its statistics reduced without atomics: one row of 8
-// counts per workgroup of kWalkBlock particles in part[ceil(n / kWalkBlock)][8],
-// then their column sums, in a fixed order, in tot[8]. Nothing needs
-// clearing beforehand; flags may be null.
+int force_blocks(int n);
+// a checked state into a surface's arrays, everything else restarted; a
+// surface's state out (outputs may be null)
+hipError_t launch_take_state(int n, const int32_t *face, const double *bary, const double *vel, int32_t *face_o,
+                             double *bary_o, double *vel_o, uint8_t *flags, FireState *fire, uint64_t *step,
+                             hipStream_t s);
+hipError_t launch_give_state(int n, const int32_t *face, const double *bary, const double *vel, int32_t *face_o,
+                             double *bary_o, double *vel_o, hipStream_t s);
+// the counter slots' sum into out (host memory) and back to zero; with an
+// energy, the sum of epart[nb] into it
+hipError_t launch_call_end(Counters *ctr, Counters *out, const double *epart, int nb, double *energy, hipStream_t s);
+// The walk of every particle, its statistics (crossings, vertex hits,
+// boundary hits, crossing-cap hits, near-vertex passes and the particles left
+// in place because their displacement or velocity was not finite) reduced
+// without atomics: one row of 8 counts per workgroup of kWalkBlock particles
+// in part[ceil(n / kWalkBlock)][8], then their column sums, in a fixed order,
+// in tot[8] (may be host memory). Nothing needs clearing beforehand; flags[n]
+// (the PF_* bits) may be null.
 constexpr int kWalkBlock = 256;
 hipError_t launch_walk_blocks(const DevMesh &m, int n, int32_t *face, double *bary, const double *disp, double *vel,
                               uint8_t *flags, unsigned long long *part, unsigned long long *tot, hipStream_t s);

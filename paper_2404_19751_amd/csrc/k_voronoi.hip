@@ -36,6 +36,7 @@ struct VorArgs {
     int64_t words;
     double tol;
     int32_t *err;  // [0] faces over the candidate limit, [1] cells over the vertex limit
+    int32_t *host_flag;  // host memory: set when either counts something
 };
 
 struct V2 {
@@ -161,7 +162,10 @@ __global__ __launch_bounds__(kWave) void k_voronoi_faces(VorArgs a) {
     __syncthreads();
     const int K = ncand;
     if (K > kCand) {
-        if (lane == 0) atomicAdd(&a.err[0], 1);
+        if (lane == 0) {
+            atomicAdd(&a.err[0], 1);
+            *a.host_flag = 1;
+        }
         return;
     }
 
@@ -241,7 +245,10 @@ __global__ __launch_bounds__(kWave) void k_voronoi_faces(VorArgs a) {
             }
         }
     }
-    if (__ballot(over) && lane == 0) atomicAdd(&a.err[1], 1);
+    if (__ballot(over) && lane == 0) {
+        atomicAdd(&a.err[1], 1);
+        *a.host_flag = 1;
+    }
 }
 
 __global__ void k_voronoi_count(const unsigned long long *__restrict__ bits, int n, int64_t words,
@@ -272,7 +279,8 @@ __global__ void k_voronoi_fill(const unsigned long long *__restrict__ bits, int 
 
 hipError_t launch_voronoi_faces(const DevMesh &m, int n, const double *xyz, const int32_t *cell_start,
                                 const int32_t *order, const int dims[3], const double lo[3], double cell,
-                                unsigned long long *bits, int64_t words, double tol, int32_t *err, hipStream_t s) {
+                                unsigned long long *bits, int64_t words, double tol, int32_t *err, int32_t *host_flag,
+                                hipStream_t s) {
     if (m.nf <= 0 || n <= 0) return hipSuccess;
     VorArgs a;
     a.m = m;
@@ -289,6 +297,7 @@ hipError_t launch_voronoi_faces(const DevMesh &m, int n, const double *xyz, cons
     a.words = words;
     a.tol = tol;
     a.err = err;
+    a.host_flag = host_flag;
     hipLaunchKernelGGL(k_voronoi_faces, dim3(m.nf), dim3(kWave), 0, s, a);
     return hipGetLastError();
 }

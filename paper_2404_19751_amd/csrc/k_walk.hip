@@ -9,43 +9,6 @@
 namespace gsim {
 namespace {
 
-// every lane of the wavefront calls it (wavefront sums, one atomic each)
-__device__ inline void flush_counts(const WalkCounts &wc, unsigned long long *stats) {
-    if (!stats) return;
-    wave_atomic_add(&stats[0], wc.cross_n);
-    wave_atomic_add(&stats[1], wc.vhit);
-    wave_atomic_add(&stats[2], wc.bhit);
-    wave_atomic_add(&stats[3], wc.cap);
-    wave_atomic_add(&stats[4], wc.near);
-    wave_atomic_add(&stats[5], wc.nonfinite);
-}
-
-__global__ __launch_bounds__(128) void k_walk(DevMesh m, int n, int32_t *__restrict__ face, double *__restrict__ bary,
-                                              const double *__restrict__ disp, double *__restrict__ vel,
-                                              unsigned long long *__restrict__ stats, uint8_t *__restrict__ flags) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    WalkCounts wc = {0, 0, 0, 0, 0, 0};
-    if (i < n) {
-        int f = face[i];
-        double b[3] = {bary[3 * i], bary[3 * i + 1], bary[3 * i + 2]};
-        const bool hv = vel != nullptr;
-        d3 v = hv ? ld3(vel + 3 * (int64_t)i) : d3{0, 0, 0};
-        uint8_t fl = 0;
-        walk_one(m, f, b, ld3(disp + 3 * (int64_t)i), v, hv, wc, fl);
-        face[i] = f;
-        bary[3 * i] = b[0];
-        bary[3 * i + 1] = b[1];
-        bary[3 * i + 2] = b[2];
-        if (hv) {
-            vel[3 * i] = v.x;
-            vel[3 * i + 1] = v.y;
-            vel[3 * i + 2] = v.z;
-        }
-        if (flags) flags[i] = fl;
-    }
-    flush_counts(wc, stats);
-}
-
 // The walk of every particle with its statistics in per-workgroup partial
 // rows instead of atomics: part[blockIdx][0..7] = crossings, vertex hits,
 // boundary hits, cap hits, near-vertex passes, non-finite particles, 0, 0.
@@ -94,7 +57,7 @@ __global__ __launch_bounds__(kWalkBlock) void k_walk_blocks(DevMesh m, int n, in
 
 // tot[0..7] = the column sums of part[nb][8], in a fixed order.
 __global__ __launch_bounds__(256) void k_walk_total(const unsigned long long *__restrict__ part, int nb,
-                                                   unsigned long long *__restrict__ tot) {
+                                                   unsigned long long *tot) {
     __shared__ unsigned long long sh[8][256];
     for (int k = 0; k < 8; ++k) {
         unsigned long long t = 0;
@@ -192,13 +155,6 @@ hipError_t launch_walk_blocks(const DevMesh &m, int n, int32_t *face, double *ba
     const int nb = (n + kWalkBlock - 1) / kWalkBlock;
     hipLaunchKernelGGL(k_walk_blocks, dim3(nb), dim3(kWalkBlock), 0, s, m, n, face, bary, disp, vel, flags, part);
     hipLaunchKernelGGL(k_walk_total, dim3(1), dim3(256), 0, s, part, nb, tot);
-    return hipGetLastError();
-}
-
-hipError_t launch_walk(const DevMesh &m, int n, int32_t *face, double *bary, const double *disp, double *vel,
-                       unsigned long long *stats, uint8_t *flags, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_walk, dim3((n + 127) / 128), dim3(128), 0, s, m, n, face, bary, disp, vel, stats, flags);
     return hipGetLastError();
 }
 

@@ -299,11 +299,14 @@ class Context:
         n = self._n[mid]
         off = np.empty(n + 1, np.int64)
         cnt = C.c_int64(0)
-        st = self.L.gsim_voronoi_neighbours(self.h, mid, _ptr(off), None, 0, C.byref(cnt))
-        if st not in (OK, E_CAPACITY):
-            self._chk(st)
-        nbr = np.empty(max(cnt.value, 1), np.int32)
-        self._chk(self.L.gsim_voronoi_neighbours(self.h, mid, _ptr(off), _ptr(nbr), cnt.value, C.byref(cnt)))
+        cap = 8 * n  # a triangulated packing has about 6 n entries
+        for _ in range(2):
+            nbr = np.empty(max(cap, 1), np.int32)
+            st = self.L.gsim_voronoi_neighbours(self.h, mid, _ptr(off), _ptr(nbr), cap, C.byref(cnt))
+            if st != E_CAPACITY:
+                break
+            cap = cnt.value
+        self._chk(st)
         return off, nbr[:cnt.value]
 
     def displace_on_surface(self, mid, disp, transport_velocity=True) -> dict:
