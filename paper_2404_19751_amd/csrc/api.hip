@@ -77,7 +77,7 @@ struct gsim_ctx {
     bool own_stream = false;
     std::string err;
     std::vector<MeshState *> meshes;
-    Buf stack, work, ctr, wpart, scan_scratch, sum_scratch, prof, desc, vdist, ttab, roots, partials, vbits, split;
+    Buf stack, work, ctr, wpart, scan_scratch, sum_scratch, prof, desc, vdist, ttab, roots, partials, vbits, split, best;
     // near passes: target areas, vertex and half-edge entries and epochs of the
     // resident wavefronts, and the layout they were last prepared for
     Buf near_t, near_v, near_h, near_e;
@@ -613,6 +613,7 @@ struct Batch {
     bool fused = false; // time steps move the particles inside the cutoff kernel
     bool near = false;  // a cutoff pass by whole-mesh propagation (many targets within the cutoff)
     BatchIdx face_blk{};  // blocks of kFaceBlock faces per surface (particles-by-face index)
+    int team = 1;       // whole-mesh passes: wavefronts per source
     int group = 1;      // sources per wavefront (FP64, more sources than resident slots: 2 or 4)
     int nslots = 0;
     GeoShape shape{};
@@ -706,7 +707,28 @@ gsim_status prepare_batch(gsim_ctx *c, Batch &B) {
     }
     // persistent grid: as many wavefronts as can be resident, at most one per source
     const bool fp32 = c->prec == GSIM_FP32_MIXED;
-    const int per_cu = std::max(1, by_face ? geodesic_all_blocks_per_cu(c->lds_stack_kb, fp32, B.near)
+    // scratch of a resident wavefront of a whole-mesh pass
+    const double all_slot = 64.0 * c->stack_cap_all + 8.0 * B.vstride + (double)bend_table_bytes(B.rcap) + 32.0 * B.tcap + 8.0 * B.hstride;
+    // whole-mesh passes with few sources: the largest team of wavefronts per
+    // source with which all sources are still resident at once, within the
+    // scratch budget and what the device has left. 100 sources on the torus of
+    // 3456 faces: 11.7 ms alone, 8.5 in twos, 6.1 in fours, 4.5 in eights; at
+    // 900 sources twos still give 50 ms for 82 (sphere of 20480 faces). Not for
+    // time steps, whose states repeat bit for bit (a team's results may differ
+    // in the last bits), nor in FP32-mixed mode, where that could move a flag.
+    B.team = 1;
+    bool teams = B.all && !fp32 && !c->profile_sources;
+    for (int i = 0; i < ns; ++i) teams = teams && !B.mem[i].integ;
+    for (int t = 8; t > 1 && B.team == 1 && teams; t /= 2) {
+        const int64_t waves = (int64_t)total * t;
+        if (waves > std::min(c->cus * geodesic_all_waves_per_cu(c->lds_stack_kb, fp32, false, t), c->max_slots)) continue;
+        if (waves * all_slot > c->stack_budget || waves * bend_table_bytes(B.rcap) > c->table_budget) continue;
+        size_t left = 0, card = 0;
+        const double more = waves * all_slot - (double)(c->stack.bytes + c->vdist.bytes + c->split.bytes + c->roots.bytes);
+        if (more > 0.0 && (hipMemGetInfo(&left, &card) != hipSuccess || more > 0.5 * (double)left)) continue;
+        B.team = t;
+    }
+    const int per_cu = std::max(1, by_face ? geodesic_all_waves_per_cu(c->lds_stack_kb, fp32, B.near, B.team)
                                            : geodesic_blocks_per_cu(c->lds_stack_kb, fp32));
     // several sources per wavefront (the largest group of at most
     // group_sources that still gives every resident wavefront a full one):
@@ -746,11 +768,10 @@ gsim_status prepare_batch(gsim_ctx *c, Batch &B) {
         }
         B.desc[0].prof = P<long long>(c->prof);
     }
-    B.nslots = std::min(std::min(total, c->cus * per_cu), c->max_slots);
+    B.nslots = std::min(std::min(total * B.team, c->cus * per_cu), c->max_slots);
     if (B.all) {
         // whole-mesh fronts are deep: fewer resident wavefronts rather than more memory
-        const double per_slot = 64.0 * c->stack_cap_all + 8.0 * B.vstride + (double)B.rstride + 32.0 * B.tcap + 8.0 * B.hstride;
-        const int64_t fit = (int64_t)(c->stack_budget / per_slot);
+        const int64_t fit = (int64_t)(c->stack_budget / all_slot);
         B.nslots = (int)std::max<int64_t>(1, std::min<int64_t>(B.nslots, fit));
     }
     if (B.near) {
@@ -782,7 +803,7 @@ gsim_status prepare_batch(gsim_ctx *c, Batch &B) {
         const int want = (B.nslots + c->cus - 1) / c->cus;
         const size_t stat = by_face ? geodesic_all_lds_bytes(c->lds_stack_kb, fp32, B.near)
                                     : geodesic_lds_bytes(c->lds_stack_kb);
-        if (want < per_cu && want > 0) {
+        if (want < per_cu && want > 0 && B.team == 1) {
             const size_t each = (size_t)c->lds_cu / (size_t)want;
             if (each > stat) B.shape.pad_lds = (int32_t)std::min(each - stat, (size_t)c->max_lds - stat);
         }
@@ -810,6 +831,8 @@ gsim_status prepare_batch(gsim_ctx *c, Batch &B) {
     if (B.all) {
         HIPCHK(c, ensure(c->vdist, sizeof(double) * (size_t)std::max(B.nslots, 1) * B.vstride));
         HIPCHK(c, ensure(c->ttab, 4 * sizeof(double) * (size_t)std::max(B.nslots, 1) * B.tcap));
+        if (B.team > 1)
+            HIPCHK(c, ensure(c->best, sizeof(unsigned long long) * (size_t)(B.nslots / B.team) * B.tcap));
         if (B.hstride) HIPCHK(c, ensure(c->split, sizeof(unsigned long long) * (size_t)std::max(B.nslots, 1) * B.hstride));
     }
     // bend-vertex tables: emptied once here, left empty by the kernels
@@ -851,7 +874,8 @@ gsim_status geodesic_pass(gsim_ctx *c, Batch &B, bool advance, bool commit_in = 
         HIPCHK(c, launch_geodesic_all(desc_dev(c), B.bi, gp, B.shape, P<char>(c->stack), P<unsigned long long>(v),
                                       B.vstride, P<char>(c->roots), B.rstride, B.rcap, B.near ? c->near_t.p : c->ttab.p,
                                       B.tcap, B.hstride ? P<unsigned long long>(h) : nullptr, B.hstride,
-                                      B.near ? P<uint32_t>(c->near_e) : nullptr, P<int32_t>(c->work),
+                                      B.near ? P<uint32_t>(c->near_e) : nullptr, B.team,
+                                      B.team > 1 ? P<unsigned long long>(c->best) : nullptr, P<int32_t>(c->work),
                                       P<Counters>(c->ctr), c->prec == GSIM_FP32_MIXED, s, st.a, st.b));
         c->passes++;
         return GSIM_OK;
@@ -968,12 +992,13 @@ std::string graph_key(gsim_ctx *c, const Batch &B, int steps) {
     put(&B.small, sizeof(B.small));
     put(&B.fused, sizeof(B.fused));
     put(&B.near, sizeof(B.near));
+    put(&B.team, sizeof(B.team));
     put(&B.face_blk, sizeof(B.face_blk));
     put(&B.group, sizeof(B.group));
     put(&c->update_block, sizeof(int));
     put(&steps, sizeof(int));
-    void *ptrs[14] = {c->stack.p, c->work.p, c->ctr.p, c->desc.p, c->scan_scratch.p, c->vdist.p, c->ttab.p,
-                      c->roots.p, c->partials.p, c->split.p, c->near_t.p, c->near_v.p, c->near_h.p, c->near_e.p};
+    void *ptrs[15] = {c->stack.p, c->work.p, c->ctr.p, c->desc.p, c->scan_scratch.p, c->vdist.p, c->ttab.p,
+                      c->roots.p, c->partials.p, c->split.p, c->best.p, c->near_t.p, c->near_v.p, c->near_h.p, c->near_e.p};
     put(ptrs, sizeof(ptrs));
     const int64_t sizes[5] = {B.rstride, B.rcap, B.tcap, B.vstride, B.hstride};
     put(sizes, sizeof(sizes));
@@ -1160,7 +1185,7 @@ void gsim_destroy(gsim_ctx *c) {
         delete ms;
     }
     for (Buf *b : {&c->stack, &c->work, &c->ctr, &c->wpart, &c->bad, &c->scan_scratch, &c->sum_scratch,
-                   &c->prof, &c->desc, &c->vdist, &c->ttab, &c->roots, &c->partials, &c->vbits, &c->split, &c->near_t, &c->near_v, &c->near_h, &c->near_e})
+                   &c->prof, &c->desc, &c->vdist, &c->ttab, &c->roots, &c->partials, &c->vbits, &c->split, &c->best, &c->near_t, &c->near_v, &c->near_h, &c->near_e})
         release(*b);
     if (c->desc_pinned) (void)hipHostFree(c->desc_pinned);
     if (c->hout) (void)hipHostFree(c->hout);

@@ -116,13 +116,20 @@ __device__ inline double uniform(double x) {
     return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
-__device__ inline int lane_id() { return threadIdx.x; }
+__device__ inline int lane_id() { return threadIdx.x & (kWave - 1); }
 // Ends one step of a loop that applies the lanes' updates to a shared table
 // one lane at a time: the next lane's loads must see this lane's stores. To
 // the compiler the lanes are separate threads, so without this it may keep a
 // table value in a register from one step to the next.
 __device__ inline void lane_step_barrier() { __asm__ __volatile__("" ::: "memory"); }
-__device__ inline uint64_t lanemask_lt() { return (1ull << threadIdx.x) - 1ull; }
+__device__ inline uint64_t lanemask_lt() { return (1ull << lane_id()) - 1ull; }
+// What the lanes of this wavefront have stored, to LDS or to global memory, is
+// visible to all of them from here on. Not a barrier: other wavefronts of the
+// workgroup go their own way.
+__device__ inline void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+}
 
 __device__ inline double wave_min(double v) {
     for (int o = 32; o > 0; o >>= 1) v = fmin(v, __shfl_xor(v, o));
@@ -309,7 +316,7 @@ __device__ inline void bend_update_loaded(const BendTable &G, BendLds &L, const 
         L.npend = np;
         L.ntouched = nt;
     }
-    __syncthreads();  // later loads of the table, by any lane, see these values
+    wave_sync();  // later loads of the table, by any lane, see these values
 }
 __device__ inline void bend_update(const BendTable &G, BendLds &L, const RootCfg &rc, bool ok, int e, double d,
                                    double tx, double ty, double alt) {
@@ -340,7 +347,7 @@ __device__ inline void bend_reset(const BendTable &G, BendLds &L) {
         L.npend = 0;
         L.ntouched = 0;
     }
-    __syncthreads();
+    wave_sync();
 }
 
 // Two-level window stack: LDS first, a per-wave global area for overflow.
@@ -384,7 +391,7 @@ struct Stack {
         }
         lsp -= take_l;
         if (nneed > take_l && gsp > 0) {
-            __syncthreads();  // make earlier global pushes of other lanes visible
+            wave_sync();  // make earlier global pushes of other lanes visible
             int take_g = min(nneed - take_l, gsp);
             if (!have && r >= take_l && r < take_l + take_g) {
                 load_rec(glb[gsp - 1 - (r - take_l)], w);
