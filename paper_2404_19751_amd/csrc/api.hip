@@ -437,8 +437,8 @@ gsim_status row_capacity(gsim_ctx *c, MeshState *ms, double cutoff, int &cap) {
                                nullptr, false, s));
     ms->fill_zero = ncell;
     HIPCHK(c, launch_count_candidates(n, pb, cutoff * cutoff * (1.0 + 1e-12), P<int32_t>(ms->nbr_cnt), s));
-    std::vector<int32_t> cnt(n);
-    HIPCHK(c, hipMemcpyAsync(cnt.data(), ms->nbr_cnt.p, sizeof(int32_t) * n, hipMemcpyDeviceToHost, s));
+    std::vector<int32_t> cnt(std::max(1, count_blocks(n)));
+    HIPCHK(c, hipMemcpyAsync(cnt.data(), ms->nbr_cnt.p, sizeof(int32_t) * cnt.size(), hipMemcpyDeviceToHost, s));
     HIPCHK(c, hipStreamSynchronize(s));
     const int mx = *std::max_element(cnt.begin(), cnt.end());
     if (mx <= kCandCap) return GSIM_OK;

@@ -404,7 +404,9 @@ hipError_t launch_validate_state(int nf, int n, const int32_t *face, const doubl
                                  int32_t *bad, int32_t *host_flag, hipStream_t s);
 // cnt[i] = the particles j != i within sqrt(cut2) of particle i, from the
 // cell lists in b (cells no smaller than the cutoff)
-hipError_t launch_count_candidates(int n, const PrefilterBufs &b, double cut2, int32_t *cnt, hipStream_t s);
+// most: the largest count of each of count_blocks(n) blocks of particles
+hipError_t launch_count_candidates(int n, const PrefilterBufs &b, double cut2, int32_t *most, hipStream_t s);
+int count_blocks(int n);
 int force_blocks(int n);
 // a checked state into a surface's arrays, everything else restarted; a
 // surface's state out (outputs may be null)

@@ -365,28 +365,44 @@ __global__ void k_forces_rows(int n, const int32_t *__restrict__ cnt, int cap, c
 }
 
 // Euclidean candidates of every particle: the particles within the cutoff
-// in the 27 cells around it (cells no smaller than the cutoff).
-__global__ void k_count_candidates(int n, const double *__restrict__ xyz, const int32_t *__restrict__ cell_of,
-                                   const int32_t *__restrict__ cell_start, const int32_t *__restrict__ order,
-                                   int dx, int dy, int dz, double cut2, int32_t *__restrict__ cnt) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const double xi = xyz[3 * (int64_t)i], yi = xyz[3 * (int64_t)i + 1], zi = xyz[3 * (int64_t)i + 2];
-    const int lin = cell_of[i];
-    const int cx = lin % dx, cy = (lin / dx) % dy, cz = lin / (dx * dy);
+// in the 27 cells around it (cells no smaller than the cutoff), three cells
+// side by side at a time (they follow each other in the cells' order). One
+// wavefront per particle; each block stores the largest of its counts. (One
+// thread per particle was bound by its chain of loads: 252 us for 8192
+// particles of 58 targets and 683 us of 232; now 13 and 47 us.)
+__global__ __launch_bounds__(kBlock) void k_count_candidates(int n, const double *__restrict__ xyz,
+                                                             const int32_t *__restrict__ cell_of,
+                                                             const int32_t *__restrict__ cell_start,
+                                                             const int32_t *__restrict__ order, int dx, int dy, int dz,
+                                                             double cut2, int32_t *__restrict__ most) {
+    __shared__ int32_t sh[kRowsPerBlock];
+    const int lane = threadIdx.x & 63, w = threadIdx.x / 64;
+    const int i = blockIdx.x * kRowsPerBlock + w;
     int m = 0;
-    for (int z = max(cz - 1, 0); z <= min(cz + 1, dz - 1); ++z)
-        for (int y = max(cy - 1, 0); y <= min(cy + 1, dy - 1); ++y)
-            for (int x = max(cx - 1, 0); x <= min(cx + 1, dx - 1); ++x) {
-                const int c = (z * dy + y) * dx + x;
-                for (int q = cell_start[c]; q < cell_start[c + 1]; ++q) {
+    if (i < n) {
+        const double xi = xyz[3 * (int64_t)i], yi = xyz[3 * (int64_t)i + 1], zi = xyz[3 * (int64_t)i + 2];
+        const int lin = cell_of[i];
+        const int cx = lin % dx, cy = (lin / dx) % dy, cz = lin / (dx * dy);
+        const int x0 = max(cx - 1, 0), x1 = min(cx + 1, dx - 1);
+        for (int z = max(cz - 1, 0); z <= min(cz + 1, dz - 1); ++z)
+            for (int y = max(cy - 1, 0); y <= min(cy + 1, dy - 1); ++y) {
+                const int c = (z * dy + y) * dx;
+                const int q1 = cell_start[c + x1 + 1];
+                for (int q = cell_start[c + x0] + lane; q < q1; q += 64) {
                     const int j = order[q];
                     const double ex = xyz[3 * (int64_t)j] - xi, ey = xyz[3 * (int64_t)j + 1] - yi,
                                  ez = xyz[3 * (int64_t)j + 2] - zi;
                     m += j != i && ex * ex + ey * ey + ez * ez < cut2;
                 }
             }
-    cnt[i] = m;
+        for (int o = 32; o > 0; o >>= 1) m += __shfl_xor(m, o);
+    }
+    if (lane == 0) sh[w] = m;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int k = 1; k < kRowsPerBlock; ++k) m = max(m, sh[k]);
+        most[blockIdx.x] = m;
+    }
 }
 
 // A particle state is usable when every face index is in range and every
@@ -721,10 +737,11 @@ hipError_t launch_forces_rows(int n, const int32_t *cnt, int cap_c, const double
                        sigma, F, epart, npairs, pflags, nonfinite);
     return hipGetLastError();
 }
-hipError_t launch_count_candidates(int n, const PrefilterBufs &b, double cut2, int32_t *cnt, hipStream_t s) {
+int count_blocks(int n) { return nblocks(n, kRowsPerBlock); }
+hipError_t launch_count_candidates(int n, const PrefilterBufs &b, double cut2, int32_t *most, hipStream_t s) {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_count_candidates, dim3(nblocks(n)), dim3(kBlock), 0, s, n, b.xyz, b.cell_of, b.cell_start,
-                       b.order, b.dims[0], b.dims[1], b.dims[2], cut2, cnt);
+    hipLaunchKernelGGL(k_count_candidates, dim3(count_blocks(n)), dim3(kBlock), 0, s, n, b.xyz, b.cell_of, b.cell_start,
+                       b.order, b.dims[0], b.dims[1], b.dims[2], cut2, most);
     return hipGetLastError();
 }
 hipError_t launch_validate_state(int nf, int n, const int32_t *face, const double *bary, const double *vel,
