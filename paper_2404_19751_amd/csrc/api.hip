@@ -883,7 +883,7 @@ gsim_status geodesic_pass(gsim_ctx *c, Batch &B, bool advance, bool commit_in = 
     {
         Stage st(c, "prefilter");
         if (B.small) {
-            HIPCHK(c, launch_bin_batch(desc_dev(c), B.bi.nsurf, P<int32_t>(c->work), advance, commit_in, s));
+            HIPCHK(c, launch_bin_batch(desc_dev(c), B.bi, P<int32_t>(c->work), advance, commit_in, s));
         } else {
             // one surface with a fine grid: multi-kernel counting sort
             MeshState *ms = B.mem[0].ms;

@@ -362,7 +362,7 @@ constexpr int kWorkInts = kWorkChunks * kWorkStride;
 // (also clears the work counters and, when `advance`, moves every surface's
 // step counter on by one)
 // commit: take the state from the next-state arrays first (fused time steps)
-hipError_t launch_bin_batch(const SurfDesc *desc, int nsurf, int32_t *work, bool advance, bool commit,
+hipError_t launch_bin_batch(const SurfDesc *desc, const BatchIdx &bi, int32_t *work, bool advance, bool commit,
                             hipStream_t s);
 hipError_t launch_fill_u64(unsigned long long *p, int64_t n, unsigned long long v, hipStream_t s);
 // fused force + integrator + walk for every particle of the batch
