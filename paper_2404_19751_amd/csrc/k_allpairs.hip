@@ -454,8 +454,8 @@ __device__ inline int one_split(unsigned long long *Hv, unsigned long long epoch
 }
 
 // Where the rays through the ends of a window's interval leave through the
-// far edge A -> C (left) or C -> B: child_left and child_right of the cutoff
-// kernel with the side selected per lane.
+// far edge A -> C (left) or C -> B, in FP64 in both precisions; the side is
+// selected per lane.
 template <typename R>
 __device__ inline void far_ends(const He<R> &h, const Win<R> &w, double txc, bool left, double &x0, double &x1) {
     const double px = w.px, py = w.py, b0 = w.b0, b1 = w.b1, cx = h.cx, cy = h.cy, L = h.L;

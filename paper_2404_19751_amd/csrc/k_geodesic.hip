@@ -253,39 +253,98 @@ __device__ inline void target_update(TL &L, const Ctx &C, bool ok, int slot, dou
     }
 }
 
-// Both children of a window. F3: the face's vertices in 3D in the order
-// (A, B, C) = (tail, head, opposite) of the entry half-edge; U3: the unit
-// directions of the half-edges (A->B, B->C, C->A).
+// Both whole-edge children of a window on an edge through the source. F3: the
+// face's vertices in 3D in the order (A, B, C) = (tail, head, opposite) of the
+// entry half-edge; U3: the unit directions of the half-edges (A->B, B->C, C->A).
 template <typename R, class TL>
-__device__ inline void children(const He<R> &h, const Win<R> &w, double txc, bool full, const Ctx &C,
-                                const double F3[3][3], const double U3[3][3], const TL &L, Win<R> &cl, bool &hl,
-                                Win<R> &cr, bool &hr, int &pruned, int tb = 0, int nc4 = -1) {
+__device__ inline void children_full(const He<R> &h, const Win<R> &w, const Ctx &C, const double F3[3][3],
+                                     const double U3[3][3], const TL &L, Win<R> &cl, bool &hl, Win<R> &cr, bool &hr,
+                                     int &pruned, int tb, int nc4) {
     hl = false;
     hr = false;
-    if (h.tp >= 0 && (full || (double)w.b0 < txc)) {
-        double x0, x1;
-        child_left(h, w, txc, full, x0, x1);
-        make_left(h, w, x0, x1, cl);
-        if (x1 - x0 > 1e-12 * (double)h.Lp) {
-            const double base = (double)w.sg + (double)seg_dist(cl.px, cl.py, cl.b0, cl.b1);
-            // edge A -> C is the reverse of half-edge prev = (C -> A)
-            const double u[3] = {-U3[2][0], -U3[2][1], -U3[2][2]};
-            if (reaches_target(L, C, F3[0], u, x0, x1, base, tb, nc4)) hl = true;
-            else ++pruned;
-        }
+    if (h.tp >= 0) {
+        make_left(h, w, 0.0, (double)h.Lp, cl);
+        const double base = (double)w.sg + (double)seg_dist(cl.px, cl.py, cl.b0, cl.b1);
+        // edge A -> C is the reverse of half-edge prev = (C -> A)
+        const double u[3] = {-U3[2][0], -U3[2][1], -U3[2][2]};
+        if (reaches_target(L, C, F3[0], u, 0.0, (double)h.Lp, base, tb, nc4)) hl = true;
+        else ++pruned;
     }
-    if (h.tn >= 0 && (full || (double)w.b1 > txc)) {
-        double x0, x1;
-        child_right(h, w, txc, full, x0, x1);
-        make_right(h, w, x0, x1, cr);
-        if (x1 - x0 > 1e-12 * (double)h.Ln) {
-            const double base = (double)w.sg + (double)seg_dist(cr.px, cr.py, cr.b0, cr.b1);
-            // edge C -> B is the reverse of half-edge next = (B -> C)
-            const double u[3] = {-U3[1][0], -U3[1][1], -U3[1][2]};
-            if (reaches_target(L, C, F3[2], u, x0, x1, base, tb, nc4)) hr = true;
-            else ++pruned;
-        }
+    if (h.tn >= 0) {
+        make_right(h, w, 0.0, (double)h.Ln, cr);
+        const double base = (double)w.sg + (double)seg_dist(cr.px, cr.py, cr.b0, cr.b1);
+        // edge C -> B is the reverse of half-edge next = (B -> C)
+        const double u[3] = {-U3[1][0], -U3[1][1], -U3[1][2]};
+        if (reaches_target(L, C, F3[2], u, 0.0, (double)h.Ln, base, tb, nc4)) hr = true;
+        else ++pruned;
     }
+}
+
+// reaches_target without branches inside a group, so that its chains overlap
+// wholly; in groups of two, for four at a time need more registers than there
+// are (1000 sources on the bumpy sphere: 103 us a pass against 102 in twos;
+// 20000 on the height field: ten steps 4.5 ms against 3.87).
+template <class TL>
+__device__ inline bool reaches_target_wide(const TL &L, const double P[3], const double u[3], double x0, double x1,
+                                           double base, int tb, int te) {
+    for (int s0 = tb; s0 < te; s0 += 2) {
+        bool hit = false;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const double *cb = L.cb[s0 + i];
+            const double rem = cb[3] - base;
+            double q0 = cb[0] - P[0], q1 = cb[1] - P[1], q2 = cb[2] - P[2];
+            double t = q0 * u[0] + q1 * u[1] + q2 * u[2];
+            t = fmin(fmax(t, x0), x1);
+            q0 -= t * u[0];
+            q1 -= t * u[1];
+            q2 -= t * u[2];
+            hit |= (rem > 0.0) & (q0 * q0 + q1 * q1 + q2 * q2 < rem * rem);
+        }
+        if (hit) return true;
+    }
+    return false;
+}
+
+// Both children of a window (fp: the face's record, k: the entry half-edge's
+// place in it) in one straight run, so that the divisions, the roots and the
+// loads of the face overlap: the latency of that chain bounds a wavefront's
+// iteration (8600 cycles, one wavefront per SIMD). The ray through each end of
+// the window meets the left or the right edge: one division each. The face is
+// loaded here, not with the window's other records: held through the target
+// queries its 18 numbers cost spilled registers.
+// With the children one after the other, each under its own branch: 1000
+// sources on the bumpy sphere, twenty steps, 2.45 ms, now 2.25; 20000 on the
+// height field, ten steps, 4.00 and 3.87.
+template <typename R, class TL>
+__device__ inline void children_of(const He<R> &h, const Win<R> &w, double txc, const Ctx &C,
+                                         const double *__restrict__ fp, int k, const TL &L, Win<R> &cl, bool &hl,
+                                         Win<R> &cr, bool &hr, int &pruned, int tb, int nc4) {
+    // A and the direction C -> A, C and the direction B -> C
+    const int kc = k == 0 ? 2 : k - 1, kb = k == 2 ? 0 : k + 1;
+    const double Pl[3] = {fp[3 * k], fp[3 * k + 1], fp[3 * k + 2]};
+    const double Pr[3] = {fp[3 * kc], fp[3 * kc + 1], fp[3 * kc + 2]};
+    const double Vl[3] = {fp[9 + 3 * kc], fp[10 + 3 * kc], fp[11 + 3 * kc]};
+    const double Vr[3] = {fp[9 + 3 * kb], fp[10 + 3 * kb], fp[11 + 3 * kb]};
+    const double px = w.px, py = w.py, b0 = w.b0, b1 = w.b1, cx = h.cx, cy = h.cy, Lh = h.L, Lp = h.Lp, Ln = h.Ln;
+    const double e0 = b0 - px, e1 = b1 - px, r = (px - cx) * (-py), t = (Lh - cx) * (-py);
+    const bool l0 = b0 < txc, l1 = b1 < txc;
+    const double q0 = (l0 ? Lp * (py * b0) : Ln * (r - (py - cy) * e0)) / ((l0 ? py * cx : t) + cy * e0);
+    const double q1 = (l1 ? Lp * (py * b1) : Ln * (r - (py - cy) * e1)) / ((l1 ? py * cx : t) + cy * e1);
+    const double xl0 = fmin(fmax(b0 <= 0.0 ? 0.0 : q0, 0.0), Lp), xl1 = fmin(fmax(b1 >= txc ? Lp : q1, 0.0), Lp);
+    const double xr0 = fmin(fmax(b0 <= txc ? 0.0 : q0, 0.0), Ln), xr1 = fmin(fmax(b1 >= Lh ? Ln : q1, 0.0), Ln);
+    make_left(h, w, xl0, xl1, cl);
+    make_right(h, w, xr0, xr1, cr);
+    const bool gl = h.tp >= 0 && l0 && xl1 - xl0 > 1e-12 * Lp;
+    const bool gr = h.tn >= 0 && b1 > txc && xr1 - xr0 > 1e-12 * Ln;
+    const double bl = (double)w.sg + (double)seg_dist(cl.px, cl.py, cl.b0, cl.b1);
+    const double br = (double)w.sg + (double)seg_dist(cr.px, cr.py, cr.b0, cr.b1);
+    // edge A -> C is the reverse of half-edge prev = (C -> A), edge C -> B
+    // that of next = (B -> C)
+    const double ul[3] = {-Vl[0], -Vl[1], -Vl[2]}, ur[3] = {-Vr[0], -Vr[1], -Vr[2]};
+    hl = gl && reaches_target_wide(L, Pl, ul, xl0, xl1, bl, tb, tb + nc4);
+    hr = gr && reaches_target_wide(L, Pr, ur, xr0, xr1, br, tb, tb + nc4);
+    pruned += (gl && !hl) + (gr && !hr);
 }
 
 struct SrcStats {
@@ -941,7 +1000,7 @@ __device__ __attribute__((always_inline)) inline unsigned run_sources(const GeoA
                     w.py = R(0);
                     double F3[3][3], U3[3][3];
                     face_xyz(sd.m, Rh.twin / 3, Rh.twin % 3, F3, U3);
-                    children(Ht, w, 0.0, true, C, F3, U3, L, wa, wantA, wb, wantB, pruned, q * tspan, nc4_of(q));
+                    children_full(Ht, w, C, F3, U3, L, wa, wantA, wb, wantB, pruned, q * tspan, nc4_of(q));
                 }
             }
         }
@@ -1030,7 +1089,6 @@ __device__ __attribute__((always_inline)) inline unsigned run_sources(const GeoA
         bool hl = false, hr = false;
         He<R> H;
         double txc = 0.0;
-        double F3[3][3], U3[3][3];
         double wtx = 0.0, wty = 0.0, wD2 = INFINITY;  // the root's tangent and other-direction distance
         int f = -1, k = 0;
         // the window's source: its targets, hash buckets and bend-vertex entries
@@ -1042,7 +1100,6 @@ __device__ __attribute__((always_inline)) inline unsigned run_sources(const GeoA
             f = w.he / 3;
             k = w.he % 3;
             H = load_he(sd.m, w.he, R(0));
-            face_xyz(sd.m, f, k, F3, U3);
             double rD = 0.0, rL = INFINITY;
             if (w.root >= 0) {
                 rD = G.rD[w.root];
@@ -1132,7 +1189,8 @@ __device__ __attribute__((always_inline)) inline unsigned run_sources(const GeoA
             alt3 = alt;
             if (ok) pE = bend_load(G, pe3);
         }
-        if (have) children(H, w, txc, false, C, F3, U3, L, cl, hl, cr, hr, pruned, tb, nc4_of(q));
+        if (have)
+            children_of(H, w, txc, C, sd.m.fpos + 18 * (int64_t)f, k, L, cl, hl, cr, hr, pruned, tb, nc4_of(q));
         bend_update_loaded(G, L.B, C.rc, ok3, pe3, d3, tx3, ty3, alt3, pE);
         // keep one child in the lane, push the other
         S.push(hl && hr, cr, overflow);

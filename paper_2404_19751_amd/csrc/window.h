@@ -403,37 +403,8 @@ struct Stack {
     }
 };
 
-// Child intervals. Left child: across C->A (stored on tp, frame origin A,
-// x towards C). Right child: across B->C (stored on tn, frame origin C, x
-// towards B). The endpoint intersections are evaluated in FP64 in both
-// precisions.
-template <typename R>
-__device__ inline void child_left(const He<R> &h, const Win<R> &w, double txc, bool full, double &x0, double &x1) {
-    if (full) {
-        x0 = 0.0;
-        x1 = (double)h.Lp;
-        return;
-    }
-    const double px = w.px, py = w.py, b0 = w.b0, b1 = w.b1, cx = h.cx, cy = h.cy, Lp = h.Lp;
-    x0 = b0 <= 0.0 ? 0.0 : Lp * (py * b0) / (py * cx + cy * (b0 - px));
-    x1 = b1 >= txc ? Lp : Lp * (py * b1) / (py * cx + cy * (b1 - px));
-    x0 = fmin(fmax(x0, 0.0), Lp);
-    x1 = fmin(fmax(x1, 0.0), Lp);
-}
-template <typename R>
-__device__ inline void child_right(const He<R> &h, const Win<R> &w, double txc, bool full, double &x0, double &x1) {
-    if (full) {
-        x0 = 0.0;
-        x1 = (double)h.Ln;
-        return;
-    }
-    const double px = w.px, py = w.py, b0 = w.b0, b1 = w.b1, cx = h.cx, cy = h.cy, L = h.L, Ln = h.Ln;
-    x0 = b0 <= txc ? 0.0 : Ln * ((px - cx) * (-py) - (py - cy) * (b0 - px)) / ((L - cx) * (-py) + cy * (b0 - px));
-    x1 = b1 >= L ? Ln : Ln * ((px - cx) * (-py) - (py - cy) * (b1 - px)) / ((L - cx) * (-py) + cy * (b1 - px));
-    x0 = fmin(fmax(x0, 0.0), Ln);
-    x1 = fmin(fmax(x1, 0.0), Ln);
-}
-
+// Children of a window. Left: across C->A (stored on tp, frame origin A, x
+// towards C). Right: across B->C (stored on tn, frame origin C, x towards B).
 // Frame changes into the child windows (the interval [x0, x1] already
 // computed): left child on twin(prev(h)) with origin A, right child on
 // twin(next(h)) with origin C.
