@@ -337,9 +337,9 @@ gsim_status gsim_step_batched(gsim_ctx *ctx, int32_t nmesh, const int32_t *mesh_
  *                   at that count, checked against the free device memory
  *                   before each pass, as a pairs call's output is before it
  *                   is written; GSIM_E_LIMIT names the bytes). Without
- *                   it, the cutoff kernel takes up to 4096 Euclidean candidates
- *                   per source: up to 128 in an LDS table, more with the targets
- *                   in global memory and rows sized from a count of the
+ *                   it, passes with a cutoff take up to 4096 Euclidean candidates
+ *                   per source: up to 128 in an LDS table, more by whole-mesh
+ *                   propagation up to the cutoff and rows sized from a count of the
  *                   candidates at the start of each call (GSIM_E_LIMIT beyond
  *                   4096, or when moving particles outgrow that count within a
  *                   call by more than a quarter plus 32)
