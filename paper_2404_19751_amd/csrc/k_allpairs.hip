@@ -31,8 +31,8 @@
 // face's several targets are offered to all lanes' windows side by side
 // (offer_pairs). With hundreds of targets the cutoff kernel's per-target
 // pruning keeps nearly every window; domination keeps 700 of its 2670 a
-// source on the benchmark torus at 232 targets: 8192 sources 5.95 -> 1.43 ms
-// a pass, at 58 targets 0.94 -> 0.45 ms.
+// source on the benchmark torus at 232 targets: 8192 sources 5.95 -> 1.34 ms
+// a pass, at 58 targets 0.94 -> 0.47 ms.
 //
 // Mapping: the state of all n targets (best distance, best distance of
 // another direction, tangent; 32 bytes each), the vertex table, the
