@@ -803,16 +803,16 @@ gsim_status prepare_batch(gsim_ctx *c, Batch &B) {
         // at most the needed number fit on a compute unit and the grid spreads
         // over all of them instead of filling some
         const int want = (B.nslots + c->cus - 1) / c->cus;
-        const size_t stat = by_face ? geodesic_all_lds_bytes(c->lds_stack_kb, fp32, B.near)
-                                    : geodesic_lds_bytes(c->lds_stack_kb);
         if (want < per_cu && want > 0 && B.team == 1) {
             // (whole LDS blocks of the allocator, so that the needed number
             // does fit: a third, fifth, sixth or seventh of the LDS rounded up
             // let one workgroup fewer in, and the rest ran as a second round.
             // 1030 sources on the sphere of 20480 faces: 143 ms so, 91 now;
             // twenty steps of 760 on the bumpy sphere 2.67 and 2.11 ms)
+            const size_t stat = by_face ? geodesic_all_lds_bytes(c->lds_stack_kb, fp32, B.near)
+                                        : geodesic_lds_bytes(c->lds_stack_kb, fp32, B.group);
             const size_t each = (size_t)c->lds_cu / (size_t)want / kLdsBlock * kLdsBlock;
-            if (each > stat) B.shape.pad_lds = (int32_t)std::min(each - stat, (size_t)c->max_lds - stat);
+            if (std::min(each, (size_t)c->max_lds) > stat) B.shape.pad_lds = (int32_t)(std::min(each, (size_t)c->max_lds) - stat);
         }
     }
     const int cap_rec = B.all ? c->stack_cap_all : c->gp.stack_cap;

@@ -348,8 +348,9 @@ constexpr int kFireBlock = 256;
 hipError_t launch_fire_control(const SurfDesc *desc, const BatchIdx &blk, double *partials, Counters *ctr,
                                hipStream_t s);
 
-// LDS bytes of one geodesic workgroup for a stack size (occupancy planning)
-size_t geodesic_lds_bytes(int lds_stack_kb);
+// LDS bytes of one geodesic workgroup (the largest over the launch modes; for
+// occupancy planning: more than it has on error)
+size_t geodesic_lds_bytes(int lds_stack_kb, bool fp32, int group);
 // positions + cell counting sort, one workgroup per surface (every surface's
 // grid must have at most kSmallCells cells)
 constexpr int kSmallCells = 4096;

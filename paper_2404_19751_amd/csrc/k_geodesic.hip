@@ -1456,33 +1456,25 @@ __global__ __launch_bounds__(kWave, 2) void k_geodesic(GeoArgs a) {
     }
 }
 
-template <bool kMixed, int kStk, int kMode, int kG = 1>
-void launch_one(int nslots, size_t pad, const GeoArgs &a, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
-    if (ev0 || ev1)
-        hipExtLaunchKernelGGL((k_geodesic<kMixed, kStk, kMode, kG>), dim3(nslots), dim3(kWave), (uint32_t)pad, s,
-                              ev0, ev1, 0, a);
-    else hipLaunchKernelGGL((k_geodesic<kMixed, kStk, kMode, kG>), dim3(nslots), dim3(kWave), pad, s, a);
-}
-// the grouped instantiations: persistent grid, LDS tables
-template <bool kMixed, int kG>
-void launch_groups(int kb, int nslots, size_t pad, const GeoArgs &a, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
-    if (kb <= 4) launch_one<kMixed, 4096, 0, kG>(nslots, pad, a, s, ev0, ev1);
-    else if (kb <= 8) launch_one<kMixed, 8192, 0, kG>(nslots, pad, a, s, ev0, ev1);
-    else launch_one<kMixed, 16384, 0, kG>(nslots, pad, a, s, ev0, ev1);
-}
-template <bool kMixed, int kMode>
-void launch_stack(int kb, int nslots, size_t pad, const GeoArgs &a, hipStream_t s, hipEvent_t ev0,
-                  hipEvent_t ev1) {
-    if (kb <= 4) launch_one<kMixed, 4096, kMode>(nslots, pad, a, s, ev0, ev1);
-    else if (kb <= 8) launch_one<kMixed, 8192, kMode>(nslots, pad, a, s, ev0, ev1);
-    else launch_one<kMixed, 16384, kMode>(nslots, pad, a, s, ev0, ev1);
+using GeoKernel = void (*)(GeoArgs);
+template <bool kMixed, int kMode, int kG>
+GeoKernel kernel_of(int kb) {
+    if (kb <= 4) return &k_geodesic<kMixed, 4096, kMode, kG>;
+    if (kb <= 8) return &k_geodesic<kMixed, 8192, kMode, kG>;
+    return &k_geodesic<kMixed, 16384, kMode, kG>;
 }
 template <bool kMixed>
-void launch_variant(int mode, int kb, int nslots, size_t pad, const GeoArgs &a, hipStream_t s, hipEvent_t ev0,
-                    hipEvent_t ev1) {
-    if (mode == 2) launch_stack<kMixed, 2>(kb, nslots, pad, a, s, ev0, ev1);
-    else if (mode == 1) launch_stack<kMixed, 1>(kb, nslots, pad, a, s, ev0, ev1);
-    else launch_stack<kMixed, 0>(kb, nslots, pad, a, s, ev0, ev1);
+GeoKernel kernel_of(int kb, int mode, int group) {
+    // the grouped instantiations: persistent grid
+    if (group == 2) return kernel_of<kMixed, 0, 2>(kb);
+    if (group == 4) return kernel_of<kMixed, 0, 4>(kb);
+    if (group == 8) return kernel_of<kMixed, 0, 8>(kb);
+    if (mode == 2) return kernel_of<kMixed, 2, 1>(kb);
+    if (mode == 1) return kernel_of<kMixed, 1, 1>(kb);
+    return kernel_of<kMixed, 0, 1>(kb);
+}
+GeoKernel kernel_for(int kb, bool fp32, int mode, int group) {
+    return fp32 ? kernel_of<true>(kb, mode, group) : kernel_of<false>(kb, mode, group);
 }
 
 }  // namespace
@@ -1510,26 +1502,17 @@ hipError_t launch_geodesic(const SurfDesc *desc, const BatchIdx &bi, const GeoPa
 
     if (shape.nslots < 1 || total < 1) return hipSuccess;
     if (fuse && total > shape.nslots) return hipErrorInvalidValue;  // the fused update needs a slot per source
-    const size_t pad = shape.pad_lds > 0 ? (size_t)shape.pad_lds : 0;
     if (group > 1) {
         // several sources per wavefront: persistent grid, LDS tables, claims
         // of a multiple of the group so that groups come from one claimed
         // range
         if ((group != 2 && group != 4 && group != 8) || mode != 0 || rcap % group) return hipErrorInvalidValue;
         a.grab = group * a.grab;
-        if (fp32) {
-            if (group == 2) launch_groups<true, 2>(shape.lds_stack_kb, shape.nslots, pad, a, s, ev0, ev1);
-            else if (group == 4) launch_groups<true, 4>(shape.lds_stack_kb, shape.nslots, pad, a, s, ev0, ev1);
-            else launch_groups<true, 8>(shape.lds_stack_kb, shape.nslots, pad, a, s, ev0, ev1);
-        } else {
-            if (group == 2) launch_groups<false, 2>(shape.lds_stack_kb, shape.nslots, pad, a, s, ev0, ev1);
-            else if (group == 4) launch_groups<false, 4>(shape.lds_stack_kb, shape.nslots, pad, a, s, ev0, ev1);
-            else launch_groups<false, 8>(shape.lds_stack_kb, shape.nslots, pad, a, s, ev0, ev1);
-        }
-        return hipGetLastError();
     }
-    if (fp32) launch_variant<true>(mode, shape.lds_stack_kb, shape.nslots, pad, a, s, ev0, ev1);
-    else launch_variant<false>(mode, shape.lds_stack_kb, shape.nslots, pad, a, s, ev0, ev1);
+    const GeoKernel f = kernel_for(shape.lds_stack_kb, fp32, mode, group);
+    const uint32_t pad = shape.pad_lds > 0 ? (uint32_t)shape.pad_lds : 0;
+    if (ev0 || ev1) hipExtLaunchKernelGGL(f, dim3(shape.nslots), dim3(kWave), pad, s, ev0, ev1, 0, a);
+    else hipLaunchKernelGGL(f, dim3(shape.nslots), dim3(kWave), pad, s, a);
     return hipGetLastError();
 }
 
@@ -1546,19 +1529,24 @@ hipError_t launch_candidates(const SurfDesc *desc, const BatchIdx &bi, int group
 
 int geodesic_blocks_per_cu(int lds_stack_kb, bool fp32) {
     int nb = 0;
-    const void *f;
-    if (lds_stack_kb <= 4)
-        f = fp32 ? (const void *)&k_geodesic<true, 4096, 0> : (const void *)&k_geodesic<false, 4096, 0>;
-    else if (lds_stack_kb <= 8)
-        f = fp32 ? (const void *)&k_geodesic<true, 8192, 0> : (const void *)&k_geodesic<false, 8192, 0>;
-    else f = fp32 ? (const void *)&k_geodesic<true, 16384, 0> : (const void *)&k_geodesic<false, 16384, 0>;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, f, kWave, 0) != hipSuccess) return 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, (const void *)kernel_for(lds_stack_kb, fp32, 0, 1), kWave,
+                                                     0) != hipSuccess)
+        return 0;
     return nb;
 }
 
-size_t geodesic_lds_bytes(int lds_stack_kb) {
-    const int kb = lds_stack_kb <= 4 ? 4 : (lds_stack_kb <= 8 ? 8 : 16);
-    return sizeof(Lds) + (size_t)kb * 1024;
+size_t geodesic_lds_bytes(int lds_stack_kb, bool fp32, int group) {
+    // asked of the compiled kernels: the compiler may keep a local array of
+    // each lane in LDS beside the declared tables (4608 bytes where the
+    // stack has 16 KiB), and padding on top of a smaller count asked for more
+    // LDS than a compute unit has, which aborts the queue
+    size_t most = 0;
+    for (int mode = 0; mode < (group > 1 ? 1 : 3); ++mode) {
+        hipFuncAttributes at{};
+        if (hipFuncGetAttributes(&at, (const void *)kernel_for(lds_stack_kb, fp32, mode, group)) != hipSuccess) return 65536;
+        most = std::max(most, (size_t)at.sharedSizeBytes);
+    }
+    return most;
 }
 
 }  // namespace gsim
