@@ -1827,6 +1827,7 @@ gsim_status gsim_autotune(gsim_ctx *c, int32_t nmesh, const int32_t *mesh_ids, c
             (void)hipEventCreate(&a0);
             (void)hipEventCreate(&a1);
             double bt = INFINITY;
+            c->ctr_clean = false;  // the update launches count too
             for (int blk : {64, 128, 256}) {
                 double tmin = INFINITY;
                 for (int r = 0; r < reps + 1; ++r) {
