@@ -613,9 +613,10 @@ __device__ inline void query_pairs(const FaceTarget *ftgt, AllLds &L, const Targ
 
 // Launch the pending bend vertices (their distance improved, or their best
 // direction changed, or a tie appeared), their fans flattened over the lanes
-// a chunk of vertices at a time.
+// a chunk of vertices at a time. Returns whether a window found no room (the
+// caller ends the source).
 template <typename R, bool kNear, int kTeam>
-__device__ void launch_roots(const SurfDesc &sd, AllLds &L, const BendTable &G, const TargetTable<kNear> &td,
+__device__ bool launch_roots(const SurfDesc &sd, AllLds &L, const BendTable &G, const TargetTable<kNear> &td,
                              const VertexTable<kNear> &Dv, const ACtx &C, RoundStack<R> &S, double T, int src,
                              SrcStats &st) {
     const int lane = lane_id();
@@ -628,6 +629,7 @@ __device__ void launch_roots(const SurfDesc &sd, AllLds &L, const BendTable &G, 
     // take the pending list (its vertices may be queued again while they launch)
     const int npend = L.B.npend;
     const double maxb = L.maxb;
+    bool lost = false;
     int nsel = 0;
     for (int base = 0; base < npend; base += kWave) {
         const int k = base + lane;
@@ -777,10 +779,11 @@ __device__ void launch_roots(const SurfDesc &sd, AllLds &L, const BendTable &G, 
                 });
             bend_update(G, L.B, C.rc, e1 >= 0, e1, D + Rh.L, vtx, vty, D2 + Rh.L);
             bend_update(G, L.B, C.rc, e2 >= 0, e2, D + Rh.Lp, vtx, vty, D2 + Rh.Lp);
-            S.push(want, later, nw, st.overflow);
+            S.push(want, later, nw, lost);
         }
         wave_sync();  // the chunk arrays are rewritten by the next chunk
     }
+    return __ballot(lost) != 0;
 }
 
 // One source's whole-mesh propagation and its row of results. With a
@@ -1053,7 +1056,7 @@ __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, 
         bool busy = S.refill(have, w);
         if (!busy && L.B.npend > 0) {
             if (prof) L.clk[2] -= clock64();
-            launch_roots<R, kNear, kTeam>(sd, L, G, td, Dv, C, S, T, src, st);
+            if (launch_roots<R, kNear, kTeam>(sd, L, G, td, Dv, C, S, T, src, st)) overflow = true;
             if (prof) L.clk[2] += clock64();
             // no lane holds a window here: nothing of one has to live through the launch
             w = Win<R>{};

@@ -361,14 +361,16 @@ struct SrcStats {
 // of vertices at a time, so one launch round costs a few memory round trips,
 // not one per vertex. In the grouped instantiations entry e stands for bend
 // vertex e / kG of source e mod kG (its targets from q tspan on).
+// Returns whether a window found no room (the caller ends the source).
 template <typename R, class TL, int kG = 1>
-__device__ void launch_roots(const GeoArgs &a, const SurfDesc &sd, TL &L, const BendTable &G, const Ctx &C,
+__device__ bool launch_roots(const GeoArgs &a, const SurfDesc &sd, TL &L, const BendTable &G, const Ctx &C,
                              Stack<R> &S, SrcStats &st, int tspan = 0, const int *ncs = nullptr) {
     constexpr int kB = kG == 1 ? TL::kBuckets : kGroupBuckets<kG>;
     const int lane = lane_id();
     const DevMesh &M = sd.m;
     const HeRec *__restrict__ he = M.he;
     const int npend = L.B.npend;
+    bool lost = false;
     // the first wavefront's worth of pending entries is read once for both
     // passes below
     int e0 = 0;
@@ -533,10 +535,11 @@ __device__ void launch_roots(const GeoArgs &a, const SurfDesc &sd, TL &L, const 
             const int u2 = act ? Rh.opp_flags >> 1 : 0;
             const int p2 = act && D + Rh.Lp < C.cut_acc ? M.pidx[u2] : -1;
             bend_update(G, L.B, C.rc, p2 >= 0, bend_entry<kG>(p2, q), D + Rh.Lp, vtx, vty, D2 + Rh.Lp);
-            S.push(want, nw, st.overflow);
+            S.push(want, nw, lost);
         }
         __syncthreads();  // the chunk arrays are rewritten by the next chunk
     }
+    return __ballot(lost) != 0;
 }
 
 // The group lists from a group search's counts (L.ncg, L.gall): sources
@@ -1070,7 +1073,7 @@ __device__ __attribute__((always_inline)) inline unsigned run_sources(const GeoA
         // once nothing is left to propagate
         if (L.B.npend > 0 && (eager || !busy)) {
             const long long t0 = clock64();
-            launch_roots<R, TL, kG>(a, sd, L, G, C, S, st, tspan, ncs);
+            if (launch_roots<R, TL, kG>(a, sd, L, G, C, S, st, tspan, ncs)) overflow = true;
             t_launch += clock64() - t0;
             if (!busy) busy = S.refill(have, w);
         }
