@@ -57,7 +57,7 @@ struct MeshState {
     // all-pairs rows and the particles-by-face index
     int cap = kCandCap;  // row capacity of the last pass
     int ident_n = -1;    // rows hold the identity lists for this n
-    Buf fstart, ffirst, ftgt, fcount;
+    Buf fstart, ffirst, ftgt, fcount, forder;
 };
 
 struct TimingRec {
@@ -580,6 +580,7 @@ gsim_status prepare_face_index(gsim_ctx *c, MeshState *ms, SurfDesc &d) {
     HIPCHK(c, ensure(ms->fstart, sizeof(int32_t) * (nf + 1)));
     HIPCHK(c, ensure(ms->ffirst, sizeof(int32_t) * nf));
     HIPCHK(c, ensure(ms->ftgt, sizeof(FaceTarget) * (size_t)ms->n));
+    HIPCHK(c, ensure(ms->forder, sizeof(int32_t) * (size_t)ms->n));
     const void *was = ms->fcount.p;
     HIPCHK(c, ensure(ms->fcount, sizeof(int32_t) * nf));
     if (ms->fcount.p != was) HIPCHK(c, launch_zero_i32(P<int32_t>(ms->fcount), (int64_t)nf, c->stream));
@@ -587,6 +588,7 @@ gsim_status prepare_face_index(gsim_ctx *c, MeshState *ms, SurfDesc &d) {
     d.ffirst = P<int32_t>(ms->ffirst);
     d.ftgt = P<FaceTarget>(ms->ftgt);
     d.fcount = P<int32_t>(ms->fcount);
+    d.forder = P<int32_t>(ms->forder);
     return GSIM_OK;
 }
 
@@ -1179,7 +1181,7 @@ void gsim_destroy(gsim_ctx *c) {
         for (Buf *b : {&ms->cell_of, &ms->cell_start, &ms->cell_fill, &ms->order, &ms->cand_cnt, &ms->cand,
                        &ms->tmp64, &ms->cdist, &ms->ctan, &ms->cflags, &ms->nbr_cnt, &ms->off, &ms->nbr, &ms->dist,
                        &ms->tan, &ms->flags, &ms->F, &ms->E, &ms->disp, &ms->wflags, &ms->step_dev,
-                       &ms->fire, &ms->fstart, &ms->ffirst, &ms->ftgt, &ms->fcount, &ms->face_nx, &ms->bary_nx,
+                       &ms->fire, &ms->fstart, &ms->ffirst, &ms->ftgt, &ms->fcount, &ms->forder, &ms->face_nx, &ms->bary_nx,
                        &ms->vel_nx})
             release(*b);
         for (void *p : {(void *)ms->face, (void *)ms->bary, (void *)ms->vel, (void *)ms->xyz})

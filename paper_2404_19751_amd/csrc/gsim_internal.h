@@ -193,9 +193,10 @@ struct SurfDesc {
     double *cdist, *ctan;
     uint8_t *cflags;
     double cutoff, cut2;
-    // particles by face (all-pairs target lookup): ftgt[fstart[f] .. fstart[f+1])
-    // (ffirst[f]: fstart[f], or -1 for a face without particles)
+    // particles by face (all-pairs target lookup): ftgt[fstart[f] .. fstart[f+1]),
+    // ascending (ffirst[f]: fstart[f], or -1 for a face without particles)
     int32_t *fstart, *ffirst, *fcount;  // (fcount: zeros between two sorts)
+    int32_t *forder;                    // the particles by face in any order within one
     struct FaceTarget *ftgt;
     // potential and integrator of the fused update
     int32_t pkind, ikind;
@@ -332,8 +333,8 @@ hipError_t launch_bend_init(char *roots, int nslots, int64_t rstride, int rcap, 
 // resident wavefronts per compute unit (0 on error)
 int geodesic_all_waves_per_cu(int lds_stack_kb, bool fp32, bool near, int team);
 size_t geodesic_all_lds_bytes(int lds_stack_kb, bool fp32, bool near);
-// The particles of every surface of a batch by face (counting sort): fstart,
-// ffirst, ftgt. fb: blocks of kFaceBlock faces per surface; part: one entry
+// The particles of every surface of a batch by face (counting sort), ascending
+// within a face: fstart, ffirst, ftgt. fb: blocks of kFaceBlock faces per surface; part: one entry
 // per block. The counts start from zeros and are zeros again afterwards. The
 // first kernel also starts a pass (work counters; with advance, the step
 // counters).

@@ -532,9 +532,15 @@ __global__ void k_fill_u64(unsigned long long *p, int64_t n, unsigned long long 
 }
 
 // ------------------------------------------------------------ particles by face
-// Four launches for a whole batch: counts, block totals, starts (each block
-// adds the totals of its surface's blocks before it), scatter. The scatter
-// takes the counts back down to zero, so none of them clears anything.
+// Five launches for a whole batch: counts, block totals, starts (each block
+// adds the totals of its surface's blocks before it), scatter, records. The
+// scatter takes the counts back down to zero, so none of them clears anything.
+// It fills a face's places in the order in which its atomics arrive, which
+// differs from run to run; the records are written in particle order, because
+// the order in which a near pass offers a face's targets decides which of two
+// equally long paths gives the tangent, and calls repeat bit for bit. (Counting
+// the smaller particles of a face costs as many reads as it has pairs, from
+// cache: 4.8 us for 8192 particles of 4648 faces.)
 __global__ void k_face_count(const SurfDesc *__restrict__ desc, BatchIdx bi, int32_t *__restrict__ work, int advance) {
     if (blockIdx.x == 0) {
         if (threadIdx.x < kWorkChunks) work[threadIdx.x * kWorkStride] = 0;
@@ -580,9 +586,20 @@ __global__ void k_face_scatter(const SurfDesc *__restrict__ desc, BatchIdx bi) {
     const int si = batch_surface(bi, g);
     const SurfDesc &sd = desc[si];
     const int i = g - bi.begin[si], f = sd.face[i];
+    sd.forder[sd.fstart[f] + atomicSub(&sd.fcount[f], 1) - 1] = i;
+}
+__global__ void k_face_records(const SurfDesc *__restrict__ desc, BatchIdx bi) {
+    const int g = blockIdx.x * blockDim.x + threadIdx.x;
+    if (g >= bi.begin[bi.nsurf]) return;
+    const int si = batch_surface(bi, g);
+    const SurfDesc &sd = desc[si];
+    const int32_t *const order = sd.forder;
+    const int i = order[g - bi.begin[si]], f = sd.face[i];
     const int64_t b = 3 * (int64_t)i;
-    const int pos = sd.fstart[f] + atomicSub(&sd.fcount[f], 1) - 1;
-    sd.ftgt[pos] = FaceTarget{{sd.bary[b], sd.bary[b + 1], sd.bary[b + 2]}, i, pos + 1 < sd.fstart[f + 1] ? 1 : 0};
+    const int a = sd.fstart[f], e = sd.fstart[f + 1];
+    int pos = a;
+    for (int q = a; q < e; ++q) pos += order[q] < i;
+    sd.ftgt[pos] = FaceTarget{{sd.bary[b], sd.bary[b + 1], sd.bary[b + 2]}, i, pos + 1 < e ? 1 : 0};
 }
 __global__ void k_identity_rows(int n, int cap, int32_t *__restrict__ cand_cnt, int32_t *__restrict__ cand) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -817,6 +834,7 @@ hipError_t launch_face_sort(const SurfDesc *desc, const BatchIdx &bi, const Batc
     hipLaunchKernelGGL(k_face_partials, dim3(nb), dim3(kFaceBlock), 0, s, desc, fb, part);
     hipLaunchKernelGGL(k_face_starts, dim3(nb), dim3(kFaceBlock), 0, s, desc, fb, part);
     hipLaunchKernelGGL(k_face_scatter, dim3(nblocks(n)), dim3(kBlock), 0, s, desc, bi);
+    hipLaunchKernelGGL(k_face_records, dim3(nblocks(n)), dim3(kBlock), 0, s, desc, bi);
     return hipGetLastError();
 }
 hipError_t launch_identity_rows(int n, int cap, int32_t *cand_cnt, int32_t *cand, hipStream_t s) {
