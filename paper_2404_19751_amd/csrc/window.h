@@ -194,7 +194,7 @@ struct BendLds {
     int32_t sface[8];  // the faces of the wavefront's sources (cutoff kernel)
     int32_t sel[kLaunchChunk];       // bend vertices of the chunk
     int32_t pref[kLaunchChunk + 1];  // prefix sums of their fan sizes
-    uint8_t win[256];                // claim
+    uint8_t win[128];                // claim
 };
 
 // Updates of a table by many lanes at once run in rounds: each lane still to
@@ -204,7 +204,9 @@ struct BendLds {
 // entry's) in the next round. Two LDS accesses a round, however many lanes
 // take part; comparing the lanes' entries one by one had cost 50 cycles a
 // lane. claim returns the winner (the lane itself when it has nothing to do).
-constexpr int kWinners = 256;
+// (as many as the cutoff kernel has target slots; 256 left room for seven of its
+// wavefronts on a compute unit instead of eight)
+constexpr int kWinners = 128;
 __device__ inline int claim(uint8_t *win, bool todo, int e) {
     if (todo) win[e & (kWinners - 1)] = (uint8_t)lane_id();
     lane_step_barrier();
