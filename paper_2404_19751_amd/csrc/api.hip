@@ -615,6 +615,7 @@ struct Batch {
     int32_t rcap = 0;     // its capacity (bend vertices)
     bool small = true;  // every surface bins in one workgroup
     bool fused = false; // time steps move the particles inside the cutoff kernel
+    AllPass pass = kWholeMesh;  // what kind of pass the whole-mesh kernel makes
     bool near = false;  // a cutoff pass by whole-mesh propagation (many targets within the cutoff)
     BatchIdx face_blk{};  // blocks of kFaceBlock faces per surface (particles-by-face index)
     int team = 1;       // whole-mesh passes: wavefronts per source
@@ -681,6 +682,23 @@ gsim_status prepare_batch(gsim_ctx *c, Batch &B) {
         B.near |= B.desc[i].cap > kCandCap || mean + 3.0 * std::sqrt(mean) > 0.5 * kCandCap;
     }
     const bool by_face = B.all || B.near;
+    // without the domination tests where they find nothing: on surfaces without
+    // bend vertices, while a disc of the cutoff covers less than half the
+    // surface and does not reach round it (area over the bounding box's
+    // diagonal: the girth of a long surface). There they drop at most one
+    // window in fifty, and everything that serves bend vertices goes with
+    // them. 500 sources of 110 targets on the sphere of 20480 faces: 2.31 ms a
+    // step by depth-first propagation without per-target tests (the cutoff
+    // kernel's way before near passes), 3.30 by the near pass with the tests,
+    // 2.03 without; 2000 of 800 targets 17.9, 10.6 and 7.5; FP32-mixed 500 of
+    // 110 4.08, 6.21 and 3.50.
+    B.pass = B.near ? kNearPlain : kWholeMesh;
+    for (int i = 0; i < ns && B.pass == kNearPlain; ++i) {
+        const DevMesh &m = B.mem[i].ms->dm;
+        const double cut = B.mem[i].cutoff, area = surface_area(B.mem[i].ms);
+        const double diag = std::hypot(m.bbmax[0] - m.bbmin[0], m.bbmax[1] - m.bbmin[1], m.bbmax[2] - m.bbmin[2]);
+        if (m.n_pseudo > 0 || M_PI * cut * cut > 0.5 * area || 2.0 * cut * diag > area) B.pass = kNearPass;
+    }
     B.face_blk.nsurf = ns;
     int nfb = 0;
     for (int i = 0; i < ns; ++i) {
@@ -725,14 +743,14 @@ gsim_status prepare_batch(gsim_ctx *c, Batch &B) {
     for (int i = 0; i < ns; ++i) teams = teams && !B.mem[i].integ;
     for (int t = 8; t > 1 && B.team == 1 && teams; t /= 2) {
         const int64_t waves = (int64_t)total * t;
-        if (waves > std::min(c->cus * geodesic_all_waves_per_cu(c->lds_stack_kb, fp32, false, t), c->max_slots)) continue;
+        if (waves > std::min(c->cus * geodesic_all_waves_per_cu(c->lds_stack_kb, fp32, kWholeMesh, t), c->max_slots)) continue;
         if (waves * all_slot > c->stack_budget || waves * bend_table_bytes(B.rcap) > c->table_budget) continue;
         size_t left = 0, card = 0;
         const double more = waves * all_slot - (double)(c->stack.bytes + c->vdist.bytes + c->split.bytes + c->roots.bytes);
         if (more > 0.0 && (hipMemGetInfo(&left, &card) != hipSuccess || more > 0.5 * (double)left)) continue;
         B.team = t;
     }
-    const int per_cu = std::max(1, by_face ? geodesic_all_waves_per_cu(c->lds_stack_kb, fp32, B.near, B.team)
+    const int per_cu = std::max(1, by_face ? geodesic_all_waves_per_cu(c->lds_stack_kb, fp32, B.pass, B.team)
                                            : geodesic_blocks_per_cu(c->lds_stack_kb, fp32));
     // several sources per wavefront (the largest group of at most
     // group_sources that still gives every resident wavefront a full one):
@@ -811,7 +829,7 @@ gsim_status prepare_batch(gsim_ctx *c, Batch &B) {
             // let one workgroup fewer in, and the rest ran as a second round.
             // 1030 sources on the sphere of 20480 faces: 143 ms so, 91 now;
             // twenty steps of 760 on the bumpy sphere 2.67 and 2.11 ms)
-            const size_t stat = by_face ? geodesic_all_lds_bytes(c->lds_stack_kb, fp32, B.near)
+            const size_t stat = by_face ? geodesic_all_lds_bytes(c->lds_stack_kb, fp32, B.pass)
                                         : geodesic_lds_bytes(c->lds_stack_kb, fp32, B.group);
             const size_t each = (size_t)c->lds_cu / (size_t)want / kLdsBlock * kLdsBlock;
             if (std::min(each, (size_t)c->max_lds) > stat) B.shape.pad_lds = (int32_t)(std::min(each, (size_t)c->max_lds) - stat);
@@ -883,7 +901,7 @@ gsim_status geodesic_pass(gsim_ctx *c, Batch &B, bool advance, bool commit_in = 
         HIPCHK(c, launch_geodesic_all(desc_dev(c), B.bi, gp, B.shape, P<char>(c->stack), P<unsigned long long>(v),
                                       B.vstride, P<char>(c->roots), B.rstride, B.rcap, B.near ? c->near_t.p : c->ttab.p,
                                       B.tcap, B.hstride ? P<unsigned long long>(h) : nullptr, B.hstride,
-                                      B.near ? P<uint32_t>(c->near_e) : nullptr, B.team,
+                                      B.near ? P<uint32_t>(c->near_e) : nullptr, B.pass, B.team,
                                       B.team > 1 ? P<unsigned long long>(c->best) : nullptr, P<int32_t>(c->work),
                                       P<Counters>(c->ctr), c->prec == GSIM_FP32_MIXED, s, st.a, st.b));
         c->passes++;
@@ -1001,6 +1019,7 @@ std::string graph_key(gsim_ctx *c, const Batch &B, int steps) {
     put(&B.small, sizeof(B.small));
     put(&B.fused, sizeof(B.fused));
     put(&B.near, sizeof(B.near));
+    put(&B.pass, sizeof(B.pass));
     put(&B.team, sizeof(B.team));
     put(&B.face_blk, sizeof(B.face_blk));
     put(&B.group, sizeof(B.group));

@@ -295,11 +295,14 @@ hipError_t launch_candidates(const SurfDesc *desc, const BatchIdx &bi, int group
 // by launch_near_init and kept by the passes themselves. team = 2, 4 or 8:
 // that many wavefronts share each source (FP64 whole-mesh passes; shape.nslots
 // counts wavefronts), with best distances of tcap targets per team in best.
+// kNearPlain: a near pass over surfaces without bend vertices, without the
+// domination tests.
+enum AllPass { kWholeMesh, kNearPass, kNearPlain };
 hipError_t launch_geodesic_all(const SurfDesc *desc, const BatchIdx &bi, const GeoParams &gp, const GeoShape &shape,
                                char *stack_mem, unsigned long long *vdist, int64_t vstride, char *roots, int64_t rstride,
                                int rcap, void *ttab, int tcap, unsigned long long *split, int64_t hstride,
-                               uint32_t *epoch, int team, unsigned long long *best, int32_t *work_ctr, Counters *ctr,
-                               bool fp32, hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+                               uint32_t *epoch, AllPass pass, int team, unsigned long long *best, int32_t *work_ctr,
+                               Counters *ctr, bool fp32, hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 int64_t near_area_bytes(int tcap);
 hipError_t launch_near_init(char *area, int nslots, int tcap, unsigned long long *vdist, int64_t vstride,
                             unsigned long long *split, int64_t hstride, uint32_t *epoch, hipStream_t s);
@@ -331,8 +334,8 @@ __host__ __device__ inline int64_t bend_table_bytes(int rcap) {
 // empty again after each source.
 hipError_t launch_bend_init(char *roots, int nslots, int64_t rstride, int rcap, hipStream_t s);
 // resident wavefronts per compute unit (0 on error)
-int geodesic_all_waves_per_cu(int lds_stack_kb, bool fp32, bool near, int team);
-size_t geodesic_all_lds_bytes(int lds_stack_kb, bool fp32, bool near);
+int geodesic_all_waves_per_cu(int lds_stack_kb, bool fp32, AllPass pass, int team);
+size_t geodesic_all_lds_bytes(int lds_stack_kb, bool fp32, AllPass pass);
 // The particles of every surface of a batch by face (counting sort), ascending
 // within a face: fstart, ffirst, ftgt. fb: blocks of kFaceBlock faces per surface; part: one entry
 // per block. The counts start from zeros and are zeros again afterwards. The

@@ -29,7 +29,10 @@
 // no table is cleared per source: vertex and half-edge entries carry the
 // source's epoch, the states of the targets reached are reset one by one. A
 // face's several targets are offered to all lanes' windows side by side
-// (offer_pairs). With hundreds of targets the cutoff kernel's per-target
+// (offer_pairs). On surfaces without bend vertices and cutoffs that stay on one
+// side of them (kDom false), the domination tests, the rounds that order them
+// and all that serves bend vertices are left out: there is next to nothing to
+// dominate (the rule and its times stand where the pass is prepared). With hundreds of targets the cutoff kernel's per-target
 // pruning keeps nearly every window; domination keeps 700 of its 2670 a
 // source on the benchmark torus at 232 targets: 8192 sources 5.95 -> 1.34 ms
 // a pass, at 58 targets 0.94 -> 0.47 ms.
@@ -509,10 +512,18 @@ template <class Cand>
 __device__ inline void offer_pairs(const FaceTarget *ftgt, AllLds &L, const TargetTable<true> &td, const ACtx &C, int cnt,
                                    int q0, int src, const Cand &cand) {
     const int lane = lane_id();
+    const uint64_t any = __ballot(cnt > 0);
+    if (!any) return;
+    // places of the pairs: a scan, which a count of lanes replaces where no
+    // face has more than one target
     int inc = cnt;
-    for (int o = 1; o < kWave; o <<= 1) {
-        const int y = __shfl_up(inc, o);
-        if (lane >= o) inc += y;
+    if (__ballot(cnt > 1)) {
+        for (int o = 1; o < kWave; o <<= 1) {
+            const int y = __shfl_up(inc, o);
+            if (lane >= o) inc += y;
+        }
+    } else {
+        inc = __popcll(any & (lanemask_lt() << 1 | 1));
     }
     const int excl = inc - cnt, total = __builtin_amdgcn_readlane(inc, kWave - 1);
     for (int base = 0; base < total; base += kWave) {
@@ -586,13 +597,13 @@ __device__ inline void query_face(const FaceTarget *ftgt, AllLds &L, const Targe
 }
 
 // The same in near passes, cnt targets from place q on.
-template <typename R>
+template <bool kRoots, typename R>
 __device__ inline void query_pairs(const FaceTarget *ftgt, AllLds &L, const TargetTable<true> &td, const ACtx &C, int cnt,
                                    int q, int src, int k, const He<R> &H, const Win<R> &w, double rtx, double rty,
                                    double rD2) {
     offer_pairs(ftgt, L, td, C, cnt, q, src,
                 [&](int own, const FaceTarget &t, double &d, double &tx, double &ty, double &alt) {
-                    const int ok_ = __shfl(k, own), root = __shfl(w.root, own);
+                    const int ok_ = __shfl(k, own), root = kRoots ? __shfl(w.root, own) : -1;
                     const R hL = __shfl(H.L, own), hcx = __shfl(H.cx, own), hcy = __shfl(H.cy, own);
                     const R px = __shfl(w.px, own), py = __shfl(w.py, own);
                     const R b0 = __shfl(w.b0, own), b1 = __shfl(w.b1, own);
@@ -601,7 +612,12 @@ __device__ inline void query_pairs(const FaceTarget *ftgt, AllLds &L, const Targ
                     const R xq = px + (qx - px) * (-py) / (qy - py), sl = (R)C.tol * hL;
                     const R dx = qx - px, dy = qy - py, l = sqrt(dx * dx + dy * dy);
                     const R c = __shfl(w.c, own), s = __shfl(w.s, own);
-                    const double ux = __shfl(rtx, own), uy = __shfl(rty, own), u2 = __shfl(rD2, own);
+                    double ux = 0.0, uy = 0.0, u2 = INFINITY;
+                    if constexpr (kRoots) {
+                        ux = __shfl(rtx, own);
+                        uy = __shfl(rty, own);
+                        u2 = __shfl(rD2, own);
+                    }
                     d = (double)__shfl(w.sg, own) + (double)l;
                     const R ex = dx / l, ey = dy / l;
                     tx = root < 0 ? (double)(c * ex - s * ey) : ux;
@@ -793,7 +809,7 @@ __device__ bool launch_roots(const SurfDesc &sd, AllLds &L, const BendTable &G, 
 // FP32 result lies within the guard band around the cutoff (the caller then
 // recomputes the source in FP64; `guard` marks that recompute). Inlined:
 // as a call, the FP32 kernel spills around it and holds one wave per SIMD.
-template <typename R, bool kNear, int kTeam>
+template <typename R, bool kNear, int kTeam, bool kDom>
 __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, const SurfDesc &sd, AllLds &L,
                                                               const TargetTable<kNear> &td, unsigned char *stk,
                                                               int stk_bytes, unsigned char *later, SortLds *sl, TeamLds &team, int member, int src, bool guard,
@@ -821,7 +837,7 @@ __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, 
     C.dom_rel = fp32 ? a.gp.dom_rel32 : a.gp.dom_rel;
     // rounds: wide ones mean fewer round changes, but on a surface with bend
     // vertices they launch vertices before their distances settle
-    C.bucket = uniform(a.gp.bucket > 0.0 ? a.gp.bucket : (M.n_pseudo > 0 ? 4.0 : 16.0) * M.max_edge);
+    C.bucket = uniform(!kDom ? INFINITY : a.gp.bucket > 0.0 ? a.gp.bucket : (M.n_pseudo > 0 ? 4.0 : 16.0) * M.max_edge);
     C.cutoff = uniform(sd.cutoff);
     if constexpr (kNear) {
         // every entry of earlier sources is void; once the epochs are used
@@ -841,7 +857,7 @@ __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, 
     // it, 112k with it); on a convex sphere one window in a hundred covers a
     // vertex, and the entries would cost more than the 1 % of windows they
     // save
-    unsigned long long *Hv = !fp32 && M.n_pseudo > 0 && a.split ? a.split + (int64_t)shared * a.hstride : nullptr;
+    unsigned long long *Hv = kDom && !fp32 && M.n_pseudo > 0 && a.split ? a.split + (int64_t)shared * a.hstride : nullptr;
     C.split_rel = fmax(1e-6, 64.0 * C.tie_rel);
     const BendTable G = bend_table(a.roots, a.rstride, slot, a.rcap);
     RoundStack<R> S;
@@ -993,7 +1009,7 @@ __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, 
                 }
             }
         }
-        bend_update(G, L.B, C.rc, rv >= 0, rv, rd, rtx, rty, INFINITY);
+        if constexpr (kDom) bend_update(G, L.B, C.rc, rv >= 0, rv, rd, rtx, rty, INFINITY);
         // on-edge sources: targets and third vertex of the face across
         for (int k = 0; k < 3; ++k) {
             const bool on = sb[(k + 2) % 3] <= 0.0 && he[3 * fs + k].twin >= 0;
@@ -1035,7 +1051,7 @@ __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, 
             const int opp = Rt.opp_flags >> 1;
             if (lane == 0) Dv.put(opp, d);
             const int eo = lane == 0 ? M.pidx[opp] : -1;
-            bend_update(G, L.B, C.rc, eo >= 0, eo, d, (c * dx - s * dy) / d, (s * dx + c * dy) / d, INFINITY);
+            if constexpr (kDom) bend_update(G, L.B, C.rc, eo >= 0, eo, d, (c * dx - s * dy) / d, (s * dx + c * dy) / d, INFINITY);
         }
         S.push(want, false, w, overflow);
         S.push(wantA, ka >= T, wa, overflow);
@@ -1054,7 +1070,7 @@ __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, 
         if (overflow) break;
         depth = max(depth, S.lsp + S.gsp + S.dsp + S.dl);
         bool busy = S.refill(have, w);
-        if (!busy && L.B.npend > 0) {
+        if (kDom && !busy && L.B.npend > 0) {
             if (prof) L.clk[2] -= clock64();
             if (launch_roots<R, kNear, kTeam>(sd, L, G, td, Dv, C, S, T, src, st)) overflow = true;
             if (prof) L.clk[2] += clock64();
@@ -1112,7 +1128,7 @@ __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, 
             }
             if (Hv) hw = Hv[w.he];
             double rD = 0.0, rL = INFINITY;
-            if (w.root >= 0) {
+            if (kDom && w.root >= 0) {
                 rD = G.rD[w.root];
                 rL = G.rL[w.root];
                 wtx = G.rtx[w.root];
@@ -1139,14 +1155,16 @@ __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, 
         if (act) {
             // a lane that goes on with a child has the distances of the
             // half-edge's ends from the parent's face
-            if (!(DA < INFINITY)) DA = Dv[vA];
-            if (!(DB < INFINITY)) DB = Dv[vB];
-            DC = Dv[H.opp];
+            if constexpr (kDom) {
+                if (!(DA < INFINITY)) DA = Dv[vA];
+                if (!(DB < INFINITY)) DB = Dv[vB];
+                DC = Dv[H.opp];
+            }
             if (!kNear && q0 >= 0) {
                 t0 = ftgt[q0];
                 c0 = td[q0];
             }
-            if (H.pseudo) eo = pidx[H.opp];
+            if (kDom && H.pseudo) eo = pidx[H.opp];
             const double px = w.px, py = w.py, sg = w.sg;
             txc = px + ((double)H.cx - px) * (-py) / ((double)H.cy - py);
             const double sl = C.tol * (double)H.L;
@@ -1165,26 +1183,28 @@ __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, 
             // vertices of the face reached through this window: the table's
             // values are combined with this window's own paths, which then go
             // to the table (compared in squares first: few are shorter)
-            const double rA = px * px + py * py, rB = ((double)H.L - px) * ((double)H.L - px) + py * py;
-            if ((double)w.b0 <= 0.0 && Dv.shorter(rA, DA, sg)) {
-                DA = fmin(DA, sg + sqrt(rA));
-                Dv.put(vA, DA);
-            }
-            if ((double)w.b1 >= (double)H.L && Dv.shorter(rB, DB, sg)) {
-                DB = fmin(DB, sg + sqrt(rB));
-                Dv.put(vB, DB);
-            }
-            if (cin) {
-                const double dx = (double)H.cx - px, dy = (double)H.cy - py;
-                const double rC = dx * dx + dy * dy;
-                if (!Hv) dcv = sg + sqrt(rC);
-                if (Dv.shorter(rC, DC, sg)) {
-                    DC = fmin(DC, dcv);
-                    Dv.put(H.opp, DC);
+            if constexpr (kDom) {
+                const double rA = px * px + py * py, rB = ((double)H.L - px) * ((double)H.L - px) + py * py;
+                if ((double)w.b0 <= 0.0 && Dv.shorter(rA, DA, sg)) {
+                    DA = fmin(DA, sg + sqrt(rA));
+                    Dv.put(vA, DA);
+                }
+                if ((double)w.b1 >= (double)H.L && Dv.shorter(rB, DB, sg)) {
+                    DB = fmin(DB, sg + sqrt(rB));
+                    Dv.put(vB, DB);
+                }
+                if (cin) {
+                    const double dx = (double)H.cx - px, dy = (double)H.cy - py;
+                    const double rC = dx * dx + dy * dy;
+                    if (!Hv) dcv = sg + sqrt(rC);
+                    if (Dv.shorter(rC, DC, sg)) {
+                        DC = fmin(DC, dcv);
+                        Dv.put(H.opp, DC);
+                    }
                 }
             }
         }
-        if constexpr (kNear) query_pairs(ftgt, L, td, C, qcnt, q0, src, k, H, w, wtx, wty, wD2);
+        if constexpr (kNear) query_pairs<kDom>(ftgt, L, td, C, qcnt, q0, src, k, H, w, wtx, wty, wD2);
         else query_face(ftgt, L, td, C, q0, src, k, H, w, wtx, wty, wD2, t0, c0);
         // third vertex as a bend vertex: its entry is loaded here and updated
         // after the children
@@ -1219,8 +1239,9 @@ __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, 
             const double ox = (double)ax * rx + (double)ay * ry, oy = (double)ax * ry - (double)ay * rx;
             const double cpx = c.px, cpy = c.py, sg = c.sg;
             double r0 = (x0 - cpx) * (x0 - cpx) + cpy * cpy, r1 = (x1 - cpx) * (x1 - cpx) + cpy * cpy;
-            if (vertex_trim(cpx, cpy, sg, Lc, DS, DE, C.dom_rel, x0, x1, r0, r1) &&
-                !opposite_dominates(ox, oy, DO, sg, C.dom_rel, x0, x1, r0, r1)) {
+            if (kDom ? vertex_trim(cpx, cpy, sg, Lc, DS, DE, C.dom_rel, x0, x1, r0, r1) &&
+                           !opposite_dominates(ox, oy, DO, sg, C.dom_rel, x0, x1, r0, r1)
+                     : x1 - x0 > 1e-12 * Lc) {
                 c.b0 = (R)x0;
                 c.b1 = (R)x1;
                 // the child's key (its smallest distance) against the bound
@@ -1236,7 +1257,7 @@ __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, 
             far_ends(H, w, txc, false, xa, xb);
             child(false, xa, xb, c2, h2, l2);
         }
-        {
+        if constexpr (kDom) {
             double tx = wtx, ty = wty, alt = INFINITY;
             if (ok3) {
                 if (w.root < 0) {
@@ -1380,7 +1401,7 @@ __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, 
     st.pruned += pruned;
     st.overflow |= ovf;
     st.depth = max(st.depth, depth);
-    bend_reset(G, L.B);
+    if constexpr (kDom) bend_reset(G, L.B);
     if constexpr (kTeam > 1) {
         __syncthreads();  // the row is written, and the tables are free again
     }
@@ -1389,6 +1410,8 @@ __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, 
 
 // kNear: a pass with a cutoff whose rows hold only the targets within it
 // (whole-mesh passes: a row holds every particle).
+// kDom: with domination tests and bend vertices (false: near passes over
+// surfaces without bend vertices).
 // kTeam wavefronts per workgroup share one source (whole-mesh passes with few
 // sources, whose one wavefront each would leave most of the device idle): each
 // starts from its share of the source's angles and propagates on its own, with
@@ -1402,8 +1425,9 @@ __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, 
 // bend vertices that tie to rounding may give results that differ in the last
 // bits (1e-15 relative): FP64 only, and not for time steps, whose states repeat
 // bit for bit.
-template <bool kMixed, int kStk, bool kNear, int kTeam>
+template <bool kMixed, int kStk, bool kNear, int kTeam, bool kDom>
 __global__ __launch_bounds__(kWave *kTeam, 2) void k_geodesic_all(AllArgs a) {
+    static_assert(kDom || kNear, "without domination: near passes only");
     static_assert(kTeam == 1 || (!kNear && !kMixed), "teams: whole-mesh passes, FP64");
     __shared__ AllLds Ls[kTeam];
     __shared__ typename SortOf<kNear>::T sorted;
@@ -1462,11 +1486,11 @@ __global__ __launch_bounds__(kWave *kTeam, 2) void k_geodesic_all(AllArgs a) {
         if (!kNear && threadIdx.x == 0) sd.cand_cnt[src] = sd.n;
         st.overflow = false;
         bool again = !kMixed;
-        if (kMixed) again = run_all<float, kNear, kTeam>(a, sd, L, td, stk, kStk, later, sl, team, member, src, false, epoch, st);
+        if (kMixed) again = run_all<float, kNear, kTeam, kDom>(a, sd, L, td, stk, kStk, later, sl, team, member, src, false, epoch, st);
         if (again) {
             // FP64 (the plain path, or the recompute of an FP32 source whose
             // results come too close to the cutoff to decide in FP32)
-            run_all<double, kNear, kTeam>(a, sd, L, td, stk, kStk, later, sl, team, member, src, kMixed, epoch, st);
+            run_all<double, kNear, kTeam, kDom>(a, sd, L, td, stk, kStk, later, sl, team, member, src, kMixed, epoch, st);
             st.guards += kMixed && member == 0 ? 1 : 0;
         }
         if (st.overflow && member == 0) ++c_limited;
@@ -1491,20 +1515,21 @@ __global__ __launch_bounds__(kWave *kTeam, 2) void k_geodesic_all(AllArgs a) {
 }
 
 using AllKernel = void (*)(AllArgs);
-template <bool kMixed, bool kNear>
+template <bool kMixed, bool kNear, bool kDom>
 AllKernel kernel_of(int kb, int team) {
     if constexpr (!kNear && !kMixed) {
-        if (team == 8) return &k_geodesic_all<kMixed, 4096, kNear, 8>;
-        if (team == 4) return &k_geodesic_all<kMixed, 4096, kNear, 4>;
-        if (team == 2) return &k_geodesic_all<kMixed, 4096, kNear, 2>;
+        if (team == 8) return &k_geodesic_all<kMixed, 4096, kNear, 8, kDom>;
+        if (team == 4) return &k_geodesic_all<kMixed, 4096, kNear, 4, kDom>;
+        if (team == 2) return &k_geodesic_all<kMixed, 4096, kNear, 2, kDom>;
     }
-    if (kb <= 4) return &k_geodesic_all<kMixed, 4096, kNear, 1>;
-    if (kb <= 8) return &k_geodesic_all<kMixed, 8192, kNear, 1>;
-    return &k_geodesic_all<kMixed, 16384, kNear, 1>;
+    if (kb <= 4) return &k_geodesic_all<kMixed, 4096, kNear, 1, kDom>;
+    if (kb <= 8) return &k_geodesic_all<kMixed, 8192, kNear, 1, kDom>;
+    return &k_geodesic_all<kMixed, 16384, kNear, 1, kDom>;
 }
-AllKernel kernel_for(int kb, bool fp32, bool near, int team) {
-    if (near) return fp32 ? kernel_of<true, true>(kb, team) : kernel_of<false, true>(kb, team);
-    return fp32 ? kernel_of<true, false>(kb, team) : kernel_of<false, false>(kb, team);
+AllKernel kernel_for(int kb, bool fp32, AllPass pass, int team) {
+    if (pass == kNearPlain) return fp32 ? kernel_of<true, true, false>(kb, team) : kernel_of<false, true, false>(kb, team);
+    if (pass == kNearPass) return fp32 ? kernel_of<true, true, true>(kb, team) : kernel_of<false, true, true>(kb, team);
+    return fp32 ? kernel_of<true, false, true>(kb, team) : kernel_of<false, false, true>(kb, team);
 }
 
 // Byte offsets of one wavefront's near-pass area: target states, reached
@@ -1537,9 +1562,10 @@ hipError_t launch_near_init(char *area, int nslots, int tcap, unsigned long long
 hipError_t launch_geodesic_all(const SurfDesc *desc, const BatchIdx &bi, const GeoParams &gp, const GeoShape &shape,
                                char *stack_mem, unsigned long long *vdist, int64_t vstride, char *roots, int64_t rstride,
                                int rcap, void *ttab, int tcap, unsigned long long *split, int64_t hstride,
-                               uint32_t *epoch, int team, unsigned long long *best, int32_t *work_ctr, Counters *ctr,
-                               bool fp32, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
-    const bool near = epoch != nullptr;
+                               uint32_t *epoch, AllPass pass, int team, unsigned long long *best, int32_t *work_ctr,
+                               Counters *ctr, bool fp32, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+    const bool near = pass != kWholeMesh;
+    if (near && !epoch) return hipErrorInvalidValue;
     AllArgs a;
     a.sd = desc;
     a.bi = bi;
@@ -1565,7 +1591,7 @@ hipError_t launch_geodesic_all(const SurfDesc *desc, const BatchIdx &bi, const G
     if (shape.nslots < 1 || bi.begin[bi.nsurf] < 1) return hipSuccess;
     if (team < 1 || shape.nslots % team || (team > 1 && (near || fp32 || !best))) return hipErrorInvalidValue;
     a.best = best;
-    const AllKernel f = kernel_for(shape.lds_stack_kb, fp32, near, team);
+    const AllKernel f = kernel_for(shape.lds_stack_kb, fp32, pass, team);
     const dim3 grid(shape.nslots / team), block(kWave * team);
     const uint32_t pad = shape.pad_lds > 0 ? (uint32_t)shape.pad_lds : 0;
     if (ev0 || ev1) hipExtLaunchKernelGGL(f, grid, block, pad, s, ev0, ev1, 0, a);
@@ -1573,15 +1599,15 @@ hipError_t launch_geodesic_all(const SurfDesc *desc, const BatchIdx &bi, const G
     return hipGetLastError();
 }
 
-size_t geodesic_all_lds_bytes(int lds_stack_kb, bool fp32, bool near) {
+size_t geodesic_all_lds_bytes(int lds_stack_kb, bool fp32, AllPass pass) {
     hipFuncAttributes at{};
-    if (hipFuncGetAttributes(&at, (const void *)kernel_for(lds_stack_kb, fp32, near, 1)) != hipSuccess) return 65536;
+    if (hipFuncGetAttributes(&at, (const void *)kernel_for(lds_stack_kb, fp32, pass, 1)) != hipSuccess) return 65536;
     return at.sharedSizeBytes;
 }
 
-int geodesic_all_waves_per_cu(int lds_stack_kb, bool fp32, bool near, int team) {
+int geodesic_all_waves_per_cu(int lds_stack_kb, bool fp32, AllPass pass, int team) {
     int nb = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, (const void *)kernel_for(lds_stack_kb, fp32, near, team),
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, (const void *)kernel_for(lds_stack_kb, fp32, pass, team),
                                                      kWave * team, 0) != hipSuccess)
         return 0;
     return nb * team;
