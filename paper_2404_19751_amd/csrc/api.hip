@@ -253,6 +253,7 @@ hipError_t ensure(Buf &b, size_t bytes) {
     size_t want = std::max<size_t>(bytes + bytes / 4, 256);
     hipError_t e = hipMalloc(&b.p, want);
     if (e == hipSuccess) b.bytes = want;
+    else (void)hipGetLastError();  // reported here: the next launch's check must not find it again
     return e;
 }
 void release(Buf &b) {
