@@ -81,9 +81,8 @@ struct gsim_ctx {
     std::vector<MeshState *> meshes;
     Buf stack, work, ctr, wpart, scan_scratch, sum_scratch, prof, desc, vdist, ttab, roots, partials, vbits, split, best;
     // near passes: target areas, vertex and half-edge entries and epochs of the
-    // resident wavefronts, and the layout they were last prepared for
+    // resident wavefronts, and the layout and number they were last prepared for
     Buf near_t, near_v, near_h, near_e;
-    void *near_p[4] = {};
     int64_t near_layout[3] = {};  // tcap, vstride, hstride
     int near_slots = 0;
     Buf bad;                  // device counts of a state check or of Voronoi limits: zeros between calls
@@ -119,7 +118,6 @@ struct gsim_ctx {
     int group_sources = 4;  // FP64 persistent passes: sources per wavefront, at most (1, 2 or 4)
     bool fuse_update = true;  // time steps move each particle inside the cutoff kernel
     // layout the bend-vertex tables were last emptied for
-    void *roots_p = nullptr;
     int64_t roots_stride = 0;
     int32_t roots_rcap = 0, roots_slots = 0;
     int max_lds = 65536;  // LDS bytes one workgroup may use
@@ -839,19 +837,24 @@ gsim_status prepare_batch(gsim_ctx *c, Batch &B) {
     const int cap_rec = B.all ? c->stack_cap_all : c->gp.stack_cap;
     HIPCHK(c, ensure(c->stack, (size_t)std::max(B.nslots, 1) * cap_rec * 64));
     if (B.near) {
-        // prepared once per layout; the passes keep the tables themselves
+        // prepared once per layout; the passes keep the tables themselves.
+        // near_slots, the tables that hold prepared entries, is zero from the
+        // first of these allocations until all is prepared: a new allocation
+        // may come at the address of the one before it, so addresses tell
+        // nothing.
         const int nsl = std::max(B.nslots, 1);
-        HIPCHK(c, ensure(c->near_t, (size_t)nsl * (size_t)near_area_bytes(B.tcap)));
-        HIPCHK(c, ensure(c->near_v, sizeof(unsigned long long) * (size_t)nsl * B.vstride));
-        if (B.hstride) HIPCHK(c, ensure(c->near_h, sizeof(unsigned long long) * (size_t)nsl * B.hstride));
-        HIPCHK(c, ensure(c->near_e, sizeof(uint32_t) * (size_t)(nsl + 1)));
-        void *const p[4] = {c->near_t.p, c->near_v.p, c->near_h.p, c->near_e.p};
         const int64_t lay[3] = {B.tcap, B.vstride, B.hstride};
-        if (std::memcmp(p, c->near_p, sizeof p) != 0 || std::memcmp(lay, c->near_layout, sizeof lay) != 0 ||
-            nsl > c->near_slots) {
+        const size_t need[4] = {(size_t)nsl * (size_t)near_area_bytes(B.tcap), sizeof(unsigned long long) * (size_t)nsl * B.vstride,
+                                sizeof(unsigned long long) * (size_t)nsl * B.hstride, sizeof(uint32_t) * (size_t)(nsl + 1)};
+        Buf *const buf[4] = {&c->near_t, &c->near_v, &c->near_h, &c->near_e};
+        for (int k = 0; k < 4; ++k)
+            if (buf[k]->bytes < need[k]) c->near_slots = 0;
+        if (std::memcmp(lay, c->near_layout, sizeof lay) != 0 || nsl > c->near_slots) {
+            c->near_slots = 0;
+            for (int k = 0; k < 4; ++k)
+                if (need[k]) HIPCHK(c, ensure(*buf[k], need[k]));
             HIPCHK(c, launch_near_init(P<char>(c->near_t), nsl, B.tcap, P<unsigned long long>(c->near_v), B.vstride,
                                        P<unsigned long long>(c->near_h), B.hstride, P<uint32_t>(c->near_e), c->stream));
-            std::memcpy(c->near_p, p, sizeof p);
             std::memcpy(c->near_layout, lay, sizeof lay);
             c->near_slots = nsl;
         }
@@ -865,12 +868,12 @@ gsim_status prepare_batch(gsim_ctx *c, Batch &B) {
     }
     // bend-vertex tables: emptied once here, left empty by the kernels
     const int nsl = std::max(B.nslots, 1);
-    HIPCHK(c, ensure(c->roots, (size_t)nsl * B.rstride));
-    if (c->roots.p != c->roots_p || B.rstride != c->roots_stride || B.rcap != c->roots_rcap ||
+    if (c->roots.bytes < (size_t)nsl * B.rstride || B.rstride != c->roots_stride || B.rcap != c->roots_rcap ||
         nsl > c->roots_slots) {
         if (c->capturing) return fail(c, GSIM_E_STATE, "bend-vertex tables change during graph capture");
+        c->roots_slots = 0;  // as near_slots above
+        HIPCHK(c, ensure(c->roots, (size_t)nsl * B.rstride));
         HIPCHK(c, launch_bend_init(P<char>(c->roots), nsl, B.rstride, B.rcap, c->stream));
-        c->roots_p = c->roots.p;
         c->roots_stride = B.rstride;
         c->roots_rcap = B.rcap;
         c->roots_slots = nsl;
