@@ -733,10 +733,12 @@ gsim_status prepare_batch(gsim_ctx *c, Batch &B) {
     // whole-mesh passes with few sources: the largest team of wavefronts per
     // source with which all sources are still resident at once, within the
     // scratch budget and what the device has left. 100 sources on the torus of
-    // 3456 faces: 11.7 ms alone, 8.5 in twos, 6.1 in fours, 4.5 in eights; at
-    // 900 sources twos still give 50 ms for 82 (sphere of 20480 faces). Not for
-    // time steps, whose states repeat bit for bit (a team's results may differ
-    // in the last bits), nor in FP32-mixed mode, where that could move a flag.
+    // 3456 faces: 11.2 ms alone, 4.3 in eights; 200 on the sphere of 5120 faces
+    // 9.8 and 2.1, 800 in twos 12.0 and 7.9. Results of a team equal one
+    // wavefront's to rounding. Pair and force calls in FP64: time steps keep to
+    // one wavefront, so that a run does not change its last bits with the room
+    // that the device happens to have, and in FP32-mixed mode another order of
+    // paths could move a flag.
     B.team = 1;
     bool teams = B.all && !fp32 && !c->profile_sources;
     for (int i = 0; i < ns; ++i) teams = teams && !B.mem[i].integ;

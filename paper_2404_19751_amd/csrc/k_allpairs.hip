@@ -121,10 +121,11 @@ struct SortLds {
 };
 struct NoSort {};
 
-// A team's wavefronts (one source each workgroup): the source taken, and what
-// any of them met.
+// A team's wavefronts (one source each workgroup): the source taken, what any
+// of them met, and whether any has windows left for the next round (by the
+// round's parity).
 struct TeamLds {
-    int32_t idx, overflow;
+    int32_t idx, overflow, more[2];
 };
 template <bool kNear>
 struct SortOf {
@@ -802,6 +803,37 @@ __device__ bool launch_roots(const SurfDesc &sd, AllLds &L, const BendTable &G, 
     return __ballot(lost) != 0;
 }
 
+// Windows with a larger key than the farthest target's distance (dist(q) of n
+// targets; widened by the tie gap) cannot improve any.
+template <class Dist>
+__device__ inline void key_bound(AllLds &L, const ACtx &C, int n, const Dist &dist) {
+    double mx = 0.0;
+    for (int q = lane_id(); q < n; q += kWave) mx = fmax(mx, dist(q));
+    for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o));
+    if (lane_id() == 0) L.maxb = fmin(L.maxb, mx * (1.0 + C.tie_rel) + 1e-12 * mx);
+}
+
+// An entry that other wavefronts of the team have updated by atomics, read
+// where those act (not from this compute unit's vector cache).
+__device__ inline unsigned long long team_load(const unsigned long long *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// The smallest of the members' entries into all of them: tab, the first
+// member's table of n entries, the others' stride entries apart.
+template <int kTeam>
+__device__ inline void team_merge(unsigned long long *tab, int64_t stride, int n) {
+    for (int i = threadIdx.x; i < n; i += kWave * kTeam) {
+        unsigned long long x[kTeam], m = ~0ull;
+#pragma unroll
+        for (int k = 0; k < kTeam; ++k) x[k] = team_load(tab + k * stride + i);
+#pragma unroll
+        for (int k = 0; k < kTeam; ++k) m = x[k] < m ? x[k] : m;
+#pragma unroll
+        for (int k = 0; k < kTeam; ++k)
+            if (x[k] != m) tab[k * stride + i] = m;
+    }
+}
+
 // One source's whole-mesh propagation and its row of results. With a
 // finite cutoff, windows whose key reaches it are dropped (in FP32 a little
 // beyond it, by the acceptance slack) and the row keeps every target; the
@@ -816,8 +848,7 @@ __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, 
                                                               uint32_t &epoch,
                                                               SrcStats &st) {
     const int lane = lane_id();
-    // the tables of this wavefront, and those that a team shares
-    const int slot = kTeam == 1 ? (int)blockIdx.x : (int)blockIdx.x * kTeam + member, shared = blockIdx.x;
+    const int slot = kTeam == 1 ? (int)blockIdx.x : (int)blockIdx.x * kTeam + member;
     const bool fp32 = sizeof(R) == 4;
     const int n = sd.n;
     // the mesh and the target index through local pointers: read from the
@@ -836,8 +867,15 @@ __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, 
     C.rc = {C.root_keep, C.tie_dir, C.tie_rel};
     C.dom_rel = fp32 ? a.gp.dom_rel32 : a.gp.dom_rel;
     // rounds: wide ones mean fewer round changes, but on a surface with bend
-    // vertices they launch vertices before their distances settle
-    C.bucket = uniform(!kDom ? INFINITY : a.gp.bucket > 0.0 ? a.gp.bucket : (M.n_pseudo > 0 ? 4.0 : 16.0) * M.max_edge);
+    // vertices they launch vertices before their distances settle. A team
+    // launches at round changes only and shares its distances there, so its
+    // rounds are narrow: half an edge, three quarters, an edge, two and four
+    // give 100 sources on the aspect-3 torus of 3456 faces 11.1, 11.5, 12.0, 13.7
+    // and 16.1 M windows in 4.3, 4.3, 5.0, 6.9 and 8.3 ms (alone 11.3 M, 11.2 ms);
+    // 100 on a flat grid of 3200, where half an edge is less than the smallest
+    // step between vertices, 10.4, 6.0 and 5.9 ms for the first three (18.6).
+    const double width = M.n_pseudo == 0 ? 16.0 : kTeam > 1 ? 0.75 : 4.0;
+    C.bucket = uniform(!kDom ? INFINITY : a.gp.bucket > 0.0 ? a.gp.bucket : width * M.max_edge);
     C.cutoff = uniform(sd.cutoff);
     if constexpr (kNear) {
         // every entry of earlier sources is void; once the epochs are used
@@ -850,14 +888,14 @@ __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, 
         }
     }
     const unsigned long long ep = kNear ? epoch : 0;
-    const VertexTable<kNear> Dv{a.vdist + (int64_t)shared * a.vstride, ep};
+    const VertexTable<kNear> Dv{a.vdist + (int64_t)slot * a.vstride, ep};
     // one_split: FP64 passes (the FP32 pass's tie band is as wide as its
     // distances' errors) on surfaces with bend vertices, whose windows split
     // often (an aspect-3 torus of 3456 faces: 188k windows a source without
     // it, 112k with it); on a convex sphere one window in a hundred covers a
     // vertex, and the entries would cost more than the 1 % of windows they
     // save
-    unsigned long long *Hv = kDom && !fp32 && M.n_pseudo > 0 && a.split ? a.split + (int64_t)shared * a.hstride : nullptr;
+    unsigned long long *Hv = kDom && !fp32 && M.n_pseudo > 0 && a.split ? a.split + (int64_t)slot * a.hstride : nullptr;
     C.split_rel = fmax(1e-6, 64.0 * C.tie_rel);
     const BendTable G = bend_table(a.roots, a.rstride, slot, a.rcap);
     RoundStack<R> S;
@@ -878,13 +916,13 @@ __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, 
     }
     // ---- tables
     if constexpr (!kNear) {
-        constexpr int kAll = kWave * kTeam;
-        for (int v = threadIdx.x; v < M.nv; v += kAll) Dv.p[v] = (unsigned long long)__double_as_longlong(INFINITY);
+        for (int v = lane; v < M.nv; v += kWave) Dv.p[v] = (unsigned long long)__double_as_longlong(INFINITY);
         if (Hv)
-            for (int h = threadIdx.x; h < 3 * M.nf; h += kAll) Hv[h] = ~0ull;
+            for (int h = lane; h < 3 * M.nf; h += kWave) Hv[h] = ~0ull;
         if (kTeam > 1)
-            for (int q = threadIdx.x; q < n; q += kAll) td.best[q] = (unsigned long long)__double_as_longlong(INFINITY);
-        if (kTeam > 1 && threadIdx.x == 0) team.overflow = 0;
+            for (int q = threadIdx.x; q < n; q += kWave * kTeam)
+                td.best[q] = (unsigned long long)__double_as_longlong(INFINITY);
+        if (kTeam > 1 && threadIdx.x == 0) team.overflow = team.more[0] = team.more[1] = 0;
         for (int j = lane; j < n; j += kWave) td[j] = TgtState{};
     }
     if (lane == 0) {
@@ -894,7 +932,7 @@ __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, 
         L.maxb = C.cutoff < INFINITY ? C.cutoff * (fp32 ? 1.0 + fmax(a.gp.slack32, a.gp.guard_rel) : 1.0)
                                      : INFINITY;
     }
-    if (kTeam > 1) __syncthreads();  // the shared tables are ready
+    if (kTeam > 1) __syncthreads();  // the shared state is ready
     else wave_sync();
     bool overflow = false;
     double T = C.bucket;
@@ -1065,12 +1103,19 @@ __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, 
     double DA = INFINITY, DB = INFINITY;  // vertex distances of the window's half-edge (infinite: not read yet)
     unsigned long long nwin = 0;
     int pruned = 0, depth = 0;
+    int round = 0;
     for (;;) {
         if (__ballot(overflow)) overflow = true;
-        if (overflow) break;
+        if (overflow) {
+            if (kTeam == 1) break;
+            // the others learn of it at the end of the round
+            S.lsp = S.gsp = S.dsp = S.dl = 0;
+            L.B.npend = 0;
+            have = false;
+        }
         depth = max(depth, S.lsp + S.gsp + S.dsp + S.dl);
         bool busy = S.refill(have, w);
-        if (kDom && !busy && L.B.npend > 0) {
+        if (kDom && kTeam == 1 && !busy && L.B.npend > 0) {
             if (prof) L.clk[2] -= clock64();
             if (launch_roots<R, kNear, kTeam>(sd, L, G, td, Dv, C, S, T, src, st)) overflow = true;
             if (prof) L.clk[2] += clock64();
@@ -1079,19 +1124,43 @@ __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, 
             DA = DB = INFINITY;
             busy = S.refill(have, w);
         }
+        if (kTeam > 1 && !busy) {
+            // the end of the round, for the whole team: what each member has
+            // learned on its own becomes common, then the bend vertices that
+            // the round reached are launched, and the next one begins
+            S.next_round(overflow);
+            const bool lost = __ballot(overflow) != 0;
+            if (lane == 0) {
+                if (lost) team.overflow = 1;
+                if (L.B.npend > 0 || S.gsp > 0) team.more[round & 1] = 1;
+            }
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this member's entries have arrived
+            __syncthreads();
+            const bool more = !team.overflow && team.more[round & 1];
+            team_merge<kTeam>(a.vdist + (int64_t)blockIdx.x * kTeam * a.vstride, a.vstride, M.nv);
+            key_bound(L, C, n, [&](int q) {
+                return sd.ftgt[q].j == src ? 0.0 : __longlong_as_double((long long)team_load(td.best + q));
+            });
+            if (threadIdx.x == 0) team.more[~round & 1] = 0;
+            __syncthreads();
+            if (!more) break;
+            T += C.bucket;
+            if (L.B.npend > 0) {
+                if (launch_roots<R, kNear, kTeam>(sd, L, G, td, Dv, C, S, T, src, st)) overflow = true;
+                w = Win<R>{};
+                DA = DB = INFINITY;
+            }
+            ++round;
+            continue;
+        }
         if (!busy) {
             if (S.dsp + S.dl == 0 && L.B.npend == 0) break;
             // next round; once every target is reached, bound the keys
             S.next_round(overflow);
             T += C.bucket;
-            if (!kNear && (kTeam > 1 || L.unfound == 0)) {
+            if (!kNear && L.unfound == 0) {
                 wave_sync();  // every lane's target stores are visible
-                double mx = 0.0;
-                for (int q = lane; q < n; q += kWave)
-                    if (sd.ftgt[q].j != src)
-                        mx = fmax(mx, kTeam > 1 ? __longlong_as_double((long long)td.best[q]) : td[q].d1);
-                for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o));
-                if (lane == 0) L.maxb = fmin(L.maxb, mx * (1.0 + C.tie_rel) + 1e-12 * mx);
+                key_bound(L, C, n, [&](int q) { return sd.ftgt[q].j == src ? 0.0 : td[q].d1; });
             }
             wave_sync();
             continue;
@@ -1099,7 +1168,8 @@ __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, 
         nwin += (unsigned long long)__popcll(__ballot(have));
         if (nwin > (unsigned long long)a.gp.max_windows) {
             overflow = true;
-            break;
+            if (kTeam == 1) break;
+            continue;
         }
         if (prof) ++L.clk[3];
         // Three rounds of loads an iteration, each issued as a whole: the
@@ -1414,17 +1484,17 @@ __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, 
 // surfaces without bend vertices).
 // kTeam wavefronts per workgroup share one source (whole-mesh passes with few
 // sources, whose one wavefront each would leave most of the device idle): each
-// starts from its share of the source's angles and propagates on its own, with
-// its own stack, bend-vertex table and target states. Vertex distances and
-// half-edge entries are the team's, so every member's paths dominate; a bend
-// vertex is launched by the member that reached it first by length; the best
-// distances of the targets bound everyone's keys, and the states are merged
-// when all are done. 100 sources on the aspect-3 torus of 3456 faces take
-// 11.0 ms alone and 4.5 ms in teams of eight.
-// Whose window reaches a table first differs from run to run, so paths through
-// bend vertices that tie to rounding may give results that differ in the last
-// bits (1e-15 relative): FP64 only, and not for time steps, whose states repeat
-// bit for bit.
+// starts from its share of the source's angles and propagates a round on its
+// own, with its own stack and tables. At the end of a round the team meets: the
+// smallest vertex distance of any member becomes everyone's, the targets' best
+// distances bound everyone's keys, and each member launches the bend vertices
+// that it reached first by length. The target states are merged when all are
+// done. Nothing that a member reads changes between two meetings, and minima
+// do not depend on their order, so results repeat bit for bit. (Sharing the
+// half-edge entries as well saves one window in a hundred and costs a sixth of
+// the time.) 100 sources on the aspect-3 torus of 3456 faces take 11.2 ms alone
+// and 4.3 ms in teams of eight, 200 on the sphere of 5120 faces 9.8 and 2.1.
+// FP64 only: in FP32-mixed mode another order of paths could move a flag.
 template <bool kMixed, int kStk, bool kNear, int kTeam, bool kDom>
 __global__ __launch_bounds__(kWave *kTeam, 2) void k_geodesic_all(AllArgs a) {
     static_assert(kDom || kNear, "without domination: near passes only");

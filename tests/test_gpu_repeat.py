@@ -1,7 +1,8 @@
-"""Calls repeat bit for bit: pairs of many targets within a cutoff, and time
-steps over them, on surfaces whose symmetry makes paths of equal length meet at
-many targets (several in one face). Twelve calls each; every array of each
-equals the first call's exactly."""
+"""Calls repeat bit for bit: pairs without a cutoff of few sources (several
+wavefronts share each), pairs of many targets within a cutoff, and time steps
+over them, on surfaces whose symmetry makes paths of equal length meet at many
+targets (several in one face). Twelve calls each; every array of each equals
+the first call's exactly."""
 import math
 
 import numpy as np
@@ -36,6 +37,18 @@ def repeats(m, f, b, cutoff, calls=12, **tune) -> dict:
                 bad[k] = bad.get(k, 0) + 1
     ctx.close()
     return bad
+
+
+@pytest.mark.parametrize("name", ["cube", "torus", "bumpy"])
+def test_pairs_of_few_sources(name):
+    m = {"cube": lambda: W.cube(4), "torus": lambda: W.torus(3.0, 1.0, 36, 12),
+         "bumpy": lambda: W.bumpy_sphere(3, 0.2)}[name]()
+    if name == "cube":
+        f, b = lattice(m, 1)
+    else:
+        f, b = W.random_particles(m.nf, 100, 4)
+    bad = repeats(m, f[:200], b[:200], math.inf)
+    assert not bad
 
 
 @pytest.mark.parametrize("name", ["flat", "torus", "cube", "bumpy"])
