@@ -4,6 +4,7 @@
 #include <cmath>
 
 #include "gsim_internal.h"
+#include "launch_plan.h"
 #include "particle_ops.h"
 #include "window.h"
 
@@ -25,26 +26,27 @@ __global__ void k_xyz(const double *__restrict__ V, const int32_t *__restrict__ 
     for (int d = 0; d < 3; ++d) xyz[3 * j + d] = b0 * p0[d] + b1 * p1[d] + b2 * p2[d];
 }
 
+// Fills stride over their items (fill_blocks).
+__device__ inline int64_t fill_first() { return int64_t(blockIdx.x) * blockDim.x + threadIdx.x; }
+__device__ inline int64_t fill_stride() { return int64_t(gridDim.x) * blockDim.x; }
 __global__ void k_zero_i32(int32_t *p, int64_t n) {
-    int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0;
+    for (int64_t i = fill_first(); i < n; i += fill_stride()) p[i] = 0;
 }
 __global__ void k_zero_u64(unsigned long long *p, int64_t n) {
-    int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0ull;
+    for (int64_t i = fill_first(); i < n; i += fill_stride()) p[i] = 0ull;
 }
 
 // Empty bend-vertex tables: entry e of slot s gets infinite distances and
 // is not queued (the tangent fields are written on insertion).
 __global__ void k_bend_init(char *roots, int64_t rstride, int rcap, int64_t n) {
-    const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const int slot = (int)(i / rcap), e = (int)(i % rcap);
-    const wnd::BendTable g = wnd::bend_table(roots, rstride, slot, rcap);
-    g.rD[e] = INFINITY;
-    g.rL[e] = INFINITY;
-    g.rD2[e] = INFINITY;
-    g.queued[e] = 0;
+    for (int64_t i = fill_first(); i < n; i += fill_stride()) {
+        const int slot = (int)(i / rcap), e = (int)(i % rcap);
+        const wnd::BendTable g = wnd::bend_table(roots, rstride, slot, rcap);
+        g.rD[e] = INFINITY;
+        g.rL[e] = INFINITY;
+        g.rD2[e] = INFINITY;
+        g.queued[e] = 0;
+    }
 }
 
 // ------------------------------------------------------------ scans
@@ -527,8 +529,7 @@ __global__ __launch_bounds__(kBlock) void k_call_end(unsigned long long *__restr
 }
 
 __global__ void k_fill_u64(unsigned long long *p, int64_t n, unsigned long long v) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = v;
+    for (int64_t i = fill_first(); i < n; i += fill_stride()) p[i] = v;
 }
 
 // ------------------------------------------------------------ particles by face
@@ -701,19 +702,19 @@ hipError_t launch_xyz(const DevMesh &m, int n, const int32_t *face, const double
 }
 hipError_t launch_zero_i32(int32_t *p, int64_t n, hipStream_t s) {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_zero_i32, dim3(nblocks(n)), dim3(kBlock), 0, s, p, n);
+    hipLaunchKernelGGL(k_zero_i32, dim3(fill_blocks(n, kBlock)), dim3(kBlock), 0, s, p, n);
     return hipGetLastError();
 }
 hipError_t launch_bend_init(char *roots, int nslots, int64_t rstride, int rcap, hipStream_t s) {
     const int64_t n = (int64_t)nslots * rcap;
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_bend_init, dim3(nblocks(n)), dim3(kBlock), 0, s, roots, rstride, rcap, n);
+    hipLaunchKernelGGL(k_bend_init, dim3(fill_blocks(n, kBlock)), dim3(kBlock), 0, s, roots, rstride, rcap, n);
     return hipGetLastError();
 }
 
 hipError_t launch_zero_u64(unsigned long long *p, int64_t n, hipStream_t s) {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_zero_u64, dim3(nblocks(n)), dim3(kBlock), 0, s, p, n);
+    hipLaunchKernelGGL(k_zero_u64, dim3(fill_blocks(n, kBlock)), dim3(kBlock), 0, s, p, n);
     return hipGetLastError();
 }
 
@@ -764,7 +765,7 @@ hipError_t launch_bin_batch(const SurfDesc *desc, const BatchIdx &bi, int32_t *w
 }
 hipError_t launch_fill_u64(unsigned long long *p, int64_t n, unsigned long long v, hipStream_t s) {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_fill_u64, dim3(nblocks(n)), dim3(kBlock), 0, s, p, n, v);
+    hipLaunchKernelGGL(k_fill_u64, dim3(fill_blocks(n, kBlock)), dim3(kBlock), 0, s, p, n, v);
     return hipGetLastError();
 }
 
