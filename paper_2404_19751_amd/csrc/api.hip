@@ -600,6 +600,18 @@ gsim_status take_bad(gsim_ctx *c, int32_t hb[4]) {
     return GSIM_OK;
 }
 
+// The wavefronts of a near pass, at most `waves`: what the scratch budgets and
+// the device's free memory (looked at only where a buffer has to grow) hold.
+int64_t near_fit(gsim_ctx *c, NearNeed w, int64_t waves) {
+    w.waves = std::max<int64_t>(1, std::min<int64_t>(waves, (int64_t)(c->table_budget / (double)std::max<int64_t>(w.roots, 1))));
+    const double held[kNearBufs] = {(double)c->stack.bytes,  (double)c->roots.bytes,  (double)c->near_t.bytes,
+                                    (double)c->near_v.bytes, (double)c->near_h.bytes, (double)c->near_e.bytes};
+    const int64_t n = near_waves(w, c->stack_budget, INFINITY, held);
+    size_t fr = 0, tot = 0;
+    if (near_growth(w, n, held) <= 0.0 || hipMemGetInfo(&fr, &tot) != hipSuccess) return n;
+    return near_waves(w, c->stack_budget, (double)fr, held);
+}
+
 struct Batch {
     std::vector<Member> mem;
     std::vector<SurfDesc> desc;
@@ -615,6 +627,7 @@ struct Batch {
     bool small = true;  // every surface bins in one workgroup
     bool fused = false; // time steps move the particles inside the cutoff kernel
     AllPass pass = kWholeMesh;  // what kind of pass the whole-mesh kernel makes
+    NearNeed need{};            // near passes: tables and stack of a wavefront
     bool near = false;  // a cutoff pass by whole-mesh propagation (many targets within the cutoff)
     BatchIdx face_blk{};  // blocks of kFaceBlock faces per surface (particles-by-face index)
     int team = 1;       // whole-mesh passes: wavefronts per source
@@ -791,18 +804,14 @@ gsim_status prepare_batch(gsim_ctx *c, Batch &B) {
         }
         B.desc[0].prof = P<long long>(c->prof);
     }
+    if (B.near) B.need = NearNeed{{B.tcap, B.vstride, B.hstride}, B.rstride, 64 * (int64_t)c->gp.stack_cap, 1};
     B.nslots = std::min(std::min(total * B.team, c->cus * per_cu), c->max_slots);
     if (B.all) {
         // whole-mesh fronts are deep: fewer resident wavefronts rather than more memory
         const int64_t fit = (int64_t)(c->stack_budget / all_slot);
         B.nslots = (int)std::max<int64_t>(1, std::min<int64_t>(B.nslots, fit));
     }
-    if (B.near) {
-        const double per_slot = 64.0 * c->gp.stack_cap + 8.0 * B.vstride + 8.0 * B.hstride + (double)B.rstride +
-                                (double)near_area_bytes(B.tcap);
-        const int64_t fit = (int64_t)(c->stack_budget / per_slot);
-        B.nslots = (int)std::max<int64_t>(1, std::min<int64_t>(B.nslots, fit));
-    }
+    if (B.near) B.nslots = (int)near_fit(c, B.need, B.nslots);
     {
         // the bend-vertex tables of the resident wavefronts stay within a budget too
         const int64_t fit = (int64_t)(c->table_budget / (double)std::max<int64_t>(B.rstride, 1));
@@ -846,7 +855,7 @@ gsim_status prepare_batch(gsim_ctx *c, Batch &B) {
         // nothing.
         const int nsl = std::max(B.nslots, 1);
         const int64_t lay[3] = {B.tcap, B.vstride, B.hstride};
-        const size_t need[4] = {(size_t)nsl * (size_t)near_area_bytes(B.tcap), sizeof(unsigned long long) * (size_t)nsl * B.vstride,
+        const size_t need[4] = {(size_t)nsl * (size_t)NearArea(B.tcap).bytes, sizeof(unsigned long long) * (size_t)nsl * B.vstride,
                                 sizeof(unsigned long long) * (size_t)nsl * B.hstride, sizeof(uint32_t) * (size_t)(nsl + 1)};
         Buf *const buf[4] = {&c->near_t, &c->near_v, &c->near_h, &c->near_e};
         for (int k = 0; k < 4; ++k)

@@ -7,6 +7,8 @@
 #include <string>
 #include <vector>
 
+#include "launch_plan.h"
+
 namespace gsim {
 
 // Per-half-edge unfolding record. Half-edge h = 3f + k runs from vertex
@@ -218,7 +220,6 @@ struct SurfDesc {
 // more run as near passes (rows as wide as the largest count needs, up to
 // kBigCandMax).
 constexpr int kCandCap = 128;
-constexpr int kBigCandMax = 4096;
 // Most particles on one surface in whole-mesh passes. The rows hold n x n
 // pair slots of 37 bytes (indices are 64-bit): about 79 GB at this count,
 // and a pairs call's compacted output up to as much again, which fits one
@@ -291,7 +292,7 @@ hipError_t launch_candidates(const SurfDesc *desc, const BatchIdx &bi, int group
 // bytes for rcap bend vertices (bend_table_bytes); ttab: the state of tcap
 // targets (4 doubles each). With epoch (one per wavefront), a near pass: a
 // finite cutoff, rows of the targets within it (at most sd.cap, of at most
-// kBigCandMax), ttab areas of near_area_bytes(tcap), all tables prepared once
+// kBigCandMax), ttab areas of NearArea(tcap).bytes, all tables prepared once
 // by launch_near_init and kept by the passes themselves. team = 2, 4 or 8:
 // that many wavefronts share each source (FP64 whole-mesh passes; shape.nslots
 // counts wavefronts), with best distances of tcap targets per team in best.
@@ -303,7 +304,6 @@ hipError_t launch_geodesic_all(const SurfDesc *desc, const BatchIdx &bi, const G
                                int rcap, void *ttab, int tcap, unsigned long long *split, int64_t hstride,
                                uint32_t *epoch, AllPass pass, int team, unsigned long long *best, int32_t *work_ctr,
                                Counters *ctr, bool fp32, hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
-int64_t near_area_bytes(int tcap);
 hipError_t launch_near_init(char *area, int nslots, int tcap, unsigned long long *vdist, int64_t vstride,
                             unsigned long long *split, int64_t hstride, uint32_t *epoch, hipStream_t s);
 // In-surface Voronoi neighbours (k_voronoi.hip): at most kVoronoiMax

@@ -1602,24 +1602,15 @@ AllKernel kernel_for(int kb, bool fp32, AllPass pass, int team) {
     return fp32 ? kernel_of<true, false, true>(kb, team) : kernel_of<false, false, true>(kb, team);
 }
 
-// Byte offsets of one wavefront's near-pass area: target states, reached
-// list, sort keys.
-struct NearArea {
-    int64_t touch, sort, bytes;
-    explicit NearArea(int tcap)
-        : touch((int64_t)tcap * sizeof(TgtState)), sort((touch + 4 * (int64_t)tcap + 15) / 16 * 16),
-          bytes((sort + 8 * (int64_t)kBigCandMax + 255) / 256 * 256) {}
-};
+static_assert(sizeof(TgtState) == 32, "a NearArea's target state");
 
 }  // namespace
-
-int64_t near_area_bytes(int tcap) { return NearArea(tcap).bytes; }
 
 hipError_t launch_near_init(char *area, int nslots, int tcap, unsigned long long *vdist, int64_t vstride,
                             unsigned long long *split, int64_t hstride, uint32_t *epoch, hipStream_t s) {
     // every target unreached, every vertex and half-edge entry void. (A
     // double of all-ones bits would be a NaN: the states get infinities.)
-    hipError_t e = launch_fill_u64(reinterpret_cast<unsigned long long *>(area), (int64_t)nslots * near_area_bytes(tcap) / 8,
+    hipError_t e = launch_fill_u64(reinterpret_cast<unsigned long long *>(area), (int64_t)nslots * NearArea(tcap).bytes / 8,
                                    0x7ff0000000000000ull, s);
     if (e == hipSuccess) e = launch_fill_u64(vdist, (int64_t)nslots * vstride, ~0ull, s);
     if (e == hipSuccess && hstride) e = launch_fill_u64(split, (int64_t)nslots * hstride, ~0ull, s);

@@ -4,7 +4,6 @@
 #include <cmath>
 
 #include "gsim_internal.h"
-#include "launch_plan.h"
 #include "particle_ops.h"
 #include "window.h"
 

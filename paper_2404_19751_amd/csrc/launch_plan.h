@@ -14,4 +14,62 @@ inline int fill_blocks(int64_t n, int block) {
     return (int)std::min<int64_t>((n + block - 1) / block, kFillBlocksMax);
 }
 
+// Byte offsets of one wavefront's near-pass area for tcap particles: target
+// states (32 bytes each), the list of targets reached, sort keys.
+constexpr int kBigCandMax = 4096;  // the most targets of a source
+struct NearArea {
+    int64_t touch, sort, bytes;
+    explicit NearArea(int64_t tcap)
+        : touch(32 * tcap), sort((touch + 4 * tcap + 15) / 16 * 16),
+          bytes((sort + 8 * (int64_t)kBigCandMax + 255) / 256 * 256) {}
+};
+
+// The tables of one wavefront of a near pass: target area of tcap particles,
+// vertex and half-edge entries.
+struct NearLayout {
+    int64_t tcap = 0, vstride = 0, hstride = 0;
+    bool operator==(const NearLayout &o) const { return tcap == o.tcap && vstride == o.vstride && hstride == o.hstride; }
+};
+// What a near pass asks for: its layout, bytes of a bend-vertex table and of a
+// window stack, and the wavefronts that could run at once.
+struct NearNeed {
+    NearLayout lay;
+    int64_t roots = 0, stack = 0;
+    int64_t waves = 1;
+};
+// Bytes of a wavefront's buffers, in this order: stack, bend-vertex table,
+// target area, vertex entries, half-edge entries, epoch.
+constexpr int kNearBufs = 6;
+inline void near_wave_bytes(const NearNeed &w, double b[kNearBufs]) {
+    b[0] = (double)w.stack;
+    b[1] = (double)w.roots;
+    b[2] = (double)NearArea(w.lay.tcap).bytes;
+    b[3] = 8.0 * (double)w.lay.vstride;
+    b[4] = 8.0 * (double)w.lay.hstride;
+    b[5] = 4.0;
+}
+// Bytes that the buffers (holding `held`) must grow by for `waves` wavefronts:
+// a buffer too small is freed and allocated anew with a quarter more.
+inline double near_growth(const NearNeed &w, int64_t waves, const double held[kNearBufs]) {
+    double b[kNearBufs], g = 0.0;
+    near_wave_bytes(w, b);
+    for (int k = 0; k < kNearBufs; ++k)
+        if ((double)waves * b[k] > held[k]) g += 1.25 * (double)waves * b[k] - held[k];
+    return g;
+}
+// The wavefronts of a near pass: as many as could run, within the scratch
+// budget and with room left on the device (nine tenths of what is free).
+inline int64_t near_waves(const NearNeed &w, double budget, double free_bytes, const double held[kNearBufs]) {
+    double b[kNearBufs], all = 0.0;
+    near_wave_bytes(w, b);
+    for (double x : b) all += x;
+    int64_t lo = 1, hi = std::max<int64_t>(1, std::min<int64_t>(w.waves, (int64_t)(budget / all)));
+    while (lo < hi) {
+        const int64_t mid = (lo + hi + 1) / 2;
+        if (near_growth(w, mid, held) <= 0.9 * free_bytes) lo = mid;
+        else hi = mid - 1;
+    }
+    return lo;
+}
+
 }  // namespace gsim

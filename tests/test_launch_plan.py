@@ -12,6 +12,10 @@ WRAP = """
 using namespace gsim;
 extern "C" {
 int w_fill_blocks(int64_t n, int block) { return fill_blocks(n, block); }
+int64_t w_near_waves(int64_t tcap, int64_t vstride, int64_t hstride, int64_t roots, int64_t stack, int64_t waves,
+                     double budget, double free_bytes, const double *held) {
+    return near_waves(NearNeed{{tcap, vstride, hstride}, roots, stack, waves}, budget, free_bytes, held);
+}
 }
 """
 
@@ -23,7 +27,11 @@ def plan(tmp_path_factory):
     src.write_text(WRAP)
     subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I",
                            os.path.join(ROOT, "paper_2404_19751_amd", "csrc"), str(src), "-o", str(so)])
-    return ctypes.CDLL(str(so))
+    L = ctypes.CDLL(str(so))
+    I, D = ctypes.c_int64, ctypes.c_double
+    L.w_near_waves.argtypes = [I] * 6 + [D, D, ctypes.POINTER(D)]
+    L.w_near_waves.restype = I
+    return L
 
 
 @pytest.mark.parametrize("n", [1, 255, 256, 257, 10 ** 6, 2 ** 28, 2 ** 28 + 1, 2048 * (36 * 466000 + 32768) // 8,
@@ -36,3 +44,35 @@ def test_fills_stay_within_a_launch(plan, n):
     assert 1 <= b and b * 256 < 2 ** 32
     # every item is reached: one per thread, or by strides of the whole grid
     assert b * 256 >= n or b == 2 ** 20
+
+
+def near(plan, tcap, vstride, hstride, roots, stack, waves, budget=40e9, free=1e18, held=(0,) * 6):
+    return plan.w_near_waves(tcap, vstride, hstride, roots, stack, waves, budget, free, (ctypes.c_double * 6)(*held))
+
+
+def wave_bytes(tcap, vstride, hstride, roots, stack):
+    area = ((32 * tcap + 4 * tcap + 15) // 16 * 16 + 8 * 4096 + 255) // 256 * 256
+    return [stack, roots, area, 8 * vstride, 8 * hstride, 4]
+
+
+@pytest.mark.parametrize("tcap", [1, 100, 8192, 466000, 4000000])
+@pytest.mark.parametrize("free", [1e6, 3e8, 3e9, 3e10, 1e18])
+def test_near_waves_fit(plan, tcap, free):
+    """As many wavefronts as run, budget and free memory allow, at least one,
+    and one more would not fit."""
+    lay = (tcap, 2324, 13944, 90112, 64 * 16384)
+    b = wave_bytes(*lay)
+    held = [1e8, 0, 2e8, 0, 0, 0]
+    n = near(plan, *lay, 2048, free=free, held=held)
+    assert 1 <= n <= 2048
+
+    def growth(k):
+        return sum(max(0.0, 1.25 * k * x - h) for x, h in zip(b, held) if k * x > h)
+    assert n == 1 or (n * sum(b) <= 40e9 and growth(n) <= 0.9 * free)
+    assert n == 2048 or (n + 1) * sum(b) > 40e9 or growth(n + 1) > 0.9 * free
+
+
+def test_near_waves_held_memory_counts(plan):
+    lay = (8192, 2324, 13944, 90112, 64 * 16384)
+    held = [2048 * x for x in wave_bytes(*lay)]
+    assert near(plan, *lay, 2048, free=0.0, held=held) == 2048  # nothing has to grow
