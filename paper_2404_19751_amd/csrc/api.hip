@@ -628,6 +628,7 @@ struct Batch {
     bool fused = false; // time steps move the particles inside the cutoff kernel
     AllPass pass = kWholeMesh;  // what kind of pass the whole-mesh kernel makes
     NearNeed need{};            // near passes: tables and stack of a wavefront
+    int stack_rec = 0;          // window records of a wavefront's stack
     bool near = false;  // a cutoff pass by whole-mesh propagation (many targets within the cutoff)
     BatchIdx face_blk{};  // blocks of kFaceBlock faces per surface (particles-by-face index)
     int team = 1;       // whole-mesh passes: wavefronts per source
@@ -804,7 +805,12 @@ gsim_status prepare_batch(gsim_ctx *c, Batch &B) {
         }
         B.desc[0].prof = P<long long>(c->prof);
     }
-    if (B.near) B.need = NearNeed{{B.tcap, B.vstride, B.hstride}, B.rstride, 64 * (int64_t)c->gp.stack_cap, 1};
+    B.stack_rec = B.all ? c->stack_cap_all : c->gp.stack_cap;
+    for (int i = 0; i < ns && B.pass == kNearPass; ++i) {
+        const double cut = B.mem[i].cutoff, share = M_PI * cut * cut / std::max(surface_area(B.mem[i].ms), 1e-300);
+        B.stack_rec = std::max(B.stack_rec, near_stack_records(B.mem[i].ms->dm.nf, share, c->gp.stack_cap, c->stack_cap_all));
+    }
+    if (B.near) B.need = NearNeed{{B.tcap, B.vstride, B.hstride}, B.rstride, 64 * (int64_t)B.stack_rec, 1};
     B.nslots = std::min(std::min(total * B.team, c->cus * per_cu), c->max_slots);
     if (B.all) {
         // whole-mesh fronts are deep: fewer resident wavefronts rather than more memory
@@ -845,8 +851,7 @@ gsim_status prepare_batch(gsim_ctx *c, Batch &B) {
             if (std::min(each, (size_t)c->max_lds) > stat) B.shape.pad_lds = (int32_t)(std::min(each, (size_t)c->max_lds) - stat);
         }
     }
-    const int cap_rec = B.all ? c->stack_cap_all : c->gp.stack_cap;
-    HIPCHK(c, ensure(c->stack, (size_t)std::max(B.nslots, 1) * cap_rec * 64));
+    HIPCHK(c, ensure(c->stack, (size_t)std::max(B.nslots, 1) * B.stack_rec * 64));
     if (B.near) {
         // prepared once per layout; the passes keep the tables themselves.
         // near_slots, the tables that hold prepared entries, is zero from the
@@ -907,10 +912,8 @@ gsim_status geodesic_pass(gsim_ctx *c, Batch &B, bool advance, bool commit_in = 
                                        advance, s));
         }
         GeoParams gp = c->gp;
-        if (B.all) {
-            gp.stack_cap = c->stack_cap_all;
-            gp.max_windows = c->max_windows_all;
-        }
+        gp.stack_cap = B.stack_rec;
+        if (B.all) gp.max_windows = c->max_windows_all;
         Buf &v = B.near ? c->near_v : c->vdist, &h = B.near ? c->near_h : c->split;
         Stage st(c, "geodesic", true);
         HIPCHK(c, launch_geodesic_all(desc_dev(c), B.bi, gp, B.shape, P<char>(c->stack), P<unsigned long long>(v),
@@ -1035,6 +1038,7 @@ std::string graph_key(gsim_ctx *c, const Batch &B, int steps) {
     put(&B.fused, sizeof(B.fused));
     put(&B.near, sizeof(B.near));
     put(&B.pass, sizeof(B.pass));
+    put(&B.stack_rec, sizeof(B.stack_rec));
     put(&B.team, sizeof(B.team));
     put(&B.face_blk, sizeof(B.face_blk));
     put(&B.group, sizeof(B.group));

@@ -30,6 +30,21 @@ struct NearLayout {
     int64_t tcap = 0, vstride = 0, hstride = 0;
     bool operator==(const NearLayout &o) const { return tcap == o.tcap && vstride == o.vstride && hstride == o.hstride; }
 };
+// Records (of 64 bytes) of a near pass's window stack. Near passes go round by
+// round: what waits at once is a front around the source, not a depth-first
+// path. The deepest measured hold 3.6 records for each face within the cutoff
+// (a flat disc's share of nf faces) in FP64 and 3.3 in FP32-mixed (tori, bumpy
+// spheres, height fields, flat and corrugated sheets, 5 to 55 % of the surface;
+// whole-mesh passes, which go the same way, have `all` records). At least
+// `cap` records, the depth of depth-first passes, and in powers of two so that
+// cutoffs next to each other ask for the same.
+inline int near_stack_records(double nf, double disc_share, int cap, int all) {
+    const double want = 8.0 * nf * std::min(1.0, disc_share);
+    int64_t n = 1024;
+    while ((double)n < want && n < all) n *= 2;
+    return (int)std::max<int64_t>(cap, std::min<int64_t>(n, all));
+}
+
 // What a near pass asks for: its layout, bytes of a bend-vertex table and of a
 // window stack, and the wavefronts that could run at once.
 struct NearNeed {

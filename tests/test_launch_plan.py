@@ -12,6 +12,7 @@ WRAP = """
 using namespace gsim;
 extern "C" {
 int w_fill_blocks(int64_t n, int block) { return fill_blocks(n, block); }
+int w_near_stack_records(double nf, double share, int cap, int all) { return near_stack_records(nf, share, cap, all); }
 int64_t w_near_waves(int64_t tcap, int64_t vstride, int64_t hstride, int64_t roots, int64_t stack, int64_t waves,
                      double budget, double free_bytes, const double *held) {
     return near_waves(NearNeed{{tcap, vstride, hstride}, roots, stack, waves}, budget, free_bytes, held);
@@ -29,6 +30,7 @@ def plan(tmp_path_factory):
                            os.path.join(ROOT, "paper_2404_19751_amd", "csrc"), str(src), "-o", str(so)])
     L = ctypes.CDLL(str(so))
     I, D = ctypes.c_int64, ctypes.c_double
+    L.w_near_stack_records.argtypes = [D, D, ctypes.c_int, ctypes.c_int]
     L.w_near_waves.argtypes = [I] * 6 + [D, D, ctypes.POINTER(D)]
     L.w_near_waves.restype = I
     return L
@@ -76,3 +78,14 @@ def test_near_waves_held_memory_counts(plan):
     lay = (8192, 2324, 13944, 90112, 64 * 16384)
     held = [2048 * x for x in wave_bytes(*lay)]
     assert near(plan, *lay, 2048, free=0.0, held=held) == 2048  # nothing has to grow
+
+
+def test_near_stack_records(plan):
+    f = plan.w_near_stack_records
+    assert f(4648, 0.007, 16384, 262144) == 16384  # a narrow cutoff: the depth-first depth
+    assert f(4648, 0.007, 64, 262144) == 1024
+    for nf in (320, 20480, 81920, 10 ** 6):
+        for share in (0.01, 0.3, 0.55, 1.0, 7.0):
+            n = f(nf, share, 16384, 262144)
+            assert 16384 <= n <= 262144 and (n >= 8 * nf * min(1.0, share) or n == 262144)
+    assert f(10 ** 6, 0.9, 1 << 20, 262144) == 1 << 20  # a caller's larger depth stands
