@@ -83,7 +83,7 @@ struct gsim_ctx {
     // near passes: target areas, vertex and half-edge entries and epochs of the
     // resident wavefronts, and the layout and number they were last prepared for
     Buf near_t, near_v, near_h, near_e;
-    int64_t near_layout[3] = {};  // tcap, vstride, hstride
+    NearLayout near_layout;
     int near_slots = 0;
     Buf bad;                  // device counts of a state check or of Voronoi limits: zeros between calls
     HostOut *hout = nullptr;  // pinned: what kernels hand to the host
@@ -817,7 +817,17 @@ gsim_status prepare_batch(gsim_ctx *c, Batch &B) {
         const int64_t fit = (int64_t)(c->stack_budget / all_slot);
         B.nslots = (int)std::max<int64_t>(1, std::min<int64_t>(B.nslots, fit));
     }
-    if (B.near) B.nslots = (int)near_fit(c, B.need, B.nslots);
+    if (B.near) {
+        // the layout of the calls before, widened, unless that costs wavefronts
+        const int64_t own = near_fit(c, B.need, B.nslots);
+        NearNeed joint = B.need;
+        joint.lay = near_joint(c->near_layout, B.need.lay);
+        if (!(joint.lay == B.need.lay) && near_fit(c, joint, B.nslots) >= own) B.need = joint;
+        B.nslots = (int)own;
+        B.tcap = (int)B.need.lay.tcap;
+        B.vstride = B.need.lay.vstride;
+        B.hstride = B.need.lay.hstride;
+    }
     {
         // the bend-vertex tables of the resident wavefronts stay within a budget too
         const int64_t fit = (int64_t)(c->table_budget / (double)std::max<int64_t>(B.rstride, 1));
@@ -859,19 +869,20 @@ gsim_status prepare_batch(gsim_ctx *c, Batch &B) {
         // may come at the address of the one before it, so addresses tell
         // nothing.
         const int nsl = std::max(B.nslots, 1);
-        const int64_t lay[3] = {B.tcap, B.vstride, B.hstride};
         const size_t need[4] = {(size_t)nsl * (size_t)NearArea(B.tcap).bytes, sizeof(unsigned long long) * (size_t)nsl * B.vstride,
                                 sizeof(unsigned long long) * (size_t)nsl * B.hstride, sizeof(uint32_t) * (size_t)(nsl + 1)};
         Buf *const buf[4] = {&c->near_t, &c->near_v, &c->near_h, &c->near_e};
+        if (!(c->near_layout == B.need.lay)) c->near_slots = 0;
         for (int k = 0; k < 4; ++k)
             if (buf[k]->bytes < need[k]) c->near_slots = 0;
-        if (std::memcmp(lay, c->near_layout, sizeof lay) != 0 || nsl > c->near_slots) {
+        if (nsl > c->near_slots) {
+            const int first = c->near_slots;
             c->near_slots = 0;
             for (int k = 0; k < 4; ++k)
                 if (need[k]) HIPCHK(c, ensure(*buf[k], need[k]));
-            HIPCHK(c, launch_near_init(P<char>(c->near_t), nsl, B.tcap, P<unsigned long long>(c->near_v), B.vstride,
+            HIPCHK(c, launch_near_init(P<char>(c->near_t), first, nsl, B.tcap, P<unsigned long long>(c->near_v), B.vstride,
                                        P<unsigned long long>(c->near_h), B.hstride, P<uint32_t>(c->near_e), c->stream));
-            std::memcpy(c->near_layout, lay, sizeof lay);
+            c->near_layout = B.need.lay;
             c->near_slots = nsl;
         }
     }

@@ -304,7 +304,8 @@ hipError_t launch_geodesic_all(const SurfDesc *desc, const BatchIdx &bi, const G
                                int rcap, void *ttab, int tcap, unsigned long long *split, int64_t hstride,
                                uint32_t *epoch, AllPass pass, int team, unsigned long long *best, int32_t *work_ctr,
                                Counters *ctr, bool fp32, hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
-hipError_t launch_near_init(char *area, int nslots, int tcap, unsigned long long *vdist, int64_t vstride,
+// (wavefronts first .. nslots - 1)
+hipError_t launch_near_init(char *area, int first, int nslots, int tcap, unsigned long long *vdist, int64_t vstride,
                             unsigned long long *split, int64_t hstride, uint32_t *epoch, hipStream_t s);
 // In-surface Voronoi neighbours (k_voronoi.hip): at most kVoronoiMax
 // particles (an n x n adjacency bitset). launch_voronoi_faces marks every
@@ -369,6 +370,7 @@ constexpr int kWorkInts = kWorkChunks * kWorkStride;
 // commit: take the state from the next-state arrays first (fused time steps)
 hipError_t launch_bin_batch(const SurfDesc *desc, const BatchIdx &bi, int32_t *work, bool advance, bool commit,
                             hipStream_t s);
+hipError_t launch_fill_u32(uint32_t *p, int64_t n, uint32_t v, hipStream_t s);
 hipError_t launch_fill_u64(unsigned long long *p, int64_t n, unsigned long long v, hipStream_t s);
 // fused force + integrator + walk for every particle of the batch
 hipError_t launch_update_batch(const SurfDesc *desc, const BatchIdx &bi, int block, Counters *ctr,

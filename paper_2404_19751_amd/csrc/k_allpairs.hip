@@ -1606,17 +1606,16 @@ static_assert(sizeof(TgtState) == 32, "a NearArea's target state");
 
 }  // namespace
 
-hipError_t launch_near_init(char *area, int nslots, int tcap, unsigned long long *vdist, int64_t vstride,
+hipError_t launch_near_init(char *area, int first, int nslots, int tcap, unsigned long long *vdist, int64_t vstride,
                             unsigned long long *split, int64_t hstride, uint32_t *epoch, hipStream_t s) {
     // every target unreached, every vertex and half-edge entry void. (A
     // double of all-ones bits would be a NaN: the states get infinities.)
-    hipError_t e = launch_fill_u64(reinterpret_cast<unsigned long long *>(area), (int64_t)nslots * NearArea(tcap).bytes / 8,
+    const int64_t n = nslots - first, bytes = NearArea(tcap).bytes;
+    hipError_t e = launch_fill_u64(reinterpret_cast<unsigned long long *>(area + first * bytes), n * bytes / 8,
                                    0x7ff0000000000000ull, s);
-    if (e == hipSuccess) e = launch_fill_u64(vdist, (int64_t)nslots * vstride, ~0ull, s);
-    if (e == hipSuccess && hstride) e = launch_fill_u64(split, (int64_t)nslots * hstride, ~0ull, s);
-    if (e == hipSuccess)
-        e = launch_fill_u64(reinterpret_cast<unsigned long long *>(epoch), (nslots + 1) / 2,
-                            (unsigned long long)kEpochMax << 32 | kEpochMax, s);
+    if (e == hipSuccess) e = launch_fill_u64(vdist + first * vstride, n * vstride, ~0ull, s);
+    if (e == hipSuccess && hstride) e = launch_fill_u64(split + first * hstride, n * hstride, ~0ull, s);
+    if (e == hipSuccess) e = launch_fill_u32(epoch + first, n, kEpochMax, s);
     return e;
 }
 

@@ -527,6 +527,9 @@ __global__ __launch_bounds__(kBlock) void k_call_end(unsigned long long *__restr
     if (threadIdx.x == 0) *energy = sh[0];
 }
 
+__global__ void k_fill_u32(uint32_t *p, int64_t n, uint32_t v) {
+    for (int64_t i = fill_first(); i < n; i += fill_stride()) p[i] = v;
+}
 __global__ void k_fill_u64(unsigned long long *p, int64_t n, unsigned long long v) {
     for (int64_t i = fill_first(); i < n; i += fill_stride()) p[i] = v;
 }
@@ -760,6 +763,11 @@ hipError_t launch_bin_batch(const SurfDesc *desc, const BatchIdx &bi, int32_t *w
         hipLaunchKernelGGL(k_bin_batch<false>, dim3(bi.nsurf), dim3(kBinThreads), 0, s, desc, work, advance ? 1 : 0,
                            commit ? 1 : 0);
     }
+    return hipGetLastError();
+}
+hipError_t launch_fill_u32(uint32_t *p, int64_t n, uint32_t v, hipStream_t s) {
+    if (n <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_fill_u32, dim3(fill_blocks(n, kBlock)), dim3(kBlock), 0, s, p, n, v);
     return hipGetLastError();
 }
 hipError_t launch_fill_u64(unsigned long long *p, int64_t n, unsigned long long v, hipStream_t s) {

@@ -87,4 +87,18 @@ inline int64_t near_waves(const NearNeed &w, double budget, double free_bytes, c
     return lo;
 }
 
+// The layout to run a pass in that needs `need` where the tables are prepared
+// for `cur`: one that holds both, so that surfaces and particle counts used in
+// turn settle on one layout (tables of another are prepared anew, which costs
+// a fill of all of them), with a quarter to spare where the particles have
+// outgrown it.
+inline NearLayout near_joint(const NearLayout &cur, const NearLayout &need) {
+    if (cur.tcap == 0) return need;
+    NearLayout j;
+    j.tcap = need.tcap > cur.tcap ? std::max(need.tcap, cur.tcap + cur.tcap / 4) : cur.tcap;
+    j.vstride = std::max(cur.vstride, need.vstride);
+    j.hstride = std::max(cur.hstride, need.hstride);
+    return j;
+}
+
 }  // namespace gsim

@@ -55,3 +55,24 @@ def test_after_a_call_without_room():
         ok = same(ctx.geodesic_pairs(mid, cutoff), want)
         assert all(ok.values()), ok
     ctx.close()
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32_mixed"])
+def test_layouts_in_turn(prec):
+    """Meshes with and without bend vertices, particle counts and numbers of
+    wavefronts in turn in one context; FP32-mixed results repeat bit for bit
+    here too (every source runs alone)."""
+    cases = [(W.torus(3.0, 1.0, 48, 16), 1200, 60.0), (W.icosphere(4), 900, 150.0), (W.bumpy_sphere(3, 0.2), 2500, 50.0),
+             (W.torus(3.0, 1.0, 48, 16), 1500, 200.0), (W.icosphere(3), 300, 250.0)]
+    ins = [(m, *dense(m, n, mean)) for m, n, mean in cases]
+    want = [fresh(*x, prec) for x in ins]
+    ctx = gsim.Context(0, prec)
+    mids = [ctx.mesh_upload(x[0].V, x[0].T) for x in ins]
+    for turn in range(3):
+        for k in (0, 1, 2, 3, 4, 0, 2, 1):
+            ctx.tune(max_slots=[65536, 64, 777][turn])
+            m, f, b, cutoff = ins[k]
+            ctx.particles_set(mids[k], f, b)
+            ok = same(ctx.geodesic_pairs(mids[k], cutoff), want[k])
+            assert all(ok.values()), (turn, k, ok)
+    ctx.close()

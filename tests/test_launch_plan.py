@@ -12,6 +12,10 @@ WRAP = """
 using namespace gsim;
 extern "C" {
 int w_fill_blocks(int64_t n, int block) { return fill_blocks(n, block); }
+void w_near_joint(int64_t *cur, const int64_t *need) {
+    const NearLayout j = near_joint(NearLayout{cur[0], cur[1], cur[2]}, NearLayout{need[0], need[1], need[2]});
+    cur[0] = j.tcap, cur[1] = j.vstride, cur[2] = j.hstride;
+}
 int w_near_stack_records(double nf, double share, int cap, int all) { return near_stack_records(nf, share, cap, all); }
 int64_t w_near_waves(int64_t tcap, int64_t vstride, int64_t hstride, int64_t roots, int64_t stack, int64_t waves,
                      double budget, double free_bytes, const double *held) {
@@ -89,3 +93,25 @@ def test_near_stack_records(plan):
             n = f(nf, share, 16384, 262144)
             assert 16384 <= n <= 262144 and (n >= 8 * nf * min(1.0, share) or n == 262144)
     assert f(10 ** 6, 0.9, 1 << 20, 262144) == 1 << 20  # a caller's larger depth stands
+
+
+def test_layouts_used_in_turn_settle(plan):
+    """Surfaces and particle counts in turn prepare tables a few times, then no
+    more; a layout always holds what the pass needs."""
+    I3 = ctypes.c_int64 * 3
+    needs = [(8192, 2324, 13944), (1000, 10242, 0), (8200, 2324, 13944), (500, 642, 3840)]
+    cur, changes = I3(0, 0, 0), 0
+    for k in range(40):
+        need, was = needs[k % 4], list(cur)
+        plan.w_near_joint(cur, I3(*need))
+        assert all(c >= n for c, n in zip(cur, need))
+        changes += list(cur) != was
+    assert changes <= 4
+    # particles added one at a time: the tables grow by quarters
+    cur, changes = I3(1000, 642, 0), 0
+    for n in range(1000, 10000):
+        was = cur[0]
+        plan.w_near_joint(cur, I3(n, 642, 0))
+        assert cur[0] >= n
+        changes += cur[0] != was
+    assert changes <= 12
