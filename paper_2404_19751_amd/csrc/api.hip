@@ -459,7 +459,7 @@ struct Member {
 };
 
 // Buffers and descriptor of one surface of a batch.
-gsim_status prepare_surface(gsim_ctx *c, const Member &mb, bool small, int src_begin, SurfDesc &d) {
+gsim_status prepare_surface(gsim_ctx *c, const Member &mb, bool small, SurfDesc &d) {
     MeshState *ms = mb.ms;
     const int n = ms->n;
     const DevMesh &m = ms->dm;
@@ -519,7 +519,6 @@ gsim_status prepare_surface(gsim_ctx *c, const Member &mb, bool small, int src_b
     ms->cap = (int)cap;
     d.m = m;
     d.n = n;
-    d.src_begin = src_begin;
     d.face = ms->face;
     d.bary = ms->bary;
     d.vel = ms->vel;
@@ -612,6 +611,27 @@ int64_t near_fit(gsim_ctx *c, NearNeed w, int64_t waves) {
     return near_waves(w, c->stack_budget, (double)fr, held);
 }
 
+// Surfaces of a batch that go through one geodesic launch together.
+struct Part {
+    int first = 0, ns = 0;        // the batch's surfaces first .. first + ns - 1
+    BatchIdx bi{};                // their sources, from zero
+    BatchIdx face_blk{};          // blocks of kFaceBlock faces per surface (particles-by-face index)
+    bool near = false;            // a cutoff pass by whole-mesh propagation (many targets within the cutoff)
+    bool by_face = false;         // targets through the particles-by-face index (whole-mesh and near passes)
+    AllPass pass = kWholeMesh;    // what kind of pass the whole-mesh kernel makes
+    int tcap = 0;                 // target-table capacity
+    int64_t vstride = 0;          // vertex-table stride
+    int64_t hstride = 0;          // half-edge entries per wavefront (0: no surface has bend vertices)
+    int32_t rcap = 1;             // bend vertices of a surface, at most
+    int team = 1;                 // whole-mesh passes: wavefronts per source
+    int group = 1;                // sources per wavefront (more sources than resident slots: 2, 4 or 8)
+    int per_cu = 1;               // resident wavefronts of a compute unit
+    int stack_rec = 0;            // window records of a wavefront's stack
+    int nslots = 0;
+    GeoShape shape{};
+    int total() const { return bi.begin[bi.nsurf]; }
+};
+
 struct Batch {
     std::vector<Member> mem;
     std::vector<SurfDesc> desc;
@@ -619,22 +639,11 @@ struct Batch {
     BatchIdx fire_blk{};  // blocks of kFireBlock particles per surface (FIRE reductions)
     bool any_fire = false;
     bool all = false;     // all-pairs surfaces (no cutoff)
-    int tcap = 0;         // all-pairs target-table capacity
-    int64_t vstride = 0;  // all-pairs vertex-table stride
-    int64_t hstride = 0;  // all-pairs half-edge entries per wavefront (0: no surface has bend vertices)
     int64_t rstride = 0;  // bend-vertex table bytes per wavefront
     int32_t rcap = 0;     // its capacity (bend vertices)
     bool small = true;  // every surface bins in one workgroup
     bool fused = false; // time steps move the particles inside the cutoff kernel
-    AllPass pass = kWholeMesh;  // what kind of pass the whole-mesh kernel makes
-    NearNeed need{};            // near passes: tables and stack of a wavefront
-    int stack_rec = 0;          // window records of a wavefront's stack
-    bool near = false;  // a cutoff pass by whole-mesh propagation (many targets within the cutoff)
-    BatchIdx face_blk{};  // blocks of kFaceBlock faces per surface (particles-by-face index)
-    int team = 1;       // whole-mesh passes: wavefronts per source
-    int group = 1;      // sources per wavefront (FP64, more sources than resident slots: 2 or 4)
-    int nslots = 0;
-    GeoShape shape{};
+    std::vector<Part> parts;  // one, or the cutoff kernel's surfaces and those of a near pass
 };
 
 gsim_status upload_descs(gsim_ctx *c, const std::vector<SurfDesc> &d) {
@@ -646,6 +655,203 @@ gsim_status upload_descs(gsim_ctx *c, const std::vector<SurfDesc> &d) {
     HIPCHK(c, hipMemcpyAsync(c->desc.p, c->desc_pinned, bytes, hipMemcpyHostToDevice, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     c->desc_cached = d;
+    return GSIM_OK;
+}
+
+// Scratch bytes of a resident wavefront of a whole-mesh pass.
+double whole_mesh_slot(const gsim_ctx *c, const Part &Q) {
+    return 64.0 * c->stack_cap_all + 8.0 * Q.vstride + (double)bend_table_bytes(Q.rcap) + 32.0 * Q.tcap + 8.0 * Q.hstride;
+}
+
+// A flat disc of the cutoff as a share of the surface, and the Euclidean
+// candidates that a source expects in it (uniform density).
+double disc_share(const Member &mb) { return M_PI * mb.cutoff * mb.cutoff / std::max(surface_area(mb.ms), 1e-300); }
+double mean_candidates(const Member &mb) { return mb.ms->n * disc_share(mb); }
+
+// Does a surface run in a near pass?
+bool near_rule(const Member &mb, int cap) {
+    // near passes: some surface may have more candidates per source than the
+    // cutoff kernel's LDS table holds, or so many that two sources' would not
+    // fit it together. There the cutoff kernel runs one source per wavefront
+    // and prunes little for its per-target tests. Cell sort and pass, cutoff
+    // kernel against near pass: at 48 expected candidates 0.88 against 0.43
+    // ms (benchmark torus, 7218 sources), 1.46 / 0.72 (torus of 13,824 faces),
+    // 1.10 / 0.76 (bumpy sphere, 9002), 1.33 / 0.92 (height field of 20,000
+    // faces, 9731), 0.26 / 0.18 (sphere of 5120 faces, 2130); at 24, where
+    // sources pair up, 0.28 / 0.25, 0.50 / 0.43, 0.41 / 0.42, 0.43 / 0.50,
+    // 0.16 / 0.15; at 8 a third to half as long as a near pass.
+    const double mean = mean_candidates(mb);
+    return cap > kCandCap || mean + 3.0 * std::sqrt(mean) > 0.5 * kCandCap;
+}
+
+// The kind of a part's pass, its sources and its tables' sizes, and how
+// wavefronts and sources pair up.
+gsim_status plan_part(gsim_ctx *c, Batch &B, Part &Q) {
+    const bool fp32 = c->prec == GSIM_FP32_MIXED;
+    // without the domination tests where they find nothing: on surfaces without
+    // bend vertices, while a disc of the cutoff covers less than half the
+    // surface and does not reach round it (area over the bounding box's
+    // diagonal: the girth of a long surface). There they drop at most one
+    // window in fifty, and everything that serves bend vertices goes with
+    // them. 500 sources of 110 targets on the sphere of 20480 faces: 2.31 ms a
+    // step by depth-first propagation without per-target tests (the cutoff
+    // kernel's way before near passes), 3.30 by the near pass with the tests,
+    // 2.03 without; 2000 of 800 targets 17.9, 10.6 and 7.5; FP32-mixed 500 of
+    // 110 4.08, 6.21 and 3.50.
+    Q.pass = Q.near ? kNearPlain : kWholeMesh;
+    Q.bi.nsurf = Q.face_blk.nsurf = Q.ns;
+    int total = 0, nfb = 0;
+    double mean = 0.0;  // expected Euclidean candidates of a source (uniform density)
+    bool teams = B.all && !fp32 && !c->profile_sources;
+    for (int k = 0; k < Q.ns; ++k) {
+        const Member &mb = B.mem[Q.first + k];
+        const DevMesh &m = mb.ms->dm;
+        const double cut = mb.cutoff;
+        const double diag = std::hypot(m.bbmax[0] - m.bbmin[0], m.bbmax[1] - m.bbmin[1], m.bbmax[2] - m.bbmin[2]);
+        if (Q.near && (m.n_pseudo > 0 || disc_share(mb) > 0.5 || 2.0 * cut * diag > surface_area(mb.ms))) Q.pass = kNearPass;
+        Q.bi.begin[k] = total;
+        total += mb.ms->n;
+        Q.face_blk.begin[k] = nfb;
+        if (Q.by_face) {
+            gsim_status st = prepare_face_index(c, mb.ms, B.desc[Q.first + k]);
+            if (st != GSIM_OK) return st;
+            nfb += (m.nf + kFaceBlock - 1) / kFaceBlock;
+        }
+        Q.tcap = std::max(Q.tcap, mb.ms->n);
+        Q.vstride = std::max<int64_t>(Q.vstride, m.nv);
+        if (Q.by_face && m.n_pseudo > 0 && !(fp32 && !finite_cutoff(cut))) Q.hstride = std::max<int64_t>(Q.hstride, 3 * (int64_t)m.nf);
+        Q.rcap = std::max(Q.rcap, m.n_pseudo);
+        mean = std::max(mean, mean_candidates(mb));
+        teams = teams && !mb.integ;
+    }
+    Q.bi.begin[Q.ns] = total;
+    Q.face_blk.begin[Q.ns] = nfb;
+    if (Q.by_face) HIPCHK(c, ensure(c->scan_scratch, sizeof(int32_t) * (size_t)nfb));
+    // persistent grid: as many wavefronts as can be resident, at most one per source
+    const double all_slot = whole_mesh_slot(c, Q);
+    // whole-mesh passes with few sources: the largest team of wavefronts per
+    // source with which all sources are still resident at once, within the
+    // scratch budget and what the device has left. 100 sources on the torus of
+    // 3456 faces: 11.2 ms alone, 4.3 in eights; 200 on the sphere of 5120 faces
+    // 9.8 and 2.1, 800 in twos 12.0 and 7.9. Results of a team equal one
+    // wavefront's to rounding. Pair and force calls in FP64: time steps keep to
+    // one wavefront, so that a run does not change its last bits with the room
+    // that the device happens to have, and in FP32-mixed mode another order of
+    // paths could move a flag.
+    for (int t = 8; t > 1 && Q.team == 1 && teams; t /= 2) {
+        const int64_t waves = (int64_t)total * t;
+        if (waves > std::min(c->cus * geodesic_all_waves_per_cu(c->lds_stack_kb, fp32, kWholeMesh, t), c->max_slots)) continue;
+        if (waves * all_slot > c->stack_budget || waves * bend_table_bytes(Q.rcap) > c->table_budget) continue;
+        size_t left = 0, card = 0;
+        const double more = waves * all_slot - (double)(c->stack.bytes + c->vdist.bytes + c->split.bytes + c->roots.bytes);
+        if (more > 0.0 && (hipMemGetInfo(&left, &card) != hipSuccess || more > 0.5 * (double)left)) continue;
+        Q.team = t;
+    }
+    Q.per_cu = std::max(1, Q.by_face ? geodesic_all_waves_per_cu(c->lds_stack_kb, fp32, Q.pass, Q.team)
+                                     : geodesic_blocks_per_cu(c->lds_stack_kb, fp32));
+    // several sources per wavefront (the largest group of at most
+    // group_sources that still gives every resident wavefront a full one):
+    // each of a group's sources has its own bend-vertex entries in the
+    // wavefront's table
+    if (!Q.by_face && !c->profile_sources) {
+        // a group's sources share the table, so twice the expected candidates
+        // plus 8 must fit a share, or too many sources would run alone (three
+        // standard deviations of a Poisson count above the mean: a few in a
+        // thousand), and the resident wavefronts' bend-vertex tables (g
+        // entries per bend vertex each) must fit the table budget, or the
+        // group would cost resident wavefronts
+        const double slots = (double)std::min(c->cus * Q.per_cu, c->max_slots);
+        for (int g = c->group_sources; g > 1 && Q.group == 1; g /= 2)
+            if (total >= (int64_t)g * c->cus * Q.per_cu && mean + 3.0 * std::sqrt(mean) <= (double)(kCandCap / g) &&
+                slots * (double)bend_table_bytes(g * Q.rcap) <= c->table_budget)
+                Q.group = g;
+    }
+    return GSIM_OK;
+}
+
+// A part's resident wavefronts, their scratch and the launch shape.
+gsim_status shape_part(gsim_ctx *c, Batch &B, Part &Q) {
+    const bool fp32 = c->prec == GSIM_FP32_MIXED;
+    Q.stack_rec = B.all ? c->stack_cap_all : c->gp.stack_cap;
+    for (int k = 0; k < Q.ns && Q.pass == kNearPass; ++k) {
+        const Member &mb = B.mem[Q.first + k];
+        Q.stack_rec = std::max(Q.stack_rec, near_stack_records(mb.ms->dm.nf, disc_share(mb), c->gp.stack_cap, c->stack_cap_all));
+    }
+    Q.nslots = std::min(std::min(Q.total() * Q.team, c->cus * Q.per_cu), c->max_slots);
+    if (B.all) {
+        // whole-mesh fronts are deep: fewer resident wavefronts rather than more memory
+        const int64_t fit = (int64_t)(c->stack_budget / whole_mesh_slot(c, Q));
+        Q.nslots = (int)std::max<int64_t>(1, std::min<int64_t>(Q.nslots, fit));
+    }
+    if (Q.near) {
+        // the layout of the calls before, widened, unless that costs wavefronts
+        NearNeed need{{Q.tcap, Q.vstride, Q.hstride}, B.rstride, 64 * (int64_t)Q.stack_rec, 1};
+        const int64_t own = near_fit(c, need, Q.nslots);
+        NearNeed joint = need;
+        joint.lay = near_joint(c->near_layout, need.lay);
+        if (!(joint.lay == need.lay) && near_fit(c, joint, Q.nslots) >= own) need = joint;
+        Q.nslots = (int)own;
+        Q.tcap = (int)need.lay.tcap;
+        Q.vstride = need.lay.vstride;
+        Q.hstride = need.lay.hstride;
+    }
+    {
+        // the bend-vertex tables of the resident wavefronts stay within a budget too
+        const int64_t fit = (int64_t)(c->table_budget / (double)std::max<int64_t>(B.rstride, 1));
+        Q.nslots = (int)std::max<int64_t>(1, std::min<int64_t>(Q.nslots, fit));
+    }
+    Q.shape.lds_stack_kb = c->lds_stack_kb;
+    Q.shape.nslots = Q.nslots;
+    Q.shape.grab = c->grab;
+    Q.shape.pad_lds = 0;
+    {
+        // fewer sources than resident slots: pad each workgroup's LDS so that
+        // at most the needed number fit on a compute unit and the grid spreads
+        // over all of them instead of filling some
+        const int want = (Q.nslots + c->cus - 1) / c->cus;
+        if (want < Q.per_cu && want > 0 && Q.team == 1) {
+            // (whole LDS blocks of the allocator, so that the needed number
+            // does fit: a third, fifth, sixth or seventh of the LDS rounded up
+            // let one workgroup fewer in, and the rest ran as a second round.
+            // 1030 sources on the sphere of 20480 faces: 143 ms so, 91 now;
+            // twenty steps of 760 on the bumpy sphere 2.67 and 2.11 ms)
+            const size_t stat = Q.by_face ? geodesic_all_lds_bytes(c->lds_stack_kb, fp32, Q.pass)
+                                          : geodesic_lds_bytes(c->lds_stack_kb, fp32, Q.group);
+            const size_t each = std::min((size_t)c->lds_cu / (size_t)want / kLdsBlock * kLdsBlock, (size_t)c->max_lds);
+            if (each > stat) Q.shape.pad_lds = (int32_t)(each - stat);
+        }
+    }
+    const size_t nsl = std::max(Q.nslots, 1);
+    if (Q.near) {
+        // prepared once per layout; the passes keep the tables themselves.
+        // near_slots, the tables that hold prepared entries, is zero from the
+        // first of these allocations until all is prepared: a new allocation
+        // may come at the address of the one before it, so addresses tell
+        // nothing.
+        const NearLayout lay{Q.tcap, Q.vstride, Q.hstride};
+        const size_t need[4] = {nsl * (size_t)NearArea(Q.tcap).bytes, sizeof(unsigned long long) * nsl * Q.vstride,
+                                sizeof(unsigned long long) * nsl * Q.hstride, sizeof(uint32_t) * nsl};
+        Buf *const buf[4] = {&c->near_t, &c->near_v, &c->near_h, &c->near_e};
+        if (!(c->near_layout == lay)) c->near_slots = 0;
+        for (int k = 0; k < 4; ++k)
+            if (buf[k]->bytes < need[k]) c->near_slots = 0;
+        if ((int)nsl > c->near_slots) {
+            const int first = c->near_slots;
+            c->near_slots = 0;
+            for (int k = 0; k < 4; ++k)
+                if (need[k]) HIPCHK(c, ensure(*buf[k], need[k]));
+            HIPCHK(c, launch_near_init(P<char>(c->near_t), first, (int)nsl, Q.tcap, P<unsigned long long>(c->near_v), Q.vstride,
+                                       P<unsigned long long>(c->near_h), Q.hstride, P<uint32_t>(c->near_e), c->stream));
+            c->near_layout = lay;
+            c->near_slots = (int)nsl;
+        }
+    }
+    if (B.all) {
+        HIPCHK(c, ensure(c->vdist, sizeof(double) * nsl * Q.vstride));
+        HIPCHK(c, ensure(c->ttab, 4 * sizeof(double) * nsl * Q.tcap));
+        if (Q.team > 1) HIPCHK(c, ensure(c->best, sizeof(unsigned long long) * (size_t)(Q.nslots / Q.team) * Q.tcap));
+        if (Q.hstride) HIPCHK(c, ensure(c->split, sizeof(unsigned long long) * nsl * Q.hstride));
+    }
     return GSIM_OK;
 }
 
@@ -669,131 +875,54 @@ gsim_status prepare_batch(gsim_ctx *c, Batch &B) {
         B.small = (int64_t)dims[0] * dims[1] * dims[2] <= kSmallCells;
     }
     B.desc.resize(ns);
-    B.bi.nsurf = ns;
-    int total = 0;
+    std::vector<char> near(ns, 0);
+    for (int i = 0; i < ns; ++i) {
+        gsim_status st = prepare_surface(c, B.mem[i], B.small || ns > 1, B.desc[i]);
+        if (st != GSIM_OK) return st;
+        near[i] = !B.all && near_rule(B.mem[i], B.desc[i].cap);
+    }
+    // the cutoff kernel's surfaces first, then those of a near pass: each kind
+    // is a launch of its own. A surface's kind follows from the surface alone,
+    // so that its steps in a batch repeat those by itself bit for bit, and a
+    // sparse surface does not pay a near pass, which takes two to three times
+    // as long over it: fifteen surfaces of 3000 sources and 8 candidates beside
+    // a torus of 1000 and 60 take 1.29 ms a step, 2.02 in one near pass; of
+    // 1000 sources and 25 (few sources with wide cutoffs, where a near pass is
+    // the quicker) 4.1 and 2.9.
+    const int ncut = (int)std::count(near.begin(), near.end(), 0);
+    if (ncut > 0 && ncut < ns) {
+        std::vector<Member> mem;
+        std::vector<SurfDesc> desc;
+        for (char kind : {0, 1})
+            for (int i = 0; i < ns; ++i)
+                if (near[i] == kind) {
+                    mem.push_back(B.mem[i]);
+                    desc.push_back(B.desc[i]);
+                }
+        B.mem.swap(mem);
+        B.desc.swap(desc);
+    }
+    B.parts.clear();
+    for (int first = 0; first < ns;) {
+        Part P;
+        P.first = first;
+        P.near = first >= ncut;
+        P.by_face = B.all || P.near;
+        P.ns = P.near || ncut == ns ? ns - first : ncut;
+        first += P.ns;
+        B.parts.push_back(P);
+    }
+    B.bi.nsurf = B.fire_blk.nsurf = ns;
+    B.any_fire = false;
+    int total = 0, nblk = 0;
     for (int i = 0; i < ns; ++i) {
         B.bi.begin[i] = total;
-        gsim_status st = prepare_surface(c, B.mem[i], B.small || ns > 1, total, B.desc[i]);
-        if (st != GSIM_OK) return st;
-        total += B.mem[i].ms->n;
-    }
-    B.bi.begin[ns] = total;
-    // near passes: some surface may have more candidates per source than the
-    // cutoff kernel's LDS table holds, or so many that two sources' would not
-    // fit it together. There the cutoff kernel runs one source per wavefront
-    // and prunes little for its per-target tests. Cell sort and pass, cutoff
-    // kernel against near pass: at 48 expected candidates 0.88 against 0.43
-    // ms (benchmark torus, 7218 sources), 1.46 / 0.72 (torus of 13,824 faces),
-    // 1.10 / 0.76 (bumpy sphere, 9002), 1.33 / 0.92 (height field of 20,000
-    // faces, 9731), 0.26 / 0.18 (sphere of 5120 faces, 2130); at 24, where
-    // sources pair up, 0.28 / 0.25, 0.50 / 0.43, 0.41 / 0.42, 0.43 / 0.50,
-    // 0.16 / 0.15; at 8 a third to half as long as a near pass.
-    B.near = false;
-    for (int i = 0; i < ns && !B.all; ++i) {
-        const double cut = B.mem[i].cutoff;
-        const double mean = B.mem[i].ms->n * M_PI * cut * cut / std::max(surface_area(B.mem[i].ms), 1e-300);
-        B.near |= B.desc[i].cap > kCandCap || mean + 3.0 * std::sqrt(mean) > 0.5 * kCandCap;
-    }
-    const bool by_face = B.all || B.near;
-    // without the domination tests where they find nothing: on surfaces without
-    // bend vertices, while a disc of the cutoff covers less than half the
-    // surface and does not reach round it (area over the bounding box's
-    // diagonal: the girth of a long surface). There they drop at most one
-    // window in fifty, and everything that serves bend vertices goes with
-    // them. 500 sources of 110 targets on the sphere of 20480 faces: 2.31 ms a
-    // step by depth-first propagation without per-target tests (the cutoff
-    // kernel's way before near passes), 3.30 by the near pass with the tests,
-    // 2.03 without; 2000 of 800 targets 17.9, 10.6 and 7.5; FP32-mixed 500 of
-    // 110 4.08, 6.21 and 3.50.
-    B.pass = B.near ? kNearPlain : kWholeMesh;
-    for (int i = 0; i < ns && B.pass == kNearPlain; ++i) {
-        const DevMesh &m = B.mem[i].ms->dm;
-        const double cut = B.mem[i].cutoff, area = surface_area(B.mem[i].ms);
-        const double diag = std::hypot(m.bbmax[0] - m.bbmin[0], m.bbmax[1] - m.bbmin[1], m.bbmax[2] - m.bbmin[2]);
-        if (m.n_pseudo > 0 || M_PI * cut * cut > 0.5 * area || 2.0 * cut * diag > area) B.pass = kNearPass;
-    }
-    B.face_blk.nsurf = ns;
-    int nfb = 0;
-    for (int i = 0; i < ns; ++i) {
-        B.face_blk.begin[i] = nfb;
-        if (by_face) {
-            gsim_status st = prepare_face_index(c, B.mem[i].ms, B.desc[i]);
-            if (st != GSIM_OK) return st;
-            nfb += (B.mem[i].ms->dm.nf + kFaceBlock - 1) / kFaceBlock;
-        }
-    }
-    B.face_blk.begin[ns] = nfb;
-    if (by_face) HIPCHK(c, ensure(c->scan_scratch, sizeof(int32_t) * (size_t)nfb));
-    B.fire_blk.nsurf = ns;
-    B.any_fire = false;
-    int nblk = 0;
-    B.tcap = 0;
-    B.vstride = B.hstride = 0;
-    B.rcap = 1;
-    for (int i = 0; i < ns; ++i) {
         B.fire_blk.begin[i] = nblk;
+        total += B.mem[i].ms->n;
         nblk += (B.mem[i].ms->n + kFireBlock - 1) / kFireBlock;
         B.any_fire |= B.mem[i].integ && B.mem[i].integ->kind == GSIM_INT_FIRE;
-        B.tcap = std::max(B.tcap, B.mem[i].ms->n);
-        B.vstride = std::max<int64_t>(B.vstride, B.mem[i].ms->dm.nv);
-        if (by_face && B.mem[i].ms->dm.n_pseudo > 0 && !(c->prec == GSIM_FP32_MIXED && !finite_cutoff(B.mem[i].cutoff)))
-            B.hstride = std::max<int64_t>(B.hstride, 3 * (int64_t)B.mem[i].ms->dm.nf);
-        B.rcap = std::max(B.rcap, B.mem[i].ms->dm.n_pseudo);
     }
-    // persistent grid: as many wavefronts as can be resident, at most one per source
-    const bool fp32 = c->prec == GSIM_FP32_MIXED;
-    // scratch of a resident wavefront of a whole-mesh pass
-    const double all_slot = 64.0 * c->stack_cap_all + 8.0 * B.vstride + (double)bend_table_bytes(B.rcap) + 32.0 * B.tcap + 8.0 * B.hstride;
-    // whole-mesh passes with few sources: the largest team of wavefronts per
-    // source with which all sources are still resident at once, within the
-    // scratch budget and what the device has left. 100 sources on the torus of
-    // 3456 faces: 11.2 ms alone, 4.3 in eights; 200 on the sphere of 5120 faces
-    // 9.8 and 2.1, 800 in twos 12.0 and 7.9. Results of a team equal one
-    // wavefront's to rounding. Pair and force calls in FP64: time steps keep to
-    // one wavefront, so that a run does not change its last bits with the room
-    // that the device happens to have, and in FP32-mixed mode another order of
-    // paths could move a flag.
-    B.team = 1;
-    bool teams = B.all && !fp32 && !c->profile_sources;
-    for (int i = 0; i < ns; ++i) teams = teams && !B.mem[i].integ;
-    for (int t = 8; t > 1 && B.team == 1 && teams; t /= 2) {
-        const int64_t waves = (int64_t)total * t;
-        if (waves > std::min(c->cus * geodesic_all_waves_per_cu(c->lds_stack_kb, fp32, kWholeMesh, t), c->max_slots)) continue;
-        if (waves * all_slot > c->stack_budget || waves * bend_table_bytes(B.rcap) > c->table_budget) continue;
-        size_t left = 0, card = 0;
-        const double more = waves * all_slot - (double)(c->stack.bytes + c->vdist.bytes + c->split.bytes + c->roots.bytes);
-        if (more > 0.0 && (hipMemGetInfo(&left, &card) != hipSuccess || more > 0.5 * (double)left)) continue;
-        B.team = t;
-    }
-    const int per_cu = std::max(1, by_face ? geodesic_all_waves_per_cu(c->lds_stack_kb, fp32, B.pass, B.team)
-                                           : geodesic_blocks_per_cu(c->lds_stack_kb, fp32));
-    // several sources per wavefront (the largest group of at most
-    // group_sources that still gives every resident wavefront a full one):
-    // each of a group's sources has its own bend-vertex entries in the
-    // wavefront's table
-    B.group = 1;
-    if (!by_face && !c->profile_sources) {
-        // the expected Euclidean candidates of a source (uniform density):
-        // a group's sources share the table, so twice that plus 8 must fit a
-        // share, or too many sources would run alone (three standard
-        // deviations of a Poisson count above the mean: a few in a thousand)
-        double mean = 0.0;
-        for (int i = 0; i < ns; ++i) {
-            const MeshState *ms = B.mem[i].ms;
-            const double cut = B.mem[i].cutoff;
-            mean = std::max(mean, ms->n * M_PI * cut * cut / std::max(surface_area(B.mem[i].ms), 1e-300));
-        }
-        // and the resident wavefronts' bend-vertex tables (g entries per
-        // bend vertex each) must fit the table budget, or the group would
-        // cost resident wavefronts
-        const double slots = (double)std::min(c->cus * per_cu, c->max_slots);
-        for (int g = c->group_sources; g > 1 && B.group == 1; g /= 2)
-            if (total >= (int64_t)g * c->cus * per_cu && mean + 3.0 * std::sqrt(mean) <= (double)(kCandCap / g) &&
-                slots * (double)bend_table_bytes(g * B.rcap) <= c->table_budget)
-                B.group = g;
-    }
-    B.rcap *= B.group;
-    B.rstride = bend_table_bytes(B.rcap);
+    B.bi.begin[ns] = total;
     B.fire_blk.begin[ns] = nblk;
     if (B.any_fire) HIPCHK(c, ensure(c->partials, sizeof(double) * 3 * (size_t)std::max(nblk, 1)));
     if (c->profile_sources && ns == 1) {
@@ -805,100 +934,38 @@ gsim_status prepare_batch(gsim_ctx *c, Batch &B) {
         }
         B.desc[0].prof = P<long long>(c->prof);
     }
-    B.stack_rec = B.all ? c->stack_cap_all : c->gp.stack_cap;
-    for (int i = 0; i < ns && B.pass == kNearPass; ++i) {
-        const double cut = B.mem[i].cutoff, share = M_PI * cut * cut / std::max(surface_area(B.mem[i].ms), 1e-300);
-        B.stack_rec = std::max(B.stack_rec, near_stack_records(B.mem[i].ms->dm.nf, share, c->gp.stack_cap, c->stack_cap_all));
+    // one bend-vertex table per resident wavefront serves every part: its
+    // capacity is a multiple of every group
+    B.rcap = 1;
+    for (Part &Q : B.parts) {
+        gsim_status st = plan_part(c, B, Q);
+        if (st != GSIM_OK) return st;
+        B.rcap = std::max(B.rcap, Q.rcap * Q.group);
     }
-    if (B.near) B.need = NearNeed{{B.tcap, B.vstride, B.hstride}, B.rstride, 64 * (int64_t)B.stack_rec, 1};
-    B.nslots = std::min(std::min(total * B.team, c->cus * per_cu), c->max_slots);
-    if (B.all) {
-        // whole-mesh fronts are deep: fewer resident wavefronts rather than more memory
-        const int64_t fit = (int64_t)(c->stack_budget / all_slot);
-        B.nslots = (int)std::max<int64_t>(1, std::min<int64_t>(B.nslots, fit));
+    if (B.parts.size() > 1) B.rcap = (B.rcap + 7) / 8 * 8;
+    B.rstride = bend_table_bytes(B.rcap);
+    int nsl = 1;
+    size_t stack = 0;
+    for (Part &Q : B.parts) {
+        gsim_status st = shape_part(c, B, Q);
+        if (st != GSIM_OK) return st;
+        nsl = std::max(nsl, Q.nslots);
+        stack = std::max(stack, (size_t)std::max(Q.nslots, 1) * Q.stack_rec * 64);
     }
-    if (B.near) {
-        // the layout of the calls before, widened, unless that costs wavefronts
-        const int64_t own = near_fit(c, B.need, B.nslots);
-        NearNeed joint = B.need;
-        joint.lay = near_joint(c->near_layout, B.need.lay);
-        if (!(joint.lay == B.need.lay) && near_fit(c, joint, B.nslots) >= own) B.need = joint;
-        B.nslots = (int)own;
-        B.tcap = (int)B.need.lay.tcap;
-        B.vstride = B.need.lay.vstride;
-        B.hstride = B.need.lay.hstride;
-    }
-    {
-        // the bend-vertex tables of the resident wavefronts stay within a budget too
-        const int64_t fit = (int64_t)(c->table_budget / (double)std::max<int64_t>(B.rstride, 1));
-        B.nslots = (int)std::max<int64_t>(1, std::min<int64_t>(B.nslots, fit));
-    }
+    HIPCHK(c, ensure(c->stack, stack));
     // time steps move the particles inside the geodesic launch when there is
     // at most one source per SIMD (four per compute unit): each wavefront's
     // one source then only grows by a walk, and the separate update launch
     // goes. With more sources, every one of them would carry the serial move
     // (measured: a loss from two wavefronts per SIMD on).
-    B.fused = c->fuse_update && !by_face && !B.any_fire && total <= B.nslots && total <= 4 * c->cus;
+    B.fused = c->fuse_update && B.parts.size() == 1 && !B.parts[0].by_face && !B.any_fire &&
+              total <= B.parts[0].nslots && total <= 4 * c->cus;
     for (int i = 0; i < ns; ++i) B.fused = B.fused && B.mem[i].integ != nullptr;
-    B.shape.lds_stack_kb = c->lds_stack_kb;
-    B.shape.nslots = B.nslots;
-    B.shape.grab = c->grab;
-    B.shape.pad_lds = 0;
-    {
-        // fewer sources than resident slots: pad each workgroup's LDS so that
-        // at most the needed number fit on a compute unit and the grid spreads
-        // over all of them instead of filling some
-        const int want = (B.nslots + c->cus - 1) / c->cus;
-        if (want < per_cu && want > 0 && B.team == 1) {
-            // (whole LDS blocks of the allocator, so that the needed number
-            // does fit: a third, fifth, sixth or seventh of the LDS rounded up
-            // let one workgroup fewer in, and the rest ran as a second round.
-            // 1030 sources on the sphere of 20480 faces: 143 ms so, 91 now;
-            // twenty steps of 760 on the bumpy sphere 2.67 and 2.11 ms)
-            const size_t stat = by_face ? geodesic_all_lds_bytes(c->lds_stack_kb, fp32, B.pass)
-                                        : geodesic_lds_bytes(c->lds_stack_kb, fp32, B.group);
-            const size_t each = (size_t)c->lds_cu / (size_t)want / kLdsBlock * kLdsBlock;
-            if (std::min(each, (size_t)c->max_lds) > stat) B.shape.pad_lds = (int32_t)(std::min(each, (size_t)c->max_lds) - stat);
-        }
-    }
-    HIPCHK(c, ensure(c->stack, (size_t)std::max(B.nslots, 1) * B.stack_rec * 64));
-    if (B.near) {
-        // prepared once per layout; the passes keep the tables themselves.
-        // near_slots, the tables that hold prepared entries, is zero from the
-        // first of these allocations until all is prepared: a new allocation
-        // may come at the address of the one before it, so addresses tell
-        // nothing.
-        const int nsl = std::max(B.nslots, 1);
-        const size_t need[4] = {(size_t)nsl * (size_t)NearArea(B.tcap).bytes, sizeof(unsigned long long) * (size_t)nsl * B.vstride,
-                                sizeof(unsigned long long) * (size_t)nsl * B.hstride, sizeof(uint32_t) * (size_t)(nsl + 1)};
-        Buf *const buf[4] = {&c->near_t, &c->near_v, &c->near_h, &c->near_e};
-        if (!(c->near_layout == B.need.lay)) c->near_slots = 0;
-        for (int k = 0; k < 4; ++k)
-            if (buf[k]->bytes < need[k]) c->near_slots = 0;
-        if (nsl > c->near_slots) {
-            const int first = c->near_slots;
-            c->near_slots = 0;
-            for (int k = 0; k < 4; ++k)
-                if (need[k]) HIPCHK(c, ensure(*buf[k], need[k]));
-            HIPCHK(c, launch_near_init(P<char>(c->near_t), first, nsl, B.tcap, P<unsigned long long>(c->near_v), B.vstride,
-                                       P<unsigned long long>(c->near_h), B.hstride, P<uint32_t>(c->near_e), c->stream));
-            c->near_layout = B.need.lay;
-            c->near_slots = nsl;
-        }
-    }
-    if (B.all) {
-        HIPCHK(c, ensure(c->vdist, sizeof(double) * (size_t)std::max(B.nslots, 1) * B.vstride));
-        HIPCHK(c, ensure(c->ttab, 4 * sizeof(double) * (size_t)std::max(B.nslots, 1) * B.tcap));
-        if (B.team > 1)
-            HIPCHK(c, ensure(c->best, sizeof(unsigned long long) * (size_t)(B.nslots / B.team) * B.tcap));
-        if (B.hstride) HIPCHK(c, ensure(c->split, sizeof(unsigned long long) * (size_t)std::max(B.nslots, 1) * B.hstride));
-    }
     // bend-vertex tables: emptied once here, left empty by the kernels
-    const int nsl = std::max(B.nslots, 1);
     if (c->roots.bytes < (size_t)nsl * B.rstride || B.rstride != c->roots_stride || B.rcap != c->roots_rcap ||
         nsl > c->roots_slots) {
         if (c->capturing) return fail(c, GSIM_E_STATE, "bend-vertex tables change during graph capture");
-        c->roots_slots = 0;  // as near_slots above
+        c->roots_slots = 0;  // as near_slots
         HIPCHK(c, ensure(c->roots, (size_t)nsl * B.rstride));
         HIPCHK(c, launch_bend_init(P<char>(c->roots), nsl, B.rstride, B.rcap, c->stream));
         c->roots_stride = B.rstride;
@@ -910,36 +977,36 @@ gsim_status prepare_batch(gsim_ctx *c, Batch &B) {
 
 const SurfDesc *desc_dev(gsim_ctx *c) { return static_cast<const SurfDesc *>(c->desc.p); }
 
-// Binning, candidate search and geodesics of every source of the batch.
-// commit_in: the state to bin is in the next-state arrays (the previous
-// fused step of the same call wrote it there).
-gsim_status geodesic_pass(gsim_ctx *c, Batch &B, bool advance, bool commit_in = false) {
+// Binning, candidate search and geodesics of a part's sources. commit_in: the
+// state to bin is in the next-state arrays (the previous fused step of the
+// same call wrote it there).
+gsim_status part_pass(gsim_ctx *c, Batch &B, const Part &Q, bool advance, bool commit_in) {
     hipStream_t s = c->stream;
-    if (B.all || B.near) {
+    const SurfDesc *desc = desc_dev(c) + Q.first;
+    const bool fp32 = c->prec == GSIM_FP32_MIXED;
+    GeoParams gp = c->gp;
+    gp.stack_cap = Q.stack_rec;
+    if (Q.by_face) {
         {
             // starts the pass too (work counters, step counters)
             Stage st(c, "prefilter");
-            HIPCHK(c, launch_face_sort(desc_dev(c), B.bi, B.face_blk, P<int32_t>(c->scan_scratch), P<int32_t>(c->work),
-                                       advance, s));
+            HIPCHK(c, launch_face_sort(desc, Q.bi, Q.face_blk, P<int32_t>(c->scan_scratch), P<int32_t>(c->work), advance, s));
         }
-        GeoParams gp = c->gp;
-        gp.stack_cap = B.stack_rec;
         if (B.all) gp.max_windows = c->max_windows_all;
-        Buf &v = B.near ? c->near_v : c->vdist, &h = B.near ? c->near_h : c->split;
+        Buf &v = Q.near ? c->near_v : c->vdist, &h = Q.near ? c->near_h : c->split;
         Stage st(c, "geodesic", true);
-        HIPCHK(c, launch_geodesic_all(desc_dev(c), B.bi, gp, B.shape, P<char>(c->stack), P<unsigned long long>(v),
-                                      B.vstride, P<char>(c->roots), B.rstride, B.rcap, B.near ? c->near_t.p : c->ttab.p,
-                                      B.tcap, B.hstride ? P<unsigned long long>(h) : nullptr, B.hstride,
-                                      B.near ? P<uint32_t>(c->near_e) : nullptr, B.pass, B.team,
-                                      B.team > 1 ? P<unsigned long long>(c->best) : nullptr, P<int32_t>(c->work),
-                                      P<Counters>(c->ctr), c->prec == GSIM_FP32_MIXED, s, st.a, st.b));
-        c->passes++;
+        HIPCHK(c, launch_geodesic_all(desc, Q.bi, gp, Q.shape, P<char>(c->stack), P<unsigned long long>(v), Q.vstride,
+                                      P<char>(c->roots), B.rstride, B.rcap, Q.near ? c->near_t.p : c->ttab.p, Q.tcap,
+                                      Q.hstride ? P<unsigned long long>(h) : nullptr, Q.hstride,
+                                      Q.near ? P<uint32_t>(c->near_e) : nullptr, Q.pass, Q.team,
+                                      Q.team > 1 ? P<unsigned long long>(c->best) : nullptr, P<int32_t>(c->work),
+                                      P<Counters>(c->ctr), fp32, s, st.a, st.b));
         return GSIM_OK;
     }
     {
         Stage st(c, "prefilter");
         if (B.small) {
-            HIPCHK(c, launch_bin_batch(desc_dev(c), B.bi, P<int32_t>(c->work), advance, commit_in, s));
+            HIPCHK(c, launch_bin_batch(desc, Q.bi, P<int32_t>(c->work), advance, commit_in, s));
         } else {
             // one surface with a fine grid: multi-kernel counting sort
             MeshState *ms = B.mem[0].ms;
@@ -955,23 +1022,29 @@ gsim_status geodesic_pass(gsim_ctx *c, Batch &B, bool advance, bool commit_in = 
             pb.cap_c = kCandCap;
             for (int k = 0; k < 3; ++k) pb.dims[k] = d.dims[k];
             pb.cell = d.cell;
-            if (commit_in) HIPCHK(c, launch_commit_batch(desc_dev(c), B.bi, s));
+            if (commit_in) HIPCHK(c, launch_commit_batch(desc, Q.bi, s));
             // starts the pass too (work counters, step counter)
             HIPCHK(c, launch_cell_sort(ms->dm, n, ms->face, ms->bary, pb, P<int64_t>(c->scan_scratch),
-                                       ms->fill_zero < ncell, desc_dev(c), P<int32_t>(c->work), advance, s));
+                                       ms->fill_zero < ncell, desc, P<int32_t>(c->work), advance, s));
             ms->fill_zero = std::max<int64_t>(ms->fill_zero, ncell);
         }
         // several sources per wavefront: their candidate searches run ahead
         // of the pass, at the occupancy of a small kernel
-        if (B.group > 1) HIPCHK(c, launch_candidates(desc_dev(c), B.bi, B.group, s));
+        if (Q.group > 1) HIPCHK(c, launch_candidates(desc, Q.bi, Q.group, s));
     }
-    GeoParams gp = c->gp;
     if (!(gp.launch_delta > 0.0)) gp.launch_delta = 0.5 * B.mem[0].ms->dm.mean_edge;
-    {
-        Stage st(c, "geodesic", true);
-        HIPCHK(c, launch_geodesic(desc_dev(c), B.bi, gp, B.shape, P<char>(c->stack), P<char>(c->roots), B.rstride,
-                                  B.rcap, P<int32_t>(c->work), P<Counters>(c->ctr), c->prec == GSIM_FP32_MIXED,
-                                  advance && B.fused, s, st.a, st.b, B.group, B.group > 1));
+    Stage st(c, "geodesic", true);
+    HIPCHK(c, launch_geodesic(desc, Q.bi, gp, Q.shape, P<char>(c->stack), P<char>(c->roots), B.rstride, B.rcap,
+                              P<int32_t>(c->work), P<Counters>(c->ctr), fp32, advance && B.fused, s, st.a, st.b, Q.group,
+                              Q.group > 1));
+    return GSIM_OK;
+}
+
+// One pass over every source of the batch.
+gsim_status geodesic_pass(gsim_ctx *c, Batch &B, bool advance, bool commit_in = false) {
+    for (const Part &Q : B.parts) {
+        gsim_status st = part_pass(c, B, Q, advance, commit_in);
+        if (st != GSIM_OK) return st;
     }
     c->passes++;
     return GSIM_OK;
@@ -1044,21 +1117,21 @@ std::string graph_key(gsim_ctx *c, const Batch &B, int steps) {
     put(B.desc.data(), sizeof(SurfDesc) * B.desc.size());
     put(&B.bi, sizeof(B.bi));
     put(&c->gp, sizeof(c->gp));
-    put(&B.shape, sizeof(B.shape));
     put(&B.small, sizeof(B.small));
     put(&B.fused, sizeof(B.fused));
-    put(&B.near, sizeof(B.near));
-    put(&B.pass, sizeof(B.pass));
-    put(&B.stack_rec, sizeof(B.stack_rec));
-    put(&B.team, sizeof(B.team));
-    put(&B.face_blk, sizeof(B.face_blk));
-    put(&B.group, sizeof(B.group));
+    for (const Part &Q : B.parts) {
+        put(&Q.bi, sizeof(Q.bi));
+        put(&Q.face_blk, sizeof(Q.face_blk));
+        put(&Q.shape, sizeof(Q.shape));
+        const int64_t f[] = {Q.first, Q.near, Q.pass, Q.tcap, Q.vstride, Q.hstride, Q.team, Q.group, Q.stack_rec};
+        put(f, sizeof(f));
+    }
     put(&c->update_block, sizeof(int));
     put(&steps, sizeof(int));
     void *ptrs[15] = {c->stack.p, c->work.p, c->ctr.p, c->desc.p, c->scan_scratch.p, c->vdist.p, c->ttab.p,
                       c->roots.p, c->partials.p, c->split.p, c->best.p, c->near_t.p, c->near_v.p, c->near_h.p, c->near_e.p};
     put(ptrs, sizeof(ptrs));
-    const int64_t sizes[5] = {B.rstride, B.rcap, B.tcap, B.vstride, B.hstride};
+    const int64_t sizes[2] = {B.rstride, B.rcap};
     put(sizes, sizeof(sizes));
     return k;
 }

@@ -176,7 +176,6 @@ hipError_t launch_scan_i32_to_i64(const int32_t *in, int64_t *out, int n, int64_
 struct SurfDesc {
     DevMesh m;
     int32_t n;          // particles on the surface
-    int32_t src_begin;  // index of its first source in the batch
     int32_t *face;
     double *bary, *vel, *xyz;
     // next state, written by the cutoff kernel's fused update (time steps
