@@ -669,7 +669,7 @@ double disc_share(const Member &mb) { return M_PI * mb.cutoff * mb.cutoff / std:
 double mean_candidates(const Member &mb) { return mb.ms->n * disc_share(mb); }
 
 // Does a surface run in a near pass?
-bool near_rule(const Member &mb, int cap) {
+bool near_rule(const gsim_ctx *c, const Member &mb, int cap) {
     // near passes: some surface may have more candidates per source than the
     // cutoff kernel's LDS table holds, or so many that two sources' would not
     // fit it together. There the cutoff kernel runs one source per wavefront
@@ -681,7 +681,12 @@ bool near_rule(const Member &mb, int cap) {
     // sources pair up, 0.28 / 0.25, 0.50 / 0.43, 0.41 / 0.42, 0.43 / 0.50,
     // 0.16 / 0.15; at 8 a third to half as long as a near pass.
     const double mean = mean_candidates(mb);
-    return cap > kCandCap || mean + 3.0 * std::sqrt(mean) > 0.5 * kCandCap;
+    if (cap > kCandCap) return true;
+    if (mean + 3.0 * std::sqrt(mean) <= 0.5 * kCandCap) return false;
+    const DevMesh &m = mb.ms->dm;
+    const int records = near_stack_records(m.nf, disc_share(mb), c->gp.stack_cap, c->stack_cap_all);
+    const NearNeed w{{mb.ms->n, m.nv, m.n_pseudo > 0 ? 3 * (int64_t)m.nf : 0}, bend_table_bytes(std::max(m.n_pseudo, 1)), 64 * (int64_t)records, 1};
+    return near_fills_device(w, std::min(8 * c->cus, c->max_slots), c->stack_budget);
 }
 
 // The kind of a part's pass, its sources and its tables' sizes, and how
@@ -879,7 +884,7 @@ gsim_status prepare_batch(gsim_ctx *c, Batch &B) {
     for (int i = 0; i < ns; ++i) {
         gsim_status st = prepare_surface(c, B.mem[i], B.small || ns > 1, B.desc[i]);
         if (st != GSIM_OK) return st;
-        near[i] = !B.all && near_rule(B.mem[i], B.desc[i].cap);
+        near[i] = !B.all && near_rule(c, B.mem[i], B.desc[i].cap);
     }
     // the cutoff kernel's surfaces first, then those of a near pass: each kind
     // is a launch of its own. A surface's kind follows from the surface alone,

@@ -87,6 +87,17 @@ inline int64_t near_waves(const NearNeed &w, double budget, double free_bytes, c
     return lo;
 }
 
+// Does a near pass of n particles have room for half the wavefronts that could
+// run (`resident` on the device)? Every wavefront keeps a state for each of the
+// surface's particles, so with a million the budget holds a thousand of them,
+// and a pass whose targets fit the cutoff kernel's table is better off there.
+inline bool near_fills_device(const NearNeed &w, int64_t resident, double budget) {
+    double b[kNearBufs], all = 0.0;
+    near_wave_bytes(w, b);
+    for (double x : b) all += x;
+    return 2.0 * budget / all >= (double)std::min(resident, w.lay.tcap);
+}
+
 // The layout to run a pass in that needs `need` where the tables are prepared
 // for `cur`: one that holds both, so that surfaces and particle counts used in
 // turn settle on one layout (tables of another are prepared anew, which costs

@@ -16,6 +16,9 @@ void w_near_joint(int64_t *cur, const int64_t *need) {
     const NearLayout j = near_joint(NearLayout{cur[0], cur[1], cur[2]}, NearLayout{need[0], need[1], need[2]});
     cur[0] = j.tcap, cur[1] = j.vstride, cur[2] = j.hstride;
 }
+int w_near_fills(int64_t n, int64_t nv, int64_t nh, int64_t roots, int64_t stack, int64_t resident, double budget) {
+    return near_fills_device(NearNeed{{n, nv, nh}, roots, stack, 1}, resident, budget);
+}
 int w_near_stack_records(double nf, double share, int cap, int all) { return near_stack_records(nf, share, cap, all); }
 int64_t w_near_waves(int64_t tcap, int64_t vstride, int64_t hstride, int64_t roots, int64_t stack, int64_t waves,
                      double budget, double free_bytes, const double *held) {
@@ -35,6 +38,7 @@ def plan(tmp_path_factory):
     L = ctypes.CDLL(str(so))
     I, D = ctypes.c_int64, ctypes.c_double
     L.w_near_stack_records.argtypes = [D, D, ctypes.c_int, ctypes.c_int]
+    L.w_near_fills.argtypes = [I] * 6 + [D]
     L.w_near_waves.argtypes = [I] * 6 + [D, D, ctypes.POINTER(D)]
     L.w_near_waves.restype = I
     return L
@@ -115,3 +119,13 @@ def test_layouts_used_in_turn_settle(plan):
         assert cur[0] >= n
         changes += cur[0] != was
     assert changes <= 12
+
+
+def test_large_surfaces_stay_on_the_cutoff_kernel(plan):
+    """Sphere of 81,920 faces, 16,384 records a stack: half of 2048 wavefronts
+    fit the budget up to about a million particles."""
+    def fills(n, resident=2048):
+        return bool(plan.w_near_fills(n, 40962, 0, 256, 64 * 16384, resident, 40e9))
+    assert fills(100) and fills(8192) and fills(466000) and fills(900000)
+    assert not fills(1200000) and not fills(4000000)
+    assert fills(1200000, 256)
