@@ -264,6 +264,19 @@ T *P(Buf &b) {
     return static_cast<T *>(b.p);
 }
 
+// May a kernel of the context's device write `p`, elements of `size` bytes?
+// Results go straight into the caller's arrays where it may; memory of another
+// device, ordinary host memory and unaligned addresses are left to a copy.
+bool kernel_writes(const gsim_ctx *c, const void *p, size_t size) {
+    if (!p) return true;
+    hipPointerAttribute_t at{};
+    if ((uintptr_t)p % size != 0 || hipPointerGetAttributes(&at, p) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return at.type == hipMemoryTypeDevice && at.device == c->device;
+}
+
 hipEvent_t take_event(gsim_ctx *c) {
     if (!c->free_events.empty()) {
         hipEvent_t e = c->free_events.back();
@@ -1536,7 +1549,14 @@ gsim_status gsim_particles_get_dev(gsim_ctx *c, int32_t id, int32_t *face, doubl
         if (!ms) return fail(c, GSIM_E_ARG, "unknown mesh id");
         if (ms->n <= 0) return fail(c, GSIM_E_STATE, "no particles on this mesh");
         hipStream_t s = c->stream;
-        HIPCHK(c, launch_give_state(ms->n, ms->face, ms->bary, ms->vel, face, bary, vel, s));
+        if (kernel_writes(c, face, 4) && kernel_writes(c, bary, 8) && kernel_writes(c, vel, 8)) {
+            HIPCHK(c, launch_give_state(ms->n, ms->face, ms->bary, ms->vel, face, bary, vel, s));
+            return GSIM_OK;
+        }
+        const size_t n = (size_t)ms->n;
+        if (face) HIPCHK(c, hipMemcpyAsync(face, ms->face, sizeof(int32_t) * n, hipMemcpyDefault, s));
+        if (bary) HIPCHK(c, hipMemcpyAsync(bary, ms->bary, sizeof(double) * 3 * n, hipMemcpyDefault, s));
+        if (vel) HIPCHK(c, hipMemcpyAsync(vel, ms->vel, sizeof(double) * 3 * n, hipMemcpyDefault, s));
         return GSIM_OK;
     }
     GSIM_CATCH(c)
@@ -1562,13 +1582,15 @@ static gsim_status pairs_to(gsim_ctx *c, int32_t id, double cutoff, gsim_pairs *
         c->cum_pairs += c->last.nbr_pairs;
         hipStream_t s = c->stream;
         const bool fits = out->capacity >= total && out->off && (!total || (out->nbr && out->dist && out->tan));
-        if (kind == hipMemcpyDeviceToDevice) {
+        if (kind == hipMemcpyDeviceToDevice && kernel_writes(c, out->nbr, 4) && kernel_writes(c, out->dist, 8) &&
+            kernel_writes(c, out->tan, 8) && kernel_writes(c, out->flags, 1)) {
             // the caller's arrays are device memory: the rows go straight there
             out->count = total;
             if (!fits) return fail(c, GSIM_E_CAPACITY, "pair buffers too small: " + std::to_string(total) + " needed");
             HIPCHK(c, hipMemcpyAsync(out->off, ms->off.p, sizeof(int64_t) * (ms->n + 1), kind, s));
             return total ? compact_pairs(c, ms, cutoff, out->nbr, out->dist, out->tan, out->flags) : GSIM_OK;
         }
+        const hipMemcpyKind to = kind == hipMemcpyDeviceToHost ? kind : hipMemcpyDefault;
         const size_t t1 = (size_t)total + 1;
         st = check_room(c, {{&ms->nbr, 4 * t1}, {&ms->dist, 8 * t1}, {&ms->tan, 24 * t1}, {&ms->flags, t1}},
                         "the " + std::to_string(total) + " pairs of this call (37 bytes each)");
@@ -1579,17 +1601,17 @@ static gsim_status pairs_to(gsim_ctx *c, int32_t id, double cutoff, gsim_pairs *
         HIPCHK(c, ensure(ms->dist, sizeof(double) * t1));
         HIPCHK(c, ensure(ms->tan, sizeof(double) * 3 * t1));
         HIPCHK(c, ensure(ms->flags, t1));
-        HIPCHK(c, hipMemcpyAsync(out->off, ms->off.p, sizeof(int64_t) * (ms->n + 1), kind, s));
+        HIPCHK(c, hipMemcpyAsync(out->off, ms->off.p, sizeof(int64_t) * (ms->n + 1), to, s));
         if (total) {
             st = compact_pairs(c, ms, cutoff, P<int32_t>(ms->nbr), P<double>(ms->dist), P<double>(ms->tan),
                                P<uint8_t>(ms->flags));
             if (st != GSIM_OK) return st;
-            HIPCHK(c, hipMemcpyAsync(out->nbr, ms->nbr.p, sizeof(int32_t) * total, kind, s));
-            HIPCHK(c, hipMemcpyAsync(out->dist, ms->dist.p, sizeof(double) * total, kind, s));
-            HIPCHK(c, hipMemcpyAsync(out->tan, ms->tan.p, sizeof(double) * 3 * total, kind, s));
-            if (out->flags) HIPCHK(c, hipMemcpyAsync(out->flags, ms->flags.p, total, kind, s));
+            HIPCHK(c, hipMemcpyAsync(out->nbr, ms->nbr.p, sizeof(int32_t) * total, to, s));
+            HIPCHK(c, hipMemcpyAsync(out->dist, ms->dist.p, sizeof(double) * total, to, s));
+            HIPCHK(c, hipMemcpyAsync(out->tan, ms->tan.p, sizeof(double) * 3 * total, to, s));
+            if (out->flags) HIPCHK(c, hipMemcpyAsync(out->flags, ms->flags.p, total, to, s));
         }
-        HIPCHK(c, hipStreamSynchronize(s));
+        if (kind == hipMemcpyDeviceToHost) HIPCHK(c, hipStreamSynchronize(s));
         return GSIM_OK;
     }
     GSIM_CATCH(c)
@@ -1694,17 +1716,18 @@ static gsim_status forces_to(gsim_ctx *c, int32_t id, const gsim_potential *pot,
         Batch B;
         if ((st = begin_call(c)) != GSIM_OK) return st;
         if ((st = single(c, ms, pot->cutoff, pot, B)) != GSIM_OK) return st;
-        const bool dev = kind == hipMemcpyDeviceToDevice;
+        const bool dev = kind == hipMemcpyDeviceToDevice && kernel_writes(c, force, 8) && kernel_writes(c, energy, 8);
         if (!dev) HIPCHK(c, ensure(ms->F, sizeof(double) * 3 * ms->n));
         HIPCHK(c, ensure(ms->E, sizeof(double)));
         // device buffers of the caller are written in place
         double *F = dev ? force : P<double>(ms->F);
         if ((st = run_forces(c, ms, pot, F)) != GSIM_OK) return st;
-        if (!dev) HIPCHK(c, hipMemcpyAsync(force, F, sizeof(double) * 3 * ms->n, kind, c->stream));
+        const hipMemcpyKind to = kind == hipMemcpyDeviceToHost ? kind : hipMemcpyDefault;
+        if (!dev) HIPCHK(c, hipMemcpyAsync(force, F, sizeof(double) * 3 * ms->n, to, c->stream));
         double *E = dev && energy ? energy : P<double>(ms->E);
         st = end_call(c, P<double>(c->sum_scratch), force_blocks(ms->n), E);
         if (!dev && energy && (st == GSIM_OK || st == GSIM_E_NONFINITE || st == GSIM_E_LIMIT)) {
-            HIPCHK(c, hipMemcpyAsync(energy, E, sizeof(double), kind, c->stream));
+            HIPCHK(c, hipMemcpyAsync(energy, E, sizeof(double), to, c->stream));
             HIPCHK(c, hipStreamSynchronize(c->stream));
         }
         return st;
