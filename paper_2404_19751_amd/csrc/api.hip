@@ -1091,7 +1091,6 @@ gsim_status single(gsim_ctx *c, MeshState *ms, double cutoff, const gsim_potenti
 gsim_status count_pairs(gsim_ctx *c, MeshState *ms, double cutoff) {
     hipStream_t s = c->stream;
     const int n = ms->n;
-    Stage st(c, "compact");
     HIPCHK(c, ensure(ms->nbr_cnt, sizeof(int32_t) * (n + 1)));
     HIPCHK(c, ensure(ms->off, sizeof(int64_t) * (n + 1)));
     HIPCHK(c, ensure(c->scan_scratch, sizeof(int64_t) * ((size_t)(n + 1023) / 1024 + 2)));
@@ -1105,7 +1104,6 @@ gsim_status count_pairs(gsim_ctx *c, MeshState *ms, double cutoff) {
 // The candidate rows as CSR into the given device arrays (flags may be null).
 gsim_status compact_pairs(gsim_ctx *c, MeshState *ms, double cutoff, int32_t *nbr, double *dist, double *tan,
                           uint8_t *flags) {
-    Stage st(c, "compact");
     HIPCHK(c, launch_compact_rows(ms->n, P<int32_t>(ms->cand_cnt), ms->cap, P<int32_t>(ms->cand), P<double>(ms->cdist),
                                   P<double>(ms->ctan), P<uint8_t>(ms->cflags), cutoff, P<int64_t>(ms->off), nbr, dist,
                                   tan, flags, c->stream));
@@ -1574,6 +1572,7 @@ static gsim_status pairs_to(gsim_ctx *c, int32_t id, double cutoff, gsim_pairs *
         if ((st = begin_call(c)) != GSIM_OK) return st;
         if ((st = single(c, ms, cutoff, nullptr, B)) != GSIM_OK) return st;
         if (!finite_cutoff(cutoff)) cutoff = INFINITY;
+        Stage stage(c, "compact");  // from the rows' counts to the last row's entries
         if ((st = count_pairs(c, ms, cutoff)) != GSIM_OK) return st;
         if ((st = end_call(c)) != GSIM_OK) return st;
         const int64_t total = c->hout->total;
