@@ -464,10 +464,10 @@ __global__ void k_validate_state(int nf, int n, const int32_t *__restrict__ face
 
 // A checked state into a surface's arrays, and the rest of the state as it is
 // after particles are set: no velocities unless given, no flags, FIRE state
-// and step counter restarted.
-__global__ void k_take_state(int n, const int32_t *__restrict__ face, const double *__restrict__ bary,
-                             const double *__restrict__ vel, int32_t *__restrict__ face_o, double *__restrict__ bary_o,
-                             double *__restrict__ vel_o, uint8_t *__restrict__ flags, FireState *fire, uint64_t *step) {
+// and step counter restarted. (The state may be in the surface's arrays
+// already: inputs and outputs may be the same.)
+__global__ void k_take_state(int n, const int32_t *face, const double *bary, const double *vel, int32_t *face_o,
+                             double *bary_o, double *vel_o, uint8_t *flags, FireState *fire, uint64_t *step) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i == 0) {
         *fire = FireState{};
