@@ -327,6 +327,9 @@ gsim_status gsim_step_batched(gsim_ctx *ctx, int32_t nmesh, const int32_t *mesh_
  *                   move each particle inside the geodesic launch; 0: always a
  *                   separate update launch per step
  *   "graph_steps"   steps captured per HIP graph in step calls (0 = no graphs)
+ *   "near_epochs"   passes of many targets: sources that a wavefront takes between
+ *                   two clears of its vertex and half-edge tables (1 .. 1048574,
+ *                   the default)
  *   "time_geodesic_only"  1: while timing is on, record events around the
  *                   geodesic stage only (each event record costs the stream a few
  *                   microseconds)

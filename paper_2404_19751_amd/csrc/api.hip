@@ -85,6 +85,7 @@ struct gsim_ctx {
     Buf near_t, near_v, near_h, near_e;
     NearLayout near_layout;
     int near_slots = 0;
+    uint32_t near_epochs = kEpochMax;  // sources a wavefront takes between two clears
     Buf bad;                  // device counts of a state check or of Voronoi limits: zeros between calls
     HostOut *hout = nullptr;  // pinned: what kernels hand to the host
     bool ctr_clean = false;   // the device counters hold zeros
@@ -859,7 +860,7 @@ gsim_status shape_part(gsim_ctx *c, Batch &B, Part &Q) {
             for (int k = 0; k < 4; ++k)
                 if (need[k]) HIPCHK(c, ensure(*buf[k], need[k]));
             HIPCHK(c, launch_near_init(P<char>(c->near_t), first, (int)nsl, Q.tcap, P<unsigned long long>(c->near_v), Q.vstride,
-                                       P<unsigned long long>(c->near_h), Q.hstride, P<uint32_t>(c->near_e), c->stream));
+                                       P<unsigned long long>(c->near_h), Q.hstride, P<uint32_t>(c->near_e), c->near_epochs, c->stream));
             c->near_layout = lay;
             c->near_slots = (int)nsl;
         }
@@ -1016,7 +1017,7 @@ gsim_status part_pass(gsim_ctx *c, Batch &B, const Part &Q, bool advance, bool c
         HIPCHK(c, launch_geodesic_all(desc, Q.bi, gp, Q.shape, P<char>(c->stack), P<unsigned long long>(v), Q.vstride,
                                       P<char>(c->roots), B.rstride, B.rcap, Q.near ? c->near_t.p : c->ttab.p, Q.tcap,
                                       Q.hstride ? P<unsigned long long>(h) : nullptr, Q.hstride,
-                                      Q.near ? P<uint32_t>(c->near_e) : nullptr, Q.pass, Q.team,
+                                      Q.near ? P<uint32_t>(c->near_e) : nullptr, c->near_epochs, Q.pass, Q.team,
                                       Q.team > 1 ? P<unsigned long long>(c->best) : nullptr, P<int32_t>(c->work),
                                       P<Counters>(c->ctr), fp32, s, st.a, st.b));
         return GSIM_OK;
@@ -2075,7 +2076,10 @@ gsim_status gsim_tune_set(gsim_ctx *c, const char *name, double value) {
         else if (k == "dom_rel" && value >= 0.0) c->gp.dom_rel = value;
         else if (k == "dom_rel32" && value >= 0.0) c->gp.dom_rel32 = value;
         else if (k == "whole_mesh" && (value == 0.0 || value == 1.0)) c->whole_mesh = value != 0.0;
-        else if (k == "group_sources" && (value == 1.0 || value == 2.0 || value == 4.0 || value == 8.0))
+        else if (k == "near_epochs" && value >= 1 && value <= kEpochMax) {
+            c->near_epochs = (uint32_t)value;
+            c->near_slots = 0;  // the epochs start over
+        } else if (k == "group_sources" && (value == 1.0 || value == 2.0 || value == 4.0 || value == 8.0))
             c->group_sources = (int)value;
         else if (k == "fuse_update" && (value == 0.0 || value == 1.0)) c->fuse_update = value != 0.0;
         else if (k == "time_geodesic_only" && (value == 0.0 || value == 1.0)) c->time_geodesic_only = value != 0.0;

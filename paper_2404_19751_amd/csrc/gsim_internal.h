@@ -301,11 +301,14 @@ enum AllPass { kWholeMesh, kNearPass, kNearPlain };
 hipError_t launch_geodesic_all(const SurfDesc *desc, const BatchIdx &bi, const GeoParams &gp, const GeoShape &shape,
                                char *stack_mem, unsigned long long *vdist, int64_t vstride, char *roots, int64_t rstride,
                                int rcap, void *ttab, int tcap, unsigned long long *split, int64_t hstride,
-                               uint32_t *epoch, AllPass pass, int team, unsigned long long *best, int32_t *work_ctr,
-                               Counters *ctr, bool fp32, hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
-// (wavefronts first .. nslots - 1)
+                               uint32_t *epoch, uint32_t epoch_max, AllPass pass, int team, unsigned long long *best,
+                               int32_t *work_ctr, Counters *ctr, bool fp32, hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+// (wavefronts first .. nslots - 1; a wavefront's sources take the epochs from
+// epoch_max, at most kEpochMax, down to 1, then its tables are cleared)
+constexpr uint32_t kEpochMax = (1u << 20) - 2;
 hipError_t launch_near_init(char *area, int first, int nslots, int tcap, unsigned long long *vdist, int64_t vstride,
-                            unsigned long long *split, int64_t hstride, uint32_t *epoch, hipStream_t s);
+                            unsigned long long *split, int64_t hstride, uint32_t *epoch, uint32_t epoch_max,
+                            hipStream_t s);
 // In-surface Voronoi neighbours (k_voronoi.hip): at most kVoronoiMax
 // particles (an n x n adjacency bitset). launch_voronoi_faces marks every
 // pair of particles whose cells share a boundary longer than tol; cell lists

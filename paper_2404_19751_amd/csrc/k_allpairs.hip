@@ -100,6 +100,7 @@ struct AllArgs {
     int32_t *touch;  // near passes, per wavefront: the targets reached (tcap entries)
     unsigned long long *sort;  // near passes, per wavefront: kBigCandMax sort keys
     uint32_t *epoch; // near passes, per wavefront: the epoch of its last source
+    uint32_t epoch_max;  // the first source's
     int tcap;
     int grab;
 };
@@ -250,7 +251,7 @@ struct RoundStack {
 // (a longer path through the vertex dominates less: exact, only the pruning
 // is weaker by the rounding, 6e-8).
 constexpr int kEpochShift = 44;
-constexpr uint32_t kEpochMax = (1u << 20) - 2;  // the first source's; all ones marks an entry never written
+static_assert(kEpochMax < (1u << 20) - 1, "all ones marks an entry never written");
 template <bool kNear>
 struct VertexTable {
     unsigned long long *p;
@@ -883,7 +884,7 @@ __device__ __attribute__((always_inline)) inline bool run_all(const AllArgs &a, 
         if (--epoch == 0) {
             for (int v = lane; v < (int)a.vstride; v += kWave) a.vdist[(int64_t)slot * a.vstride + v] = ~0ull;
             for (int h = lane; h < (int)a.hstride; h += kWave) a.split[(int64_t)slot * a.hstride + h] = ~0ull;
-            epoch = kEpochMax;
+            epoch = a.epoch_max;
             wave_sync();
         }
     }
@@ -1607,7 +1608,7 @@ static_assert(sizeof(TgtState) == 32, "a NearArea's target state");
 }  // namespace
 
 hipError_t launch_near_init(char *area, int first, int nslots, int tcap, unsigned long long *vdist, int64_t vstride,
-                            unsigned long long *split, int64_t hstride, uint32_t *epoch, hipStream_t s) {
+                            unsigned long long *split, int64_t hstride, uint32_t *epoch, uint32_t epoch_max, hipStream_t s) {
     // every target unreached, every vertex and half-edge entry void. (A
     // double of all-ones bits would be a NaN: the states get infinities.)
     const int64_t n = nslots - first, bytes = NearArea(tcap).bytes;
@@ -1615,15 +1616,15 @@ hipError_t launch_near_init(char *area, int first, int nslots, int tcap, unsigne
                                    0x7ff0000000000000ull, s);
     if (e == hipSuccess) e = launch_fill_u64(vdist + first * vstride, n * vstride, ~0ull, s);
     if (e == hipSuccess && hstride) e = launch_fill_u64(split + first * hstride, n * hstride, ~0ull, s);
-    if (e == hipSuccess) e = launch_fill_u32(epoch + first, n, kEpochMax, s);
+    if (e == hipSuccess) e = launch_fill_u32(epoch + first, n, epoch_max, s);
     return e;
 }
 
 hipError_t launch_geodesic_all(const SurfDesc *desc, const BatchIdx &bi, const GeoParams &gp, const GeoShape &shape,
                                char *stack_mem, unsigned long long *vdist, int64_t vstride, char *roots, int64_t rstride,
                                int rcap, void *ttab, int tcap, unsigned long long *split, int64_t hstride,
-                               uint32_t *epoch, AllPass pass, int team, unsigned long long *best, int32_t *work_ctr,
-                               Counters *ctr, bool fp32, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+                               uint32_t *epoch, uint32_t epoch_max, AllPass pass, int team, unsigned long long *best,
+                               int32_t *work_ctr, Counters *ctr, bool fp32, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
     const bool near = pass != kWholeMesh;
     if (near && !epoch) return hipErrorInvalidValue;
     AllArgs a;
@@ -1647,6 +1648,7 @@ hipError_t launch_geodesic_all(const SurfDesc *desc, const BatchIdx &bi, const G
     a.touch = near ? reinterpret_cast<int32_t *>(static_cast<char *>(ttab) + na.touch) : nullptr;
     a.sort = near ? reinterpret_cast<unsigned long long *>(static_cast<char *>(ttab) + na.sort) : nullptr;
     a.epoch = epoch;
+    a.epoch_max = epoch_max;
     a.grab = shape.grab < 1 ? 1 : shape.grab;
     if (shape.nslots < 1 || bi.begin[bi.nsurf] < 1) return hipSuccess;
     if (team < 1 || shape.nslots % team || (team > 1 && (near || fp32 || !best))) return hipErrorInvalidValue;
