@@ -196,7 +196,10 @@ gsim_status gsim_particle_flags_dev(gsim_ctx *ctx, int32_t mesh_id, uint8_t *fla
  * for every pair closer than `cutoff` (Sec. 3.1: sequence-tree distances and
  * tangents relative to the source; submeshing by the Euclidean lower bound).
  * Euclidean prefilter, window propagation and target query run on the GPU;
- * the CSR is then copied to the caller's host buffers. */
+ * the CSR is then copied to the caller's host buffers. In FP64 mode calls
+ * repeat bit for bit. Without a cutoff (or with "whole_mesh") and with few
+ * particles several wavefronts share a source there, as many as the device has
+ * room for: another number of them changes results by rounding at most. */
 gsim_status gsim_geodesic_pairs(gsim_ctx *ctx, int32_t mesh_id, double cutoff, gsim_pairs *out);
 /* The same, with every buffer of `out` (off, nbr, dist, tan, flags) in device
  * memory, written on the context's stream (the call waits only to learn the
@@ -270,12 +273,12 @@ gsim_status gsim_step(gsim_ctx *ctx, int32_t mesh_id, const gsim_potential *pot,
 /* step_batched: nsteps full time steps of several independent surfaces at
  * once (the same per-surface work as gsim_step, Sec. 3.1 and 3.2). Every
  * step is one binning, one geodesic and one update (or commit) launch for the whole
- * batch: the persistent geodesic grid takes sources from all surfaces, so
+ * batch (surfaces of near passes have a binning and a geodesic launch of their own): the persistent geodesic grid takes sources from all surfaces, so
  * small surfaces share the GPU instead of leaving it idle. mesh_ids[nmesh]
  * (1..64 distinct meshes, each with particles), pots[nmesh], integs[nmesh].
- * With a finite cutoff, no FIRE surface in the batch and at most four
- * particles per compute unit in all, the update is fused into the geodesic
- * launch ("fuse_update", default 1): each source's wavefront moves its
+ * With a finite cutoff, no FIRE surface and no near pass ("whole_mesh" below)
+ * in the batch and at most four particles per compute unit in all, the update
+ * is fused into the geodesic launch ("fuse_update", default 1): each source's wavefront moves its
  * particle (force from its row, integrator, walk) into a next-state array as
  * soon as its row is final; the next step's binning, or a commit launch after
  * the last step, makes that the current state. The results are bit-identical
@@ -291,7 +294,10 @@ gsim_status gsim_step_batched(gsim_ctx *ctx, int32_t nmesh, const int32_t *mesh_
  * exact, only the amount of work or the launch shape changes):
  *   "launch_delta"  bend-vertex launch bucket width (0 = half the mean edge)
  *   "stack_cap"     window-stack capacity per resident wavefront, cutoff passes
- *                   (64 .. 4M records of 64 bytes; default 16384)
+ *                   (64 .. 4M records of 64 bytes; default 16384). Near passes
+ *                   (below "whole_mesh") on surfaces with bend vertices take at
+ *                   least eight records for each face within the cutoff, up to
+ *                   "stack_cap_all"
  *   "max_slots"     resident wavefronts of the persistent grid (1 .. 65536)
  *   "max_windows"   per-source work limit (GSIM_E_LIMIT beyond it)
  *   "cone_tol"      closed-cone slack relative to the edge length
@@ -341,16 +347,23 @@ gsim_status gsim_step_batched(gsim_ctx *ctx, int32_t nmesh, const int32_t *mesh_
  *                   before each pass, as a pairs call's output is before it
  *                   is written; GSIM_E_LIMIT names the bytes). Without
  *                   it, passes with a cutoff take up to 4096 Euclidean candidates
- *                   per source: up to 128 in an LDS table, more by whole-mesh
- *                   propagation up to the cutoff and rows sized from a count of the
- *                   candidates at the start of each call (GSIM_E_LIMIT beyond
- *                   4096, or when moving particles outgrow that count within a
- *                   call by more than a quarter plus 32)
+ *                   per source, in one of two ways, chosen for each surface by
+ *                   itself. The cutoff kernel holds up to 128 candidates in an LDS
+ *                   table. Near passes, by whole-mesh propagation up to the cutoff,
+ *                   run where a source may have more (the candidates are counted
+ *                   at the start of each call where that is plausible, and rows
+ *                   sized by the count), and from about 45 expected candidates
+ *                   (uniform density: mean plus three standard deviations of a
+ *                   Poisson count above 64) unless the surface's particles leave
+ *                   room for fewer than half the wavefronts. GSIM_E_LIMIT beyond
+ *                   4096, or when moving particles outgrow the count within a
+ *                   call by more than a quarter plus 32
  *   Whole-mesh passes (no cutoff, or "whole_mesh" = 1):
  *   "stack_cap_all" window records per resident wavefront (1024 .. 4M)
  *   "max_windows_all" per-source work limit
- *   "bucket"        key width of one processing round (0 = 16 max edge lengths,
- *                   4 on a surface with saddle or boundary vertices)
+ *   "bucket"        key width of one processing round (0 = 16 max edge lengths;
+ *                   4 on a surface with saddle or boundary vertices, 3/4 there
+ *                   where several wavefronts share a source)
  *   "dom_rel", "dom_rel32"  margins of the vertex-path domination tests */
 gsim_status gsim_tune_set(gsim_ctx *ctx, const char *name, double value);
 

@@ -43,7 +43,7 @@ struct MeshState {
     int32_t *face = nullptr;
     double *bary = nullptr, *vel = nullptr, *xyz = nullptr;
     // prefilter
-    Buf cell_of, cell_start, cell_fill, order, cand_cnt, cand, tmp64;
+    Buf cell_of, cell_start, cell_fill, order, cand_cnt, cand;
     int64_t fill_zero = 0;  // leading cells of cell_fill known to hold zeros
     // candidate-layout results
     Buf cdist, ctan, cflags;
@@ -436,7 +436,6 @@ gsim_status row_capacity(gsim_ctx *c, MeshState *ms, double cutoff, int &cap) {
     HIPCHK(c, ensure(ms->cell_start, sizeof(int32_t) * (ncell + 1)));
     HIPCHK(c, ensure(ms->cell_fill, sizeof(int32_t) * ncell));
     HIPCHK(c, ensure(ms->order, sizeof(int32_t) * n));
-    HIPCHK(c, ensure(ms->tmp64, sizeof(int64_t) * (std::max<int64_t>(ncell, n) + 1)));
     HIPCHK(c, ensure(c->scan_scratch, sizeof(int64_t) * ((std::max<int64_t>(ncell, n) + 1023) / 1024 + 2)));
     HIPCHK(c, ensure(ms->nbr_cnt, sizeof(int32_t) * (n + 1)));
     PrefilterBufs pb{};
@@ -517,7 +516,6 @@ gsim_status prepare_surface(gsim_ctx *c, const Member &mb, bool small, SurfDesc 
     HIPCHK(c, ensure(ms->cdist, sizeof(double) * (size_t)n * cap));
     HIPCHK(c, ensure(ms->ctan, sizeof(double) * 3 * (size_t)n * cap));
     HIPCHK(c, ensure(ms->cflags, (size_t)n * cap));
-    HIPCHK(c, ensure(ms->tmp64, sizeof(int64_t) * (std::max<int64_t>(ncell, n) + 1)));
     HIPCHK(c, ensure(ms->wflags, n));
     HIPCHK(c, ensure(c->scan_scratch, sizeof(int64_t) * ((std::max<int64_t>(ncell, n) + 1023) / 1024 + 2)));
     HIPCHK(c, ensure(ms->F, sizeof(double) * 3 * n));
@@ -693,7 +691,12 @@ bool near_rule(const gsim_ctx *c, const Member &mb, int cap) {
     // 1.10 / 0.76 (bumpy sphere, 9002), 1.33 / 0.92 (height field of 20,000
     // faces, 9731), 0.26 / 0.18 (sphere of 5120 faces, 2130); at 24, where
     // sources pair up, 0.28 / 0.25, 0.50 / 0.43, 0.41 / 0.42, 0.43 / 0.50,
-    // 0.16 / 0.15; at 8 a third to half as long as a near pass.
+    // 0.16 / 0.15; at 8 a third to half as long as a near pass. Few sources
+    // gain more (a step at 48 candidates, with the update fused on the cutoff
+    // kernel's side: torus 200 sources 19.1 / 4.1, 1000 1.78 / 0.63; height
+    // field 200 35.5 / 15.9; sphere of 20480 faces 500 2.24 / 1.11), FP32-mixed
+    // less (torus 1000 2.78 / 1.08, bumpy sphere 1000 5.58 / 4.02, height field
+    // 500 14.0 / 11.1).
     const double mean = mean_candidates(mb);
     if (cap > kCandCap) return true;
     if (mean + 3.0 * std::sqrt(mean) <= 0.5 * kCandCap) return false;
@@ -1318,7 +1321,7 @@ void gsim_destroy(gsim_ctx *c) {
     for (MeshState *ms : c->meshes) {
         if (!ms) continue;
         for (Buf *b : {&ms->cell_of, &ms->cell_start, &ms->cell_fill, &ms->order, &ms->cand_cnt, &ms->cand,
-                       &ms->tmp64, &ms->cdist, &ms->ctan, &ms->cflags, &ms->nbr_cnt, &ms->off, &ms->nbr, &ms->dist,
+                       &ms->cdist, &ms->ctan, &ms->cflags, &ms->nbr_cnt, &ms->off, &ms->nbr, &ms->dist,
                        &ms->tan, &ms->flags, &ms->F, &ms->E, &ms->disp, &ms->wflags, &ms->step_dev,
                        &ms->fire, &ms->fstart, &ms->ffirst, &ms->ftgt, &ms->fcount, &ms->forder, &ms->face_nx, &ms->bary_nx,
                        &ms->vel_nx})
@@ -1328,7 +1331,7 @@ void gsim_destroy(gsim_ctx *c) {
         for (void *p : {(void *)ms->dm.V, (void *)ms->dm.T, (void *)ms->dm.he, (void *)ms->dm.twin, (void *)ms->dm.hef,
                         (void *)ms->dm.vflag, (void *)ms->dm.theta, (void *)ms->dm.fan_off, (void *)ms->dm.fan,
                         (void *)ms->dm.corner, (void *)ms->dm.fnrm, (void *)ms->dm.fpos,
-                        (void *)ms->dm.pidx, (void *)ms->dm.pvert, (void *)ms->dm.prec})
+                        (void *)ms->dm.pidx, (void *)ms->dm.prec})
             if (p) (void)hipFree(p);
         delete ms;
     }
@@ -1384,7 +1387,6 @@ gsim_status gsim_mesh_upload(gsim_ctx *c, int32_t nv, const double *xyz, int32_t
         HIPCHK(c, upload(d.fnrm, H.fnrm.data(), H.fnrm.size(), s));
         HIPCHK(c, upload(d.fpos, H.fpos.data(), H.fpos.size(), s));
         HIPCHK(c, upload(d.pidx, H.pidx.data(), H.pidx.size(), s));
-        HIPCHK(c, upload(d.pvert, H.pvert.data(), H.pvert.size(), s));
         HIPCHK(c, upload(d.prec, H.prec.data(), H.prec.size(), s));
         for (int k = 0; k < 3; ++k) {
             d.bbmin[k] = H.bbmin[k];
@@ -1651,7 +1653,6 @@ gsim_status gsim_voronoi_neighbours(gsim_ctx *c, int32_t id, int64_t *off, int32
             if (ms->cell_fill.p != was) ms->fill_zero = 0;
         }
         HIPCHK(c, ensure(ms->order, sizeof(int32_t) * n));
-        HIPCHK(c, ensure(ms->tmp64, sizeof(int64_t) * (std::max<int64_t>(ncell, n) + 1)));
         HIPCHK(c, ensure(c->scan_scratch, sizeof(int64_t) * ((std::max<int64_t>(ncell, n) + 1023) / 1024 + 2)));
         const int64_t words = (n + 63) / 64;
         HIPCHK(c, ensure(c->vbits, sizeof(unsigned long long) * (size_t)n * words));

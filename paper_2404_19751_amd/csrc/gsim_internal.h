@@ -70,7 +70,6 @@ struct DevMesh {
     double *fpos = nullptr;     // [nf][18]: the face's vertex positions in slot order, then the unit
                                 // directions of its half-edges 3f+0..2
     int32_t *pidx = nullptr;    // [nv] bend-vertex number (0..n_pseudo-1) of a pseudo-source, else -1
-    int32_t *pvert = nullptr;   // [max(n_pseudo,1)] the vertex of each bend-vertex number
     PseudoRec *prec = nullptr;  // [max(n_pseudo,1)] its position and fan
     double bbmin[3], bbmax[3];
     double mean_edge = 0, min_edge = 0, max_edge = 0;
@@ -88,7 +87,7 @@ struct HostMesh {
     std::vector<uint8_t> vflag;
     std::vector<double> theta, corner, fnrm, fpos;
     std::vector<int32_t> fan_off, fan;
-    std::vector<int32_t> pidx, pvert;
+    std::vector<int32_t> pidx;
     std::vector<PseudoRec> prec;
     double bbmin[3], bbmax[3];
     double mean_edge = 0, min_edge = 0, max_edge = 0;

@@ -53,8 +53,8 @@
 // are on their way, a child takes its edge's vertex distances from its
 // parent, and global stack traffic goes a wavefront's worth at a time.
 // Together with records read in whole rounds: 2000 sources on that sphere
-// 0.953 -> 0.639 s a pass (22 -> 34 G windows/s), 100 sources on an aspect-3
-// torus of 3456 faces 18.7 -> 12.4 ms (and 18.8 -> 11.5 M windows). Fetching
+// 0.953 -> 0.652 s a pass (23 -> 33 G windows/s), 100 sources on an aspect-3
+// torus of 3456 faces 18.7 -> 11.2 ms (and 18.8 -> 11.3 M windows). Fetching
 // the next half-edge record straight into LDS an iteration ahead was slower
 // (0.84 s, and 0.98 s with lanes sharing the loads): every later LDS access
 // of the iteration waits for such a fetch.

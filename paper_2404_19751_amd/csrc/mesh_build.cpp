@@ -144,27 +144,22 @@ std::string build_host_mesh(int nv, const double *xyz, int nf, const int32_t *tr
         M.vflag[v] = fl;
         if (fl & VF_PSEUDO) M.n_pseudo++;
     }
-    // dense numbering of the pseudo-sources (the whole-mesh kernel's bend-vertex table)
+    // dense numbering of the pseudo-sources (the bend-vertex tables) and their records
     M.pidx.assign(nv, -1);
-    M.pvert.clear();
+    M.prec.clear();
     for (int v = 0; v < nv; ++v)
         if (M.vflag[v] & VF_PSEUDO) {
-            M.pidx[v] = (int32_t)M.pvert.size();
-            M.pvert.push_back(v);
+            M.pidx[v] = (int32_t)M.prec.size();
+            PseudoRec r{};
+            r.x = M.V[3 * size_t(v)];
+            r.y = M.V[3 * size_t(v) + 1];
+            r.z = M.V[3 * size_t(v) + 2];
+            r.v = v;
+            r.fan_beg = M.fan_off[v];
+            r.fan_deg = M.fan_off[v + 1] - M.fan_off[v];
+            M.prec.push_back(r);
         }
-    if (M.pvert.empty()) M.pvert.push_back(-1);
-    M.prec.assign(M.pvert.size(), PseudoRec{0.0, 0.0, 0.0, -1, 0, 0, 0});
-    for (size_t e = 0; e < M.pvert.size(); ++e) {
-        const int v = M.pvert[e];
-        if (v < 0) continue;
-        PseudoRec &r = M.prec[e];
-        r.x = M.V[3 * size_t(v)];
-        r.y = M.V[3 * size_t(v) + 1];
-        r.z = M.V[3 * size_t(v) + 2];
-        r.v = v;
-        r.fan_beg = M.fan_off[v];
-        r.fan_deg = M.fan_off[v + 1] - M.fan_off[v];
-    }
+    if (M.prec.empty()) M.prec.push_back(PseudoRec{0.0, 0.0, 0.0, -1, 0, 0, 0});
 
     // unfolding records
     M.he.resize(ne);
